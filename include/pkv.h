@@ -57,7 +57,7 @@ typedef struct {
                                  one partial result (max, sum, row) may cover: a multiple
                                  of B in [B, 65536], or 0 to let the library choose.
                                  Partial results of one request and KV head that the same
-                                 wavefront produced are merged on chip; the merge pass
+                                 wavefront produced are merged on chip; the reduce pass
                                  combines the rest.  P does not change the workspace.    */
   int32_t max_context_len;    /* host upper bound on every context_lens[s]; 0 means
                                  MAXB*B.  A smaller bound only shrinks the launch;

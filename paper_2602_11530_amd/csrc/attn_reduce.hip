@@ -1,13 +1,17 @@
-// Split-K merge for paged decode attention on gfx950: combines the partial
-// records (reference max, partial sum, un-normalised row) that the stream pass
-// left for one (request, query head) into the final bf16 row.  The maxima are in
-// log2 units.  A wavefront fetches the records' statistics side by side, then
-// streams the partial rows eight at a time so that the pass is not a chain of
-// dependent loads.  A full batch gives a row a handful of records and one
-// wavefront per row; a batch of a few requests spreads each (request, KV head)
-// over hundreds of stream wavefronts, and then a workgroup shares the row.
-// Which slots hold a segment's records follows from the stream layout described
-// in pkv_kernels.h.
+// Split-K merge for paged decode attention on gfx950: folds the records (reference max, partial
+// sum, un-normalised row; the maxima are in log2 units) that the stream pass left of the segments
+// (request, KV head) that several of its wavefronts share into the final bf16 rows.  Segments
+// that one share holds are finished there.  Bound by latency: where the records are, then the
+// records.  Two layouts (pkv_kernels.h):
+//
+// A batch of many segments leaves at most one shared segment per workgroup of the stream pass,
+// whose wavefronts have met in LDS, so that a segment has a handful of records: one workgroup
+// here for each there (256), which reads one word and is done when nothing begins there.
+//
+// A batch of few segments (by_row) spreads each over hundreds of wavefronts, and their records come as
+// they are: a wavefront or a workgroup for each row fetches the statistics side by side and then
+// streams the partial rows eight at a time.
+#include "attn_partial.h"
 #include "pkv_kernels.h"
 
 namespace pkv {
@@ -16,21 +20,12 @@ namespace {
 constexpr int kRowsPerGroup = 4;   // wavefronts per workgroup
 constexpr int kBatch = 8;          // partial rows in flight per wavefront
 constexpr int kMaxWideWaves = 16;  // wavefronts of a workgroup that share one row (small batches)
-constexpr float kNegInf = -__builtin_huge_valf();
 
 // kPer = D / 64 consecutive floats of a row per lane
 template <int kPer> struct Chunk { typedef float T __attribute__((ext_vector_type(kPer))); };
 template <> struct Chunk<1> { typedef float T; };
 template <int kPer> __device__ __forceinline__ float chunk_get(const typename Chunk<kPer>::T& v, int i) { return v[i]; }
 template <> __device__ __forceinline__ float chunk_get<1>(const float& v, int) { return v; }
-
-// fp32 -> bf16, round to nearest even (a NaN stays a NaN)
-__device__ __forceinline__ uint16_t bf16_bits(float x) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  const f32x2 f = {x, 0.f};
-  return (uint16_t)(__builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2)) & 0xffffu);
-}
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
@@ -44,7 +39,8 @@ __device__ __forceinline__ float wave_sum(float x) {
 }
 
 // Where the records of row (s, h) lie: the slots of its segment's first and last
-// block's owners (see pkv_kernels.h).  Returns false for an empty request.
+// block's owners (see pkv_kernels.h).  Returns false when there is nothing to fold: an empty
+// request, a segment that one wavefront finished, a batch that was cut along its segments.
 struct RowRecords {
   int first;   // slot of the first record
   int np;      // one record per wavefront that streamed part of this segment
@@ -56,14 +52,14 @@ __device__ __forceinline__ bool locate_records(const AttnLaunch& a, int row, Row
   r.g = h - kvh * a.G;
   const int* cumB = a.ws_cum;
   const int nb = cumB[s + 1] - cumB[s];
-  if (nb <= 0) return false;
-  const int64_t T = (int64_t)a.Hkv * cumB[a.S];
-  const int64_t W = min((int64_t)a.waves, T);
-  const int64_t pos_a = (int64_t)a.Hkv * cumB[s] + (int64_t)kvh * nb;   // the segment's first block
-  const int seg = s * a.Hkv + kvh;
-  r.first = seg + share_owner(pos_a, T, W);
-  r.np = seg + share_owner(pos_a + nb - 1, T, W) - r.first + 1;
-  return true;
+  if (nb <= 0 || cumB[0] < 0) return false;
+  const int T = a.Hkv * cumB[a.S];
+  const ShareMap shares(T, share_count(T, a.waves));
+  const int pos_a = a.Hkv * cumB[s] + kvh * nb;   // the segment's first block
+  const int seg = s * a.Hkv + kvh, first = shares.owner(pos_a);
+  r.first = seg + first;
+  r.np = shares.owner(pos_a + nb - 1) - first + 1;
+  return r.np > 1;
 }
 
 // One wavefront folds `count` records of a row (records begin, begin + stride, ...
@@ -133,26 +129,22 @@ __device__ __forceinline__ void store_row(uint16_t* dst, const float (&acc)[kPer
   const float inv = lsum > 0.f ? out_scale / lsum : 0.f;
   uint16_t r[kPer];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) r[i] = bf16_bits(acc[i] * inv);
+  for (int i = 0; i < kPer; ++i) r[i] = (uint16_t)pack_bf16(acc[i] * inv, 0.f);
   if (kPer == 1) dst[0] = r[0];
   else if (kPer == 2) *(uint32_t*)dst = r[0] | ((uint32_t)r[1] << 16);
   else *(uint2*)dst = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
 }
 
-// One wavefront per row: the shape of a full batch, where a row has a handful of records.
+// One wavefront per row.
 template <int kD>
-__global__ __launch_bounds__(kRowsPerGroup * 64) void attn_reduce_kernel(AttnLaunch a) {
+__global__ __launch_bounds__(kRowsPerGroup * 64) void attn_reduce_row_kernel(AttnLaunch a) {
   constexpr int kPer = kD / 64;
   const int row = blockIdx.x * kRowsPerGroup + (threadIdx.x >> 6);   // s*Hq + h
   if (row >= a.S * a.Hq) return;
   const int lane = threadIdx.x & 63;
   uint16_t* dst = a.out + (int64_t)row * kD + kPer * lane;
   RowRecords r;
-  if (!locate_records(a, row, r)) {   // an empty request owes a zero row
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) dst[i] = 0;
-    return;
-  }
+  if (!locate_records(a, row, r)) return;
   float M, lsum, acc[kPer];
   fold_records<kD>(a, r, 0, 1, r.np, lane, M, lsum, acc);
   store_row<kPer>(dst, acc, lsum, a.out_scale);
@@ -164,7 +156,7 @@ __global__ __launch_bounds__(kRowsPerGroup * 64) void attn_reduce_kernel(AttnLau
 // records i, i + n, i + 2n, ... (n = wavefronts in the group), the partial
 // results meet in LDS and wavefront 0 folds those.
 template <int kD>
-__global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_kernel(AttnLaunch a) {
+__global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_row_kernel(AttnLaunch a) {
   constexpr int kPer = kD / 64;
   __shared__ float part_stats[kMaxWideWaves][2];
   __shared__ float part_acc[kMaxWideWaves][kD];
@@ -173,13 +165,7 @@ __global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_kernel(At
   const int width = blockDim.x >> 6;
   uint16_t* dst = a.out + (int64_t)row * kD + kPer * lane;
   RowRecords r;
-  if (!locate_records(a, row, r)) {   // the same for every wavefront of the group
-    if (wave == 0) {
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) dst[i] = 0;
-    }
-    return;
-  }
+  if (!locate_records(a, row, r)) return;   // the same for every wavefront of the group
   float M, lsum, acc[kPer];
   const int count = r.np > wave ? (r.np - wave + width - 1) / width : 0;
   fold_records<kD>(a, r, wave, width, count, lane, M, lsum, acc);
@@ -204,9 +190,61 @@ __global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_kernel(At
   store_row<kPer>(dst, total, lall, a.out_scale);
 }
 
+// One workgroup per workgroup of the stream pass: the segment that begins in that one and goes on in
+// others.  A thread owns 16 bytes of the rows and every sets-th record; the sets meet in LDS.
+constexpr int kGroupThreads = 512;
+template <int kD>
+__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a) {
+  __shared__ f32x4 rows[kGroupThreads];
+  __shared__ f32x2 stats[kGroupThreads];
+  const int group = blockIdx.x;
+  const SharedSegment seg = *shared_segment(a, group);
+  if (seg.count == 0) return;
+  const int items = a.G * (kD / 4);
+  const int sets = min(max(kGroupThreads / items, 1), seg.count);
+  uint16_t* out = a.out + (int64_t)seg.row * kD;
+  for (int t = threadIdx.x; t < max(items, kGroupThreads); t += kGroupThreads) {
+    const int set = t / items, item = t - set * items, head = item / (kD / 4);
+    Partial p = kNothing;
+    for (int i0 = set; set < sets && i0 < seg.count; i0 += kBatch * sets) {
+      f32x4 x[kBatch];
+      f32x2 ml[kBatch];
+#pragma unroll
+      for (int z = 0; z < kBatch; ++z) {
+        const int i = min(i0 + z * sets, seg.count - 1);
+        const float* rec = group_record(a, kD, group + i, i == 0);
+        x[z] = *(const f32x4*)(rec + 4 * item);
+        ml[z] = *(const f32x2*)(rec + a.G * kD + 2 * head);
+        if (i0 + z * sets >= seg.count) ml[z].x = kNegInf;
+      }
+      fold(p, ml, x);
+    }
+    if (sets > 1) {   // then every thread is in its only turn of this loop
+      rows[t] = p.x;
+      stats[t] = f32x2{p.m, p.l};
+      __syncthreads();
+      if (set != 0) return;
+      for (int z = 1; z < sets; ++z) {
+        const f32x2 ml[1] = {stats[t + z * items]};
+        const f32x4 x[1] = {rows[t + z * items]};
+        fold(p, ml, x);
+      }
+    }
+    if (set == 0) *(u32x2*)(out + 4 * item) = finish_row4(p.x, inverse(p.l, a.out_scale));
+  }
+}
+
 }  // namespace
 
 hipError_t launch_attn_reduce(const AttnLaunch& a, hipStream_t stream) {
+  if (!a.by_row) {
+    const dim3 grid(a.waves / group_waves(a.D)), block(kGroupThreads);
+    if (a.D == 64) hipLaunchKernelGGL(attn_reduce_group_kernel<64>, grid, block, 0, stream, a);
+    else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_group_kernel<128>, grid, block, 0, stream, a);
+    else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_group_kernel<256>, grid, block, 0, stream, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   const int rows = a.S * a.Hq;
   // A segment's records come from the wavefronts that streamed it: about
   // waves / (S * Hkv) of them when the batch is large enough to occupy them all.
@@ -218,17 +256,17 @@ hipError_t launch_attn_reduce(const AttnLaunch& a, hipStream_t stream) {
   if (per_row >= 32) {
     const int width = per_row >= 64 ? 16 : 8;
     const dim3 grid((unsigned)rows), block(width * 64);
-    if (a.D == 64) hipLaunchKernelGGL(attn_reduce_wide_kernel<64>, grid, block, 0, stream, a);
-    else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_wide_kernel<128>, grid, block, 0, stream, a);
-    else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_wide_kernel<256>, grid, block, 0, stream, a);
+    if (a.D == 64) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<64>, grid, block, 0, stream, a);
+    else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<128>, grid, block, 0, stream, a);
+    else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<256>, grid, block, 0, stream, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
   dim3 grid((unsigned)((rows + kRowsPerGroup - 1) / kRowsPerGroup), 1, 1);
   const dim3 block(kRowsPerGroup * 64);
-  if (a.D == 64) hipLaunchKernelGGL(attn_reduce_kernel<64>, grid, block, 0, stream, a);
-  else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_kernel<128>, grid, block, 0, stream, a);
-  else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_kernel<256>, grid, block, 0, stream, a);
+  if (a.D == 64) hipLaunchKernelGGL(attn_reduce_row_kernel<64>, grid, block, 0, stream, a);
+  else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_row_kernel<128>, grid, block, 0, stream, a);
+  else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_row_kernel<256>, grid, block, 0, stream, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

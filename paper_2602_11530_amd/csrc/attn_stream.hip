@@ -8,10 +8,25 @@
 // every wavefront reads the same number of blocks (+-1), starts streaming at
 // once, never idles between requests, and there is no tail of late workgroups.
 // A wavefront computes one partial result per run (a stretch of its share inside
-// one request, one KV head and one P-token partition), folds the runs of one
-// (request, KV head) into a single record while that record is still parked in
-// LDS, and writes one record per (wavefront, request, KV head); the merge pass
-// combines the records of each (request, query head).
+// one request, one KV head and one P-token partition) and folds the runs of one
+// (request, KV head) together.  What lies wholly inside its share is finished there and
+// then: normalised, rounded and staged in LDS for a burst of stores (512 requests of 16
+// to 512 tokens: 1.5 MB of records and their reduce pass instead of 16 MB, call 125 ->
+// 115 us).  Of what it shares with other wavefronts it leaves one record, and the
+// reduce pass (attn_reduce.hip) combines the records of each (request, KV head).
+//
+// Three ways to that end, by what the segments are like:
+//   many segments    the wavefronts of a workgroup fold what they share in LDS first, so at most
+//                    two records per workgroup reach memory (64 requests of 1024..8192 tokens: the
+//                    reduce pass takes 4.6 us instead of 5.2, the call 191.0 instead of 194.2 us)
+//   few (by_row)     every segment is shared by dozens of wavefronts; their records go to memory as
+//                    they are and the reduce pass has a workgroup per row (one request of 8191 tokens:
+//                    meeting in LDS first took 2 us here and gave 2 us there)
+//   few and short    one workgroup per segment, which meets in LDS and finishes it: no records, and no
+//                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
+//                    heads: 10.8 us instead of 6.8 + 6.4 and a launch less; the call 17.8 -> 14.5 us).
+//                    Up to 6 blocks per wavefront, where streaming one segment with one workgroup
+//                    costs no more than the records and the reduce pass do.
 //
 // Per 16-token block, lane = 16*c + n, head_dim D = 128 (64 and 256 below):
 //   S^T = K . Q^T   D/32 v_mfma_f32_16x16x32_bf16 (k = 32 dims each).
@@ -49,6 +64,7 @@
 // kRing - 1 blocks (one) in flight per wavefront.  Finished records are parked in LDS and written in
 // bursts of full-width write-through stores that the compiler's wait-count
 // bookkeeping does not see (see store_record16).
+#include "attn_partial.h"
 #include "pkv_kernels.h"
 
 namespace pkv {
@@ -99,21 +115,11 @@ template <int kD> __device__ __forceinline__ int tile_group_dim(int t, int n) {
   if (kD == 128) return 8 * n + 4 * t;
   return 128 * (t >> 1) + 8 * n + 4 * (t & 1);
 }
-constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kLazyLog2 = 8.f;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Two fp32 -> packed bf16, round to nearest even (v_cvt_pk_bf16_f32).
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const f32x2 f = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
 // The same rounding, then the fp32 value of what was kept.
 __device__ __forceinline__ float bf16_round(float x, uint32_t& bits) {
   bits = pack_bf16(x, 0.f) & 0xffffu;
@@ -137,7 +143,7 @@ __device__ __forceinline__ u32x2 widen_e4m3x4(uint32_t w) {
 // sc1 makes the store write through instead of leaving a dirty line behind for a
 // later eviction (measured while records were still written once per partition:
 // 512-token partitions then cost 8 % instead of 13 % on the long-context batch).
-__device__ __forceinline__ void store_record16(float* p, f32x4 v) {
+__device__ __forceinline__ void store16(void* p, u32x4 v) {
   // the trailing s_nop covers the wait states a wide store needs before a vector
   // op may overwrite its data registers (the compiler cannot see that this is a store)
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
@@ -146,42 +152,71 @@ __device__ __forceinline__ void store_record16(float* p, f32x4 v) {
 // One window of block descriptors: lane i describes stream index jbase + i.
 struct Window {
   int slab;   // which slab (16 tokens of one KV head; 4 KiB at D = 128 in bf16), counted from the pool's start; 0 when not read
-  int meta;   // bits 0-7 valid tokens (0..16), bit 8 closes a run, bit 9 first block of a segment here
+  int meta;   // bits 0-7 valid tokens (0..16), then the kMeta flags
   int qrow;   // s * Hq + kvh * G: first query/output row of the segment
-  int slot;   // partial-record slot of the run this block belongs to
 };
-constexpr int kMetaLast = 1 << 8;
-constexpr int kMetaSegFirst = 1 << 9;
+// A position of the stream: block b of the nb blocks of request s, KV head kvh.
+struct Place {
+  int s, kvh, b, nb;
+};
+
+constexpr int kMetaLast = 1 << 8;       // closes a run
+constexpr int kMetaSegFirst = 1 << 9;   // first block of its segment in this share
+constexpr int kMetaSegEnd = 1 << 10;    // last block of its segment
+constexpr int kMetaOpenLeft = 1 << 11;  // its segment begins before this share
+
+// How a wavefront's share ends, left in LDS for the workgroup's merge.
+constexpr int kEndsLeft = 1;      // the left record is in use: the first segment begins before the share
+constexpr int kEndsThrough = 2;   // and goes on after it
+constexpr int kEndsRight = 4;     // the right record is in use: the last segment begins in the share and goes on
+
+// The launch descriptor once more, from the kernel's argument block: what only the merge needs
+// is then loaded after the stream and does not take up scalar registers during it.
+__device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
+  typedef const AttnLaunch __attribute__((address_space(4))) * ArgPtr;
+  ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const AttnLaunch*)p;
+}
 
 template <int kD, bool kFp8>
-__global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(AttnLaunch a) {
+__global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a) {
   typedef Dim<kD, kFp8> DD;
   typedef typename DD::VReg VReg;                 // one V load as it arrives
   typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
   constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
+  constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
   static_assert(kWindow % kRing == 0, "the window must be a whole number of ring turns");
   extern __shared__ int smem[];
   int* cumB = smem;                  // [S+1] blocks before request s
   int* lens = smem + (a.S + 1);      // [S]   clamped context lengths
-  // then room for rec_buffered finished records per wavefront, 16-byte aligned
+  // then, 16-byte aligned, each wavefront's left record and its right record; the right
+  // record shares its room with finished rows that wait to be stored
   const int rec_floats = record_floats(a.G, kD);
-  float* rec_stage = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3)) +
-                     (threadIdx.x >> 6) * a.rec_buffered * rec_floats;
+  float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
+  __shared__ int ends[kGroupWaves];      // kEnds* flags
+  __shared__ int left_row[kGroupWaves];   // qrow of the segment that the share's first block belongs to
+  __shared__ int right_row[kGroupWaves];  // qrow of the segment parked in the right record
+  __shared__ int any_long;
 
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
   const int G = a.G, S = a.S, Hkv = a.Hkv;
   const int bpp = a.P / kBlockTokens;   // blocks per partition
+  float* rec_left = wave_lds + wave * a.wave_lds_floats;
+  float* rec_right = rec_left + rec_floats;
+  uint16_t* staged = (uint16_t*)rec_right;
 
   // Prefix sums over the requests (wavefront 0 of every workgroup; S is small).
   if (wave == 0) {
-    int runB = 0;
+    int runB = 0, longest = 0;
     for (int base = 0; base < S; base += 64) {
       const int i = base + lane;
       const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
       const int nb = (L + kBlockTokens - 1) / kBlockTokens;
+      longest = max(longest, nb);
       int xb = nb;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -191,40 +226,77 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
       if (i < S) { lens[i] = L; cumB[i] = runB + xb - nb; }
       runB += __shfl(xb, 63);
     }
-    if (lane == 0) cumB[S] = runB;
+    const bool some_long = __any(longest > short_segment(kGroupWaves));
+    if (lane == 0) { cumB[S] = runB; any_long = some_long; }
   }
   __syncthreads();
-  if (blockIdx.x == 0) {   // the merge pass reads the same prefix array
-    for (int i = threadIdx.x; i < S + 1; i += blockDim.x) a.ws_cum[i] = smem[i];
-  }
 
-  // Every participating wavefront gets at least one block, so that consecutive
-  // runs of a segment always belong to the same or to adjacent wavefronts.
-  const int64_t T = (int64_t)Hkv * cumB[S];
-  const int W = (int)min((int64_t)a.waves, T);
-  const int w = blockIdx.x * kStreamWavesPerGroup + wave;
-  if (w >= W) return;
-  const int pos0 = (int)share_start(w, T, W);
-  const int nshare = (int)share_start(w + 1, T, W) - pos0;
+  // An empty request owes zero rows.
+  const int w = blockIdx.x * kGroupWaves + wave;
+  auto zero_empty_rows = [&]() {
+    for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
+      if (cumB[s + 1] != cumB[s]) continue;
+      uint32_t* dst = (uint32_t*)(a.out + (int64_t)s * a.Hq * kD);
+      for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
+    }
+  };
+
+  // Equal shares: every participating wavefront gets at least one block, so that consecutive
+  // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
+  // short segments is cut along the segments instead, one to a workgroup (see short_segment).
+  const int T = Hkv * cumB[S];
+  const bool whole = !any_long && S * Hkv <= (int)gridDim.x;
+  int W, first_wave, last_wave, pos0 = 0, nshare = 0;
+  if (whole) {
+    const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
+    const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
+    W = min(kGroupWaves, nb);
+    first_wave = 0;
+    last_wave = W - 1;
+    if (wave < W) {
+      const ShareMap shares(nb, W);
+      pos0 = Hkv * cumB[s] + kvh * nb + shares.start(wave);
+      nshare = shares.start(wave + 1) - shares.start(wave);
+    }
+  } else {
+    W = share_count(T, a.waves);
+    first_wave = blockIdx.x * kGroupWaves;
+    last_wave = min(kGroupWaves, W - first_wave) - 1;
+    if (w < W) {
+      const ShareMap shares(T, W);
+      pos0 = shares.start(w);
+      nshare = shares.start(w + 1) - pos0;
+    }
+  }
+  if (a.by_row && blockIdx.x == 0) {   // for the reduce pass
+    for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
+  }
+  if (last_wave < 0) {   // nothing for this workgroup
+    if (threadIdx.x == 0 && !a.by_row) shared_segment(a, blockIdx.x)->count = 0;
+    zero_empty_rows();
+    return;
+  }
 
   // Descriptors of stream indices jb .. jb+63 of this share.
   int search_steps = 0;
   while ((1 << search_steps) < S) ++search_steps;
   int refused = 0;   // table entries outside the pool met while describing this share
-  auto describe = [&](int jb) -> Window {
-    const int j = jb + lane;
-    const bool live = j < nshare;
-    const int pos = pos0 + min(j, nshare - 1);
+  auto place = [&](int pos) -> Place {
     int lo = 0, hi = S;   // largest s with Hkv * cumB[s] <= pos
     for (int it = 0; it < search_steps; ++it) {
       const int mid = (lo + hi) >> 1;
       if (mid > lo && Hkv * cumB[mid] <= pos) lo = mid; else if (mid > lo) hi = mid;
     }
-    const int s = lo;
-    const int nb = cumB[s + 1] - cumB[s];
-    const int o = pos - Hkv * cumB[s];
+    const int nb = cumB[lo + 1] - cumB[lo];
+    const int o = pos - Hkv * cumB[lo];
     const int kvh = o / nb;
-    const int b = o - kvh * nb;
+    return Place{lo, kvh, o - kvh * nb, nb};
+  };
+  auto describe = [&](int jb) -> Window {
+    const int j = jb + lane;
+    const bool live = j < nshare;
+    const Place at = place(pos0 + max(min(j, nshare - 1), 0));
+    const int s = at.s, kvh = at.kvh, b = at.b, nb = at.nb;
     int ntok = min(kBlockTokens, lens[s] - kBlockTokens * b);
     // unit b of the request lies in physical block b / upb, at unit b % upb of the KV head's rows
     const int tb = b / a.upb;
@@ -236,9 +308,9 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
     d.slab = mapped ? (id * Hkv + kvh) * a.upb + (b - tb * a.upb) : 0;
     const bool last = (b + 1 == nb) || ((b + 1) % bpp == 0) || (j + 1 == nshare);
     const bool seg_first = (b == 0) || (j == 0);
-    d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0);
+    d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0) |
+             (b + 1 == nb ? kMetaSegEnd : 0) | (b > j ? kMetaOpenLeft : 0);
     d.qrow = s * a.Hq + kvh * G;
-    d.slot = s * Hkv + kvh + w;
     return d;
   };
 
@@ -287,23 +359,23 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
     }
   };
 
-  // Finished records wait in LDS and go out several at a time, with full-width
-  // stores, and the rest when the share is done.  A store in the middle of the
-  // stream is expensive out of proportion to its size: loads and stores retire
-  // through one counter, so the KV loads issued after it cannot be consumed
-  // before it has been acknowledged, and that costs one stall of several
-  // microseconds per burst of stores however few bytes it carries.
-  int nrec = 0;        // records parked in LDS
-  int rec_slots = 0;   // lane r: slot of parked record r
-  bool seg_open = false;   // the newest parked record belongs to the segment being streamed
-  auto drain_records = [&]() {
-    for (int r = 0; r < nrec; ++r) {
-      const int slot = __builtin_amdgcn_readlane(rec_slots, r);
-      float* dst = a.ws_rec + (int64_t)slot * rec_floats;
-      const float* src = rec_stage + r * rec_floats;
-      for (int f = 4 * lane; f < rec_floats; f += 256) store_record16(dst + f, *(const f32x4*)(src + f));
+  // Finished rows wait in LDS and go out several segments at a time, and the rest when
+  // the share is done.  A store in the middle of the stream is expensive out of
+  // proportion to its size: loads and stores retire through one counter, so the KV loads
+  // issued after it cannot be consumed before it has been acknowledged, and that costs one
+  // stall of several microseconds per burst of stores however few bytes it carries.
+  int nstaged = 0;       // finished segments whose rows are in LDS
+  int staged_rows = 0;   // lane r: first output row of staged segment r
+  bool seg_open = false;   // a parked record belongs to the segment being streamed
+  int ends_flags = 0, left_q = 0, right_q = 0;   // as left in LDS for the merge
+  auto store_staged = [&]() {
+    for (int r = 0; r < nstaged; ++r) {
+      const int qrow = __builtin_amdgcn_readlane(staged_rows, r);
+      float* dst = (float*)(a.out + (int64_t)qrow * kD);
+      const float* src = (const float*)(staged + r * G * kD);
+      for (int f = 4 * lane; f < G * kD / 2; f += 256) store16(dst + f, *(const u32x4*)(src + f));
     }
-    nrec = 0;
+    nstaged = 0;
   };
 
   auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int j) {
@@ -424,21 +496,18 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
     }
 
     if (meta & kMetaLast) {
-      // The run ends here.  The first run of a (request, KV head) in this share
-      // parks its partial result in LDS as a new record, assembled in its memory
-      // order; every later run of the same segment (the next P-token partitions)
-      // is folded into that parked record with the split-K merge formula, so
-      // memory sees one record per (wavefront, segment) however small P is.
+      // The run ends here.  A segment that lies wholly inside the share is finished now:
+      // its rows are normalised, rounded and staged.  Of a segment that other wavefronts
+      // share, or of which more partitions follow, the partial result is parked in a
+      // record in LDS (the left one when the segment begins before the share, else the
+      // right one); a later run of the same segment (the next P-token partition) is folded
+      // into it with the split-K merge formula, so there is one record per (wavefront,
+      // segment) however small P is.
+      const bool open_left = meta & kMetaOpenLeft;
+      const bool done = (meta & kMetaSegEnd) && !open_left;
+      float* rec = open_left ? rec_left : rec_right;
       float lt = l + __shfl_xor(l, 16);
       lt += __shfl_xor(lt, 32);
-      if (!seg_open) {
-        if (nrec == a.rec_buffered) drain_records();
-        const int slot = __builtin_amdgcn_readlane(dA.slot, idx);
-        rec_slots = (lane == nrec) ? slot : rec_slots;
-        ++nrec;
-      }
-      float* rec = rec_stage + (nrec - 1) * rec_floats;
-      float keep[4] = {0.f, 0.f, 0.f, 0.f}, add[4] = {1.f, 1.f, 1.f, 1.f};
       if (seg_open) {
         // parked (m1, l1, rows1) and this run's (m, lt, o): weights 2^(m1-M) and 2^(m-M),
         // a side whose maximum is -inf (nothing valid seen) gets weight 0 by select
@@ -450,28 +519,55 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
         m = M;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          keep[r] = __shfl(w1, 4 * c + r);
-          add[r] = __shfl(w2, 4 * c + r);
-        }
-      }
+          const float keep = __shfl(w1, 4 * c + r), add = __shfl(w2, 4 * c + r);
+          if (4 * c + r < G) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int h = 4 * c + r;
-        if (h < G) {
+            for (int t = 0; t < kTiles / 4; ++t) {
+              const f32x4 p4 = *(const f32x4*)(rec + (4 * c + r) * kD + tile_group_dim<kD>(t, n));
 #pragma unroll
-          for (int t = 0; t < kTiles / 4; ++t) {
-            f32x4* dst = (f32x4*)(rec + h * kD + tile_group_dim<kD>(t, n));
-            f32x4 x4 = {o[4 * t][r], o[4 * t + 1][r], o[4 * t + 2][r], o[4 * t + 3][r]};
-            if (seg_open) {
-              const f32x4 p4 = *dst;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) x4[e] = keep[r] * p4[e] + add[r] * x4[e];
+              for (int e = 0; e < 4; ++e) o[4 * t + e][r] = keep * p4[e] + add * o[4 * t + e][r];
             }
-            *dst = x4;
           }
         }
       }
-      if (c == 0) *(f32x2*)(rec + G * kD + 2 * n) = (n < G) ? f32x2{m, lt} : f32x2{kNegInf, 0.f};
+      if (done) {
+        if (nstaged == a.staged_max) store_staged();
+        const int qrow = __builtin_amdgcn_readlane(dA.qrow, idx);
+        staged_rows = (lane == nstaged) ? qrow : staged_rows;
+        uint16_t* rows = staged + nstaged * G * kD;
+        const float inv = inverse(lt, a.out_scale);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int h = 4 * c + r;
+          const float f = __shfl(inv, h);
+          if (h < G) {
+#pragma unroll
+            for (int t = 0; t < kTiles / 4; ++t)
+              *(u32x2*)(rows + h * kD + tile_group_dim<kD>(t, n)) =
+                  finish_row4(f32x4{o[4 * t][r], o[4 * t + 1][r], o[4 * t + 2][r], o[4 * t + 3][r]}, f);
+          }
+        }
+        ++nstaged;
+        ends_flags &= ~kEndsRight;
+      } else {
+        if (!open_left) store_staged();   // the staged rows lie where the record goes
+        const int qrow = __builtin_amdgcn_readlane(dA.qrow, idx);
+        ends_flags = !open_left ? ends_flags | kEndsRight
+                     : (meta & kMetaSegEnd) ? kEndsLeft : kEndsLeft | kEndsThrough;
+        left_q = open_left ? qrow : left_q;
+        right_q = open_left ? right_q : qrow;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int h = 4 * c + r;
+          if (h < G) {
+#pragma unroll
+            for (int t = 0; t < kTiles / 4; ++t)
+              *(f32x4*)(rec + h * kD + tile_group_dim<kD>(t, n)) =
+                  f32x4{o[4 * t][r], o[4 * t + 1][r], o[4 * t + 2][r], o[4 * t + 3][r]};
+          }
+        }
+        if (c == 0) *(f32x2*)(rec + G * kD + 2 * n) = (n < G) ? f32x2{m, lt} : f32x2{kNegInf, 0.f};
+      }
       seg_open = true;
       m = kNegInf;
       l = 0.f;
@@ -502,33 +598,115 @@ __global__ __launch_bounds__(kStreamWavesPerGroup * 64) void attn_stream_kernel(
       dB = describe(jbase + kWindow);
     }
   }
-  drain_records();
+  store_staged();
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
+  zero_empty_rows();
+
+  // The workgroup's merge.  Segments that meet inside the workgroup's range are finished from
+  // the records in LDS.  What is left are at most two segments that it shares with other
+  // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
+  // shared segment begins in leaves word of it.
+  const AttnLaunch& b = reread(a);
+  if (b.by_row && !whole) {
+    // Few segments: nearly all of them are shared by many wavefronts, and the reduce pass has a
+    // workgroup for every row, so each wavefront's records go to memory as they are.
+    auto store_record = [&](const float* rec, int qrow) {
+      float* dst = wave_record(b, kD, qrow / G, w);
+      for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
+    };
+    if (ends_flags & kEndsLeft) store_record(rec_left, left_q);
+    if (ends_flags & kEndsRight) store_record(rec_right, right_q);
+    return;
+  }
+  if (lane == 0) { ends[wave] = ends_flags; left_row[wave] = left_q; right_row[wave] = right_q; }
+  if (wave == 0) {   // the first to finish, as a rule
+    // The segment of the workgroup's last block: does it begin here and go on elsewhere?
+    int row = 0, count = 0;
+    if (!whole && first_wave + kGroupWaves < W) {
+      const ShareMap shares(T, W);
+      const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
+      const Place at = place(next - 1);
+      const int seg_pos = next - 1 - at.b;
+      if (seg_pos >= begin && seg_pos + at.nb > next) {
+        row = at.s * b.Hq + at.kvh * G;
+        count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
+      }
+    }
+    if (lane == 0 && !b.by_row) *shared_segment(b, blockIdx.x) = SharedSegment{row, count};
+  }
+  __syncthreads();
+  const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
+  // One chain of LDS records per wavefront v whose left record ends its segment or is the
+  // workgroup's last, and one for the last wavefront's right record.
+#pragma unroll 1
+  for (int i = threadIdx.x; i < (kGroupWaves + 1) * q4; i += kThreads) {
+    const int chain = i / q4, item = i - chain * q4;
+    const bool right_only = chain == kGroupWaves;
+    const int v = right_only ? last_wave : chain;
+    if (v > last_wave) continue;
+    const int e = ends[v];
+    int u = v;
+    bool from_right = true;   // the chain begins with wavefront u's right record
+    if (right_only) {
+      if (!(e & kEndsRight)) continue;
+    } else {
+      if (!(e & kEndsLeft) || ((e & kEndsThrough) && v != last_wave)) continue;
+      u = v - 1;
+      while (u >= 0 && (ends[u] & kEndsThrough)) --u;
+      if (u < 0) { u = 0; from_right = false; }
+    }
+    const bool open_right = right_only || (e & kEndsThrough);
+    const int h = item / (kD / 4);
+    Partial p = kNothing;
+#pragma unroll 1
+    for (int k = u; k <= v; k += 2) {
+      const float* rec0 = wave_lds + k * b.wave_lds_floats + (k == u && from_right ? rec_floats : 0);
+      const float* rec1 = wave_lds + min(k + 1, v) * b.wave_lds_floats;
+      f32x2 ml[2] = {*(const f32x2*)(rec0 + G * kD + 2 * h), *(const f32x2*)(rec1 + G * kD + 2 * h)};
+      const f32x4 x[2] = {*(const f32x4*)(rec0 + 4 * item), *(const f32x4*)(rec1 + 4 * item)};
+      if (k == v) ml[1].x = kNegInf;
+      fold(p, ml, x);
+    }
+    if (from_right && !open_right) {
+      *(u32x2*)(b.out + (int64_t)left_row[v] * kD + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+    } else {
+      float* rec = group_record(b, kD, blockIdx.x, from_right);
+      store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));
+      if (item % (kD / 4) == 0) *(f32x2*)(rec + G * kD + 2 * h) = f32x2{p.m, p.l};
+    }
+  }
 }
 
 }  // namespace
 
+template <int kD, bool kFp8>
+static void launch_one(const AttnLaunch& a, size_t lds, hipStream_t stream) {
+  hipLaunchKernelGGL((attn_stream_kernel<kD, kFp8>), dim3(a.waves / group_waves(kD)),
+                     dim3(group_waves(kD) * 64), lds, stream, a);
+}
+
 hipError_t launch_attn_stream(const AttnLaunch& a_in, hipStream_t stream) {
   AttnLaunch a = a_in;
-  // LDS per workgroup: the prefix arrays, then as many parked records per
-  // wavefront as fit in 64 KiB (at most 8).
-  const size_t cum_bytes = (size_t)((2 * (a.S + 1) + 3) & ~3) * sizeof(int);
-  const size_t rec_bytes = (size_t)record_floats(a.G, a.D) * sizeof(float);
-  const size_t room = (size_t)64 * 1024 - cum_bytes;
-  a.rec_buffered = (int)(room / (kStreamWavesPerGroup * rec_bytes));
-  if (a.rec_buffered > 8) a.rec_buffered = 8;
-  if (a.rec_buffered < 1) return hipErrorInvalidValue;
-  const size_t lds = cum_bytes + (size_t)kStreamWavesPerGroup * a.rec_buffered * rec_bytes;
-  const dim3 grid(a.waves / kStreamWavesPerGroup), block(kStreamWavesPerGroup * 64);
+  const int group = group_waves(a.D);
+  // LDS per workgroup: the prefix arrays, then per wavefront a left record and room for a
+  // right record or up to 8 finished segments' rows, as long as two workgroups fit a CU.
+  const int cum = (2 * (a.S + 1) + 3) & ~3;
+  const int rec = record_floats(a.G, a.D), rows = a.G * a.D / 2;   // in 4-byte units
+  const int budget = (78 * 256 - cum) / group - rec;
+  int room = budget < 8 * rows ? budget : 8 * rows;
+  if (room < rec) room = rec;
+  a.staged_max = room / rows;
+  a.wave_lds_floats = rec + room;
+  const size_t lds = (size_t)(cum + group * a.wave_lds_floats) * sizeof(float);
   if (a.kv_fp8) {
-    if (a.D == 64) hipLaunchKernelGGL((attn_stream_kernel<64, true>), grid, block, lds, stream, a);
-    else if (a.D == 128) hipLaunchKernelGGL((attn_stream_kernel<128, true>), grid, block, lds, stream, a);
-    else if (a.D == 256) hipLaunchKernelGGL((attn_stream_kernel<256, true>), grid, block, lds, stream, a);
+    if (a.D == 64) launch_one<64, true>(a, lds, stream);
+    else if (a.D == 128) launch_one<128, true>(a, lds, stream);
+    else if (a.D == 256) launch_one<256, true>(a, lds, stream);
     else return hipErrorInvalidValue;
-  } else if (a.D == 64) hipLaunchKernelGGL((attn_stream_kernel<64, false>), grid, block, lds, stream, a);
-  else if (a.D == 128) hipLaunchKernelGGL((attn_stream_kernel<128, false>), grid, block, lds, stream, a);
-  else if (a.D == 256) hipLaunchKernelGGL((attn_stream_kernel<256, false>), grid, block, lds, stream, a);
+  } else if (a.D == 64) launch_one<64, false>(a, lds, stream);
+  else if (a.D == 128) launch_one<128, false>(a, lds, stream);
+  else if (a.D == 256) launch_one<256, false>(a, lds, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

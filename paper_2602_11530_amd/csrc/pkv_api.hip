@@ -69,7 +69,7 @@ int check_shape(const pkv_attn_shape* sh, Geometry* g) {
   g->G = G;
   g->P = P;
   g->max_ctx = max_ctx;
-  // one record per (wavefront, request, KV head) that meet: slot = segment + wavefront
+  // at most one record per (wavefront, request, KV head) that meet
   g->slots = (int64_t)sh->num_kv_heads * sh->num_seqs + pkv::kStreamWaves;
   return PKV_OK;
 }
@@ -200,6 +200,15 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->D = shape->head_dim;
   // a D = 256 wavefront needs the registers of a whole SIMD lane: one wavefront per SIMD
   a->waves = shape->head_dim == 256 ? pkv::kStreamWaves / 2 : pkv::kStreamWaves;
+  // A small bound on the blocks (or the segments, when a batch is cut along those) needs no more
+  // workgroups; the shares are the same either way.
+  const int group = pkv::group_waves(shape->head_dim);
+  const int64_t segments = (int64_t)a->S * a->Hkv;
+  const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
+  const int64_t bound = segments * max_blocks > group * segments ? segments * max_blocks : group * segments;
+  if (bound < a->waves) a->waves = (int)(bound + group - 1) / group * group;
+  a->by_row = segments <= pkv::kRowSegments;
+  a->one_pass = segments <= a->waves / group && max_blocks <= pkv::short_segment(group);
   a->id_faults = g_id_faults;
   a->MAXB = shape->max_blocks_per_seq;
   a->upb = shape->block_size / pkv::kBlockTokens;
@@ -209,10 +218,8 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->scale_log2e = scale * 1.4426950408889634f;
   a->out_scale = 1.f;
   a->kv_fp8 = 0;
-  const WorkspaceLayout lay = workspace_layout(shape, g);
-  char* ws = static_cast<char*>(workspace);
-  a->ws_rec = reinterpret_cast<float*>(ws);
-  a->ws_cum = reinterpret_cast<int32_t*>(ws + lay.rec_bytes);
+  a->ws_rec = static_cast<float*>(workspace);
+  a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
   return PKV_OK;
 }
 
@@ -230,8 +237,7 @@ static int launch_layer(pkv::AttnLaunch& a, const void* q, const void* k_pool, c
   a.v_pool = v_pool;
   a.out = static_cast<uint16_t*>(out);
   hipError_t e = pkv::launch_attn_stream(a, st);
-  if (e != hipSuccess) return launch_status(e);
-  e = pkv::launch_attn_reduce(a, st);
+  if (e == hipSuccess && !a.one_pass) e = pkv::launch_attn_reduce(a, st);
   if (e != hipSuccess) return launch_status(e);
   return PKV_OK;
 }

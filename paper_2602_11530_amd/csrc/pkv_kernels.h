@@ -36,23 +36,63 @@ constexpr int kStreamWaves = kStreamGroups * kStreamWavesPerGroup;
 //   A run is a maximal stretch of one wavefront's share inside one segment and
 //   one partition (P tokens of the request); every run yields one partial result
 //   (max, sum, un-normalised row) per query head of the group.  The runs of one
-//   segment inside one share are folded into one record before it leaves the
-//   wavefront, stored at
+//   segment inside one share are folded together.  A segment that lies wholly
+//   inside a share is finished there; of any other the wavefront leaves a record.
+//   In a batch of few segments (by_row) it is stored at
 //       slot = s * Hkv + kvh + w,
 //   which is unique and increases along the stream (from one record to the next
 //   the segment, the wavefront or both advance), so the records of a segment are
 //   the consecutive slots from (its index + the owner of its first block) to
 //   (its index + the owner of its last block); slots skipped where a share and a
-//   segment end together belong to nobody and are never read.
-__host__ __device__ inline int64_t share_start(int64_t w, int64_t T, int64_t W) { return w * T / W; }
-// The wavefront whose share holds position pos.
-__host__ __device__ inline int share_owner(int64_t pos, int64_t T, int64_t W) {
-  return (int)(((pos + 1) * W - 1) / T);
+//   segment end together belong to nobody and are never read.  In a larger batch the
+//   wavefronts of a workgroup fold their records in LDS, finish the segments that lie
+//   inside the workgroup's range and leave one record for each of the two segments
+//   that may cross its ends (group_record); the workgroup in which a crossing segment
+//   begins leaves word of it (SharedSegment).
+//
+// Shares begin at floor(w * T / W), so that the longer ones are spread evenly over the compute
+// units: with the longer ones first, the units that hold them end last (1.5 % on 64 requests of
+// 1024..8192 tokens, whose shares have 70 and 71 blocks).  In 32 bits, and with shifts where W is
+// a power of two, which a full launch's is: both functions sit on short critical chains.
+struct ShareMap {
+  uint32_t T, W, len, more;   // more of the W shares have len + 1 positions
+  __host__ __device__ ShareMap(uint32_t T_, uint32_t W_) : T(T_), W(W_), len(div(T_)), more(T_ - len * W_) {}
+  __host__ __device__ uint32_t div(uint32_t x) const { return (W & (W - 1)) == 0 ? x >> __builtin_ctz(W) : x / W; }
+  __host__ __device__ uint32_t start(uint32_t w) const { return w * len + div(w * more); }   // W <= 2^16
+  // The wavefront whose share holds position pos: an estimate that is off by less than one, put right.
+  __host__ __device__ uint32_t owner(uint32_t pos) const {
+    uint32_t w = (uint32_t)((float)pos * ((float)W / (float)T));
+    w = w < W ? w : W - 1;
+    const uint32_t at = start(w), next = start(w + 1);
+    return at > pos ? w - 1 : next <= pos ? w + 1 : w;
+  }
+};
+__host__ __device__ inline int64_t share_start(int64_t w, int64_t T, int64_t W) {
+  return ShareMap((uint32_t)T, (uint32_t)W).start((uint32_t)w);
 }
+__host__ __device__ inline int share_owner(int64_t pos, int64_t T, int64_t W) {
+  return (int)ShareMap((uint32_t)T, (uint32_t)W).owner((uint32_t)pos);
+}
+// Wavefronts that take part.
+__host__ __device__ inline int share_count(int T, int waves) { return T < waves ? T : waves; }
+// Wavefronts per workgroup: a compute unit's worth.
+__host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; }
 
 // One partial record: G un-normalised rows of D floats, then (reference max in
 // log2 units, partial sum) for up to kMaxGroup heads.  Rows are 16-byte multiples.
 __host__ __device__ inline int record_floats(int G, int D) { return G * D + 2 * kMaxGroup; }
+
+// A batch whose segments all fit one workgroup each (at most kStreamGroups / 2 segments, none
+// longer than this many blocks) is cut along the segments.
+__host__ __device__ constexpr int short_segment(int group_waves) { return 6 * group_waves; }
+// Up to this many segments the reduce pass goes by rows.
+constexpr int kRowSegments = 64;
+
+// A segment that several workgroups share, as the workgroup that it begins in leaves it.
+struct SharedSegment {
+  int row;     // first output row
+  int count;   // workgroups that share it, 0 when there is none
+};
 
 struct AttnLaunch {
   const uint16_t* q;
@@ -62,7 +102,9 @@ struct AttnLaunch {
   const int32_t* context_lens;
   uint16_t* out;
   float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
-  int32_t* ws_cum; // [S + 1] cumB, written by the stream pass for the merge
+  int32_t* ws_cum; // [S + 1] by_row: cumB for the reduce pass (the first one -1 when it has nothing to do)
+  int by_row;      // few segments: the reduce pass has a workgroup per row
+  int one_pass;    // the bounds alone say that no segment will be shared: no reduce pass
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
   float out_scale;     // applied to the normalised row: 1, or the V pool's scale
   int kv_fp8;          // the pools hold one-byte e4m3 values
@@ -74,12 +116,26 @@ struct AttnLaunch {
   int P;           // partition size, tokens
   int max_ctx;     // context lengths are clamped to [0, max_ctx] (<= MAXB * 16)
   int NB;          // physical blocks per pool; ids outside [0, NB) are never followed
-  int rec_buffered; // finished records a wavefront keeps in LDS before writing them out (>= 1)
+  int wave_lds_floats;  // a wavefront's share of LDS: its left record, then its right record or staged rows
+  int staged_max;       // finished segments whose rows a wavefront can stage in LDS
 };
+
+// The workspace of a batch of few segments (by_row): a record per (wavefront, shared segment).
+__host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int segment, int wave) {
+  return a.ws_rec + (int64_t)(segment + wave) * record_floats(a.G, D);
+}
+// Of any other batch: two records per workgroup of the stream pass (of the shared segment that begins in
+// it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.
+__host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int group, bool begins_here) {
+  return a.ws_rec + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
+}
+__host__ __device__ inline SharedSegment* shared_segment(const AttnLaunch& a, int group) {
+  return (SharedSegment*)(a.ws_rec + (int64_t)kStreamWaves / 4 * record_floats(a.G, a.D)) + group;
+}
 
 // Stream pass: kStreamWaves persistent wavefronts, each writing its runs' partial records.
 hipError_t launch_attn_stream(const AttnLaunch& a, hipStream_t stream);
-// Merge: one wavefront per (request, query head).
+// Reduce pass: the segments that several workgroups share, from their records.
 hipError_t launch_attn_reduce(const AttnLaunch& a, hipStream_t stream);
 
 // Whole-block copies; `gather` selects the direction.

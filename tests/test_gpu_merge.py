@@ -1,0 +1,91 @@
+"""GPU tests of the merge inside the stream pass: segments that lie in one wavefront's share, in one
+workgroup, in a few workgroups and in more than one workgroup reads at once (two levels), on workspaces
+whose earlier contents vary, called repeatedly and replayed from a graph."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import MAX_ABS, REL_L2, abs_error_within_bar, device_tensors, run_attn_dev, shape_of, to_bits, to_dev
+from paper_2602_11530_amd import binding as pkv
+from paper_2602_11530_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# lengths, query heads, KV heads, head dim: how many workgroups (of 2048/8, or 1024/4 at D = 256) share a segment
+SHAPES = [
+    ([33000], 8, 1, 128),            # all 256: two levels
+    ([17000, 16000], 8, 2, 64),      # 64 each, and a boundary inside a workgroup
+    ([9000, 1, 20000], 5, 1, 256),   # two long segments and a one-block one between them
+    ([4200] * 8, 16, 1, 128),        # 32 each: the most that are read in one go
+    ([4300] * 7 + [2000], 16, 1, 128),   # just beyond it
+    ([2048] * 64, 8, 4, 128),        # shares and segments end together: nothing is shared
+    ([1, 16, 17, 0, 33] * 60, 10, 2, 64),    # many segments inside one share
+    ([16] * 700 + [30000], 12, 1, 128),      # staged rows fill up; then one long segment
+    ([700, 0, 5000, 3, 129], 40, 8, 128),
+    ([768, 0, 1, 130, 17], 8, 2, 128),       # cut along the segments: the longest that is (6 blocks per wavefront)
+    ([769, 0, 1, 130, 17], 8, 2, 128),       # and one token beyond
+    ([384, 16, 15, 0], 8, 1, 256),
+    ([385, 16, 15, 0], 8, 1, 256),
+    ([768, 5, 300, 0] * 8, 32, 8, 64),       # as many segments as workgroups
+    ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
+    ([2000, 30] * 4, 8, 8, 64),              # the fewest segments that one launch finishes
+    ([2000, 30] * 4, 7, 7, 64),
+]
+
+
+def setup(lens, hq, hkv, dim, seed):
+    w = wl.custom(lens, hq, hkv, head_dim=dim, seed=seed)
+    q, k, v = device_tensors(w)
+    return w, (q.view(torch.int16), k.view(torch.int16), v.view(torch.int16), to_dev(w.block_tables), to_dev(w.context_lens))
+
+
+def reference(w, dev):
+    host = [to_bits(t).reshape(s) for t, s in zip(dev[:3], (w.q_shape(), w.pool_shape(), w.pool_shape()))]
+    return oracle.paged_decode_attn(*host, w.block_tables, w.context_lens, w.scale)
+
+
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+@pytest.mark.parametrize("partition", [0, 64])
+def test_shared_segments(device, i, partition):
+    w, dev = setup(*SHAPES[i], seed=300 + i)
+    shape = shape_of(w, partition)
+    ws = torch.full((pkv.pkv_attn_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device=device)
+    first = to_bits(run_attn_dev(w, *dev, partition_size=partition, workspace=ws))
+    ref = reference(w, dev)
+    c = oracle.compare(first, ref)
+    assert abs_error_within_bar(first, ref) and c["rel_l2"] <= REL_L2, c
+    for fill in (None, 0, "noise"):
+        if fill == 0:
+            ws.zero_()
+        elif fill:
+            ws.random_(0, 256)
+        again = to_bits(run_attn_dev(w, *dev, partition_size=partition, workspace=ws))
+        assert np.array_equal(first, again)   # whoever finishes a segment, its rows are the same bits
+
+
+def test_replays_with_growing_lengths(device):
+    """A replayed launch carries the same number as the one before it: nothing of that one may be left over."""
+    w, (q, k, v, tables, lens) = setup([40, 3000, 9, 12000], 8, 1, 128, seed=400)
+    w.context_lens[:] = [17, 16, 9, 33]
+    lens.copy_(torch.from_numpy(w.context_lens))
+    shape = shape_of(w)
+    ws = torch.empty(pkv.pkv_attn_workspace_bytes(shape), dtype=torch.uint8, device=device)
+    out = torch.empty(w.q_shape(), dtype=torch.int16, device=device)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pkv.paged_decode_attn(q, k, v, tables, lens, float(w.scale), out, shape, ws, torch.cuda.current_stream())
+    for step in ([17, 16, 9, 33], [40, 3000, 9, 12000], [1, 2900, 0, 12000], [40, 0, 0, 700], [40, 3000, 9, 11999]):
+        w.context_lens[:] = step
+        lens.copy_(torch.from_numpy(w.context_lens))
+        out.fill_(0x7FC1)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = to_bits(out)
+        eager = to_bits(run_attn_dev(w, q, k, v, tables, lens))
+        assert np.array_equal(got, eager), step
+        ref = reference(w, (q, k, v))
+        c = oracle.compare(got, ref)
+        assert c["max_abs"] <= MAX_ABS and c["rel_l2"] <= REL_L2, (step, c)
