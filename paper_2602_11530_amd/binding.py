@@ -53,11 +53,18 @@ class PkvError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
+_raw_stream = None   # () -> handle of the current stream, where this torch has the lookups
+
+
+def _find_raw_stream(torch):
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return (lambda: stream(device())) if device and stream else None
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises if it is missing."""
-    global _lib
+    global _lib, _raw_stream
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -66,7 +73,7 @@ def lib() -> ctypes.CDLL:
         # PyTorch owns the device memory and the streams this library is handed,
         # so both must sit on one HIP runtime: load torch (and with it the
         # runtime it ships) before libpkv.so resolves its own dependency.
-        import torch  # noqa: F401
+        import torch
         L = ctypes.CDLL(LIB_PATH)
         vp, i64, i32p = ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p
         shp = ctypes.POINTER(AttnShape)
@@ -107,6 +114,7 @@ def lib() -> ctypes.CDLL:
         L.kv_append_fp8.restype = ctypes.c_int
         L.kv_append.argtypes = [vp, vp, vp, vp, i32p, i32p, shp, vp]
         L.kv_append.restype = ctypes.c_int
+        _raw_stream = _find_raw_stream(torch)
         _lib = L
     return _lib
 
@@ -126,10 +134,17 @@ def _ptr(t) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    h = int(getattr(stream, "cuda_stream", stream))
-    return h or None
+        return _current_stream() or None
+    return int(getattr(stream, "cuda_stream", stream)) or None
+
+
+def _current_stream() -> int:
+    """Handle of the current device's current stream.  ``torch.cuda.current_stream()`` builds a Stream
+    object for it, 2.8 us of a call's 4.5 on the host; the two lookups below are 0.2 us."""
+    import torch
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
 
 
 def pkv_set_id_fault_counter(counter) -> None:
