@@ -20,8 +20,6 @@ namespace {
 // a cached image only evicts itself (8 % slower than streaming at 370 MB), so
 // larger images are streamed with nontemporal accesses on both sides.
 constexpr int kCopyThreads = 256;
-constexpr int kChunksPerThread = 8;                               // 16-byte chunks
-constexpr int kChunksPerGroup = kCopyThreads * kChunksPerThread;  // 32 KiB per workgroup
 constexpr int64_t kCachedStagingBytes = (int64_t)256 << 20;       // staging images up to this size stay on chip
 
 enum Policy { kStream, kPlain, kWriteThrough };
@@ -41,54 +39,47 @@ __device__ __forceinline__ void st16(u32x4* p, u32x4 v) {
   else *p = v;
 }
 
-// One workgroup moves one slice (kChunksPerGroup chunks of one block): all
-// loads first, then all stores.
-template <int kLd, int kSt>
-__device__ __forceinline__ void copy_slice(const u32x4* __restrict__ s, u32x4* __restrict__ d,
-                                           int64_t slice, int64_t chunks_per_block) {
-  const int64_t c0 = slice * kChunksPerGroup + threadIdx.x;
-  if ((slice + 1) * kChunksPerGroup <= chunks_per_block) {
-    // Whole slice inside the block (always, for 32 KiB blocks): all loads are
-    // issued before the first store, with no per-lane guard in the way.
-    u32x4 v[kChunksPerThread];
-#pragma unroll
-    for (int u = 0; u < kChunksPerThread; ++u) v[u] = ld16<kLd>(s + c0 + (int64_t)u * kCopyThreads);
-#pragma unroll
-    for (int u = 0; u < kChunksPerThread; ++u) st16<kSt>(d + c0 + (int64_t)u * kCopyThreads, v[u]);
-  } else {
-    // Ragged last slice of an odd block size.
-    for (int u = 0; u < kChunksPerThread; ++u) {
-      const int64_t c = c0 + (int64_t)u * kCopyThreads;
-      if (c < chunks_per_block) st16<kSt>(d + c, ld16<kLd>(s + c));
-    }
-  }
-}
-
-// kMode 0: staging[i] = pool[ids_a[i]]; 1: pool[ids_a[i]] = staging[i];
-// 2: dst[ids_b[i]] = src[ids_a[i]].  A unit is one slice of one listed block;
-// the physical ids are wave-uniform, so the pool-side base address is scalar;
-// byte offsets are 64-bit (a pool passes 2 GiB at the long-context sizes).
-template <int kMode, bool kCachedStaging>
+// The listed blocks, one after the other, are one row of 16-byte chunks, and a lane moves one of them:
+// a copy lives on how many of its loads the chip has under way and how evenly they fall on the memory
+// channels, and 4 KiB slices dealt round the compute dies do both better than the 32 KiB slices (eight
+// chunks per lane, all loads before the first store) that stood here before.  Measured on image
+// sizes from 0.25 to 800 MB and blocks from 2 to 128 KiB: 128 KiB blocks, 800 MB: move 327 -> 272 us,
+// scatter 320 -> 273; 32 KiB blocks: scatter 321 -> 301, gather 280 -> 270, move 329 -> 333; 2 KiB blocks,
+// 150 MB: 82 -> 66; 5 MB of 16 KiB blocks, which a 32 KiB slice left to 320 workgroups that moved one chunk
+// after the other: 5.4 -> 4.4 us.  Two and four chunks per lane lie between.
+//
+// kMode 0: staging[i] = pool[ids_a[i]]; 1: pool[ids_a[i]] = staging[i]; 2: dst[ids_b[i]] = src[ids_a[i]].
+// kWhole: a block is a whole number of slices, so the ids are the same for the workgroup and the
+// base addresses scalar; otherwise each lane looks its chunk's block up.  Byte offsets are 64-bit (a
+// pool passes 2 GiB at the long-context sizes).
+template <int kMode, bool kCachedStaging, bool kWhole>
 __global__ __launch_bounds__(kCopyThreads) void kv_block_copy_kernel(
     const u32x4* __restrict__ src, u32x4* __restrict__ dst, const int32_t* __restrict__ ids_a,
-    const int32_t* __restrict__ ids_b, int64_t chunks_per_block, int64_t src_pool_blocks,
-    int64_t dst_pool_blocks, int64_t n_blocks, int slices, int32_t* __restrict__ id_faults) {
-  const int64_t n_units = n_blocks * slices;
-  for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x) {
-    const int64_t i = u / slices, slice = u - i * slices;
-    int64_t from = i, to = i;
-    if (kMode == 0 || kMode == 2) from = ids_a[i];
-    if (kMode == 1) to = ids_a[i];
-    if (kMode == 2) to = ids_b[i];
+    const int32_t* __restrict__ ids_b, uint32_t chunks_per_block, int64_t src_pool_blocks,
+    int64_t dst_pool_blocks, int64_t n_blocks, int64_t slices, int32_t* __restrict__ id_faults) {
+  constexpr int kLd = (kMode == 1 && kCachedStaging) ? kPlain : kStream;
+  constexpr int kSt = (kMode == 0 && kCachedStaging) ? kWriteThrough : kStream;
+  for (int64_t slice = blockIdx.x; slice < slices; slice += gridDim.x) {
+    int64_t i;         // listed block
+    uint32_t chunk;    // within it
+    if (kWhole) {
+      const uint32_t per = chunks_per_block / kCopyThreads;
+      i = slices >> 32 ? slice / per : (int64_t)((uint32_t)slice / per);
+      chunk = (uint32_t)(slice - i * per) * kCopyThreads + threadIdx.x;
+    } else {
+      const int64_t c = slice * kCopyThreads + threadIdx.x;
+      i = (slices * kCopyThreads) >> 32 ? c / chunks_per_block : (int64_t)((uint32_t)c / chunks_per_block);
+      chunk = (uint32_t)(c - i * chunks_per_block);
+      if (i >= n_blocks) continue;
+    }
+    const int64_t from = kMode == 1 ? i : ids_a[i];
+    const int64_t to = kMode == 0 ? i : kMode == 1 ? ids_a[i] : ids_b[i];
     if (from < 0 || from >= src_pool_blocks || to < 0 || to >= dst_pool_blocks) {
       // never follow a corrupt id; the skipped block is reported once
-      if (id_faults && slice == 0 && threadIdx.x == 0) atomicAdd(id_faults, 1);
+      if (id_faults && chunk == 0) atomicAdd(id_faults, 1);
       continue;
     }
-    constexpr int kLd = (kMode == 1 && kCachedStaging) ? kPlain : kStream;
-    constexpr int kSt = (kMode == 0 && kCachedStaging) ? kWriteThrough : kStream;
-    copy_slice<kLd, kSt>(src + from * chunks_per_block, dst + to * chunks_per_block, slice,
-                         chunks_per_block);
+    st16<kSt>(dst + to * chunks_per_block + chunk, ld16<kLd>(src + from * chunks_per_block + chunk));
   }
 }
 
@@ -96,19 +87,21 @@ template <int kMode>
 hipError_t launch(const void* src, void* dst, const int32_t* ids_a, const int32_t* ids_b,
                   int64_t src_pool_blocks, int64_t dst_pool_blocks, int64_t n_blocks,
                   int64_t block_bytes, int32_t* id_faults, hipStream_t stream) {
-  const int64_t chunks = block_bytes / 16;
-  const int64_t slices = (chunks + kChunksPerGroup - 1) / kChunksPerGroup;
-  const int64_t units = n_blocks * slices;
-  // one workgroup per slice (the hardware dispatcher balances them better than a
-  // persistent grid did: 5.4 against 5.2-5.3 TB/s); a list of more than kMaxGroups slices
-  // (256 GiB of 32 KiB slices, or very many tiny blocks) is walked with a stride, which
-  // keeps the launch below 2^32 work-items
+  const int64_t chunks = block_bytes / 16;   // at most 2^26
+  const int64_t slices = (n_blocks * chunks + kCopyThreads - 1) / kCopyThreads;
+  // one workgroup per slice (the hardware dispatcher balances them better than a persistent grid
+  // did); a list of more than kMaxGroups slices (32 GiB) is walked with a stride, which keeps the
+  // launch below 2^32 work-items
   constexpr int64_t kMaxGroups = (int64_t)1 << 23;
-  const dim3 grid((unsigned)(units > kMaxGroups ? kMaxGroups : units));
+  const dim3 grid((unsigned)(slices > kMaxGroups ? kMaxGroups : slices));
   const bool cached = kMode != 2 && n_blocks * block_bytes <= kCachedStagingBytes;
-  auto kernel = cached ? kv_block_copy_kernel<kMode, true> : kv_block_copy_kernel<kMode, false>;
+  const bool whole = chunks % kCopyThreads == 0;
+  auto kernel = cached ? (whole ? kv_block_copy_kernel<kMode, kMode != 2, true>
+                                : kv_block_copy_kernel<kMode, kMode != 2, false>)
+                       : (whole ? kv_block_copy_kernel<kMode, false, true>
+                                : kv_block_copy_kernel<kMode, false, false>);
   hipLaunchKernelGGL(kernel, grid, dim3(kCopyThreads), 0, stream, (const u32x4*)src, (u32x4*)dst,
-                     ids_a, ids_b, chunks, src_pool_blocks, dst_pool_blocks, n_blocks, (int)slices,
+                     ids_a, ids_b, (uint32_t)chunks, src_pool_blocks, dst_pool_blocks, n_blocks, slices,
                      id_faults);
   return hipGetLastError();
 }
