@@ -132,8 +132,9 @@ int paged_decode_attn(const void* q, const void* k_pool, const void* v_pool,
  * own q, K pool, V pool and output (the decode iteration of paper Section II-A
  * runs the attention of every layer over that layer's KV cache).  Equivalent to
  * calling paged_decode_attn for l = 0 .. num_layers-1 in order on `stream`
- * with the one workspace; the layers run one after the other.  All arguments of
- * all layers are validated before the first launch.
+ * with the one workspace, to the bit.  Layers of which none writes what another
+ * reads or writes may share a launch.  All arguments of all layers are validated
+ * before the first launch.
  *
  *   q, k_pools, v_pools, out   host arrays [num_layers] of device pointers, each
  *                              as the argument of the same name above

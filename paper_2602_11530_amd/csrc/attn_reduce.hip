@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kRowsPerGroup * 64) void attn_reduce_row_kernel(Att
   const int row = blockIdx.x * kRowsPerGroup + (threadIdx.x >> 6);   // s*Hq + h
   if (row >= a.S * a.Hq) return;
   const int lane = threadIdx.x & 63;
-  uint16_t* dst = a.out + (int64_t)row * kD + kPer * lane;
+  uint16_t* dst = a.layer.out + (int64_t)row * kD + kPer * lane;
   RowRecords r;
   if (!locate_records(a, row, r)) return;
   float M, lsum, acc[kPer];
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_row_kerne
   const int row = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int width = blockDim.x >> 6;
-  uint16_t* dst = a.out + (int64_t)row * kD + kPer * lane;
+  uint16_t* dst = a.layer.out + (int64_t)row * kD + kPer * lane;
   RowRecords r;
   if (!locate_records(a, row, r)) return;   // the same for every wavefront of the group
   float M, lsum, acc[kPer];
@@ -193,16 +193,16 @@ __global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_row_kerne
 // One workgroup per workgroup of the stream pass: the segment that begins in that one and goes on in
 // others.  A thread owns 16 bytes of the rows and every sets-th record; the sets meet in LDS.
 constexpr int kGroupThreads = 512;
-template <int kD>
-__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a) {
+template <int kD, typename Layers>
+__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
   __shared__ f32x4 rows[kGroupThreads];
   __shared__ f32x2 stats[kGroupThreads];
   const int group = blockIdx.x;
-  const SharedSegment seg = *shared_segment(a, group);
+  const SharedSegment seg = *shared_segment(a, blockIdx.y, group);
   if (seg.count == 0) return;
   const int items = a.G * (kD / 4);
   const int sets = min(max(kGroupThreads / items, 1), seg.count);
-  uint16_t* out = a.out + (int64_t)seg.row * kD;
+  uint16_t* out = layer_of(a, layers).out + (int64_t)seg.row * kD;
   for (int t = threadIdx.x; t < max(items, kGroupThreads); t += kGroupThreads) {
     const int set = t / items, item = t - set * items, head = item / (kD / 4);
     Partial p = kNothing;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLa
 #pragma unroll
       for (int z = 0; z < kBatch; ++z) {
         const int i = min(i0 + z * sets, seg.count - 1);
-        const float* rec = group_record(a, kD, group + i, i == 0);
+        const float* rec = group_record(a, kD, blockIdx.y, group + i, i == 0);
         x[z] = *(const f32x4*)(rec + 4 * item);
         ml[z] = *(const f32x2*)(rec + a.G * kD + 2 * head);
         if (i0 + z * sets >= seg.count) ml[z].x = kNegInf;
@@ -236,15 +236,22 @@ __global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLa
 
 }  // namespace
 
-hipError_t launch_attn_reduce(const AttnLaunch& a, hipStream_t stream) {
+template <int kD>
+static void launch_group(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
+  const dim3 grid(a.waves / group_waves(kD), layers ? layers->count : 1), block(kGroupThreads);
+  if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), grid, block, 0, stream, a, *layers);
+  else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), grid, block, 0, stream, a, OneLayer{});
+}
+
+hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
   if (!a.by_row) {
-    const dim3 grid(a.waves / group_waves(a.D)), block(kGroupThreads);
-    if (a.D == 64) hipLaunchKernelGGL(attn_reduce_group_kernel<64>, grid, block, 0, stream, a);
-    else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_group_kernel<128>, grid, block, 0, stream, a);
-    else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_group_kernel<256>, grid, block, 0, stream, a);
+    if (a.D == 64) launch_group<64>(a, layers, stream);
+    else if (a.D == 128) launch_group<128>(a, layers, stream);
+    else if (a.D == 256) launch_group<256>(a, layers, stream);
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
+  if (layers) return hipErrorInvalidValue;   // by rows: one layer has the whole workspace
   const int rows = a.S * a.Hq;
   // A segment's records come from the wavefronts that streamed it: about
   // waves / (S * Hkv) of them when the batch is large enough to occupy them all.

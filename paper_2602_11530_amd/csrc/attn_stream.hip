@@ -179,8 +179,8 @@ __device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
   return *(const AttnLaunch*)p;
 }
 
-template <int kD, bool kFp8>
-__global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a) {
+template <int kD, bool kFp8, typename Layers>
+__global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
   typedef Dim<kD, kFp8> DD;
   typedef typename DD::VReg VReg;                 // one V load as it arrives
   typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
@@ -201,6 +201,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   __shared__ int any_long;
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
 
+  const AttnLayer layer = layer_of(a, layers);
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   auto zero_empty_rows = [&]() {
     for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
       if (cumB[s + 1] != cumB[s]) continue;
-      uint32_t* dst = (uint32_t*)(a.out + (int64_t)s * a.Hq * kD);
+      uint32_t* dst = (uint32_t*)(layer.out + (int64_t)s * a.Hq * kD);
       for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
     }
   };
@@ -287,11 +288,11 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       nshare = shares.start(w + 1) - pos0;
     }
   }
-  if (a.by_row && blockIdx.x == 0) {   // for the reduce pass
+  if (a.by_row && blockIdx.x == 0 && blockIdx.y == 0) {   // for the reduce pass
     for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
   }
   if (last_wave < 0) {   // nothing for this workgroup
-    if (threadIdx.x == 0 && !a.by_row) shared_segment(a, blockIdx.x)->count = 0;
+    if (threadIdx.x == 0 && !a.by_row) shared_segment(a, blockIdx.y, blockIdx.x)->count = 0;
     zero_empty_rows();
     return;
   }
@@ -362,8 +363,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     int slab = (idx < kWindow) ? sa : sb;
     if (j >= nshare) slab = 0;
     const int64_t base = (int64_t)slab * slab_bytes;
-    const u32x4* kp = (const u32x4*)((const char*)a.k_pool + base) + koff;
-    const VReg* vp = (const VReg*)((const char*)a.v_pool + base) + voff;
+    const u32x4* kp = (const u32x4*)((const char*)layer.k_pool + base) + koff;
+    const VReg* vp = (const VReg*)((const char*)layer.v_pool + base) + voff;
 #pragma unroll
     for (int jj = 0; jj < kKLoads; ++jj) k[jj] = __builtin_nontemporal_load(kp + 4 * jj);
     if (kD == 256) {
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   auto store_staged = [&]() {
     for (int r = 0; r < nstaged; ++r) {
       const int qrow = __builtin_amdgcn_readlane(staged_rows, r);
-      float* dst = (float*)(a.out + (int64_t)qrow * kD);
+      float* dst = (float*)(layer.out + (int64_t)qrow * kD);
       const float* src = (const float*)(staged + r * G * kD);
       for (int f = 4 * lane; f < G * kD / 2; f += 256) store16(dst + f, *(const u32x4*)(src + f));
     }
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // 16..512 tokens: 116.5 -> 114.1 us; 8 requests at D = 256: 36.3 -> 35.7).
   u32x4 qnext[kKSteps];
   auto load_q = [&](int qrow) {
-    const u32x4* qrow_p = (const u32x4*)(a.q + (int64_t)(qrow + min(n, G - 1)) * kD);
+    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(qrow + min(n, G - 1)) * kD);
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj)
       // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
         count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
       }
     }
-    if (lane == 0 && !b.by_row) *shared_segment(b, blockIdx.x) = SharedSegment{row, count};
+    if (lane == 0 && !b.by_row) *shared_segment(b, blockIdx.y, blockIdx.x) = SharedSegment{row, count};
   }
   __syncthreads();
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
@@ -711,9 +712,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       fold(p, ml, x);
     }
     if (from_right && !open_right) {
-      *(u32x2*)(b.out + (int64_t)left_row[v] * kD + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+      *(u32x2*)(layer.out + (int64_t)left_row[v] * kD + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
     } else {
-      float* rec = group_record(b, kD, blockIdx.x, from_right);
+      float* rec = group_record(b, kD, blockIdx.y, blockIdx.x, from_right);
       store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));
       if (item % (kD / 4) == 0) *(f32x2*)(rec + G * kD + 2 * h) = f32x2{p.m, p.l};
     }
@@ -722,13 +723,15 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
 }  // namespace
 
-template <int kD, bool kFp8>
-static void launch_one(const AttnLaunch& a, size_t lds, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_stream_kernel<kD, kFp8>), dim3(a.waves / group_waves(kD)),
-                     dim3(group_waves(kD) * 64), lds, stream, a);
+template <int kD>
+static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, size_t lds, hipStream_t stream) {
+  const dim3 grid(a.waves / group_waves(kD), layers ? layers->count : 1), block(group_waves(kD) * 64);
+  if (layers) hipLaunchKernelGGL((attn_stream_kernel<kD, false, AttnLayers>), grid, block, lds, stream, a, *layers);
+  else if (a.kv_fp8) hipLaunchKernelGGL((attn_stream_kernel<kD, true, OneLayer>), grid, block, lds, stream, a, OneLayer{});
+  else hipLaunchKernelGGL((attn_stream_kernel<kD, false, OneLayer>), grid, block, lds, stream, a, OneLayer{});
 }
 
-hipError_t launch_attn_stream(const AttnLaunch& a_in, hipStream_t stream) {
+hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, hipStream_t stream) {
   AttnLaunch a = a_in;
   const int group = group_waves(a.D);
   // LDS per workgroup: the prefix arrays, then per wavefront a left record and room for a
@@ -741,14 +744,10 @@ hipError_t launch_attn_stream(const AttnLaunch& a_in, hipStream_t stream) {
   a.staged_max = room / rows;
   a.wave_lds_floats = rec + room;
   const size_t lds = (size_t)(cum + group * a.wave_lds_floats) * sizeof(float);
-  if (a.kv_fp8) {
-    if (a.D == 64) launch_one<64, true>(a, lds, stream);
-    else if (a.D == 128) launch_one<128, true>(a, lds, stream);
-    else if (a.D == 256) launch_one<256, true>(a, lds, stream);
-    else return hipErrorInvalidValue;
-  } else if (a.D == 64) launch_one<64, false>(a, lds, stream);
-  else if (a.D == 128) launch_one<128, false>(a, lds, stream);
-  else if (a.D == 256) launch_one<256, false>(a, lds, stream);
+  if (layers && a.kv_fp8) return hipErrorInvalidValue;
+  if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
+  else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);
+  else if (a.D == 256) launch_dim<256>(a, layers, lds, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -90,10 +90,10 @@ hipError_t launch(const void* src, void* dst, const int32_t* ids_a, const int32_
   const int64_t chunks = block_bytes / 16;   // at most 2^26
   const int64_t slices = (n_blocks * chunks + kCopyThreads - 1) / kCopyThreads;
   // one workgroup per slice (the hardware dispatcher balances them better than a persistent grid
-  // did); a list of more than kMaxGroups slices (32 GiB) is walked with a stride, which keeps the
+  // did); a list of more than kLayerGroups slices (32 GiB) is walked with a stride, which keeps the
   // launch below 2^32 work-items
-  constexpr int64_t kMaxGroups = (int64_t)1 << 23;
-  const dim3 grid((unsigned)(slices > kMaxGroups ? kMaxGroups : slices));
+  constexpr int64_t kLayerGroups = (int64_t)1 << 23;
+  const dim3 grid((unsigned)(slices > kLayerGroups ? kLayerGroups : slices));
   const bool cached = kMode != 2 && n_blocks * block_bytes <= kCachedStagingBytes;
   const bool whole = chunks % kCopyThreads == 0;
   auto kernel = cached ? (whole ? kv_block_copy_kernel<kMode, kMode != 2, true>

@@ -25,6 +25,7 @@ constexpr int kMaxSeqs = 2048;       // per-request prefix arrays live in LDS
 constexpr int kStreamWavesPerGroup = 4;
 constexpr int kStreamGroups = PKV_STREAM_GROUPS;
 constexpr int kStreamWaves = kStreamGroups * kStreamWavesPerGroup;
+constexpr int kLayerGroups = 256;   // workgroups per layer of the attention pass: one per compute unit
 
 // How the batch's KV blocks are laid out as one stream and cut into shares.
 //   Segment (s, kvh) holds the nblk_s = ceil(L_s/16) 16-token units ("blocks" below;
@@ -94,13 +95,19 @@ struct SharedSegment {
   int count;   // workgroups that share it, 0 when there is none
 };
 
-struct AttnLaunch {
+// What differs between the layers of one launch.
+struct AttnLayer {
   const uint16_t* q;
   const void* k_pool;   // bf16, or e4m3 bytes when kv_fp8
   const void* v_pool;
+  uint16_t* out;
+};
+constexpr int kMaxLaunchLayers = 8;
+
+struct AttnLaunch {
+  AttnLayer layer;
   const int32_t* block_tables;
   const int32_t* context_lens;
-  uint16_t* out;
   float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
   int32_t* ws_cum; // [S + 1] by_row: cumB for the reduce pass (the first one -1 when it has nothing to do)
   int by_row;      // few segments: the reduce pass has a workgroup per row
@@ -118,7 +125,17 @@ struct AttnLaunch {
   int NB;          // physical blocks per pool; ids outside [0, NB) are never followed
   int wave_lds_floats;  // a wavefront's share of LDS: its left record, then its right record or staged rows
   int staged_max;       // finished segments whose rows a wavefront can stage in LDS
+  int64_t layer_ws_floats;   // workspace from one layer's records to the next one's
 };
+// The layers of a launch, blockIdx.y being the layer.  A second kernel argument, so that a launch of one
+// layer reads its pointers with the rest (the look-up costs one request of 8191 tokens 0.4 us).
+struct AttnLayers {
+  int count;
+  AttnLayer layer[kMaxLaunchLayers];
+};
+struct OneLayer {};
+__device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch& a, const OneLayer&) { return a.layer; }
+__device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch&, const AttnLayers& l) { return l.layer[blockIdx.y]; }
 
 // The workspace of a batch of few segments (by_row): a record per (wavefront, shared segment).
 __host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int segment, int wave) {
@@ -126,17 +143,23 @@ __host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int se
 }
 // Of any other batch: two records per workgroup of the stream pass (of the shared segment that begins in
 // it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.
-__host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int group, bool begins_here) {
-  return a.ws_rec + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
+__host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int layer, int group, bool begins_here) {
+  return a.ws_rec + layer * a.layer_ws_floats + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
 }
-__host__ __device__ inline SharedSegment* shared_segment(const AttnLaunch& a, int group) {
-  return (SharedSegment*)(a.ws_rec + (int64_t)kStreamWaves / 4 * record_floats(a.G, a.D)) + group;
+__host__ __device__ inline SharedSegment* shared_segment(const AttnLaunch& a, int layer, int group) {
+  return (SharedSegment*)(a.ws_rec + layer * a.layer_ws_floats + (int64_t)2 * kLayerGroups * record_floats(a.G, a.D)) + group;
+}
+// Per layer: a whole number of records, so that every layer's are aligned like the first one's.
+__host__ __device__ inline int64_t layer_ws_floats(int G, int D) {
+  const int64_t rec = record_floats(G, D), words = kLayerGroups * (int64_t)sizeof(SharedSegment) / sizeof(float);
+  return 2 * kLayerGroups * rec + (words + rec - 1) / rec * rec;
 }
 
 // Stream pass: kStreamWaves persistent wavefronts, each writing its runs' partial records.
-hipError_t launch_attn_stream(const AttnLaunch& a, hipStream_t stream);
+// `layers`: nullptr for the one layer of `a`.
+hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 // Reduce pass: the segments that several workgroups share, from their records.
-hipError_t launch_attn_reduce(const AttnLaunch& a, hipStream_t stream);
+hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 
 // Whole-block copies; `gather` selects the direction.
 // `id_faults` (optional, device): incremented once per listed block that is skipped because an

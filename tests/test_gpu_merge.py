@@ -89,3 +89,31 @@ def test_replays_with_growing_lengths(device):
         ref = reference(w, (q, k, v))
         c = oracle.compare(got, ref)
         assert c["max_abs"] <= MAX_ABS and c["rel_l2"] <= REL_L2, (step, c)
+
+
+@pytest.mark.parametrize("lens,hq,hkv,dim", [
+    ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # several layers to a launch
+    ([3000] * 40, 16, 2, 64),
+    ([700, 5000, 129], 16, 8, 256),                          # by rows: a launch for each
+    ([40, 3, 768, 0], 8, 2, 128),                            # cut along the segments
+])
+@pytest.mark.parametrize("layers", [1, 3, 9])
+def test_layers_in_shared_launches(device, lens, hq, hkv, dim, layers):
+    """The layers call gives the single calls' bits, also where one layer's output is the next one's q."""
+    w, (q, k, v, tables, lens_d) = setup(lens, hq, hkv, dim, seed=500 + layers)
+    shape = shape_of(w)
+    ws = torch.empty(pkv.pkv_attn_workspace_bytes(shape), dtype=torch.uint8, device=device)
+    qs = [torch.roll(q, i, 0).contiguous() for i in range(layers)]
+    ks = [torch.roll(k, i, 0).contiguous() for i in range(layers)]
+    vs = [torch.roll(v, 2 * i, 0).contiguous() for i in range(layers)]
+    for chained in (False, True):
+        outs = [torch.full_like(q, 0x7FC1) for _ in range(layers)]
+        want = []
+        for i in range(layers):
+            src = want[i - 1] if chained and i % 2 else qs[i]
+            want.append(run_attn_dev(w, src, ks[i], vs[i], tables, lens_d))
+        inputs = [outs[i - 1] if chained and i % 2 else qs[i] for i in range(layers)]
+        pkv.paged_decode_attn_layers(inputs, ks, vs, tables, lens_d, float(w.scale), outs, shape, ws)
+        torch.cuda.synchronize()
+        for i in range(layers):
+            assert torch.equal(outs[i], want[i]), (chained, i)
