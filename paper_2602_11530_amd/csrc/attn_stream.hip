@@ -61,9 +61,9 @@
 //
 // Memory traffic.  The KV loads of a block (eight of 16 bytes at D = 128) are
 // nontemporal and unconditional; a ring of kRing register buffers keeps
-// kRing - 1 blocks (one) in flight per wavefront.  Finished records are parked in LDS and written in
+// kRing - 1 blocks (one) in flight per wavefront.  Finished rows and records wait in LDS and are written in
 // bursts of full-width write-through stores that the compiler's wait-count
-// bookkeeping does not see (see store_record16).
+// bookkeeping does not see (see store16).
 #include "attn_partial.h"
 #include "pkv_kernels.h"
 
@@ -133,7 +133,7 @@ __device__ __forceinline__ u32x2 widen_e4m3x4(uint32_t w) {
   return u32x2{pack_bf16(lo.x, lo.y), pack_bf16(hi.x, hi.y)};
 }
 
-// Stores of a finished run's record.  They are written as opaque instructions on
+// Stores of finished rows and of records.  They are written as opaque instructions on
 // purpose: gfx9-family hardware counts loads and stores in one counter, and once
 // the compiler knows a store is pending it can no longer wait for "all but the N
 // youngest loads" and drains the whole ring of KV loads at the next use.  Hidden

@@ -155,7 +155,7 @@ __host__ __device__ inline int64_t layer_ws_floats(int G, int D) {
   return 2 * kLayerGroups * rec + (words + rec - 1) / rec * rec;
 }
 
-// Stream pass: kStreamWaves persistent wavefronts, each writing its runs' partial records.
+// Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 // Reduce pass: the segments that several workgroups share, from their records.
