@@ -207,8 +207,10 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
   const int64_t bound = segments * max_blocks > group * segments ? segments * max_blocks : group * segments;
   if (bound < a->waves) a->waves = (int)(bound + group - 1) / group * group;
-  a->by_row = segments <= pkv::kRowSegments;
   a->one_pass = segments <= a->waves / group && max_blocks <= pkv::short_segment(group);
+  // Nobody reads SharedSegments where there is no reduce pass, and the layers of such a launch may be
+  // more than the workspace holds records for.
+  a->by_row = a->one_pass || segments <= pkv::kRowSegments;
   a->id_faults = g_id_faults;
   a->MAXB = shape->max_blocks_per_seq;
   a->upb = shape->block_size / pkv::kBlockTokens;
@@ -339,7 +341,8 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
   // Several layers to a launch, as many as the workspace holds records for: a compute unit goes on
   // to the next layer when it is done with its share of one, and the start, the uneven end and the reduce
   // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch by rows
-  // needs the whole workspace for one layer.  Layers that depend on each other keep their order.
+  // needs the whole workspace for one layer, and a one_pass launch no records at all.  Layers that depend
+  // on each other keep their order.
   Geometry g;
   (void)check_shape(shape, &g);
   const int64_t room = a.one_pass ? pkv::kMaxLaunchLayers

@@ -110,8 +110,8 @@ struct AttnLaunch {
   const int32_t* context_lens;
   float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
   int32_t* ws_cum; // [S + 1] by_row: cumB for the reduce pass (the first one -1 when it has nothing to do)
-  int by_row;      // few segments: the reduce pass has a workgroup per row
-  int one_pass;    // the bounds alone say that no segment will be shared: no reduce pass
+  int by_row;      // few segments, or one_pass: no SharedSegments are left, and a reduce pass goes by rows
+  int one_pass;    // the bounds alone say that no segment will be shared: no reduce pass, no records
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
   float out_scale;     // applied to the normalised row: 1, or the V pool's scale
   int kv_fp8;          // the pools hold one-byte e4m3 values

@@ -1,0 +1,17 @@
+"""What the attention calls launch, walked on the host (no GPU): every write to the workspace lies inside
+it, in every layer of a launch, and the reduce pass hears of every segment that several workgroups share."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_11530_amd", "csrc")
+
+
+def test_writes_stay_in_the_workspace(tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    exe = str(tmp_path / "attn_launch_check")
+    subprocess.check_call([hipcc, "-O1", "-std=c++17", "--offload-arch=gfx950", "-x", "hip", "-I", CSRC,
+                           os.path.join(ROOT, "tests", "attn_launch_check.cpp"), os.path.join(CSRC, "pkv_api.hip"),
+                           "-o", exe], stderr=subprocess.DEVNULL)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0 and "failures=0" in out.stdout, out.stdout

@@ -117,3 +117,27 @@ def test_layers_in_shared_launches(device, lens, hq, hkv, dim, layers):
         torch.cuda.synchronize()
         for i in range(layers):
             assert torch.equal(outs[i], want[i]), (chained, i)
+
+
+@pytest.mark.parametrize("lens,hq,hkv,dim,bound", [
+    ([40, 3, 768, 0] * 4, 40, 8, 128, 768),       # 128 segments, cut along them in one launch: nothing left for a reduce pass
+    ([40, 3, 384, 0] * 8, 16, 8, 256, 384),       # as many segments as workgroups
+    ([16] * 13, 10, 5, 64, 16),                   # the fewest that are not by rows
+    ([40, 3, 769, 0] * 4, 40, 8, 128, 769),       # a token beyond: records, four layers to a launch at most
+])
+@pytest.mark.parametrize("layers", [5, 8, 9])
+def test_layers_stay_inside_the_workspace(device, lens, hq, hkv, dim, bound, layers):
+    w, (q, k, v, tables, lens_d) = setup(lens, hq, hkv, dim, seed=600 + layers)
+    shape = shape_of(w, max_context_len=bound)
+    need, guard = pkv.pkv_attn_workspace_bytes(shape), 8 << 20   # more than any layer's room
+    buf = torch.full((2 * guard + need,), 0xA5, dtype=torch.uint8, device=device)
+    qs = [torch.roll(q, i, 0).contiguous() for i in range(layers)]
+    ks = [torch.roll(k, i, 0).contiguous() for i in range(layers)]
+    vs = [torch.roll(v, 2 * i, 0).contiguous() for i in range(layers)]
+    outs = [torch.full_like(q, 0x7FC1) for _ in range(layers)]
+    pkv.paged_decode_attn_layers(qs, ks, vs, tables, lens_d, float(w.scale), outs, shape, buf[guard:guard + need])
+    torch.cuda.synchronize()
+    assert bool((buf[:guard] == 0xA5).all()) and bool((buf[guard + need:] == 0xA5).all())
+    for i in range(layers):
+        want = run_attn_dev(w, qs[i], ks[i], vs[i], tables, lens_d, max_context_len=bound)
+        assert torch.equal(outs[i], want), i
