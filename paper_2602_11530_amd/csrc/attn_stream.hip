@@ -188,7 +188,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
   static_assert(kWindow % kRing == 0, "the window must be a whole number of ring turns");
-  extern __shared__ int smem[];
+  extern __shared__ __align__(16) int smem[];
   int* cumB = smem;                  // [S+1] blocks before request s
   int* lens = smem + (a.S + 1);      // [S]   clamped context lengths
   // then, 16-byte aligned, each wavefront's left record and its right record; the right
@@ -733,17 +733,10 @@ static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, size_t lds
 
 hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, hipStream_t stream) {
   AttnLaunch a = a_in;
-  const int group = group_waves(a.D);
-  // LDS per workgroup: the prefix arrays, then per wavefront a left record and room for a
-  // right record or up to 8 finished segments' rows, as long as two workgroups fit a CU.
-  const int cum = (2 * (a.S + 1) + 3) & ~3;
-  const int rec = record_floats(a.G, a.D), rows = a.G * a.D / 2;   // in 4-byte units
-  const int budget = (78 * 256 - cum) / group - rec;
-  int room = budget < 8 * rows ? budget : 8 * rows;
-  if (room < rec) room = rec;
-  a.staged_max = room / rows;
-  a.wave_lds_floats = rec + room;
-  const size_t lds = (size_t)(cum + group * a.wave_lds_floats) * sizeof(float);
+  const StreamLds l = stream_lds(a.S, a.G, a.D);
+  a.staged_max = l.staged_max;
+  a.wave_lds_floats = l.wave;
+  const size_t lds = l.bytes;
   if (layers && a.kv_fp8) return hipErrorInvalidValue;
   if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
   else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);

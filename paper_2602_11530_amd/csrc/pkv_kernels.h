@@ -155,6 +155,31 @@ __host__ __device__ inline int64_t layer_ws_floats(int G, int D) {
   return 2 * kLayerGroups * rec + (words + rec - 1) / rec * rec;
 }
 
+// LDS of a workgroup of the stream pass, in floats: the prefix arrays, then per wavefront a left record
+// and room for a right record or up to 8 finished segments' rows, held to 78 KiB.  One workgroup takes a
+// CU's registers (all but the 8-bit kernel at D = 64), so LDS would allow twice that, but 8 staged segments
+// instead of 5 (G = 5, D = 128) gain nothing: 512 requests of 16..512 tokens 110.2 us at 78 KiB, 112.2 at
+// 152; 64 of 1024..8192 190.7 and 189.2.
+// Records and rows are read and written 16 bytes at a time and lie on 16-byte boundaries; 4-byte ones,
+// which the LDS unit also accepts, cost those 512 requests 1.6 us and 4 of 17..300 tokens 0.3 of 12.4.
+struct StreamLds {
+  int prefix, wave;   // where the wavefronts' parts begin, and from one to the next
+  int staged_max;
+  int bytes;
+};
+inline StreamLds stream_lds(int S, int G, int D) {
+  const int group = group_waves(D), rec = record_floats(G, D), rows = G * D / 2;
+  StreamLds l;
+  l.prefix = (2 * (S + 1) + 3) & ~3;
+  const int budget = ((78 * 256 - l.prefix) / group - rec) & ~3;
+  int room = budget < 8 * rows ? budget : 8 * rows;
+  if (room < rec) room = rec;
+  l.wave = rec + room;
+  l.staged_max = room / rows;
+  l.bytes = (l.prefix + group * l.wave) * (int)sizeof(float);
+  return l;
+}
+
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);

@@ -6,6 +6,9 @@
 //   - no two writes of one launch overlap
 //   - what the reduce pass reads of a segment are the records that were left of it, all of them
 //
+// And the stream pass's LDS: every part of it on a 16-byte boundary, large enough for what it holds and,
+// all together, no more than a compute unit has.
+//
 // Compiled together with csrc/pkv_api.hip and run by tests/test_attn_launch.py (host code only, no GPU).
 #include "../include/pkv.h"
 #include "pkv_kernels.h"
@@ -142,7 +145,23 @@ static void attend(const std::vector<int>& lens, int hq, int hkv, int dim, int b
   }
 }
 
+static void check_lds() {
+  using namespace pkv;
+  for (int D : {64, 128, 256})
+    for (int G = 1; G <= (D == 256 ? 8 : 16); ++G)
+      for (int S = 1; S <= kMaxSeqs; ++S) {
+        const StreamLds l = stream_lds(S, G, D);
+        const int rec = record_floats(G, D), rows = G * D / 2;   // bf16 rows, in floats
+        const bool ok = l.prefix >= 2 * S + 1 && l.prefix % 4 == 0 && l.wave % 4 == 0 && rec % 4 == 0 && rows % 4 == 0 &&
+                        l.wave >= 2 * rec && l.staged_max >= 1 && l.wave >= rec + l.staged_max * rows &&
+                        l.bytes >= 4 * (l.prefix + group_waves(D) * l.wave) && l.bytes <= 159 * 1024;   // and the static arrays
+        if (!ok && failures++ < 20)
+          printf("LDS at S=%d G=%d D=%d: prefix %d, wavefront %d, staged %d, %d bytes\n", S, G, D, l.prefix, l.wave, l.staged_max, l.bytes);
+      }
+}
+
 int main() {
+  check_lds();
   uint64_t x = 41;
   auto rnd = [&](int n) { x = x * 6364136223846793005ULL + 1442695040888963407ULL; return (int)((uint32_t)(x >> 33) % (uint32_t)n); };
   const int heads[][2] = {{40, 8}, {8, 2}, {8, 1}, {16, 8}, {7, 7}, {16, 1}, {10, 5}};

@@ -1,6 +1,7 @@
 """What the attention calls launch, walked on the host (no GPU): every write to the workspace lies inside
 it, in every layer of a launch, and the reduce pass hears of every segment that several workgroups share."""
 import os
+import re
 import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -15,3 +16,14 @@ def test_writes_stay_in_the_workspace(tmp_path):
                            "-o", exe], stderr=subprocess.DEVNULL)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and "failures=0" in out.stdout, out.stdout
+
+
+def test_stream_pass_lds_begins_aligned(tmp_path):
+    """The stream pass's dynamic LDS follows its static arrays; records and rows in it are accessed 16 bytes at a time."""
+    from paper_2602_11530_amd import build as pkv_build
+    asm = str(tmp_path / "attn_stream.s")
+    flags = [f for f in pkv_build.FLAGS if f not in ("-fPIC", "-shared")]
+    subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "attn_stream.hip"), "-o", asm],
+                          stderr=subprocess.DEVNULL)
+    sizes = re.findall(r"\.amdhsa_group_segment_fixed_size (\d+)", open(asm).read())
+    assert len(sizes) == 9 and all(int(s) % 16 == 0 for s in sizes), sizes
