@@ -153,7 +153,7 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
 struct Window {
   int slab;   // which slab (16 tokens of one KV head; 4 KiB at D = 128 in bf16), counted from the pool's start; 0 when not read
   int meta;   // bits 0-7 valid tokens (0..16), then the kMeta flags
-  int qrow;   // s * Hq + kvh * G: first query/output row of the segment
+  int seg;    // s * Hkv + kvh: the segment, whose first query/output row is seg * G
 };
 // A position of the stream: block b of the nb blocks of request s, KV head kvh.
 struct Place {
@@ -196,8 +196,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   const int rec_floats = record_floats(a.G, kD);
   float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
   __shared__ int ends[kGroupWaves];      // kEnds* flags
-  __shared__ int left_row[kGroupWaves];   // qrow of the segment that the share's first block belongs to
-  __shared__ int right_row[kGroupWaves];  // qrow of the segment parked in the right record
+  __shared__ int left_seg[kGroupWaves];   // the segment that the share's first block belongs to
   __shared__ int any_long;
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
 
@@ -251,21 +250,13 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     __syncthreads();
   }
 
-  // An empty request owes zero rows.
-  const int w = blockIdx.x * kGroupWaves + wave;
-  auto zero_empty_rows = [&]() {
-    for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
-      if (cumB[s + 1] != cumB[s]) continue;
-      uint32_t* dst = (uint32_t*)(layer.out + (int64_t)s * a.Hq * kD);
-      for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
-    }
-  };
-
   // Equal shares: every participating wavefront gets at least one block, so that consecutive
   // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
   // short segments is cut along the segments instead, one to a workgroup (see short_segment).
   const int T = Hkv * cumB[S];
-  const bool whole = !any_long && S * Hkv <= (int)gridDim.x;
+  const bool whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
+  const bool by_row = a.by_row && !whole;
+  int w = blockIdx.x * kGroupWaves + wave;
   int W, first_wave, last_wave, pos0 = 0, nshare = 0;
   if (whole) {
     const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
@@ -282,16 +273,35 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     W = share_count(T, a.waves);
     first_wave = blockIdx.x * kGroupWaves;
     last_wave = min(kGroupWaves, W - first_wave) - 1;
+    if (by_row && T < a.waves) {
+      // A block per wavefront and not enough of them to fill the compute units: one after the other round
+      // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
+      // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
+      w = wave * gridDim.x + blockIdx.x;
+      last_wave = w < W ? 0 : -1;
+    }
     if (w < W) {
       const ShareMap shares(T, W);
       pos0 = shares.start(w);
       nshare = shares.start(w + 1) - pos0;
     }
   }
+  // An empty request owes zero rows.
+  auto zero_empty_rows = [&]() {
+    for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
+      if (cumB[s + 1] != cumB[s]) continue;
+      uint32_t* dst = (uint32_t*)(layer.out + (int64_t)s * a.Hq * kD);
+      for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
+    }
+  };
+
   if (a.by_row && blockIdx.x == 0 && blockIdx.y == 0) {   // for the reduce pass
     for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
   }
-  if (last_wave < 0) {   // nothing for this workgroup
+  // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
+  // its records do not wait for the launch descriptor to be read again.
+  float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
+  if (last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
     if (threadIdx.x == 0 && !a.by_row) shared_segment(a, blockIdx.y, blockIdx.x)->count = 0;
     zero_empty_rows();
     return;
@@ -330,7 +340,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     const bool seg_first = (b == 0) || (j == 0);
     d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0) |
              (b + 1 == nb ? kMetaSegEnd : 0) | (b > j ? kMetaOpenLeft : 0);
-    d.qrow = s * a.Hq + kvh * G;
+    d.seg = s * Hkv + kvh;
     return d;
   };
 
@@ -385,13 +395,13 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // issued after it cannot be consumed before it has been acknowledged, and that costs one
   // stall of several microseconds per burst of stores however few bytes it carries.
   int nstaged = 0;       // finished segments whose rows are in LDS
-  int staged_rows = 0;   // lane r: first output row of staged segment r
+  int staged_segs = 0;   // lane r: staged segment r
   bool seg_open = false;   // a parked record belongs to the segment being streamed
-  int ends_flags = 0, left_q = 0, right_q = 0;   // as left in LDS for the merge
+  int ends_flags = 0, left = 0, right = 0;   // how the share ends, and the segments in the left and the right record
   auto store_staged = [&]() {
     for (int r = 0; r < nstaged; ++r) {
-      const int qrow = __builtin_amdgcn_readlane(staged_rows, r);
-      float* dst = (float*)(layer.out + (int64_t)qrow * kD);
+      const int seg = __builtin_amdgcn_readlane(staged_segs, r);
+      float* dst = (float*)(layer.out + (int64_t)seg * (G * kD));
       const float* src = (const float*)(staged + r * G * kD);
       for (int f = 4 * lane; f < G * kD / 2; f += 256) store16(dst + f, *(const u32x4*)(src + f));
     }
@@ -538,8 +548,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       }
       if (done) {
         if (nstaged == a.staged_max) store_staged();
-        const int qrow = __builtin_amdgcn_readlane(dA.qrow, idx);
-        staged_rows = (lane == nstaged) ? qrow : staged_rows;
+        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
+        staged_segs = (lane == nstaged) ? seg : staged_segs;
         uint16_t* rows = staged + nstaged * G * kD;
         const float inv = inverse(lt, a.out_scale);
 #pragma unroll
@@ -557,11 +567,11 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
         ends_flags &= ~kEndsRight;
       } else {
         if (!open_left) store_staged();   // the staged rows lie where the record goes
-        const int qrow = __builtin_amdgcn_readlane(dA.qrow, idx);
+        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
         ends_flags = !open_left ? ends_flags | kEndsRight
                      : (meta & kMetaSegEnd) ? kEndsLeft : kEndsLeft | kEndsThrough;
-        left_q = open_left ? qrow : left_q;
-        right_q = open_left ? right_q : qrow;
+        left = open_left ? seg : left;
+        right = open_left ? right : seg;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int h = 4 * c + r;
@@ -587,8 +597,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // first block was already to be consumed, it cost the pipeline a drain per segment (512 requests of
   // 16..512 tokens: 116.5 -> 114.1 us; 8 requests at D = 256: 36.3 -> 35.7).
   u32x4 qnext[kKSteps];
-  auto load_q = [&](int qrow) {
-    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(qrow + min(n, G - 1)) * kD);
+  auto load_q = [&](int seg) {
+    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(seg * G + min(n, G - 1)) * kD);
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj)
       // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
@@ -610,7 +620,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     for (int jj = 0; jj < kKLoads; ++jj) asm volatile("" : : "v"(k[jj]));
 #pragma unroll
     for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
-    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.qrow : dB.qrow, idx & (kWindow - 1)));
+    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
   };
 
   // A ring of kRing register buffers: kRing - 1 blocks are always in flight
@@ -620,7 +630,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
   for (int i = 0; i < kRing - 1; ++i) issue(kbuf[i], vbuf[i], i);
   static_assert(kRing == 2, "a query group is asked for one block ahead");
-  load_q(__builtin_amdgcn_readlane(dA.qrow, 0));
+  load_q(__builtin_amdgcn_readlane(dA.seg, 0));
   if (nshare > kWindow) dB = describe(kWindow);
   for (int j = 0; j < nshare; j += kRing) {
 #pragma unroll
@@ -642,27 +652,27 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   }
   store_staged();
+  if (by_row) {
+    // Few segments: nearly all of them are shared by many wavefronts, and the reduce pass has a
+    // workgroup for every row, so each wavefront's records go to memory as they are, before all else.
+    auto store_record = [&](const float* rec, int seg) {
+      float* dst = row_records + (int64_t)seg * rec_floats;
+      for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
+    };
+    if (ends_flags & kEndsLeft) store_record(rec_left, left);
+    if (ends_flags & kEndsRight) store_record(rec_right, right);
+  }
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
   zero_empty_rows();
+  if (by_row) return;
 
   // The workgroup's merge.  Segments that meet inside the workgroup's range are finished from
   // the records in LDS.  What is left are at most two segments that it shares with other
   // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
   // shared segment begins in leaves word of it.
   const AttnLaunch& b = reread(a);
-  if (b.by_row && !whole) {
-    // Few segments: nearly all of them are shared by many wavefronts, and the reduce pass has a
-    // workgroup for every row, so each wavefront's records go to memory as they are.
-    auto store_record = [&](const float* rec, int qrow) {
-      float* dst = wave_record(b, kD, qrow / G, w);
-      for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
-    };
-    if (ends_flags & kEndsLeft) store_record(rec_left, left_q);
-    if (ends_flags & kEndsRight) store_record(rec_right, right_q);
-    return;
-  }
-  if (lane == 0) { ends[wave] = ends_flags; left_row[wave] = left_q; right_row[wave] = right_q; }
+  if (lane == 0) { ends[wave] = ends_flags; left_seg[wave] = left; }
   if (wave == 0) {   // the first to finish, as a rule
     // The segment of the workgroup's last block: does it begin here and go on elsewhere?
     int row = 0, count = 0;
@@ -712,7 +722,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       fold(p, ml, x);
     }
     if (from_right && !open_right) {
-      *(u32x2*)(layer.out + (int64_t)left_row[v] * kD + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+      *(u32x2*)(layer.out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
     } else {
       float* rec = group_record(b, kD, blockIdx.y, blockIdx.x, from_right);
       store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));

@@ -201,13 +201,14 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   // a D = 256 wavefront needs the registers of a whole SIMD lane: one wavefront per SIMD
   a->waves = shape->head_dim == 256 ? pkv::kStreamWaves / 2 : pkv::kStreamWaves;
   // A small bound on the blocks (or the segments, when a batch is cut along those) needs no more
-  // workgroups; the shares are the same either way.
+  // workgroups; the shares are the same either way.  By rows, the wavefronts are dealt round all of them.
   const int group = pkv::group_waves(shape->head_dim);
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
   const int64_t bound = segments * max_blocks > group * segments ? segments * max_blocks : group * segments;
-  if (bound < a->waves) a->waves = (int)(bound + group - 1) / group * group;
   a->one_pass = segments <= a->waves / group && max_blocks <= pkv::short_segment(group);
+  if (bound < a->waves && (a->one_pass || segments > pkv::kRowSegments))
+    a->waves = (int)(bound + group - 1) / group * group;
   // Nobody reads SharedSegments where there is no reduce pass, and the layers of such a launch may be
   // more than the workspace holds records for.
   a->by_row = a->one_pass || segments <= pkv::kRowSegments;

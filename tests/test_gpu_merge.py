@@ -31,6 +31,12 @@ SHAPES = [
     ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
     ([2000, 30] * 4, 8, 8, 64),              # the fewest segments that one launch finishes
     ([2000, 30] * 4, 7, 7, 64),
+    ([16 * 2047], 8, 1, 64),                 # by rows: a block less than wavefronts, as many and one more
+    ([16 * 2048 - 5], 8, 1, 128),
+    ([16 * 2049], 8, 1, 128),
+    ([16 * 1023, 0], 8, 1, 256),
+    ([16 * 1024, 16], 8, 1, 256),
+    ([16 * 255, 3, 0, 160], 16, 1, 128),     # fewer wavefronts than twice the workgroups, and an empty request
 ]
 
 
