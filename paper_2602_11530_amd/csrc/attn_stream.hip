@@ -25,8 +25,7 @@
 //   few and short    one workgroup per segment, which meets in LDS and finishes it: no records, and no
 //                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
 //                    heads: 10.8 us instead of 6.8 + 6.4 and a launch less; the call 17.8 -> 14.5 us).
-//                    Up to 6 blocks per wavefront, where streaming one segment with one workgroup
-//                    costs no more than the records and the reduce pass do.
+//                    Up to 3 or 6 blocks per wavefront (short_segment).
 //
 // Per 16-token block, lane = 16*c + n, head_dim D = 128 (64 and 256 below):
 //   S^T = K . Q^T   D/32 v_mfma_f32_16x16x32_bf16 (k = 32 dims each).
@@ -228,7 +227,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
     if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
   }
-  const bool some_long = __any(longest > short_segment(kGroupWaves));
+  const bool some_long = __any(longest > a.short_blocks);
   if (threadIdx.x == 0) any_long = some_long;
   __syncthreads();
   if (S > 64) {

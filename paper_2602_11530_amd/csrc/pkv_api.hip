@@ -175,7 +175,7 @@ int pkv_attn_workspace_bytes(const pkv_attn_shape* shape, size_t* out_bytes) {
 
 // Validation shared by the single-layer and the multi-layer call; fills the
 // launch descriptor except for the per-layer pointers.
-static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens, float scale,
+static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens, float scale, bool kv_fp8,
                         const pkv_attn_shape* shape, void* workspace, size_t workspace_bytes_given,
                         pkv::AttnLaunch* a, bool* empty) {
   Geometry g;
@@ -206,7 +206,8 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
   const int64_t bound = segments * max_blocks > group * segments ? segments * max_blocks : group * segments;
-  a->one_pass = segments <= a->waves / group && max_blocks <= pkv::short_segment(group);
+  a->short_blocks = pkv::short_segment(segments, a->D, kv_fp8);
+  a->one_pass = segments <= a->waves / group && max_blocks <= a->short_blocks;
   if (bound < a->waves && (a->one_pass || segments > pkv::kRowSegments))
     a->waves = (int)(bound + group - 1) / group * group;
   // Nobody reads SharedSegments where there is no reduce pass, and the layers of such a launch may be
@@ -220,7 +221,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->NB = (int)shape->num_pool_blocks;
   a->scale_log2e = scale * 1.4426950408889634f;
   a->out_scale = 1.f;
-  a->kv_fp8 = 0;
+  a->kv_fp8 = kv_fp8;
   a->ws_rec = static_cast<float*>(workspace);
   a->layer_ws_floats = pkv::layer_ws_floats(g.G, a->D);
   a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
@@ -269,7 +270,7 @@ int paged_decode_attn(const void* q, const void* k_pool, const void* v_pool,
                       size_t workspace_bytes_given, void* stream) {
   pkv::AttnLaunch a;
   bool empty = false;
-  int rc = prepare_attn(block_tables, context_lens, scale, shape, workspace, workspace_bytes_given,
+  int rc = prepare_attn(block_tables, context_lens, scale, false, shape, workspace, workspace_bytes_given,
                         &a, &empty);
   if (rc != PKV_OK || empty) return rc;
   rc = check_layer_pointers(q, k_pool, v_pool, out);
@@ -289,7 +290,7 @@ int paged_decode_attn_fp8kv(const void* q, const void* k_pool, const void* v_poo
     return PKV_ERR_SHAPE;
   pkv::AttnLaunch a;
   bool empty = false;
-  rc = prepare_attn(block_tables, context_lens, scale, shape, workspace, workspace_bytes_given, &a,
+  rc = prepare_attn(block_tables, context_lens, scale, true, shape, workspace, workspace_bytes_given, &a,
                     &empty);
   if (rc != PKV_OK || empty) return rc;
   rc = check_layer_pointers(q, k_pool, v_pool, out);
@@ -298,7 +299,6 @@ int paged_decode_attn_fp8kv(const void* q, const void* k_pool, const void* v_poo
   // to the normalised row
   a.scale_log2e = scale * k_scale * 1.4426950408889634f;
   a.out_scale = v_scale;
-  a.kv_fp8 = 1;
   return launch_layer(a, q, k_pool, v_pool, out, static_cast<hipStream_t>(stream));
 }
 
@@ -317,7 +317,7 @@ int paged_decode_attn_static(const void* q, const void* k_pool, const void* v_po
   if (rc != PKV_OK) return rc;
   pkv::AttnLaunch a;
   bool empty = false;
-  rc = prepare_attn(block_tables, context_lens, scale, shape, ws, kStaticScratchBytes, &a, &empty);
+  rc = prepare_attn(block_tables, context_lens, scale, false, shape, ws, kStaticScratchBytes, &a, &empty);
   if (rc != PKV_OK || empty) return rc;
   return launch_layer(a, q, k_pool, v_pool, out, static_cast<hipStream_t>(stream));
 }
@@ -330,7 +330,7 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
   if (num_layers < 0) return PKV_ERR_SHAPE;
   pkv::AttnLaunch a;
   bool empty = false;
-  int rc = prepare_attn(block_tables, context_lens, scale, shape, workspace, workspace_bytes_given,
+  int rc = prepare_attn(block_tables, context_lens, scale, false, shape, workspace, workspace_bytes_given,
                         &a, &empty);
   if (rc != PKV_OK || empty || num_layers == 0) return rc;
   if (!q || !k_pools || !v_pools || !out) return PKV_ERR_NULL;

@@ -83,11 +83,18 @@ __host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; 
 // log2 units, partial sum) for up to kMaxGroup heads.  Rows are 16-byte multiples.
 __host__ __device__ inline int record_floats(int G, int D) { return G * D + 2 * kMaxGroup; }
 
-// A batch whose segments all fit one workgroup each (at most kStreamGroups / 2 segments, none
-// longer than this many blocks) is cut along the segments.
-__host__ __device__ constexpr int short_segment(int group_waves) { return 6 * group_waves; }
 // Up to this many segments the reduce pass goes by rows.
 constexpr int kRowSegments = 64;
+// A batch with no more segments than the launch has workgroups, none longer than this many blocks, is cut
+// along the segments.  Up to 6 blocks per wavefront; with at most kRowSegments of them, which leave most
+// compute units idle, 3 where a block is 8 KiB or more.  Cut along the segments / not, us for append and
+// attention: 8 segments of 40/8 heads at D = 128, 384 tokens (3 blocks) 13.2 / 13.4, 512 13.2 / 12.8, 768
+// 17.3 / 13.7; 16 segments of 8/1 heads, 768 tokens 20.0 / 15.5; 128 of 40/8 heads, 512 17.6 / 18.8, 768
+// 21.4 / 21.7; 240, 768 23.5 / 27.7; blocks of 4 KiB (D = 64), 8 segments of 768 tokens 12.2 / 13.0.
+inline int short_segment(int64_t segments, int D, bool kv_fp8) {
+  const int block_bytes = 2 * kBlockTokens * D * (kv_fp8 ? 1 : 2);
+  return (segments <= kRowSegments && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
+}
 
 // A segment that several workgroups share, as the workgroup that it begins in leaves it.
 struct SharedSegment {
@@ -112,6 +119,7 @@ struct AttnLaunch {
   int32_t* ws_cum; // [S + 1] by_row: cumB for the reduce pass (the first one -1 when it has nothing to do)
   int by_row;      // few segments, or one_pass: no SharedSegments are left, and a reduce pass goes by rows
   int one_pass;    // the bounds alone say that no segment will be shared: no reduce pass, no records
+  int short_blocks;    // see short_segment()
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
   float out_scale;     // applied to the normalised row: 1, or the V pool's scale
   int kv_fp8;          // the pools hold one-byte e4m3 values

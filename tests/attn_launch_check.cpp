@@ -59,7 +59,7 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
   for (int s = 0; s < a.S; ++s) {
     nblk[s] = (std::min(std::max(call.lens[s], 0), a.max_ctx) + kBlockTokens - 1) / kBlockTokens;
     cum[s + 1] = cum[s] + nblk[s];
-    any_long = any_long || nblk[s] > short_segment(group);
+    any_long = any_long || nblk[s] > a.short_blocks;
   }
   const int T = a.Hkv * cum[a.S], W = share_count(T, a.waves);
   const bool whole = !any_long && a.S * a.Hkv <= grid;

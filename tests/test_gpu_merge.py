@@ -23,10 +23,16 @@ SHAPES = [
     ([1, 16, 17, 0, 33] * 60, 10, 2, 64),    # many segments inside one share
     ([16] * 700 + [30000], 12, 1, 128),      # staged rows fill up; then one long segment
     ([700, 0, 5000, 3, 129], 40, 8, 128),
-    ([768, 0, 1, 130, 17], 8, 2, 128),       # cut along the segments: the longest that is (6 blocks per wavefront)
-    ([769, 0, 1, 130, 17], 8, 2, 128),       # and one token beyond
-    ([384, 16, 15, 0], 8, 1, 256),
-    ([385, 16, 15, 0], 8, 1, 256),
+    ([384, 0, 1, 130, 17], 8, 2, 128),       # cut along the segments: the longest that is (3 blocks per wavefront)
+    ([385, 0, 1, 130, 17], 8, 2, 128),       # and one token beyond
+    ([768, 0, 1, 130, 17], 8, 2, 128),
+    ([192, 16, 15, 0], 8, 1, 256),
+    ([193, 16, 15, 0], 8, 1, 256),
+    ([768, 0, 1, 130, 17], 8, 2, 64),        # 4 KiB blocks: 6 per wavefront
+    ([769, 0, 1, 130, 17], 8, 2, 64),
+    ([768, 5, 300, 0] * 5, 40, 8, 128),      # more than 64 segments: 6 per wavefront
+    ([769, 5, 300, 0] * 5, 40, 8, 128),
+    ([384, 16, 15, 0] * 8, 16, 8, 256),
     ([768, 5, 300, 0] * 8, 32, 8, 64),       # as many segments as workgroups
     ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
     ([2000, 30] * 4, 8, 8, 64),              # the fewest segments that one launch finishes
