@@ -164,7 +164,7 @@ constexpr int kMetaSegFirst = 1 << 9;   // first block of its segment in this sh
 constexpr int kMetaSegEnd = 1 << 10;    // last block of its segment
 constexpr int kMetaOpenLeft = 1 << 11;  // its segment begins before this share
 
-// How a wavefront's share ends, left in LDS for the workgroup's merge.
+// How a wavefront's share ends.
 constexpr int kEndsLeft = 1;      // the left record is in use: the first segment begins before the share
 constexpr int kEndsThrough = 2;   // and goes on after it
 constexpr int kEndsRight = 4;     // the right record is in use: the last segment begins in the share and goes on
@@ -194,7 +194,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // record shares its room with finished rows that wait to be stored
   const int rec_floats = record_floats(a.G, kD);
   float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
-  __shared__ int ends[kGroupWaves];      // kEnds* flags
+  __shared__ int chains, passes;          // bit per wavefront, see the workgroup's merge
+  __shared__ SharedSegment word;          // the workgroup's, for the reduce pass
   __shared__ int left_seg[kGroupWaves];   // the segment that the share's first block belongs to
   __shared__ int any_long;
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
   }
   const bool some_long = __any(longest > a.short_blocks);
-  if (threadIdx.x == 0) any_long = some_long;
+  if (threadIdx.x == 0) { any_long = some_long; chains = passes = 0; }
   __syncthreads();
   if (S > 64) {
     if (some_long && lane == 0) any_long = 1;
@@ -631,6 +632,22 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   static_assert(kRing == 2, "a query group is asked for one block ahead");
   load_q(__builtin_amdgcn_readlane(dA.seg, 0));
   if (nshare > kWindow) dB = describe(kWindow);
+  if (wave == 0 && !a.by_row) {
+    // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
+    // last block, does it begin here and go on elsewhere?
+    int row = 0, count = 0;
+    if (!whole && first_wave + kGroupWaves < W) {
+      const ShareMap shares(T, W);
+      const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
+      const Place at = place(next - 1);
+      const int seg_pos = next - 1 - at.b;
+      if (seg_pos >= begin && seg_pos + at.nb > next) {
+        row = (at.s * Hkv + at.kvh) * G;
+        count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
+      }
+    }
+    if (lane == 0) word = SharedSegment{row, count};
+  }
   for (int j = 0; j < nshare; j += kRing) {
 #pragma unroll
     for (int i = 0; i < kRing; ++i) {
@@ -671,44 +688,37 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
   // shared segment begins in leaves word of it.
   const AttnLaunch& b = reread(a);
-  if (lane == 0) { ends[wave] = ends_flags; left_seg[wave] = left; }
-  if (wave == 0) {   // the first to finish, as a rule
-    // The segment of the workgroup's last block: does it begin here and go on elsewhere?
-    int row = 0, count = 0;
-    if (!whole && first_wave + kGroupWaves < W) {
-      const ShareMap shares(T, W);
-      const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
-      const Place at = place(next - 1);
-      const int seg_pos = next - 1 - at.b;
-      if (seg_pos >= begin && seg_pos + at.nb > next) {
-        row = at.s * b.Hq + at.kvh * G;
-        count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
-      }
-    }
-    if (lane == 0 && !b.by_row) *shared_segment(b, blockIdx.y, blockIdx.x) = SharedSegment{row, count};
+  if (lane == 0) {
+    left_seg[wave] = left;
+    int chain = 0;
+    if ((ends_flags & kEndsLeft) && (!(ends_flags & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
+    if ((ends_flags & kEndsRight) && wave == last_wave) chain |= 1 << kGroupWaves;
+    if (chain) atomicOr(&chains, chain);
+    if (ends_flags & kEndsThrough) atomicOr(&passes, 1 << wave);
   }
   __syncthreads();
+  if (threadIdx.x == 0 && !b.by_row) *shared_segment(b, blockIdx.y, blockIdx.x) = word;
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
-  // workgroup's last, and one for the last wavefront's right record.
+  // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
+  // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to
+  // four rounds instead of one took 1 us more (64 requests of 50..100 tokens on 40/8 heads 18.4 -> 16.6).
+  const int ending = chains, through = passes;
 #pragma unroll 1
-  for (int i = threadIdx.x; i < (kGroupWaves + 1) * q4; i += kThreads) {
-    const int chain = i / q4, item = i - chain * q4;
+  for (int i = threadIdx.x; i < __popc(ending) * q4; i += kThreads) {
+    const int nth = i / q4, item = i - nth * q4;
+    int rest = ending;
+    for (int z = 0; z < nth; ++z) rest &= rest - 1;
+    const int chain = __ffs(rest) - 1;
     const bool right_only = chain == kGroupWaves;
     const int v = right_only ? last_wave : chain;
-    if (v > last_wave) continue;
-    const int e = ends[v];
     int u = v;
     bool from_right = true;   // the chain begins with wavefront u's right record
-    if (right_only) {
-      if (!(e & kEndsRight)) continue;
-    } else {
-      if (!(e & kEndsLeft) || ((e & kEndsThrough) && v != last_wave)) continue;
-      u = v - 1;
-      while (u >= 0 && (ends[u] & kEndsThrough)) --u;
+    if (!right_only) {
+      u = 31 - __clz(~through & ((1 << v) - 1));   // the last one before v that the segment does not go through
       if (u < 0) { u = 0; from_right = false; }
     }
-    const bool open_right = right_only || (e & kEndsThrough);
+    const bool open_right = right_only || ((through >> v) & 1);
     const int h = item / (kD / 4);
     Partial p = kNothing;
 #pragma unroll 1
