@@ -4,22 +4,21 @@
 // that one share holds are finished there.  Bound by latency: where the records are, then the
 // records.  Two layouts (pkv_kernels.h):
 //
-// A batch of many segments leaves at most one shared segment per workgroup of the stream pass,
-// whose wavefronts have met in LDS, so that a segment has a handful of records: one workgroup
+// Records of workgroups: at most one shared segment begins in a workgroup of the stream pass, whose
+// wavefronts have met in LDS, so that a segment has a handful of records: one workgroup
 // here for each there (256), which reads one word and is done when nothing begins there.
 //
-// A batch of few segments (by_row) spreads each over hundreds of wavefronts, and their records come as
-// they are: a wavefront or a workgroup for each row fetches the statistics side by side and then
-// streams the partial rows eight at a time.
+// Records of wavefronts (by rows): up to hundreds of a segment, as they come: a workgroup
+// for each row fetches the statistics side by side and then streams the partial rows
+// sixteen at a time.
 #include "attn_partial.h"
 #include "pkv_kernels.h"
 
 namespace pkv {
 namespace {
 
-constexpr int kRowsPerGroup = 4;   // wavefronts per workgroup
-constexpr int kBatch = 8;          // partial rows in flight per wavefront
-constexpr int kMaxWideWaves = 16;  // wavefronts of a workgroup that share one row (small batches)
+constexpr int kBatch = 8;      // records in flight per thread
+constexpr int kRowBatch = 16;  // partial rows in flight per wavefront, by rows
 
 // kPer = D / 64 consecutive floats of a row per lane
 template <int kPer> struct Chunk { typedef float T __attribute__((ext_vector_type(kPer))); };
@@ -40,7 +39,7 @@ __device__ __forceinline__ float wave_sum(float x) {
 
 // Where the records of row (s, h) lie: the slots of its segment's first and last
 // block's owners (see pkv_kernels.h).  Returns false when there is nothing to fold: an empty
-// request, a segment that one wavefront finished, a batch that was cut along its segments.
+// request, a segment that one wavefront finished, a batch that was cut along its segments (cumB[0] < 0).
 struct RowRecords {
   int first;   // slot of the first record
   int np;      // one record per wavefront that streamed part of this segment
@@ -102,17 +101,17 @@ __device__ __forceinline__ void fold_records(const AttnLaunch& a, const RowRecor
       lsum = __builtin_fmaf(w, ml.y, lsum);
     }
     const int cnt = min(64, count - i0);
-    for (int j0 = 0; j0 < cnt; j0 += kBatch) {
-      Vec v[kBatch];
-      float wj[kBatch];
+    for (int j0 = 0; j0 < cnt; j0 += kRowBatch) {
+      Vec v[kRowBatch];
+      float wj[kRowBatch];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
+      for (int u = 0; u < kRowBatch; ++u) {
         const int j = min(j0 + u, cnt - 1);   // clamped rows get weight 0
         wj[u] = (j0 + u < cnt) ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j)) : 0.f;
         v[u] = *((const Vec*)(record(i0 + j) + r.g * kD) + lane);
       }
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
+      for (int u = 0; u < kRowBatch; ++u) {
         // a weight of exactly zero must also silence whatever the row holds
 #pragma unroll
         for (int i = 0; i < kPer; ++i)
@@ -135,71 +134,53 @@ __device__ __forceinline__ void store_row(uint16_t* dst, const float (&acc)[kPer
   else *(uint2*)dst = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
 }
 
-// One wavefront per row.
-template <int kD>
-__global__ __launch_bounds__(kRowsPerGroup * 64) void attn_reduce_row_kernel(AttnLaunch a) {
-  constexpr int kPer = kD / 64;
-  const int row = blockIdx.x * kRowsPerGroup + (threadIdx.x >> 6);   // s*Hq + h
-  if (row >= a.S * a.Hq) return;
-  const int lane = threadIdx.x & 63;
-  uint16_t* dst = a.layer.out + (int64_t)row * kD + kPer * lane;
-  RowRecords r;
-  if (!locate_records(a, row, r)) return;
-  float M, lsum, acc[kPer];
-  fold_records<kD>(a, r, 0, 1, r.np, lane, M, lsum, acc);
-  store_row<kPer>(dst, acc, lsum, a.out_scale);
-}
-
-// One workgroup per row, for a small batch: few segments share the stream's
-// wavefronts, so a row has up to hundreds of records and a single wavefront
-// would read them in a long chain of rounds.  Wavefront i of the group folds
-// records i, i + n, i + 2n, ... (n = wavefronts in the group), the partial
-// results meet in LDS and wavefront 0 folds those.
-template <int kD>
-__global__ __launch_bounds__(kMaxWideWaves * 64) void attn_reduce_wide_row_kernel(AttnLaunch a) {
-  constexpr int kPer = kD / 64;
-  __shared__ float part_stats[kMaxWideWaves][2];
-  __shared__ float part_acc[kMaxWideWaves][kD];
-  const int row = blockIdx.x;
+// A row of a batch that goes by rows.  Wavefront i of the workgroup folds records i, i + n, i + 2n, ...
+// (n = wavefronts in the workgroup), the partial results meet in LDS and wavefront 0 folds those.
+template <int kD, int kThreads>
+__device__ __forceinline__ void reduce_row(const AttnLaunch& a, int row) {
+  constexpr int kPer = kD / 64, kWidth = kThreads / 64;
+  __shared__ float part_stats[kWidth][2];
+  __shared__ float part_acc[kWidth][kD];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int width = blockDim.x >> 6;
-  uint16_t* dst = a.layer.out + (int64_t)row * kD + kPer * lane;
   RowRecords r;
-  if (!locate_records(a, row, r)) return;   // the same for every wavefront of the group
+  if (!locate_records(a, row, r)) return;   // the same for every wavefront of the workgroup
   float M, lsum, acc[kPer];
-  const int count = r.np > wave ? (r.np - wave + width - 1) / width : 0;
-  fold_records<kD>(a, r, wave, width, count, lane, M, lsum, acc);
+  const int count = r.np > wave ? (r.np - wave + kWidth - 1) / kWidth : 0;
+  fold_records<kD>(a, r, wave, kWidth, count, lane, M, lsum, acc);
   if (lane == 0) { part_stats[wave][0] = M; part_stats[wave][1] = lsum; }
 #pragma unroll
   for (int i = 0; i < kPer; ++i) part_acc[wave][kPer * lane + i] = acc[i];
   __syncthreads();
-  if (wave != 0) return;
-  float Mall = kNegInf;
-  for (int w = 0; w < width; ++w) Mall = fmaxf(Mall, part_stats[w][0]);
-  float lall = 0.f, total[kPer];
+  if (wave == 0) {
+    float Mall = kNegInf;
+    for (int w = 0; w < kWidth; ++w) Mall = fmaxf(Mall, part_stats[w][0]);
+    float lall = 0.f, total[kPer];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) total[i] = 0.f;
-  for (int w = 0; w < width; ++w) {
-    const float m = part_stats[w][0];
-    if (m == kNegInf) continue;   // nothing valid behind this partial result: weight 0
-    const float f = __builtin_amdgcn_exp2f(m - Mall);
-    lall = __builtin_fmaf(f, part_stats[w][1], lall);
+    for (int i = 0; i < kPer; ++i) total[i] = 0.f;
+    for (int w = 0; w < kWidth; ++w) {
+      const float m = part_stats[w][0];
+      if (m == kNegInf) continue;   // nothing valid behind this partial result: weight 0
+      const float f = __builtin_amdgcn_exp2f(m - Mall);
+      lall = __builtin_fmaf(f, part_stats[w][1], lall);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) total[i] = __builtin_fmaf(f, part_acc[w][kPer * lane + i], total[i]);
+      for (int i = 0; i < kPer; ++i) total[i] = __builtin_fmaf(f, part_acc[w][kPer * lane + i], total[i]);
+    }
+    store_row<kPer>(a.layer.out + (int64_t)row * kD + kPer * lane, total, lall, a.out_scale);
   }
-  store_row<kPer>(dst, total, lall, a.out_scale);
+  __syncthreads();   // the next row uses the same LDS
+}
+template <int kD, int kThreads>
+__device__ __forceinline__ void reduce_rows(const AttnLaunch& a) {
+  for (int row = blockIdx.x; row < a.S * a.Hq; row += gridDim.x) reduce_row<kD, kThreads>(a, row);
 }
 
-// One workgroup per workgroup of the stream pass: the segment that begins in that one and goes on in
-// others.  A thread owns 16 bytes of the rows and every sets-th record; the sets meet in LDS.
+// The segment that begins in a workgroup of the stream pass and goes on in others.  A thread owns 16 bytes
+// of the rows and every sets-th record; the sets meet in LDS.
 constexpr int kGroupThreads = 512;
 template <int kD, typename Layers>
-__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
+__device__ __forceinline__ void reduce_segment(const AttnLaunch& a, const Layers& layers, const SharedSegment& seg, int group) {
   __shared__ f32x4 rows[kGroupThreads];
   __shared__ f32x2 stats[kGroupThreads];
-  const int group = blockIdx.x;
-  const SharedSegment seg = *shared_segment(a, blockIdx.y, group);
-  if (seg.count == 0) return;
   const int items = a.G * (kD / 4);
   const int sets = min(max(kGroupThreads / items, 1), seg.count);
   uint16_t* out = layer_of(a, layers).out + (int64_t)seg.row * kD;
@@ -212,7 +193,7 @@ __global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLa
 #pragma unroll
       for (int z = 0; z < kBatch; ++z) {
         const int i = min(i0 + z * sets, seg.count - 1);
-        const float* rec = group_record(a, kD, blockIdx.y, group + i, i == 0);
+        const float* rec = group_record(a, kD, layer_index(layers), group + i, i == 0);
         x[z] = *(const f32x4*)(rec + 4 * item);
         ml[z] = *(const f32x2*)(rec + a.G * kD + 2 * head);
         if (i0 + z * sets >= seg.count) ml[z].x = kNegInf;
@@ -234,46 +215,51 @@ __global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLa
   }
 }
 
+// Many segments.
+template <int kD, typename Layers>
+__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
+  const SharedSegment seg = *shared_segment(a, layer_index(layers), blockIdx.x);
+  if (seg.count > 0) reduce_segment<kD>(a, layers, seg, blockIdx.x);
+}
+// Few segments: whichever of the two the stream pass has chosen.  Registers as for the two wavefronts per
+// SIMD that there are: left to itself the compiler has fewer loads in flight (8 requests of 6000..12000
+// tokens on 8/1 heads 22.5 -> 21.7 us).
+template <int kD>
+__global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_reduce_few_kernel(AttnLaunch a) {
+  const SharedSegment seg = *shared_segment(a, 0, blockIdx.x);
+  if (seg.count == kByRows) reduce_rows<kD, kGroupThreads>(a);
+  else if (seg.count > 0) reduce_segment<kD>(a, OneLayer{}, seg, blockIdx.x);
+}
+template <int kD, int kThreads>
+__global__ __launch_bounds__(kThreads) void attn_reduce_rows_kernel(AttnLaunch a) {
+  reduce_rows<kD, kThreads>(a);
+}
+
 }  // namespace
 
 template <int kD>
-static void launch_group(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
-  const dim3 grid(a.waves / group_waves(kD), layers ? layers->count : 1), block(kGroupThreads);
-  if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), grid, block, 0, stream, a, *layers);
-  else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), grid, block, 0, stream, a, OneLayer{});
+static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
+  const dim3 groups(a.waves / group_waves(kD), layers ? layers->count : 1), block(kGroupThreads);
+  if (a.leaves == kManySegments) {
+    if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), groups, block, 0, stream, a, *layers);
+    else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), groups, block, 0, stream, a, OneLayer{});
+  } else if (a.leaves == kFewSegments) {
+    hipLaunchKernelGGL(attn_reduce_few_kernel<kD>, groups, block, 0, stream, a);
+  } else if (a.waves / (a.S * a.Hkv) >= 128) {
+    // hundreds of records for a row: 16 wavefronts for it instead of 8 (one request of 6000..12000 tokens on
+    // 8/1 heads 21.0 -> 19.2 us; 16 of 750..1500, 65 records, lose 0.9 by it)
+    hipLaunchKernelGGL((attn_reduce_rows_kernel<kD, 1024>), dim3(a.S * a.Hq), dim3(1024), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL((attn_reduce_rows_kernel<kD, 512>), dim3(a.S * a.Hq), dim3(512), 0, stream, a);
+  }
 }
 
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
-  if (!a.by_row) {
-    if (a.D == 64) launch_group<64>(a, layers, stream);
-    else if (a.D == 128) launch_group<128>(a, layers, stream);
-    else if (a.D == 256) launch_group<256>(a, layers, stream);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
-  if (layers) return hipErrorInvalidValue;   // by rows: one layer has the whole workspace
-  const int rows = a.S * a.Hq;
-  // A segment's records come from the wavefronts that streamed it: about
-  // waves / (S * Hkv) of them when the batch is large enough to occupy them all.
-  // From 32 records per row on, the row gets a workgroup of its own with one
-  // wavefront per four records (8 or 16 wavefronts); below that the wider group
-  // costs more than the rounds it saves (measured at 8 and 16 records per row).
-  const int64_t segments = (int64_t)a.S * a.Hkv;
-  const int64_t per_row = a.waves / segments;
-  if (per_row >= 32) {
-    const int width = per_row >= 64 ? 16 : 8;
-    const dim3 grid((unsigned)rows), block(width * 64);
-    if (a.D == 64) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<64>, grid, block, 0, stream, a);
-    else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<128>, grid, block, 0, stream, a);
-    else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_wide_row_kernel<256>, grid, block, 0, stream, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
-  dim3 grid((unsigned)((rows + kRowsPerGroup - 1) / kRowsPerGroup), 1, 1);
-  const dim3 block(kRowsPerGroup * 64);
-  if (a.D == 64) hipLaunchKernelGGL(attn_reduce_row_kernel<64>, grid, block, 0, stream, a);
-  else if (a.D == 128) hipLaunchKernelGGL(attn_reduce_row_kernel<128>, grid, block, 0, stream, a);
-  else if (a.D == 256) hipLaunchKernelGGL(attn_reduce_row_kernel<256>, grid, block, 0, stream, a);
+  if (layers && a.leaves != kManySegments) return hipErrorInvalidValue;   // one layer has the whole workspace
+  if (a.D == 64) launch_dim<64>(a, layers, stream);
+  else if (a.D == 128) launch_dim<128>(a, layers, stream);
+  else if (a.D == 256) launch_dim<256>(a, layers, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

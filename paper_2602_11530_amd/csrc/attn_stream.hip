@@ -16,16 +16,16 @@
 // reduce pass (attn_reduce.hip) combines the records of each (request, KV head).
 //
 // Three ways to that end, by what the segments are like:
-//   many segments    the wavefronts of a workgroup fold what they share in LDS first, so at most
-//                    two records per workgroup reach memory (64 requests of 1024..8192 tokens: the
-//                    reduce pass takes 4.6 us instead of 5.2, the call 191.0 instead of 194.2 us)
-//   few (by_row)     every segment is shared by dozens of wavefronts; their records go to memory as
-//                    they are and the reduce pass has a workgroup per row (one request of 8191 tokens:
-//                    meeting in LDS first took 2 us here and gave 2 us there)
-//   few and short    one workgroup per segment, which meets in LDS and finishes it: no records, and no
+//   workgroups' records   the wavefronts of a workgroup fold what they share in LDS first, so at most
+//                    two records per workgroup reach memory (64 requests of 1024..8192 tokens on 40/8 heads:
+//                    194.2 us -> 191.0 with the reduce pass; one of 8191 19.1 -> 17.6)
+//   by rows          the wavefronts' records go to memory as they are and the reduce pass has a workgroup
+//                    per row: few segments where meeting in LDS costs more than it saves (what_is_left,
+//                    row_blocks)
+//   cut along them   one workgroup per segment, which meets in LDS and finishes it: no records, and no
 //                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
-//                    heads: 10.8 us instead of 6.8 + 6.4 and a launch less; the call 17.8 -> 14.5 us).
-//                    Up to 3 or 6 blocks per wavefront (short_segment).
+//                    heads: 14.0 -> 11.3 us and a launch less on the host).  Few and short ones, up to 3
+//                    or 6 blocks per wavefront (short_segment).
 //
 // Per 16-token block, lane = 16*c + n, head_dim D = 128 (64 and 256 below):
 //   S^T = K . Q^T   D/32 v_mfma_f32_16x16x32_bf16 (k = 32 dims each).
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // short segments is cut along the segments instead, one to a workgroup (see short_segment).
   const int T = Hkv * cumB[S];
   const bool whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
-  const bool by_row = a.by_row && !whole;
+  bool by_row = false;
   int w = blockIdx.x * kGroupWaves + wave;
   int W, first_wave, last_wave, pos0 = 0, nshare = 0;
   if (whole) {
@@ -273,6 +273,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     W = share_count(T, a.waves);
     first_wave = blockIdx.x * kGroupWaves;
     last_wave = min(kGroupWaves, W - first_wave) - 1;
+    by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
     if (by_row && T < a.waves) {
       // A block per wavefront and not enough of them to fill the compute units: one after the other round
       // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
@@ -295,14 +296,17 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   };
 
-  if (a.by_row && blockIdx.x == 0 && blockIdx.y == 0) {   // for the reduce pass
+  // For the reduce pass.
+  const bool leaves_words = a.leaves == kManySegments || a.leaves == kFewSegments;
+  if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, layer_index(layers), blockIdx.x)->count = kByRows;
+  if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
     for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
   }
   // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
   // its records do not wait for the launch descriptor to be read again.
   float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
   if (last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
-    if (threadIdx.x == 0 && !a.by_row) shared_segment(a, blockIdx.y, blockIdx.x)->count = 0;
+    if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, layer_index(layers), blockIdx.x)->count = 0;
     zero_empty_rows();
     return;
   }
@@ -632,7 +636,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   static_assert(kRing == 2, "a query group is asked for one block ahead");
   load_q(__builtin_amdgcn_readlane(dA.seg, 0));
   if (nshare > kWindow) dB = describe(kWindow);
-  if (wave == 0 && !a.by_row) {
+  if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it begin here and go on elsewhere?
     int row = 0, count = 0;
@@ -669,8 +673,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   }
   store_staged();
   if (by_row) {
-    // Few segments: nearly all of them are shared by many wavefronts, and the reduce pass has a
-    // workgroup for every row, so each wavefront's records go to memory as they are, before all else.
+    // The reduce pass has a workgroup for every row, so each wavefront's records go to memory as they
+    // are, before all else.
     auto store_record = [&](const float* rec, int seg) {
       float* dst = row_records + (int64_t)seg * rec_floats;
       for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
@@ -697,7 +701,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (ends_flags & kEndsThrough) atomicOr(&passes, 1 << wave);
   }
   __syncthreads();
-  if (threadIdx.x == 0 && !b.by_row) *shared_segment(b, blockIdx.y, blockIdx.x) = word;
+  if (threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
+    *shared_segment(b, layer_index(layers), blockIdx.x) = word;
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
   // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
@@ -733,7 +738,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (from_right && !open_right) {
       *(u32x2*)(layer.out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
     } else {
-      float* rec = group_record(b, kD, blockIdx.y, blockIdx.x, from_right);
+      float* rec = group_record(b, kD, layer_index(layers), blockIdx.x, from_right);
       store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));
       if (item % (kD / 4) == 0) *(f32x2*)(rec + G * kD + 2 * h) = f32x2{p.m, p.l};
     }

@@ -200,19 +200,17 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->D = shape->head_dim;
   // a D = 256 wavefront needs the registers of a whole SIMD lane: one wavefront per SIMD
   a->waves = shape->head_dim == 256 ? pkv::kStreamWaves / 2 : pkv::kStreamWaves;
-  // A small bound on the blocks (or the segments, when a batch is cut along those) needs no more
-  // workgroups; the shares are the same either way.  By rows, the wavefronts are dealt round all of them.
   const int group = pkv::group_waves(shape->head_dim);
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
-  const int64_t bound = segments * max_blocks > group * segments ? segments * max_blocks : group * segments;
   a->short_blocks = pkv::short_segment(segments, a->D, kv_fp8);
-  a->one_pass = segments <= a->waves / group && max_blocks <= a->short_blocks;
-  if (bound < a->waves && (a->one_pass || segments > pkv::kRowSegments))
-    a->waves = (int)(bound + group - 1) / group * group;
-  // Nobody reads SharedSegments where there is no reduce pass, and the layers of such a launch may be
-  // more than the workspace holds records for.
-  a->by_row = a->one_pass || segments <= pkv::kRowSegments;
+  a->leaves = pkv::what_is_left(segments, g.G, a->D);
+  if (segments <= a->waves / group && max_blocks <= a->short_blocks) {
+    // Cut along its segments, a workgroup for each.  Nothing is left in the workspace, and the layers of such
+    // a launch may be more than it has room for.
+    a->leaves = pkv::kNoRecords;
+    a->waves = (int)segments * group;
+  }
   a->id_faults = g_id_faults;
   a->MAXB = shape->max_blocks_per_seq;
   a->upb = shape->block_size / pkv::kBlockTokens;
@@ -223,6 +221,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->out_scale = 1.f;
   a->kv_fp8 = kv_fp8;
   a->ws_rec = static_cast<float*>(workspace);
+  a->ws_words = a->ws_rec + (int64_t)pkv::records_before_words(a->leaves) * pkv::record_floats(g.G, a->D);
   a->layer_ws_floats = pkv::layer_ws_floats(g.G, a->D);
   a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
   return PKV_OK;
@@ -242,7 +241,7 @@ static pkv::AttnLayer layer_of(const void* q, const void* k_pool, const void* v_
 // The launches for the layer of `a`, or for `layers`.
 static int launch_attn(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers, hipStream_t st) {
   hipError_t e = pkv::launch_attn_stream(a, layers, st);
-  if (e == hipSuccess && !a.one_pass) e = pkv::launch_attn_reduce(a, layers, st);
+  if (e == hipSuccess && a.leaves != pkv::kNoRecords) e = pkv::launch_attn_reduce(a, layers, st);
   if (e != hipSuccess) return launch_status(e);
   return PKV_OK;
 }
@@ -341,14 +340,14 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
   }
   // Several layers to a launch, as many as the workspace holds records for: a compute unit goes on
   // to the next layer when it is done with its share of one, and the start, the uneven end and the reduce
-  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch by rows
-  // needs the whole workspace for one layer, and a one_pass launch no records at all.  Layers that depend
-  // on each other keep their order.
+  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch of few
+  // segments has the whole workspace for one layer, and one that leaves no records needs none of it.  Layers
+  // that depend on each other keep their order.
   Geometry g;
   (void)check_shape(shape, &g);
-  const int64_t room = a.one_pass ? pkv::kMaxLaunchLayers
-                       : a.by_row ? 1
-                                  : g.slots * pkv::record_floats(a.G, a.D) / a.layer_ws_floats;
+  const int64_t room = a.leaves == pkv::kNoRecords       ? pkv::kMaxLaunchLayers
+                       : a.leaves != pkv::kManySegments ? 1
+                                                        : g.slots * pkv::record_floats(a.G, a.D) / a.layer_ws_floats;
   const int most = room < pkv::kMaxLaunchLayers ? (int)room : pkv::kMaxLaunchLayers;
   const int launches = (num_layers + most - 1) / most;
   const int even = (num_layers + launches - 1) / launches;

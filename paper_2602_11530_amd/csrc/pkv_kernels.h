@@ -39,13 +39,13 @@ constexpr int kLayerGroups = 256;   // workgroups per layer of the attention pas
 //   (max, sum, un-normalised row) per query head of the group.  The runs of one
 //   segment inside one share are folded together.  A segment that lies wholly
 //   inside a share is finished there; of any other the wavefront leaves a record.
-//   In a batch of few segments (by_row) it is stored at
+//   In a batch that goes by rows it is stored at
 //       slot = s * Hkv + kvh + w,
 //   which is unique and increases along the stream (from one record to the next
 //   the segment, the wavefront or both advance), so the records of a segment are
 //   the consecutive slots from (its index + the owner of its first block) to
 //   (its index + the owner of its last block); slots skipped where a share and a
-//   segment end together belong to nobody and are never read.  In a larger batch the
+//   segment end together belong to nobody and are never read.  Otherwise the
 //   wavefronts of a workgroup fold their records in LDS, finish the segments that lie
 //   inside the workgroup's range and leave one record for each of the two segments
 //   that may cross its ends (group_record); the workgroup in which a crossing segment
@@ -83,24 +83,51 @@ __host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; 
 // log2 units, partial sum) for up to kMaxGroup heads.  Rows are 16-byte multiples.
 __host__ __device__ inline int record_floats(int G, int D) { return G * D + 2 * kMaxGroup; }
 
-// Up to this many segments the reduce pass goes by rows.
-constexpr int kRowSegments = 64;
+// What the stream pass leaves of the shared segments for the reduce pass, as far as the host can tell.
+enum Leaves {
+  kManySegments,   // records of workgroups
+  kFewSegments,    // records of workgroups, or of wavefronts (by rows) where a batch has few blocks
+  kRows,           // records of wavefronts, however many blocks
+  kNoRecords       // the bounds alone say that no segment will be shared: no reduce pass
+};
+// Up to kFew segments.  By rows, a workgroup of the reduce pass has one row and its records, and the
+// wavefronts of the stream pass need not meet; otherwise they meet in LDS, and a workgroup of the reduce
+// pass has a whole segment.  Rows / records of workgroups, us for append and attention:
+//   few blocks, so that a wavefront has one at most: one request of 2000..4000 tokens on 8/1 heads (227
+//   blocks) 14.5 / 15.8, 16 of 750..1500 (1047) 16.4 / 16.8; one of 1500..3000 on 32/8 heads at D = 64
+//   (1360) 14.9 / 13.2; 8 of 2000..4000 on 8/1 heads (1472) 18.1 / 16.8, 64 of them (12000) 30.2 / 26.9.
+//   a handful of segments, whose few workgroups of the reduce pass read hundreds of records each: one
+//   of 10000..16000 on 8/1 heads at D = 256 28.7 / 47, one of 16000..32000 on 16/1 heads at D = 128 37 / 47,
+//   5 of 6000..12000 on 8/1 heads at D = 256 24.9 / 27.8, where a workgroup has one thread for each 16 bytes
+//   of the rows; but on 4/1 heads, with two, 23.5 / 22.9, and 6 on 8/1 heads at D = 128 22.4 / 19.7.
+//   small records, which are soon written and read: 8 of 1500..3000 on 32/8 heads at D = 64 (1 KiB) 17.9 /
+//   18.6; 7 on 8/8 heads at D = 64 (256 bytes) 16.4 / 17.5; but 40 on 8/1 heads (2 KiB) 17.0 / 16.3, 4 on
+//   32/8 15.4 / 14.9.
+constexpr int kFew = 64;
+inline Leaves what_is_left(int64_t segments, int G, int D) {
+  if (segments > kFew) return kManySegments;
+  const int handful = D == 256 && G > 4 ? 8 : 4;
+  return segments <= handful || G * D <= 64 || (segments > kFew / 2 && G * D < 512) ? kRows : kFewSegments;
+}
+// kFewSegments: by rows up to this many blocks.
+__host__ __device__ constexpr int row_blocks(int waves) { return waves * 5 / 8; }
 // A batch with no more segments than the launch has workgroups, none longer than this many blocks, is cut
-// along the segments.  Up to 6 blocks per wavefront; with at most kRowSegments of them, which leave most
+// along the segments.  Up to 6 blocks per wavefront; with at most kFew of them, which leave most
 // compute units idle, 3 where a block is 8 KiB or more.  Cut along the segments / not, us for append and
 // attention: 8 segments of 40/8 heads at D = 128, 384 tokens (3 blocks) 13.2 / 13.4, 512 13.2 / 12.8, 768
 // 17.3 / 13.7; 16 segments of 8/1 heads, 768 tokens 20.0 / 15.5; 128 of 40/8 heads, 512 17.6 / 18.8, 768
 // 21.4 / 21.7; 240, 768 23.5 / 27.7; blocks of 4 KiB (D = 64), 8 segments of 768 tokens 12.2 / 13.0.
 inline int short_segment(int64_t segments, int D, bool kv_fp8) {
   const int block_bytes = 2 * kBlockTokens * D * (kv_fp8 ? 1 : 2);
-  return (segments <= kRowSegments && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
+  return (segments <= kFew && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
 }
 
 // A segment that several workgroups share, as the workgroup that it begins in leaves it.
 struct SharedSegment {
   int row;     // first output row
-  int count;   // workgroups that share it, 0 when there is none
+  int count;   // workgroups that share it, 0 when there is none, kByRows in a batch that goes by rows
 };
+constexpr int kByRows = -1;
 
 // What differs between the layers of one launch.
 struct AttnLayer {
@@ -116,9 +143,9 @@ struct AttnLaunch {
   const int32_t* block_tables;
   const int32_t* context_lens;
   float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
-  int32_t* ws_cum; // [S + 1] by_row: cumB for the reduce pass (the first one -1 when it has nothing to do)
-  int by_row;      // few segments, or one_pass: no SharedSegments are left, and a reduce pass goes by rows
-  int one_pass;    // the bounds alone say that no segment will be shared: no reduce pass, no records
+  float* ws_words; // the first layer's SharedSegments
+  int32_t* ws_cum; // [S + 1] by rows: cumB for the reduce pass (the first one -1 when it has nothing to do)
+  Leaves leaves;
   int short_blocks;    // see short_segment()
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
   float out_scale;     // applied to the normalised row: 1, or the V pool's scale
@@ -142,20 +169,26 @@ struct AttnLayers {
   AttnLayer layer[kMaxLaunchLayers];
 };
 struct OneLayer {};
+__device__ __forceinline__ int layer_index(const OneLayer&) { return 0; }
+__device__ __forceinline__ int layer_index(const AttnLayers&) { return blockIdx.y; }
 __device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch& a, const OneLayer&) { return a.layer; }
-__device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch&, const AttnLayers& l) { return l.layer[blockIdx.y]; }
+__device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch&, const AttnLayers& l) { return l.layer[layer_index(l)]; }
 
-// The workspace of a batch of few segments (by_row): a record per (wavefront, shared segment).
+// The workspace of a batch that goes by rows: a record per (wavefront, shared segment).
 __host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int segment, int wave) {
   return a.ws_rec + (int64_t)(segment + wave) * record_floats(a.G, D);
 }
 // Of any other batch: two records per workgroup of the stream pass (of the shared segment that begins in
-// it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.
+// it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.  With few segments
+// the SharedSegments lie behind all records that a batch may leave by rows: they tell the reduce pass which.
 __host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int layer, int group, bool begins_here) {
   return a.ws_rec + layer * a.layer_ws_floats + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
 }
 __host__ __device__ inline SharedSegment* shared_segment(const AttnLaunch& a, int layer, int group) {
-  return (SharedSegment*)(a.ws_rec + layer * a.layer_ws_floats + (int64_t)2 * kLayerGroups * record_floats(a.G, a.D)) + group;
+  return (SharedSegment*)(a.ws_words + layer * a.layer_ws_floats) + group;
+}
+constexpr int records_before_words(Leaves leaves) {
+  return leaves == kFewSegments ? kFew + row_blocks(kStreamWaves) : 2 * kLayerGroups;
 }
 // Per layer: a whole number of records, so that every layer's are aligned like the first one's.
 __host__ __device__ inline int64_t layer_ws_floats(int G, int D) {

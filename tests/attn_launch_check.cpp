@@ -63,12 +63,13 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
   }
   const int T = a.Hkv * cum[a.S], W = share_count(T, a.waves);
   const bool whole = !any_long && a.S * a.Hkv <= grid;
-  if (a.one_pass && !whole) call.wrong++;   // nobody would finish the shared segments
+  if (a.leaves == kNoRecords && !whole) call.wrong++;   // nobody would finish the shared segments
+  const bool by_row = !whole && (a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves)));
 
   Writes writes;
-  if (a.by_row) writes.add(a.ws_cum, (a.S + 1) * (int64_t)sizeof(int32_t));
+  if (by_row || a.leaves == kRows) writes.add(a.ws_cum, (a.S + 1) * (int64_t)sizeof(int32_t));
   for (int y = 0; y < count; ++y) {
-    if (!a.by_row)
+    if (a.leaves == kManySegments || a.leaves == kFewSegments)
       for (int g = 0; g < grid; ++g) writes.add(shared_segment(a, y, g), sizeof(SharedSegment));
     if (whole) continue;
     std::map<int, int> begins;   // workgroup -> segments that begin in it and go on in another one
@@ -77,13 +78,13 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
         const int first = a.Hkv * cum[s] + kvh * nblk[s], last = first + nblk[s] - 1;
         const int w0 = share_owner(first, T, W), w1 = share_owner(last, T, W);
         if (w0 == w1) continue;   // finished by its wavefront
-        if (a.by_row) {
+        if (by_row) {
           for (int w = w0; w <= w1; ++w) writes.add(wave_record(a, a.D, s * a.Hkv + kvh, w), record_bytes);
           continue;
         }
         const int g0 = w0 / group, g1 = w1 / group;
         if (g0 == g1) continue;   // finished in its workgroup
-        if (a.by_row || ++begins[g0] > 1) call.wrong++;   // the reduce pass hears of one per workgroup
+        if ((a.leaves != kManySegments && a.leaves != kFewSegments) || ++begins[g0] > 1) call.wrong++;   // the reduce pass hears of one per workgroup
         for (int g = g0; g <= g1; ++g) writes.add(group_record(a, a.D, y, g, g == g0), record_bytes);
       }
   }
@@ -98,7 +99,7 @@ hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hip
   return hipSuccess;
 }
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers*, hipStream_t) {
-  if (a.one_pass) call.wrong++;
+  if (a.leaves == kNoRecords) call.wrong++;
   return hipSuccess;
 }
 hipError_t launch_kv_block_copy(const void*, void*, const int32_t*, int64_t, int64_t, int64_t, bool, int32_t*, hipStream_t) { return hipSuccess; }

@@ -43,6 +43,17 @@ SHAPES = [
     ([16 * 1023, 0], 8, 1, 256),
     ([16 * 1024, 16], 8, 1, 256),
     ([16 * 255, 3, 0, 160], 16, 1, 128),     # fewer wavefronts than twice the workgroups, and an empty request
+    ([16 * 80] * 2, 8, 8, 128),              # 16 segments of 1280 blocks together: by rows, the most that are
+    ([16 * 80, 16 * 81], 8, 8, 128),         # beyond: workgroups' records
+    ([16 * 128, 0, 16 * 32], 16, 4, 256),    # 640 blocks
+    ([16 * 128, 0, 16 * 33], 16, 4, 256),
+    ([16 * 1000, 40] * 4, 64, 4, 128),       # 32 segments: the most that small records leave alone
+    ([16 * 200] * 8 + [9], 14, 7, 64),       # 63 small ones: by rows, however many blocks
+    ([16 * 200] * 8 + [9], 56, 7, 64),
+    ([9000, 5, 7000, 400, 1], 5, 1, 64),     # a few long segments, items that do not divide the workgroup
+    ([9000, 5, 7000, 400, 1], 4, 1, 256),    # two threads for each 16 bytes, and one
+    ([9000, 5, 7000, 400, 1], 8, 1, 256),
+    ([3000, 0, 5000] * 3, 9, 9, 64),         # records of one head
 ]
 
 
