@@ -111,10 +111,10 @@ hipError_t launch(const void* src, void* dst, const int32_t* ids_a, const int32_
   const int per = chunks_per_lane(kMode, cached, chunks, n_blocks * block_bytes);
   const int64_t slices = (n_blocks * chunks + kCopyThreads * per - 1) / (kCopyThreads * per);
   // one workgroup per slice (the hardware dispatcher balances them better than a persistent grid
-  // did); a list of more than kLayerGroups slices (32 GiB) is walked with a stride, which keeps the
+  // did); a list of more than kMaxGroups slices (32 GiB) is walked with a stride, which keeps the
   // launch below 2^32 work-items
-  constexpr int64_t kLayerGroups = (int64_t)1 << 23;
-  const dim3 grid((unsigned)(slices > kLayerGroups ? kLayerGroups : slices));
+  constexpr int64_t kMaxGroups = (int64_t)1 << 23;
+  const dim3 grid((unsigned)(slices > kMaxGroups ? kMaxGroups : slices));
   auto kernel = whole ? kv_block_copy_kernel<kMode, false, true, 1> : kv_block_copy_kernel<kMode, false, false, 1>;
   if constexpr (kMode != 2) {
     if (cached)
