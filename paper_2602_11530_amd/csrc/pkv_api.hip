@@ -47,7 +47,7 @@ int check_shape(const pkv_attn_shape* sh, Geometry* g) {
   if (sh->num_q_heads % sh->num_kv_heads != 0) return PKV_ERR_SHAPE;
   const int G = sh->num_q_heads / sh->num_kv_heads;
   if (G > pkv::kMaxGroup) return PKV_ERR_SHAPE;
-  // a wavefront parks a whole record (G rows of D floats) in its 16 KiB share of LDS
+  // a wavefront keeps two whole records (G rows of D floats) in its share of LDS
   if (D == 256 && G > 8) return PKV_ERR_SHAPE;
   if (sh->max_blocks_per_seq <= 0) return PKV_ERR_SHAPE;
   if ((int64_t)sh->max_blocks_per_seq * B > INT32_MAX) return PKV_ERR_SHAPE;
@@ -198,8 +198,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->Hkv = shape->num_kv_heads;
   a->G = g.G;
   a->D = shape->head_dim;
-  // a D = 256 wavefront needs the registers of a whole SIMD lane: one wavefront per SIMD
-  a->waves = shape->head_dim == 256 ? pkv::kStreamWaves / 2 : pkv::kStreamWaves;
+  a->waves = pkv::kLayerGroups * pkv::group_waves(shape->head_dim);
   const int group = pkv::group_waves(shape->head_dim);
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;

@@ -17,15 +17,13 @@ constexpr int kMaxGroup = 16;        // query heads per KV head
 constexpr int kMaxSeqs = 2048;       // per-request prefix arrays live in LDS
 
 // The attention pass is a persistent launch sized for the 256 compute units of
-// an MI355X: two 4-wave workgroups per unit, each wavefront streaming an equal
-// share of the batch's KV blocks.
-#ifndef PKV_STREAM_GROUPS
-#define PKV_STREAM_GROUPS 512
-#endif
-constexpr int kStreamWavesPerGroup = 4;
-constexpr int kStreamGroups = PKV_STREAM_GROUPS;
-constexpr int kStreamWaves = kStreamGroups * kStreamWavesPerGroup;
-constexpr int kLayerGroups = 256;   // workgroups per layer of the attention pass: one per compute unit
+// an MI355X: one workgroup per unit, of two wavefronts per SIMD (one at D = 256, where a
+// wavefront needs most of a SIMD's registers), each streaming an equal share of the batch's KV
+// blocks.
+constexpr int kLayerGroups = 256;   // workgroups per layer of the attention pass
+constexpr int kStreamWaves = 8 * kLayerGroups;
+// Wavefronts per workgroup.
+__host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; }
 
 // How the batch's KV blocks are laid out as one stream and cut into shares.
 //   Segment (s, kvh) holds the nblk_s = ceil(L_s/16) 16-token units ("blocks" below;
@@ -76,8 +74,6 @@ __host__ __device__ inline int share_owner(int64_t pos, int64_t T, int64_t W) {
 }
 // Wavefronts that take part.
 __host__ __device__ inline int share_count(int T, int waves) { return T < waves ? T : waves; }
-// Wavefronts per workgroup: a compute unit's worth.
-__host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; }
 
 // One partial record: G un-normalised rows of D floats, then (reference max in
 // log2 units, partial sum) for up to kMaxGroup heads.  Rows are 16-byte multiples.

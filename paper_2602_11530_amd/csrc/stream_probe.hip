@@ -1,6 +1,6 @@
 // Measurement aid, not part of the attention path: the rate at which this GPU can
 // stream KV slabs with the stream pass's own access pattern and nothing else.
-// The same persistent launch (kStreamWaves wavefronts, equal shares), the same
+// The same persistent launch (kLayerGroups workgroups of 8 wavefronts, equal shares), the same
 // two 4 KiB reads per 16-token block of one KV head at D = 128 in bf16 -- a "K"
 // slab in matrix-operand order (a 64-byte run per token row per load) and a "V"
 // slab in natural order -- the same nontemporal loads with one block in flight,
@@ -15,11 +15,12 @@ namespace pkv {
 namespace {
 
 constexpr int kSlabUnits = 256;   // 16-byte units in a 4 KiB slab
+constexpr int kProbeWaves = group_waves(128);   // wavefronts per workgroup
 
-__global__ __launch_bounds__(kStreamWavesPerGroup * 64) void stream_read_probe_kernel(
+__global__ __launch_bounds__(kProbeWaves * 64) void stream_read_probe_kernel(
     const u32x4* __restrict__ k_buf, const u32x4* __restrict__ v_buf, uint32_t num_slabs,
     uint32_t pow2_mask, int64_t total_blocks, int waves, uint32_t* __restrict__ sink) {
-  const int w = blockIdx.x * kStreamWavesPerGroup + (threadIdx.x >> 6);
+  const int w = blockIdx.x * kProbeWaves + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
   const int koff = (4 * (n & 3) + (n >> 2)) * 16 + c;   // token row tau(n), 16-byte unit c of each 64-byte run
@@ -64,7 +65,7 @@ hipError_t launch_stream_read_probe(const void* k_buf, const void* v_buf, uint32
                                     int64_t total_blocks, void* sink, hipStream_t stream) {
   uint32_t pow2 = 1;   // the smallest power of two >= num_slabs (num_slabs <= 2^30)
   while (pow2 < num_slabs) pow2 *= 2;
-  const dim3 grid(kStreamGroups), block(kStreamWavesPerGroup * 64);
+  const dim3 grid(kLayerGroups), block(kProbeWaves * 64);
   hipLaunchKernelGGL(stream_read_probe_kernel, grid, block, 0, stream, (const u32x4*)k_buf,
                      (const u32x4*)v_buf, num_slabs, pow2 - 1, total_blocks, kStreamWaves,
                      (uint32_t*)sink);
