@@ -112,7 +112,9 @@ int pkv_attn_workspace_bytes(const pkv_attn_shape* shape /* host */, size_t* out
  *   block_tables device  int32 [S][MAXB]
  *   context_lens device  int32 [S]
  *   scale        fp32 softmax scale (1/sqrt(D) for the configs here)
- *   out          device  bf16  [S][Hq][D], written in full
+ *   out          device  bf16  [S][Hq][D], written in full.  It may overlap the
+ *                inputs, which are read as they were before the call (q itself
+ *                as output costs nothing, any other overlap a copy of the rows)
  *   shape        host
  *   workspace    device, >= pkv_attn_workspace_bytes(), 16-byte aligned; may be
  *                NULL when that size is 0.  Contents need no initialisation and

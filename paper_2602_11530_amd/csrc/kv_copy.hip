@@ -130,6 +130,10 @@ hipError_t launch(const void* src, void* dst, const int32_t* ids_a, const int32_
 
 }  // namespace
 
+hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t stream) {
+  return hipMemcpyAsync(dst, src, (size_t)bytes, hipMemcpyDeviceToDevice, stream);
+}
+
 hipError_t launch_kv_block_copy(const void* src, void* dst, const int32_t* block_ids,
                                 int64_t n_blocks, int64_t block_bytes, int64_t num_pool_blocks,
                                 bool gather, int32_t* id_faults, hipStream_t stream) {

@@ -173,6 +173,11 @@ int pkv_attn_workspace_bytes(const pkv_attn_shape* shape, size_t* out_bytes) {
   return PKV_OK;
 }
 
+static void set_leaves(pkv::AttnLaunch* a, pkv::Leaves leaves) {
+  a->leaves = leaves;
+  a->ws_words = a->ws_rec + (int64_t)pkv::records_before_words(leaves) * pkv::record_floats(a->G, a->D);
+}
+
 // Validation shared by the single-layer and the multi-layer call; fills the
 // launch descriptor except for the per-layer pointers.
 static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens, float scale, bool kv_fp8,
@@ -220,7 +225,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->out_scale = 1.f;
   a->kv_fp8 = kv_fp8;
   a->ws_rec = static_cast<float*>(workspace);
-  a->ws_words = a->ws_rec + (int64_t)pkv::records_before_words(a->leaves) * pkv::record_floats(g.G, a->D);
+  set_leaves(a, a->leaves);
   a->layer_ws_floats = pkv::layer_ws_floats(g.G, a->D);
   a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
   return PKV_OK;
@@ -245,21 +250,42 @@ static int launch_attn(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers, 
   return PKV_OK;
 }
 
-static int launch_layer(pkv::AttnLaunch& a, const void* q, const void* k_pool, const void* v_pool,
-                        void* out, hipStream_t st) {
-  a.layer = layer_of(q, k_pool, v_pool, out);
-  return launch_attn(a, nullptr, st);
+static uint64_t row_bytes(const pkv::AttnLaunch& a) { return (uint64_t)a.S * a.Hq * a.D * 2; }
+
+// Does layer x's output overlap these bytes?
+static bool overlaps(const pkv::AttnLaunch& a, const pkv::AttnLayer& x, const void* p, uint64_t bytes) {
+  const uint64_t out = reinterpret_cast<uintptr_t>(x.out), at = reinterpret_cast<uintptr_t>(p);
+  return out < at + bytes && at < out + row_bytes(a);
+}
+
+static bool overlaps_pools(const pkv::AttnLaunch& a, const pkv::AttnLayer& x, const pkv::AttnLayer& y) {
+  const uint64_t pool = (uint64_t)a.NB * a.Hkv * a.upb * pkv::kBlockTokens * a.D * (a.kv_fp8 ? 1 : 2);
+  return overlaps(a, x, y.k_pool, pool) || overlaps(a, x, y.v_pool, pool);
 }
 
 // Does what layer x writes overlap what layer y reads or writes?  Then they cannot share a launch.
 static bool writes_into(const pkv::AttnLaunch& a, const pkv::AttnLayer& x, const pkv::AttnLayer& y) {
-  const uint64_t rows = (uint64_t)a.S * a.Hq * a.D * 2;
-  const uint64_t pool = (uint64_t)a.NB * a.Hkv * a.upb * pkv::kBlockTokens * a.D * 2;
-  auto overlap = [&](const void* p, uint64_t bytes) {
-    const uint64_t out = reinterpret_cast<uintptr_t>(x.out), at = reinterpret_cast<uintptr_t>(p);
-    return out < at + bytes && at < out + rows;
-  };
-  return overlap(y.q, rows) || overlap(y.out, rows) || overlap(y.k_pool, pool) || overlap(y.v_pool, pool);
+  return overlaps(a, x, y.q, row_bytes(a)) || overlaps(a, x, y.out, row_bytes(a)) || overlaps_pools(a, x, y);
+}
+
+// Does a layer write into its own inputs?  The stream pass stores rows while others are still being read, which
+// is right where the output is q itself: a segment's rows of q are read by those who write them.
+static bool writes_own_input(const pkv::AttnLaunch& a, const pkv::AttnLayer& x) {
+  return (x.out != x.q && overlaps(a, x, x.q, row_bytes(a))) || overlaps_pools(a, x, x) ||
+         overlaps(a, x, a.block_tables, (uint64_t)a.S * a.MAXB * 4) || overlaps(a, x, a.context_lens, (uint64_t)a.S * 4);
+}
+
+// One layer.  Where it writes into its own inputs the rows are kept at the end of the workspace's records until all
+// is read: a batch uses no more than kFew + row_blocks of them and a few words' worth, or fewer, except by rows
+// throughout, which is then left out.
+static int launch_layer(pkv::AttnLaunch a, const pkv::AttnLayer& layer, hipStream_t st) {
+  a.layer = layer;
+  if (!writes_own_input(a, layer)) return launch_attn(a, nullptr, st);
+  if (a.leaves == pkv::kRows) set_leaves(&a, pkv::kFewSegments);
+  a.layer.out = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.ws_cum) - row_bytes(a));
+  const int rc = launch_attn(a, nullptr, st);
+  if (rc != PKV_OK) return rc;
+  return launch_status(pkv::launch_copy(a.layer.out, layer.out, row_bytes(a), st));
 }
 
 int paged_decode_attn(const void* q, const void* k_pool, const void* v_pool,
@@ -273,7 +299,7 @@ int paged_decode_attn(const void* q, const void* k_pool, const void* v_pool,
   if (rc != PKV_OK || empty) return rc;
   rc = check_layer_pointers(q, k_pool, v_pool, out);
   if (rc != PKV_OK) return rc;
-  return launch_layer(a, q, k_pool, v_pool, out, static_cast<hipStream_t>(stream));
+  return launch_layer(a, layer_of(q, k_pool, v_pool, out), static_cast<hipStream_t>(stream));
 }
 
 int paged_decode_attn_fp8kv(const void* q, const void* k_pool, const void* v_pool,
@@ -297,7 +323,7 @@ int paged_decode_attn_fp8kv(const void* q, const void* k_pool, const void* v_poo
   // to the normalised row
   a.scale_log2e = scale * k_scale * 1.4426950408889634f;
   a.out_scale = v_scale;
-  return launch_layer(a, q, k_pool, v_pool, out, static_cast<hipStream_t>(stream));
+  return launch_layer(a, layer_of(q, k_pool, v_pool, out), static_cast<hipStream_t>(stream));
 }
 
 int paged_decode_attn_static(const void* q, const void* k_pool, const void* v_pool,
@@ -317,7 +343,7 @@ int paged_decode_attn_static(const void* q, const void* k_pool, const void* v_po
   bool empty = false;
   rc = prepare_attn(block_tables, context_lens, scale, false, shape, ws, kStaticScratchBytes, &a, &empty);
   if (rc != PKV_OK || empty) return rc;
-  return launch_layer(a, q, k_pool, v_pool, out, static_cast<hipStream_t>(stream));
+  return launch_layer(a, layer_of(q, k_pool, v_pool, out), static_cast<hipStream_t>(stream));
 }
 
 int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
@@ -356,14 +382,15 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
     while (layers.count < even && l + layers.count < num_layers) {
       const int32_t next = l + layers.count;
       const pkv::AttnLayer y = layer_of(q[next], k_pools[next], v_pools[next], out[next]);
-      bool apart = true;
+      bool apart = layers.count == 0 || !writes_own_input(a, y);
       for (int i = 0; i < layers.count; ++i)
         apart = apart && !writes_into(a, layers.layer[i], y) && !writes_into(a, y, layers.layer[i]);
       if (!apart) break;
       layers.layer[layers.count++] = y;
+      if (writes_own_input(a, y)) break;
     }
-    a.layer = layers.layer[0];
-    rc = launch_attn(a, layers.count > 1 ? &layers : nullptr, static_cast<hipStream_t>(stream));
+    rc = layers.count > 1 ? launch_attn(a, &layers, static_cast<hipStream_t>(stream))
+                          : launch_layer(a, layers.layer[0], static_cast<hipStream_t>(stream));
     if (rc != PKV_OK) return rc;
   }
   return PKV_OK;

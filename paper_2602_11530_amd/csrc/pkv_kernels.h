@@ -223,6 +223,9 @@ hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hip
 // Reduce pass: the segments that several workgroups share, from their records.
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 
+// Plain device-to-device copy.
+hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t stream);
+
 // Whole-block copies; `gather` selects the direction.
 // `id_faults` (optional, device): incremented once per listed block that is skipped because an
 // id lies outside its pool.

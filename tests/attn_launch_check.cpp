@@ -28,6 +28,8 @@ struct Call {   // the call under way
   std::vector<int> lens;
   int64_t need = 0;
   std::vector<int> layers_of_launch;
+  std::vector<std::pair<int64_t, int64_t>> written;   // by the latest launch
+  long copies = 0;
   long past_end = 0, overlaps = 0, wrong = 0;
 };
 Call call;
@@ -89,6 +91,7 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
       }
   }
   writes.done();
+  call.written = writes.spans;
 }
 
 }  // namespace
@@ -102,6 +105,15 @@ hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers*, hipStream_
   if (a.leaves == kNoRecords) call.wrong++;
   return hipSuccess;
 }
+// Rows kept in the workspace until all inputs are read.
+hipError_t launch_copy(const void* src, void*, int64_t bytes, hipStream_t) {
+  const int64_t at = static_cast<const char*>(src) - kWorkspace;
+  if (at < 0 || at % 16 != 0 || at + bytes > call.need) call.past_end++;
+  for (auto& w : call.written)
+    if (w.first < at + bytes && at < w.second) call.overlaps++;
+  call.copies++;
+  return hipSuccess;
+}
 hipError_t launch_kv_block_copy(const void*, void*, const int32_t*, int64_t, int64_t, int64_t, bool, int32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_block_move(const void*, const int32_t*, int64_t, void*, const int32_t*, int64_t, int64_t, int64_t, int32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_append(const uint16_t*, const uint16_t*, uint16_t*, uint16_t*, const int32_t*, const int32_t*, int, int, int, int, int, int, int, int32_t*, hipStream_t) { return hipSuccess; }
@@ -111,7 +123,8 @@ hipError_t launch_stream_read_probe(const void*, const void*, uint32_t, int64_t,
 
 static long failures = 0;
 
-static void attend(const std::vector<int>& lens, int hq, int hkv, int dim, int bound, int layers) {
+// into_q: the output begins that many bytes behind q.
+static void attend(const std::vector<int>& lens, int hq, int hkv, int dim, int bound, int layers, int into_q = -1) {
   call = Call();
   call.lens = lens;
   const int longest = std::max(bound, *std::max_element(lens.begin(), lens.end()));
@@ -132,13 +145,14 @@ static void attend(const std::vector<int>& lens, int hq, int hkv, int dim, int b
   std::vector<void*> out;
   for (int l = 0; l < layers; ++l) {
     for (int i = 0; i < 3; ++i) in[i].push_back(reinterpret_cast<void*>(((uintptr_t)2 << 40) + ((uintptr_t)(4 * l + i) << 36)));
-    out.push_back(reinterpret_cast<void*>(((uintptr_t)2 << 40) + ((uintptr_t)(4 * l + 3) << 36)));
+    out.push_back(reinterpret_cast<void*>(((uintptr_t)2 << 40) + (into_q < 0 ? (uintptr_t)(4 * l + 3) << 36 : ((uintptr_t)(4 * l) << 36) + into_q)));
   }
   const int32_t* p4 = reinterpret_cast<const int32_t*>((uintptr_t)1 << 39);
   if (rc == PKV_OK)
     rc = paged_decode_attn_layers(in[0].data(), in[1].data(), in[2].data(), p4, p4, 1.f, out.data(), layers, &sh, kWorkspace, need, nullptr);
   int launched = 0;
   for (int n : call.layers_of_launch) launched += n;
+  if (call.copies != (into_q > 0 ? layers : 0)) call.wrong++;   // q itself may be the output
   if (rc != PKV_OK || launched != layers || call.past_end || call.overlaps || call.wrong) {
     if (failures++ < 20)
       printf("S=%zu heads %d/%d D=%d bound %d, %d layers (%d launched in %zu): status %d, %ld writes past the workspace's %zu bytes, %ld overlaps, %ld wrong\n",
@@ -179,6 +193,7 @@ int main() {
           for (int layers : {1, 2, 4, 5, 8, 9, 17}) {
             attend(lens, h[0], h[1], dim, limit, layers);        // the bound says how long they are
             if (layers < 9) attend(lens, h[0], h[1], dim, 50000, layers);   // and does not
+            if (layers == 2) attend(lens, h[0], h[1], dim, trial % 2 ? limit : 50000, layers, 128 * (trial % 3));
             calls += 2;
           }
         }

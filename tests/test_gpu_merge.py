@@ -164,3 +164,48 @@ def test_layers_stay_inside_the_workspace(device, lens, hq, hkv, dim, bound, lay
     for i in range(layers):
         want = run_attn_dev(w, qs[i], ks[i], vs[i], tables, lens_d, max_context_len=bound)
         assert torch.equal(outs[i], want), i
+
+
+@pytest.mark.parametrize("lens,hq,hkv,dim", [
+    ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # more than 64 segments
+    ([3000, 40, 0, 700], 16, 8, 128),                        # few
+    ([1500, 0, 30] * 12, 4, 1, 64),                          # by rows
+    ([9000, 300], 8, 1, 128),
+    ([40, 3, 300, 0], 8, 2, 128),                            # cut along the segments
+])
+def test_output_over_inputs(device, lens, hq, hkv, dim):
+    """The inputs are read as they were before the call, also where the output lies over q or over a pool."""
+    w, (q, k, v, tables, lens_d) = setup(lens, hq, hkv, dim, seed=700)
+    want = run_attn_dev(w, q, k, v, tables, lens_d)
+    ref = oracle.paged_decode_attn(*[to_bits(t).reshape(s) for t, s in zip((q, k, v), (w.q_shape(), w.pool_shape(), w.pool_shape()))],
+                                   w.block_tables, w.context_lens, w.scale)
+    shape = shape_of(w)
+    ws = torch.empty(pkv.pkv_attn_workspace_bytes(shape), dtype=torch.uint8, device=device)
+
+    def check(out, what, exact):
+        torch.cuda.synchronize()
+        if exact:
+            assert torch.equal(out, want), what
+        c = oracle.compare(to_bits(out), ref)
+        assert abs_error_within_bar(to_bits(out), ref) and c["rel_l2"] <= REL_L2, (what, c)
+
+    n = q.numel()
+    for shift in (0, 8, dim, -dim, hq * dim, -3 * hq * dim):   # elements
+        buf = torch.zeros(n + 2 * abs(shift), dtype=torch.int16, device=device)
+        at = abs(shift)
+        buf[at:at + n] = q.reshape(-1)
+        out = buf[at + shift:at + shift + n].view(q.shape)
+        run_attn_dev(w, buf[at:at + n].view(q.shape), k, v, tables, lens_d, workspace=ws, out=out)
+        check(out, shift, shift == 0)
+    pool = k.clone()
+    flat = pool.view(-1)
+    out = flat[flat.numel() - n:].view(q.shape)
+    run_attn_dev(w, q, pool, v, tables, lens_d, workspace=ws, out=out)
+    check(out, "K pool", False)
+    # in the layers call the next layer reads what this one wrote
+    pool = k.clone()
+    flat = pool.view(-1)
+    outs = [flat[flat.numel() - n:].view(q.shape), torch.empty_like(q)]
+    pkv.paged_decode_attn_layers([q, q], [pool, pool], [v, v], tables, lens_d, float(w.scale), outs, shape, ws)
+    check(outs[0], "first layer", False)
+    assert torch.equal(outs[1], run_attn_dev(w, q, pool, v, tables, lens_d))
