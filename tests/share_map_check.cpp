@@ -1,10 +1,10 @@
 // Host-side brute-force check of the stream share map used by the attention kernels:
 // shares tile the stream, none is empty when there are at least as many blocks as
 // wavefronts, and share_owner inverts share_start.
-// Then the record slots: walking every wavefront's share block by block (as the
-// stream pass does), slot = segment + wavefront is unique, stays below the bound
+// Then the record slots of a batch that goes by rows: walking every wavefront's share block by block (as
+// the stream pass does), slot = segment + wavefront is unique, stays below the bound
 // the workspace is sized for, and the slots of a segment are exactly the range
-// the merge pass computes from the owners of its first and last block.
+// the reduce pass computes from the owners of its first and last block.
 // Compiled and run by tests/test_share_map.py (host code only, no GPU).
 #include "pkv_kernels.h"
 #include <cstdio>

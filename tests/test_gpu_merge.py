@@ -1,6 +1,6 @@
-"""GPU tests of the merge inside the stream pass: segments that lie in one wavefront's share, in one
-workgroup, in a few workgroups and in more than one workgroup reads at once (two levels), on workspaces
-whose earlier contents vary, called repeatedly and replayed from a graph."""
+"""GPU tests of how the partial results of a segment (request, KV head) meet: inside a wavefront's share, in a
+workgroup, over several workgroups (a record for each), by rows (a record for each wavefront), in batches cut
+along their segments; on workspaces whose earlier contents vary, called repeatedly and replayed from a graph."""
 import numpy as np
 import pytest
 import torch
@@ -12,16 +12,21 @@ from paper_2602_11530_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-# lengths, query heads, KV heads, head dim: how many workgroups (of 2048/8, or 1024/4 at D = 256) share a segment
+# lengths, query heads, KV heads, head dim
 SHAPES = [
-    ([33000], 8, 1, 128),            # all 256: two levels
-    ([17000, 16000], 8, 2, 64),      # 64 each, and a boundary inside a workgroup
+    ([33000], 8, 1, 128),            # a handful of segments, by rows: over all wavefronts
+    ([17000, 16000], 8, 2, 64),      # a boundary inside a workgroup
     ([9000, 1, 20000], 5, 1, 256),   # two long segments and a one-block one between them
-    ([4200] * 8, 16, 1, 128),        # 32 each: the most that are read in one go
-    ([4300] * 7 + [2000], 16, 1, 128),   # just beyond it
-    ([2048] * 64, 8, 4, 128),        # shares and segments end together: nothing is shared
+    ([4200] * 8, 16, 1, 128),        # few segments, workgroups' records: 32 each
+    ([4300] * 7 + [2000], 16, 1, 128),
+    ([2048] * 64, 8, 4, 128),        # many; shares and segments end together: nothing is shared
     ([1, 16, 17, 0, 33] * 60, 10, 2, 64),    # many segments inside one share
-    ([16] * 700 + [30000], 12, 1, 128),      # staged rows fill up; then one long segment
+    ([16] * 700 + [30000], 12, 1, 128),      # staged rows fill up; then one long segment, in one set of threads
+    ([16] * 100 + [30000], 2, 1, 64),        # many, one of them over nearly all workgroups: 16 sets of threads, several
+    ([16] * 100 + [30000], 5, 1, 64),        # reads for each; sets that do not fill the workgroup
+    ([16] * 100 + [30000], 4, 1, 256),
+    ([16] * 70 + [9000, 0, 7000], 8, 1, 256),
+    ([5000, 900, 1, 3000] * 18, 5, 1, 256),  # many, shared by two or three workgroups each
     ([700, 0, 5000, 3, 129], 40, 8, 128),
     ([384, 0, 1, 130, 17], 8, 2, 128),       # cut along the segments: the longest that is (3 blocks per wavefront)
     ([385, 0, 1, 130, 17], 8, 2, 128),       # and one token beyond
@@ -35,7 +40,7 @@ SHAPES = [
     ([384, 16, 15, 0] * 8, 16, 8, 256),
     ([768, 5, 300, 0] * 8, 32, 8, 64),       # as many segments as workgroups
     ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
-    ([2000, 30] * 4, 8, 8, 64),              # the fewest segments that one launch finishes
+    ([2000, 30] * 4, 8, 8, 64),              # as many as count as few, and fewer, of one head each
     ([2000, 30] * 4, 7, 7, 64),
     ([16 * 2047], 8, 1, 64),                 # by rows: a block less than wavefronts, as many and one more
     ([16 * 2048 - 5], 8, 1, 128),
@@ -87,9 +92,11 @@ def test_shared_segments(device, i, partition):
         assert np.array_equal(first, again)   # whoever finishes a segment, its rows are the same bits
 
 
-def test_replays_with_growing_lengths(device):
-    """A replayed launch carries the same number as the one before it: nothing of that one may be left over."""
-    w, (q, k, v, tables, lens) = setup([40, 3000, 9, 12000], 8, 1, 128, seed=400)
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (16, 2), (34, 17)])
+def test_replays_with_growing_lengths(device, hq, hkv):
+    """What becomes of a batch is decided on the device: replays of one launch are cut along the segments, go by rows
+    or leave workgroups' records, and nothing of an earlier one may be left over."""
+    w, (q, k, v, tables, lens) = setup([40, 3000, 9, 12000], hq, hkv, 128, seed=400)
     w.context_lens[:] = [17, 16, 9, 33]
     lens.copy_(torch.from_numpy(w.context_lens))
     shape = shape_of(w)
