@@ -194,9 +194,8 @@ __host__ __device__ inline int64_t layer_ws_floats(int G, int D) {
 
 // LDS of a workgroup of the stream pass, in floats: the prefix arrays, then per wavefront a left record
 // and room for a right record or up to 8 finished segments' rows, held to 78 KiB.  One workgroup takes a
-// CU's registers (all but the 8-bit kernel at D = 64), so LDS would allow twice that, but 8 staged segments
-// instead of 5 (G = 5, D = 128) gain nothing: 512 requests of 16..512 tokens 110.2 us at 78 KiB, 112.2 at
-// 152; 64 of 1024..8192 190.7 and 189.2.
+// CU's registers, so LDS would allow twice that, but 8 staged segments instead of 5 (G = 5, D = 128) gain
+// nothing: 512 requests of 16..512 tokens 110.2 us at 78 KiB, 112.2 at 152; 64 of 1024..8192 190.7 and 189.2.
 // Records and rows are read and written 16 bytes at a time and lie on 16-byte boundaries; 4-byte ones,
 // which the LDS unit also accepts, cost those 512 requests 1.6 us and 4 of 17..300 tokens 0.3 of 12.4.
 struct StreamLds {
@@ -220,7 +219,7 @@ inline StreamLds stream_lds(int S, int G, int D) {
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
-// Reduce pass: the segments that several workgroups share, from their records.
+// Reduce pass: the segments that several workgroups (by rows: wavefronts) share, from their records.
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 
 // Plain device-to-device copy.
