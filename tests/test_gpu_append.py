@@ -46,6 +46,27 @@ def test_append_bit_exact_and_skips(device, id_faults):
     assert np.array_equal(to_bits(v_d).reshape(v.shape), wv)
 
 
+@pytest.mark.parametrize("hq,hkv,dim,block", [(8, 1, 64, 16),     # 16 chunks: part of one wavefront
+                                              (6, 3, 128, 32),    # 96 chunks
+                                              (8, 8, 128, 16),    # 256: one full workgroup
+                                              (10, 5, 256, 64),   # 320: K and V end inside different workgroups
+                                              (40, 40, 256, 16)]) # 2560: ten workgroups a request
+def test_append_rows_of_any_width(device, id_faults, hq, hkv, dim, block):
+    """Every chunk of every KV head lands in its slot, whatever share of a workgroup the rows fill."""
+    w = wl.custom([1, 0, block, block + 1, 5 * block - 1], hq, hkv, seed=47, num_pool_blocks=40, head_dim=dim,
+                  block_size=block)
+    rng = np.random.default_rng(9)
+    k, v = (rng.integers(0, 65536, size=(40, hkv, block, dim)).astype(np.uint16) for _ in range(2))
+    k_new, v_new = (rng.integers(0, 65536, size=(w.num_seqs, hkv, dim)).astype(np.uint16) for _ in range(2))
+    k_d, v_d = to_dev(k), to_dev(v)
+    pkv.kv_append(to_dev(k_new), to_dev(v_new), k_d, v_d, to_dev(w.block_tables), to_dev(w.context_lens), shape_of(w))
+    torch.cuda.synchronize()
+    wk, wv = oracle.kv_append(k_new, v_new, k, v, w.block_tables, w.context_lens)
+    assert np.array_equal(to_bits(k_d).reshape(k.shape), wk)
+    assert np.array_equal(to_bits(v_d).reshape(v.shape), wv)
+    assert int(id_faults.item()) == 0
+
+
 def test_decode_loop_append_then_attend(device):
     """Three decode steps of a mixed batch: lengths grow by one, the new rows are
     appended through the library, attention is checked against the oracle run on
