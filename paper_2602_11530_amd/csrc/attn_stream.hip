@@ -29,9 +29,9 @@
 //
 // Per 16-token block, lane = 16*c + n, head_dim D = 128 (64 and 256 below):
 //   S^T = K . Q^T   D/32 v_mfma_f32_16x16x32_bf16 (k = 32 dims each).
-//         A = K rows: lane (n, c) loads the 16 bytes at dims 32*jj + 8*c of
-//         token tau(n) = 4*(n%4) + n/4, straight from the pool (a 64-byte run
-//         per token per load).  B = q: lane (n, c) holds the same dims of head n
+//         A = K rows: lane (n, c) has the 16 bytes at dims 32*jj + 8*c of
+//         token tau(n) = 4*(n%4) + n/4.  K is loaded in whole rows, 1 KiB in a row per
+//         load, and turned to that order in LDS.  B = q: lane (n, c) holds the same dims of head n
 //         (the GQA group padded to 16 rows).  The result leaves lane (n, c)
 //         with head n's scores for tokens 4*i + c.
 //   P     = exp2(score - m) in fp32, split into bf16 hi + lo parts so that the
@@ -59,8 +59,20 @@
 // address path of the KV loads.
 //
 // Memory traffic.  The KV loads of a block (eight of 16 bytes at D = 128) are
-// nontemporal and unconditional; a ring of kRing register buffers keeps
-// kRing - 1 blocks (one) in flight per wavefront.  Finished rows and records wait in LDS and are written in
+// nontemporal and unconditional.  A load that takes 64 bytes of each of 16 tokens, as the matrix cores
+// want K, keeps the address unit busy for twice the lines and takes each of them from the caches in two
+// halves; whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
+// latency per block and are faster where that counts (append and attention: 4 requests of 17..300 tokens
+// 11.9 -> 11.1 us, 8 at D = 256 34.5 -> 33.0, 32 at D = 64 45.9 -> 43.3, 64 on 8-bit pools 109.2 -> 105.8)
+// and equal or a little faster where the memory is saturated either way (64 of 1024..8192 190.6 -> 188.9, 128 long ones
+// 584.7 -> 577.9).  What is in flight per wavefront, 2048 of them (1024 at D = 256):
+//   blocks of up to 4 KiB, and of 16 KiB at D = 256: the next block's loads go out once this one's are there
+//   bf16 at D = 128 (8 KiB): V of this block and the first half of the next one's K go out once K is there, the
+//       other half after the block, 4 to 6 KiB at any time; with 8 KiB some dies of the chip get more than their
+//       part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584 instead of 578;
+//       with 4 KiB 4-KiB blocks lose a quarter, which is why those have all of theirs ahead)
+// Deeper rings (3 or 7 blocks ahead) only lengthen the queues.
+// Finished rows and records wait in LDS and are written in
 // bursts of full-width write-through stores that the compiler's wait-count
 // bookkeeping does not see (see store16).
 #include "attn_partial.h"
@@ -71,13 +83,8 @@ namespace {
 
 constexpr int kWindow = 64;       // descriptors per window: one per lane
 
-// Register buffers per wavefront: the block being consumed and the block in
-// flight behind it.  With 2048 wavefronts (1024 at D = 256) that is 16 MB on its
-// way at any time, which keeps the memory system saturated; deeper rings (4 and
-// 8 were measured, at every head dimension and pool format) only lengthen the
-// queues: 0.5 % slower on the Qwen-32B-shaped batches, 2 to 5 % on the variants
-// whose blocks are half the bytes, 5 to 20 % on batches of a few requests.
-constexpr int kRing = 2;
+// bf16 at D = 128: K loads, of four, of the next block that go out with this block's V.
+constexpr int kAhead = 2;
 
 // What depends on the head dimension and the pool format.
 template <int kD, bool kFp8> struct Dim;
@@ -185,8 +192,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
   constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
+  constexpr bool kVLate = kD == 128 && !kFp8;   // V goes out when K is there, not a block ahead
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
-  static_assert(kWindow % kRing == 0, "the window must be a whole number of ring turns");
   extern __shared__ __align__(16) int smem[];
   int* cumB = smem;                  // [S+1] blocks before request s
   int* lens = smem + (a.S + 1);      // [S]   clamped context lengths
@@ -287,6 +294,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       nshare = shares.start(w + 1) - pos0;
     }
   }
+  // the same for all lanes: the stream's loop and its addresses are scalar (32 requests at D = 64 43.6 -> 43.1 us)
+  pos0 = __builtin_amdgcn_readfirstlane(pos0);
+  nshare = __builtin_amdgcn_readfirstlane(nshare);
   // An empty request owes zero rows.
   auto zero_empty_rows = [&]() {
     for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     const int kvh = o / nb;
     return Place{lo, kvh, o - kvh * nb, nb};
   };
-  auto describe = [&](int jb) -> Window {
+  auto describe = [&](int jb) __attribute__((always_inline)) -> Window {
     const int j = jb + lane;
     const bool live = j < nshare;
     const Place at = place(pos0 + max(min(j, nshare - 1), 0));
@@ -354,7 +364,14 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
   const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
   const int tau = 4 * (n & 3) + (n >> 2);
-  const int koff = tau * (kD * kElemBytes / 16) + c;   // in 16-byte units within the slab
+  // K, in 16-byte pieces of the slab: a wavefront's load is 64 of them in a row, turned in LDS, where piece p of token t
+  // lies in place p ^ t of its row so that neither way has bank conflicts.  Straight in operand order, 4 of each token, where
+  // that is all of a token's (e4m3 at D = 64) and where LDS has no room (stream_lds).
+  constexpr int kPieces = kD * kElemBytes / 16;   // of a token
+  constexpr int kSwizzle = (kPieces < 16 ? kPieces : 16) - 1;
+  const bool turns = kD == 128 ? a.turns : kKLoads > 1;
+  const int koff = turns ? lane : tau * kPieces + c;
+  u32x4* turn = (u32x4*)(wave_lds + kGroupWaves * a.wave_lds_floats) + wave * (kBlockTokens * kPieces);
   // V, in units of one VReg: token 4*e + c, this lane's dims (of half h when D = 256)
   const int voff = kD == 256 ? 32 * c + n : lane;
 
@@ -365,22 +382,30 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
   for (int i = 0; i < kTiles; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Issue the loads of stream index j (K in operand order, V
-  // natural), nontemporal: the stream is read once and must not allocate in the
+  // The loads of stream index j, nontemporal: the stream is read once and must not allocate in the
   // caches it passes through.  The loads are unconditional so that every wait in the loop knows
   // exactly how many are outstanding: a block that is unmapped, or an index past
   // the share's end, reads slab 0 (which always exists) and is masked or skipped.
-  auto issue = [&](u32x4 (&k)[kKLoads], VReg (&v)[kVLoads], int j) {
+  auto slab_at = [&](int j) -> int64_t {   // byte offset of the slab of stream index j
     const int idx = j - jbase;   // 0 .. 2*kWindow-1
     const int sa = __builtin_amdgcn_readlane(dA.slab, idx & (kWindow - 1));
     const int sb = __builtin_amdgcn_readlane(dB.slab, idx & (kWindow - 1));
     int slab = (idx < kWindow) ? sa : sb;
     if (j >= nshare) slab = 0;
-    const int64_t base = (int64_t)slab * slab_bytes;
-    const u32x4* kp = (const u32x4*)((const char*)layer.k_pool + base) + koff;
-    const VReg* vp = (const VReg*)((const char*)layer.v_pool + base) + voff;
+    return (int64_t)slab * slab_bytes;
+  };
+  auto issue_k = [&](u32x4 (&k)[kKLoads], int j, int from, int to) {
+    const u32x4* kp = (const u32x4*)((const char*)layer.k_pool + slab_at(j)) + koff;
+    if (turns) {
 #pragma unroll
-    for (int jj = 0; jj < kKLoads; ++jj) k[jj] = __builtin_nontemporal_load(kp + 4 * jj);
+      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 64 * jj);
+    } else {
+#pragma unroll
+      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 4 * jj);
+    }
+  };
+  auto issue_v = [&](VReg (&v)[kVLoads], int j) {
+    const VReg* vp = (const VReg*)((const char*)layer.v_pool + slab_at(j)) + voff;
     if (kD == 256) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -390,6 +415,18 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = __builtin_nontemporal_load(vp + 64 * e);
+    }
+  };
+  // K of a block that has arrived, into LDS and back as the A operand: load L of lane (n, c) is piece 4L + c of token tau(n).
+  auto turn_k = [&](u32x4 (&k)[kKLoads]) {
+    if (turns) {
+#pragma unroll
+      for (int jj = 0; jj < kKLoads; ++jj) {
+        const int at = 64 * jj + lane;
+        turn[at ^ ((at / kPieces) & kSwizzle)] = k[jj];
+      }
+#pragma unroll
+      for (int jj = 0; jj < kKLoads; ++jj) k[jj] = turn[tau * kPieces + ((4 * jj + c) ^ (tau & kSwizzle))];
     }
   };
 
@@ -402,7 +439,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   int staged_segs = 0;   // lane r: staged segment r
   bool seg_open = false;   // a parked record belongs to the segment being streamed
   int ends_flags = 0, left = 0, right = 0;   // how the share ends, and the segments in the left and the right record
-  auto store_staged = [&]() {
+  auto store_staged = [&]() __attribute__((always_inline)) {
     for (int r = 0; r < nstaged; ++r) {
       const int seg = __builtin_amdgcn_readlane(staged_segs, r);
       float* dst = (float*)(layer.out + (int64_t)seg * (G * kD));
@@ -412,35 +449,35 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     nstaged = 0;
   };
 
-  auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int j) {
+  auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int j) __attribute__((always_inline)) {
     const int idx = j - jbase;   // always inside window A
-    // The MFMA operands.  bf16 pools: the loaded registers themselves.  e4m3 pools: load L of
-    // K holds dims 16*(4L + c) .. +15 of token tau(n), which feed steps 2L and 2L + 1 (the
+    // The MFMA operands.  bf16 pools: the registers as they are.  e4m3 pools: piece 4L + c of
+    // K's row holds dims 16*(4L + c) .. +15 of token tau(n), which feed steps 2L and 2L + 1 (the
     // contraction order is free as long as q follows it, see below); a V load holds the same
     // token and dims as in a bf16 pool, one byte each.
     u32x4 k[kKSteps];
     VOp v[kVLoads];
-    if constexpr (kFp8) {
 #pragma unroll
-      for (int jj = 0; jj < kKSteps; ++jj) {
-        const u32x2 a2 = widen_e4m3x4(kraw[jj >> 1][2 * (jj & 1)]);
-        const u32x2 b2 = widen_e4m3x4(kraw[jj >> 1][2 * (jj & 1) + 1]);
-        k[jj] = u32x4{a2.x, a2.y, b2.x, b2.y};
+    for (int jj = 0; jj < kKLoads; ++jj) {
+      const u32x4 x = kraw[jj];
+      if constexpr (kFp8) {
+        const u32x2 y[4] = {widen_e4m3x4(x.x), widen_e4m3x4(x.y), widen_e4m3x4(x.z), widen_e4m3x4(x.w)};
+        k[2 * jj] = u32x4{y[0].x, y[0].y, y[1].x, y[1].y};
+        k[2 * jj + 1] = u32x4{y[2].x, y[2].y, y[3].x, y[3].y};
+      } else {
+        k[jj] = x;
       }
+    }
 #pragma unroll
-      for (int e = 0; e < kVLoads; ++e) {
-        if constexpr (kD == 64) {
-          v[e] = widen_e4m3x4(vraw[e]);
-        } else {
-          const u32x2 a2 = widen_e4m3x4(vraw[e].x), b2 = widen_e4m3x4(vraw[e].y);
-          v[e] = VOp{a2.x, a2.y, b2.x, b2.y};
-        }
+    for (int e = 0; e < kVLoads; ++e) {
+      if constexpr (!kFp8) {
+        v[e] = vraw[e];
+      } else if constexpr (kD == 64) {
+        v[e] = widen_e4m3x4(vraw[e]);
+      } else {
+        const u32x2 a2 = widen_e4m3x4(vraw[e].x), b2 = widen_e4m3x4(vraw[e].y);
+        v[e] = VOp{a2.x, a2.y, b2.x, b2.y};
       }
-    } else {
-#pragma unroll
-      for (int jj = 0; jj < kKSteps; ++jj) k[jj] = kraw[jj];
-#pragma unroll
-      for (int e = 0; e < kVLoads; ++e) v[e] = vraw[e];
     }
     const int meta = __builtin_amdgcn_readlane(dA.meta, idx);
     const int ntok = meta & 0xff;
@@ -615,25 +652,26 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj) qop[jj] = (n < G) ? qnext[jj] : u32x4{0, 0, 0, 0};
   };
-  auto ask_q = [&](u32x4 (&k)[kKLoads], VReg (&v)[kVLoads], int j) {   // k, v: the block consumed next
+  auto ask_q = [&](int j) {
     const int idx = j - jbase;
     const int meta = __builtin_amdgcn_readlane(idx < kWindow ? dA.meta : dB.meta, idx & (kWindow - 1));
     if (j >= nshare || !(meta & kMetaSegFirst)) return;
-    // waits for that block here, where it is known how many loads are younger
-#pragma unroll
-    for (int jj = 0; jj < kKLoads; ++jj) asm volatile("" : : "v"(k[jj]));
-#pragma unroll
-    for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
     load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
   };
-
-  // A ring of kRing register buffers: kRing - 1 blocks are always in flight
-  // while one is consumed, and no buffer is ever copied.
-  u32x4 kbuf[kRing][kKLoads];
-  VReg vbuf[kRing][kVLoads];
+  // Waits for loads where it is known how many are younger.
+  auto arrived_k = [](u32x4 (&k)[kKLoads]) {
 #pragma unroll
-  for (int i = 0; i < kRing - 1; ++i) issue(kbuf[i], vbuf[i], i);
-  static_assert(kRing == 2, "a query group is asked for one block ahead");
+    for (int jj = 0; jj < kKLoads; ++jj) asm volatile("" : : "v"(k[jj]));
+  };
+  auto arrived_v = [](VReg (&v)[kVLoads]) {
+#pragma unroll
+    for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
+  };
+
+  u32x4 kbuf[2][kKLoads];   // two blocks in turn, so that no buffer is ever copied
+  VReg vbuf[2][kVLoads];
+  issue_k(kbuf[0], 0, 0, kKLoads);
+  if (!kVLate) issue_v(vbuf[0], 0);
   load_q(__builtin_amdgcn_readlane(dA.seg, 0));
   if (nshare > kWindow) dB = describe(kWindow);
   if (wave == 0 && leaves_words && !by_row) {
@@ -652,18 +690,29 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
     if (lane == 0) word = SharedSegment{row, count};
   }
-  for (int j = 0; j < nshare; j += kRing) {
+  for (int j = 0; j < nshare; j += 2) {
 #pragma unroll
-    for (int i = 0; i < kRing; ++i) {
-      constexpr int kAhead = kRing - 1;
-      issue(kbuf[(i + kAhead) % kRing], vbuf[(i + kAhead) % kRing], j + i + kAhead);
+    for (int i = 0; i < 2; ++i) {
+      u32x4 (&k)[kKLoads] = kbuf[i], (&knext)[kKLoads] = kbuf[i ^ 1];
+      VReg (&v)[kVLoads] = vbuf[i], (&vnext)[kVLoads] = vbuf[i ^ 1];
+      arrived_k(k);
+      if (!kVLate) arrived_v(v);
+      if (!kVLate) {
+        issue_k(knext, j + i + 1, 0, kKLoads);
+        issue_v(vnext, j + i + 1);
+      } else {
+        issue_v(v, j + i);
+        issue_k(knext, j + i + 1, 0, kAhead);
+      }
       if (j + i < nshare) {
         take_q(j + i);
-        ask_q(kbuf[i], vbuf[i], j + i + 1);
-        consume(kbuf[i], vbuf[i], j + i);
+        ask_q(j + i + 1);
+        turn_k(k);
+        consume(k, v, j + i);
       }
+      if (kVLate) issue_k(knext, j + i + 1, kAhead, kKLoads);
     }
-    if (j + kRing == jbase + kWindow) {
+    if (j + 2 == jbase + kWindow) {
       // The consumer leaves window A: B becomes A, and the window after it is
       // described now, 64 blocks before its first use.
       dA = dB;
@@ -757,10 +806,11 @@ static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, size_t lds
 
 hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, hipStream_t stream) {
   AttnLaunch a = a_in;
-  const StreamLds l = stream_lds(a.S, a.G, a.D);
+  const StreamLds l = stream_lds(a.S, a.G, a.D, a.kv_fp8);
   a.staged_max = l.staged_max;
   a.wave_lds_floats = l.wave;
-  const size_t lds = l.bytes;
+  a.turns = l.turn_bytes > 0;
+  const size_t lds = l.bytes + l.turn_bytes;
   if (layers && a.kv_fp8) return hipErrorInvalidValue;
   if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
   else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);

@@ -156,6 +156,7 @@ struct AttnLaunch {
   int NB;          // physical blocks per pool; ids outside [0, NB) are never followed
   int wave_lds_floats;  // a wavefront's share of LDS: its left record, then its right record or staged rows
   int staged_max;       // finished segments whose rows a wavefront can stage in LDS
+  int turns;            // there is room in LDS to turn K
   int64_t layer_ws_floats;   // workspace from one layer's records to the next one's
 };
 // The layers of a launch, blockIdx.y being the layer.  A second kernel argument, so that a launch of one
@@ -202,8 +203,9 @@ struct StreamLds {
   int prefix, wave;   // where the wavefronts' parts begin, and from one to the next
   int staged_max;
   int bytes;
+  int turn_bytes;     // behind them, a block of K per wavefront, to turn it; 0 where K is loaded in operand order
 };
-inline StreamLds stream_lds(int S, int G, int D) {
+inline StreamLds stream_lds(int S, int G, int D, bool kv_fp8 = false) {
   const int group = group_waves(D), rec = record_floats(G, D), rows = G * D / 2;
   StreamLds l;
   l.prefix = (2 * (S + 1) + 3) & ~3;
@@ -213,6 +215,10 @@ inline StreamLds stream_lds(int S, int G, int D) {
   l.wave = rec + room;
   l.staged_max = room / rows;
   l.bytes = (l.prefix + group * l.wave) * (int)sizeof(float);
+  // Two whole records per wavefront come first: at D = 128 there is no room for K with more than 12 to 15 query heads
+  // per KV head, by S and format.
+  l.turn_bytes = group * kBlockTokens * D * (kv_fp8 ? 1 : 2);
+  if (l.bytes + l.turn_bytes > 159 * 1024 || (D == 64 && kv_fp8)) l.turn_bytes = 0;
   return l;
 }
 

@@ -1,5 +1,5 @@
 // Measurement aid, not part of the attention path: the rate at which this GPU can
-// stream KV slabs with the stream pass's own access pattern and nothing else.
+// stream KV slabs as the stream pass does where LDS has no room to turn K, and nothing else.
 // The same persistent launch (kLayerGroups workgroups of 8 wavefronts, equal shares), the same
 // two 4 KiB reads per 16-token block of one KV head at D = 128 in bf16 -- a "K"
 // slab in matrix-operand order (a 64-byte run per token row per load) and a "V"

@@ -1,0 +1,15 @@
+"""Room in LDS for turning K (no GPU): its size, place and the batches that have none."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_turn_fits(tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    exe = str(tmp_path / "turn_lds_check")
+    subprocess.check_call([hipcc, "-O1", "--offload-arch=gfx950", "-x", "hip", "-I",
+                           os.path.join(ROOT, "paper_2602_11530_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "turn_lds_check.cpp"), "-o", exe], stderr=subprocess.DEVNULL)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0 and "bad=0" in out.stdout, out.stdout
