@@ -201,13 +201,17 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // record shares its room with finished rows that wait to be stored
   const int rec_floats = record_floats(a.G, kD);
   float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
-  __shared__ int chains, passes;          // bit per wavefront, see the workgroup's merge
+  __shared__ int chains[2], passes[2];    // bit per wavefront, see the workgroup's merge; the next layer uses the other ones
   __shared__ SharedSegment word;          // the workgroup's, for the reduce pass
   __shared__ int left_seg[kGroupWaves];   // the segment that the share's first block belongs to
   __shared__ int any_long;
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
 
-  const AttnLayer layer = layer_of(a, layers);
+  // Several layers to a launch: a workgroup streams its range of one after the other, or (cut along the segments) each
+  // layer has workgroups of its own.
+  const bool chained = is_layers(layers) && a.leaves == kManySegments;
+  int of = layer_index(layers);   // layer
+  AttnLayer layer = layer_of(a, layers);
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
@@ -236,7 +240,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
   }
   const bool some_long = __any(longest > a.short_blocks);
-  if (threadIdx.x == 0) { any_long = some_long; chains = passes = 0; }
+  if (threadIdx.x == 0) { any_long = some_long; chains[0] = passes[0] = 0; }
   __syncthreads();
   if (S > 64) {
     if (some_long && lane == 0) any_long = 1;
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
   // For the reduce pass.
   const bool leaves_words = a.leaves == kManySegments || a.leaves == kFewSegments;
-  if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, layer_index(layers), blockIdx.x)->count = kByRows;
+  if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
   if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
     for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
   }
@@ -316,9 +320,12 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // its records do not wait for the launch descriptor to be read again.
   float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
   if (last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
-    if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, layer_index(layers), blockIdx.x)->count = 0;
-    zero_empty_rows();
-    return;
+    for (;;) {
+      if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
+      zero_empty_rows();
+      if (!chained || ++of == layer_count(layers)) return;
+      layer = layer_at(a, layers, of);
+    }
   }
 
   // Descriptors of stream indices jb .. jb+63 of this share.
@@ -690,6 +697,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
     if (lane == 0) word = SharedSegment{row, count};
   }
+  for (int turned = 0;; turned ^= 1) {   // layers
   for (int j = 0; j < nshare; j += 2) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -735,6 +743,24 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
   zero_empty_rows();
   if (by_row) return;
+  uint16_t* out = layer.out;
+  const bool more = chained && of + 1 < layer_count(layers);
+  const int ends = ends_flags, left_end = left;
+  if (more) {
+    // The next layer: its first loads are on their way while the workgroup meets (six layers of 24 requests, with a
+    // workgroup of its own for each layer's range 760.7 us, this way 755.6).
+    layer = layer_at(a, layers, of + 1);
+    if (jbase) {   // window A is not the first one any more
+      jbase = refused = 0;
+      dA = describe(0);
+    }
+    issue_k(kbuf[0], 0, 0, kKLoads);
+    if (!kVLate) issue_v(vbuf[0], 0);
+    load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+    if (nshare > kWindow) dB = describe(kWindow);
+    seg_open = false;
+    ends_flags = left = right = 0;
+  }
 
   // The workgroup's merge.  Segments that meet inside the workgroup's range are finished from
   // the records in LDS.  What is left are at most two segments that it shares with other
@@ -742,22 +768,22 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // shared segment begins in leaves word of it.
   const AttnLaunch& b = reread(a);
   if (lane == 0) {
-    left_seg[wave] = left;
+    left_seg[wave] = left_end;
     int chain = 0;
-    if ((ends_flags & kEndsLeft) && (!(ends_flags & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
-    if ((ends_flags & kEndsRight) && wave == last_wave) chain |= 1 << kGroupWaves;
-    if (chain) atomicOr(&chains, chain);
-    if (ends_flags & kEndsThrough) atomicOr(&passes, 1 << wave);
+    if ((ends & kEndsLeft) && (!(ends & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
+    if ((ends & kEndsRight) && wave == last_wave) chain |= 1 << kGroupWaves;
+    if (chain) atomicOr(&chains[turned], chain);
+    if (ends & kEndsThrough) atomicOr(&passes[turned], 1 << wave);
   }
   __syncthreads();
   if (threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
-    *shared_segment(b, layer_index(layers), blockIdx.x) = word;
+    *shared_segment(b, of, blockIdx.x) = word;
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
   // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
   // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to
   // four rounds instead of one took 1 us more (64 requests of 50..100 tokens on 40/8 heads 18.4 -> 16.6).
-  const int ending = chains, through = passes;
+  const int ending = chains[turned], through = passes[turned];
 #pragma unroll 1
   for (int i = threadIdx.x; i < __popc(ending) * q4; i += kThreads) {
     const int nth = i / q4, item = i - nth * q4;
@@ -785,12 +811,17 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       fold(p, ml, x);
     }
     if (from_right && !open_right) {
-      *(u32x2*)(layer.out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+      *(u32x2*)(out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
     } else {
-      float* rec = group_record(b, kD, layer_index(layers), blockIdx.x, from_right);
+      float* rec = group_record(b, kD, of, blockIdx.x, from_right);
       store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));
       if (item % (kD / 4) == 0) *(f32x2*)(rec + G * kD + 2 * h) = f32x2{p.m, p.l};
     }
+  }
+  if (!more) return;
+  ++of;
+  if (threadIdx.x == 0) chains[turned ^ 1] = passes[turned ^ 1] = 0;
+  __syncthreads();   // the records in LDS have been read
   }
 }
 
@@ -798,7 +829,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
 template <int kD>
 static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, size_t lds, hipStream_t stream) {
-  const dim3 grid(a.waves / group_waves(kD), layers ? layers->count : 1), block(group_waves(kD) * 64);
+  const dim3 grid(a.waves / group_waves(kD), layers && a.leaves == kNoRecords ? layers->count : 1), block(group_waves(kD) * 64);
   if (layers) hipLaunchKernelGGL((attn_stream_kernel<kD, false, AttnLayers>), grid, block, lds, stream, a, *layers);
   else if (a.kv_fp8) hipLaunchKernelGGL((attn_stream_kernel<kD, true, OneLayer>), grid, block, lds, stream, a, OneLayer{});
   else hipLaunchKernelGGL((attn_stream_kernel<kD, false, OneLayer>), grid, block, lds, stream, a, OneLayer{});

@@ -363,7 +363,7 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
     rc = check_layer_pointers(q[l], k_pools[l], v_pools[l], out[l]);
     if (rc != PKV_OK) return rc;
   }
-  // Several layers to a launch, as many as the workspace holds records for: a compute unit goes on
+  // Several layers to a launch, as many as the workspace holds records for: a workgroup goes on
   // to the next layer when it is done with its share of one, and the start, the uneven end and the reduce
   // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch of few
   // segments has the whole workspace for one layer, and one that leaves no records needs none of it.  Layers

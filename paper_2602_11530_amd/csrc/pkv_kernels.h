@@ -159,7 +159,7 @@ struct AttnLaunch {
   int turns;            // there is room in LDS to turn K
   int64_t layer_ws_floats;   // workspace from one layer's records to the next one's
 };
-// The layers of a launch, blockIdx.y being the layer.  A second kernel argument, so that a launch of one
+// The layers of a launch, one after the other in each workgroup (where each segment has a workgroup, blockIdx.y).  A second kernel argument, so that a launch of one
 // layer reads its pointers with the rest (the look-up costs one request of 8191 tokens 0.4 us).
 struct AttnLayers {
   int count;
@@ -168,6 +168,12 @@ struct AttnLayers {
 struct OneLayer {};
 __device__ __forceinline__ int layer_index(const OneLayer&) { return 0; }
 __device__ __forceinline__ int layer_index(const AttnLayers&) { return blockIdx.y; }
+constexpr bool is_layers(const OneLayer&) { return false; }
+constexpr bool is_layers(const AttnLayers&) { return true; }
+__device__ __forceinline__ int layer_count(const OneLayer&) { return 1; }
+__device__ __forceinline__ int layer_count(const AttnLayers& l) { return l.count; }
+__device__ __forceinline__ const AttnLayer& layer_at(const AttnLaunch& a, const OneLayer&, int) { return a.layer; }
+__device__ __forceinline__ const AttnLayer& layer_at(const AttnLaunch&, const AttnLayers& l, int i) { return l.layer[i]; }
 __device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch& a, const OneLayer&) { return a.layer; }
 __device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch&, const AttnLayers& l) { return l.layer[layer_index(l)]; }
 
