@@ -66,7 +66,9 @@
 // 11.9 -> 11.1 us, 8 at D = 256 34.5 -> 33.0, 32 at D = 64 45.9 -> 43.3, 64 on 8-bit pools 109.2 -> 105.8)
 // and equal or a little faster where the memory is saturated either way (64 of 1024..8192 190.6 -> 188.9, 128 long ones
 // 584.7 -> 577.9).  What is in flight per wavefront, 2048 of them (1024 at D = 256):
-//   blocks of up to 4 KiB, and of 16 KiB at D = 256: the next block's loads go out once this one's are there
+//   e4m3 at D = 64 (2 KiB): the next block's loads go out before this one's are waited for (once they are there
+//       instead: 20 requests of 12000..16500 tokens on 40/8 heads 63.8 us, this way 61.3; 20 of 21000..28000 98.6 and 95.3)
+//   blocks of 4 KiB, e4m3 and bf16 at D = 256: the next block's loads go out once this one's are there
 //   bf16 at D = 128 (8 KiB): V of this block and the first half of the next one's K go out once K is there, the
 //       other half after the block, 4 to 6 KiB at any time; with 8 KiB some dies of the chip get more than their
 //       part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584 instead of 578;
@@ -205,6 +207,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
   constexpr bool kVLate = kD == 128 && !kFp8;   // V goes out when K is there, not a block ahead
+  constexpr bool kTwoBlocks = kD == 64 && kFp8;   // the next block's loads go out before this one's have arrived
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
   extern __shared__ __align__(16) int smem[];
   int* cumB = smem;                  // [S+1] blocks before request s
@@ -661,12 +664,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj) qop[jj] = (n < G) ? qnext[jj] : u32x4{0, 0, 0, 0};
   };
-  auto ask_q = [&](int j) {
-    const int idx = j - jbase;
-    const int meta = __builtin_amdgcn_readlane(idx < kWindow ? dA.meta : dB.meta, idx & (kWindow - 1));
-    if (j >= nshare || !(meta & kMetaSegFirst)) return;
-    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
-  };
   // Waits for loads where it is known how many are younger.
   auto arrived_k = [](u32x4 (&k)[kKLoads]) {
 #pragma unroll
@@ -675,6 +672,13 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   auto arrived_v = [](VReg (&v)[kVLoads]) {
 #pragma unroll
     for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
+  };
+  auto ask_q = [&](VReg (&v)[kVLoads], int j) {   // v: of the block before
+    const int idx = j - jbase;
+    const int meta = __builtin_amdgcn_readlane(idx < kWindow ? dA.meta : dB.meta, idx & (kWindow - 1));
+    if (j >= nshare || !(meta & kMetaSegFirst)) return;
+    if (kTwoBlocks) arrived_v(v);
+    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
   };
 
   u32x4 kbuf[2][kKLoads];   // two blocks in turn, so that no buffer is ever copied
@@ -705,18 +709,19 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     for (int i = 0; i < 2; ++i) {
       u32x4 (&k)[kKLoads] = kbuf[i], (&knext)[kKLoads] = kbuf[i ^ 1];
       VReg (&v)[kVLoads] = vbuf[i], (&vnext)[kVLoads] = vbuf[i ^ 1];
-      arrived_k(k);
-      if (!kVLate) arrived_v(v);
-      if (!kVLate) {
-        issue_k(knext, j + i + 1, 0, kKLoads);
-        issue_v(vnext, j + i + 1);
-      } else {
+      if (!kTwoBlocks) arrived_k(k);
+      if (!kTwoBlocks && !kVLate) arrived_v(v);
+      if (kVLate) {
         issue_v(v, j + i);
         issue_k(knext, j + i + 1, 0, kAhead);
+      } else {
+        issue_k(knext, j + i + 1, 0, kKLoads);
+        issue_v(vnext, j + i + 1);
       }
+      if (kTwoBlocks) arrived_k(k);
       if (j + i < nshare) {
         take_q(j + i);
-        ask_q(j + i + 1);
+        ask_q(v, j + i + 1);
         turn_k(k);
         consume(k, v, j + i);
       }

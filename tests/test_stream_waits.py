@@ -1,9 +1,11 @@
-"""The stream pass's hidden stores, in the assembly that its source gives (no GPU): the loops that send them off do not wait for
-them.  The compiler does not know these stores, so a wait for all but n loads that it puts into such a loop, because the loop
+"""The stream pass's loads and hidden stores, in the assembly that its source gives (no GPU).  The loops that send the stores off
+do not wait for them: the compiler does not know these stores, so a wait for all but n loads that it puts into such a loop, because the loop
 reuses a register that a load may still write to, also waits for all stores but the youngest n."""
 import os
 import re
 import subprocess
+
+import pytest
 
 from paper_2602_11530_amd import build as pkv_build
 
@@ -27,13 +29,25 @@ def loops_with_hidden_stores(kernel):
             yield a, b, [int(n) for x in body for n in re.findall(r"vmcnt\((\d+)\)", x)]
 
 
-def test_store_loops_do_not_wait_for_their_stores(tmp_path):
-    asm = str(tmp_path / "attn_stream.s")
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """(name, assembly) of every variant"""
+    asm = str(tmp_path_factory.mktemp("asm") / "attn_stream.s")
     flags = [f for f in pkv_build.FLAGS if f not in ("-fPIC", "-shared")]
     subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "attn_stream.hip"), "-o", asm],
                           stderr=subprocess.DEVNULL)
-    kernels = re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", open(asm).read(), re.S | re.M)
-    assert len(kernels) == 9
+    found = re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", open(asm).read(), re.S | re.M)
+    assert len(found) == 9
+    return found
+
+
+def test_small_blocks_go_out_before_the_last_has_arrived(kernels):
+    """e4m3 at D = 64: K of a block is waited for with its four V loads and the five of the next block out."""
+    waits = [max(int(n) for n in re.findall(r"vmcnt\((\d+)\)", body)) for name, body in kernels if "ILi64ELb1E" in name]
+    assert waits == [9]
+
+
+def test_store_loops_do_not_wait_for_their_stores(kernels):
     for name, body in kernels:
         found = list(loops_with_hidden_stores(body.split("\n")))
         assert len(found) >= 7, name   # finished rows in the stream (four copies of it) and behind it, two records
