@@ -39,7 +39,8 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published HBM3E bandwidth
 METRIC = "paged decode attn HBM GB/s (% of peak) + KV tokens attended/s, Qwen-32B shape"
 TOKEN_DEF = "one cached position of one request attended in one layer by all its heads"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-KERNEL_SOURCES = ["attn_stream.hip", "attn_reduce.hip", "attn_partial.h", "pkv_kernels.h"]
+KERNEL_SOURCES = ["attn_stream.hip", "attn_stream_large.hip", "attn_stream.h", "attn_reduce.hip", "attn_partial.h",
+                  "pkv_kernels.h"]
 MAX_ABS, REL_L2 = 1e-2, 5e-3
 
 

@@ -1,0 +1,849 @@
+// Paged decode attention, stream pass, for gfx950 (wave64, MFMA).
+//
+// Decode attends over every running request's whole KV cache and is bound by
+// memory bandwidth (paper Section II-A), and the batch mixes short answering
+// contexts with long reasoning ones (Section III), so equal work per wavefront
+// cannot come from a per-request grid.  Instead the batch's KV blocks form one
+// stream (layout in pkv_kernels.h) that is cut into kStreamWaves equal shares:
+// every wavefront reads the same number of blocks (+-1), starts streaming at
+// once, never idles between requests, and there is no tail of late workgroups.
+// A wavefront computes one partial result per run (a stretch of its share inside
+// one request, one KV head and one P-token partition) and folds the runs of one
+// (request, KV head) together.  What lies wholly inside its share is finished there and
+// then: normalised, rounded and staged in LDS for a burst of stores (512 requests of 16
+// to 512 tokens: 1.5 MB of records and their reduce pass instead of 16 MB, call 125 ->
+// 115 us).  Of what it shares with other wavefronts it leaves one record, and the
+// reduce pass (attn_reduce.hip) combines the records of each (request, KV head).
+//
+// Three ways to that end, by what the segments are like:
+//   workgroups' records   the wavefronts of a workgroup fold what they share in LDS first, so at most
+//                    two records per workgroup reach memory (64 requests of 1024..8192 tokens on 40/8 heads:
+//                    194.2 us -> 191.0 with the reduce pass; one of 8191 19.1 -> 17.6)
+//   by rows          the wavefronts' records go to memory as they are and the reduce pass has a workgroup
+//                    per row: few segments where meeting in LDS costs more than it saves (what_is_left,
+//                    row_blocks)
+//   cut along them   one workgroup per segment, which meets in LDS and finishes it: no records, and no
+//                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
+//                    heads: 14.0 -> 11.3 us and a launch less on the host).  Few and short ones, up to 3
+//                    or 6 blocks per wavefront (short_segment).
+//
+// Per 16-token block, lane = 16*c + n, head_dim D = 128 (64 and 256 below):
+//   S^T = K . Q^T   D/32 v_mfma_f32_16x16x32_bf16 (k = 32 dims each).
+//         A = K rows: lane (n, c) has the 16 bytes at dims 32*jj + 8*c of
+//         token tau(n) = 4*(n%4) + n/4.  K is loaded in whole rows, 1 KiB in a row per
+//         load, and turned to that order in LDS.  B = q: lane (n, c) holds the same dims of head n
+//         (the GQA group padded to 16 rows).  The result leaves lane (n, c)
+//         with head n's scores for tokens 4*i + c.
+//   P     = exp2(score - m) in fp32, split into bf16 hi + lo parts so that the
+//         weights keep ~16 mantissa bits through the second product.
+//   O    += P . V   D/16 v_mfma_f32_16x16x16_bf16 per part.  V is loaded in its
+//         natural order (lane (n, c) gets dims 8n..8n+7 of tokens 4*e + c, four
+//         fully contiguous 1 KiB loads); the operand for output dims 8*n + i
+//         pairs up the i-th halves of those four loads with v_perm_b32.  The
+//         token order 4*e + c is exactly the one the scores came out in, so P
+//         needs no shuffle between the two products.
+//   D = 64:  lane (n, c) owns dims 4n..4n+3; its V loads are 8 bytes wide (four
+//         fully contiguous 512-byte loads), two K steps, four output tiles.
+//   D = 256: lane (n, c) owns dims 8n..8n+7 of each 128-dim half; eight K steps,
+//         eight 16-byte V loads (a 256-byte run per token per load), sixteen
+//         output tiles; a block is 16 KiB here and a wavefront needs more than half
+//         of a SIMD's registers, so one wavefront per SIMD streams (half as many).
+// The running maximum m is only raised when a score exceeds it by more than
+// 2^kLazyLog2; any reference value gives the same softmax, and the bound keeps
+// every weight within fp32/bf16 range.
+//
+// Where a block lives (physical id, KV head), how many of its tokens are valid
+// and whether it closes a run is worked out 64 blocks at a time, one block per
+// lane ("descriptors"), one window ahead of use; the streaming loop itself only
+// reads a lane of those registers per block, so no memory access sits on the
+// address path of the KV loads.
+//
+// Memory traffic.  The KV loads of a block (eight of 16 bytes at D = 128) are
+// nontemporal and unconditional.  A load that takes 64 bytes of each of 16 tokens, as the matrix cores
+// want K, keeps the address unit busy for twice the lines and takes each of them from the caches in two
+// halves; whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
+// latency per block and are faster where that counts (append and attention: 4 requests of 17..300 tokens
+// 11.9 -> 11.1 us, 8 at D = 256 34.5 -> 33.0, 32 at D = 64 45.9 -> 43.3, 64 on 8-bit pools 109.2 -> 105.8)
+// and equal or a little faster where the memory is saturated either way (64 of 1024..8192 190.6 -> 188.9, 128 long ones
+// 584.7 -> 577.9).  What is in flight per wavefront, 2048 of them (1024 at D = 256):
+//   e4m3 at D = 64 (2 KiB): the next block's loads go out before this one's are waited for (once they are there
+//       instead: 20 requests of 12000..16500 tokens on 40/8 heads 63.8 us, this way 61.3; 20 of 21000..28000 98.6 and 95.3)
+//   blocks of 4 KiB, e4m3 at D = 256 (8 KiB) and small batches in bf16 at D = 256 (16 KiB): the next block's loads go out
+//       once this one's are there
+//   bf16 at D = 128 (8 KiB) and large batches at D = 256 (kLate): V of this block and kAhead loads of the next one's K go out
+//       once K is there, the rest of that K after the block: at D = 128 4 to 6 KiB at any time; with 8 KiB some dies of the chip get more than their
+//       part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584 instead of 578;
+//       with 4 KiB 4-KiB blocks lose a quarter, which is why those have all of theirs ahead)
+// Deeper rings (3 or 7 blocks ahead) only lengthen the queues.
+// Finished rows and records wait in LDS and are written in
+// bursts of full-width write-through stores that the compiler's wait-count
+// bookkeeping does not see (see store16).
+#pragma once
+
+#include "attn_partial.h"
+#include "pkv_kernels.h"
+
+namespace pkv {
+namespace {
+
+constexpr int kWindow = 64;       // descriptors per window: one per lane
+
+// kLate: K loads, of four (D = 128) or eight, of the next block that go out with this block's V.
+constexpr int kAhead = 2;
+
+// What depends on the head dimension and the pool format.
+template <int kD, bool kFp8> struct Dim;
+template <> struct Dim<64, false> {
+  static constexpr int kKSteps = 2, kKLoads = 2, kVLoads = 4, kTiles = 4, kElemBytes = 2;
+  typedef uint32_t VReg __attribute__((ext_vector_type(2)));
+};
+template <> struct Dim<128, false> {
+  static constexpr int kKSteps = 4, kKLoads = 4, kVLoads = 4, kTiles = 8, kElemBytes = 2;
+  typedef uint32_t VReg __attribute__((ext_vector_type(4)));
+};
+template <> struct Dim<256, false> {
+  static constexpr int kKSteps = 8, kKLoads = 8, kVLoads = 8, kTiles = 16, kElemBytes = 2;
+  typedef uint32_t VReg __attribute__((ext_vector_type(4)));
+};
+// K and V stored as one-byte e4m3 values: the values are widened to bf16 (exactly) in
+// registers and then take the same path as a bf16 pool.  A K load is 16 bytes = 16 dims of one token and feeds two MFMA steps; a V load is
+// the lane's dims of one token (4 bytes at D = 64, 8 bytes otherwise).
+template <> struct Dim<64, true> {
+  static constexpr int kKSteps = 2, kKLoads = 1, kVLoads = 4, kTiles = 4, kElemBytes = 1;
+  typedef uint32_t VReg;
+};
+template <> struct Dim<128, true> {
+  static constexpr int kKSteps = 4, kKLoads = 2, kVLoads = 4, kTiles = 8, kElemBytes = 1;
+  typedef uint32_t VReg __attribute__((ext_vector_type(2)));
+};
+template <> struct Dim<256, true> {
+  static constexpr int kKSteps = 8, kKLoads = 4, kVLoads = 8, kTiles = 16, kElemBytes = 1;
+  typedef uint32_t VReg __attribute__((ext_vector_type(2)));
+};
+// First dim of output tiles 4t..4t+3 (they are consecutive dims) in the lane of column n.
+template <int kD> __device__ __forceinline__ int tile_group_dim(int t, int n) {
+  if (kD == 64) return 4 * n;
+  if (kD == 128) return 8 * n + 4 * t;
+  return 128 * (t >> 1) + 8 * n + 4 * (t & 1);
+}
+constexpr float kLazyLog2 = 8.f;
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// The same rounding, then the fp32 value of what was kept.
+__device__ __forceinline__ float bf16_round(float x, uint32_t& bits) {
+  bits = pack_bf16(x, 0.f) & 0xffffu;
+  return __uint_as_float(bits << 16);
+}
+
+// Four e4m3 bytes of one dword -> four bf16 (exact: every e4m3 value is a bf16 value).
+__device__ __forceinline__ u32x2 widen_e4m3x4(uint32_t w) {
+  const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false);
+  const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
+  return u32x2{pack_bf16(lo.x, lo.y), pack_bf16(hi.x, hi.y)};
+}
+
+// Stores of finished rows and of records.  They are written as opaque instructions on
+// purpose: gfx9-family hardware counts loads and stores in one counter, and once
+// the compiler knows a store is pending it can no longer wait for "all but the N
+// youngest loads" and drains the whole ring of KV loads at the next use.  Hidden
+// from that bookkeeping, a wait sized for the loads alone is still sufficient
+// (loads retire in order among themselves, so extra pending stores only make the
+// same wait stricter), and the record itself is only read by the next kernel.
+// sc1 makes the store write through instead of leaving a dirty line behind for a
+// later eviction (measured while records were still written once per partition:
+// 512-token partitions then cost 8 % instead of 13 % on the long-context batch).
+__device__ __forceinline__ void store16(void* p, u32x4 v) {
+  // the trailing s_nop covers the wait states a wide store needs before a vector
+  // op may overwrite its data registers (the compiler cannot see that this is a store)
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+
+// One window of block descriptors: lane i describes stream index jbase + i.
+struct Window {
+  int slab;   // which slab (16 tokens of one KV head; 4 KiB at D = 128 in bf16), counted from the pool's start; 0 when not read
+  int meta;   // bits 0-7 valid tokens (0..16), then the kMeta flags
+  int seg;    // s * Hkv + kvh: the segment, whose first query/output row is seg * G
+};
+// A position of the stream: block b of the nb blocks of request s, KV head kvh.
+struct Place {
+  int s, kvh, b, nb;
+};
+
+constexpr int kMetaLast = 1 << 8;       // closes a run
+constexpr int kMetaSegFirst = 1 << 9;   // first block of its segment in this share
+constexpr int kMetaSegEnd = 1 << 10;    // last block of its segment
+constexpr int kMetaOpenLeft = 1 << 11;  // its segment begins before this share
+
+// How a wavefront's share ends.
+constexpr int kEndsLeft = 1;      // the left record is in use: the first segment begins before the share
+constexpr int kEndsThrough = 2;   // and goes on after it
+constexpr int kEndsRight = 4;     // the right record is in use: the last segment begins in the share and goes on
+
+// Inclusive prefix sum over the wavefront, in the vector unit.  It stands before the first load of the stream: by six shuffles
+// through LDS, 4 requests of 17..300 tokens took 11.2 us for append and attention, this way 10.9; one of 8191 16.95 and 16.7.
+__device__ __forceinline__ int wave_prefix(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8 within 16 lanes
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // lane 15 of each row to the next row: rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 to rows 2 and 3
+  return x;
+}
+
+// The launch descriptor once more, from the kernel's argument block: what only the merge needs
+// is then loaded after the stream and does not take up scalar registers during it.
+__device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
+  typedef const AttnLaunch __attribute__((address_space(4))) * ArgPtr;
+  ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const AttnLaunch*)p;
+}
+
+// kLate, bf16: V goes out when K is there, not a block ahead.
+template <int kD, bool kFp8, typename Layers, bool kLate>
+__global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
+  typedef Dim<kD, kFp8> DD;
+  typedef typename DD::VReg VReg;                 // one V load as it arrives
+  typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
+  constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
+                kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
+  constexpr bool kTwoBlocks = kD == 64 && kFp8;   // the next block's loads go out before this one's have arrived
+  constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
+  extern __shared__ __align__(16) int smem[];
+  int* cumB = smem;                  // [S+1] blocks before request s
+  int* lens = smem + (a.S + 1);      // [S]   clamped context lengths
+  // then, 16-byte aligned, each wavefront's left record and its right record; the right
+  // record shares its room with finished rows that wait to be stored
+  const int rec_floats = record_floats(a.G, kD);
+  float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
+  __shared__ int chains[2], passes[2];    // bit per wavefront, see the workgroup's merge; the next layer uses the other ones
+  __shared__ SharedSegment word;          // the workgroup's, for the reduce pass
+  __shared__ int left_seg[kGroupWaves];   // the segment that the share's first block belongs to
+  __shared__ int any_long;
+  __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
+
+  // Several layers to a launch: a workgroup streams its range of one after the other, or (cut along the segments) each
+  // layer has workgroups of its own.
+  const bool chained = is_layers(layers) && a.leaves == kManySegments;
+  int of = layer_index(layers);   // layer
+  AttnLayer layer = layer_of(a, layers);
+  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, c = lane >> 4;
+  const int G = a.G, S = a.S, Hkv = a.Hkv;
+  const int bpp = a.P / kBlockTokens;   // blocks per partition
+  float* rec_left = wave_lds + wave * a.wave_lds_floats;
+  float* rec_right = rec_left + rec_floats;
+  uint16_t* staged = (uint16_t*)rec_right;
+
+  // Prefix sums over the requests, 64 to a wavefront at a time: first within each 64, then, when
+  // there are more, the sums of the 64s before them (512 requests in turns of one wavefront took 3.6 us
+  // to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
+  int longest = 0;
+  for (int base = 64 * wave; base < S; base += kThreads) {
+    const int i = base + lane;
+    const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
+    const int nb = (L + kBlockTokens - 1) / kBlockTokens;
+    longest = max(longest, nb);
+    const int xb = wave_prefix(nb);
+    if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
+    if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
+  }
+  const bool some_long = __any(longest > a.short_blocks);
+  if (threadIdx.x == 0) { any_long = some_long; chains[0] = passes[0] = 0; }
+  __syncthreads();
+  if (S > 64) {
+    if (some_long && lane == 0) any_long = 1;
+    // lane c: all requests before the c-th 64 (kMaxSeqs = 32 of them)
+    const int mine = lane < (S + 63) >> 6 ? sum64[lane] : 0;
+    int before = wave_prefix(mine);
+    if (threadIdx.x == 63) cumB[S] = before;
+    before -= mine;
+    for (int base = 64 * wave; base < S; base += kThreads) {
+      const int add = __shfl(before, base >> 6);
+      if (base > 0 && base + lane < S) cumB[base + lane] += add;
+    }
+    __syncthreads();
+  }
+
+  // Equal shares: every participating wavefront gets at least one block, so that consecutive
+  // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
+  // short segments is cut along the segments instead, one to a workgroup (see short_segment).
+  const int T = Hkv * cumB[S];
+  const bool whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
+  bool by_row = false;
+  int w = blockIdx.x * kGroupWaves + wave;
+  int W, first_wave, last_wave, pos0 = 0, nshare = 0;
+  if (whole) {
+    const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
+    const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
+    W = min(kGroupWaves, nb);
+    first_wave = 0;
+    last_wave = W - 1;
+    if (wave < W) {
+      const ShareMap shares(nb, W);
+      pos0 = Hkv * cumB[s] + kvh * nb + shares.start(wave);
+      nshare = shares.start(wave + 1) - shares.start(wave);
+    }
+  } else {
+    W = share_count(T, a.waves);
+    first_wave = blockIdx.x * kGroupWaves;
+    last_wave = min(kGroupWaves, W - first_wave) - 1;
+    by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
+    if (by_row && T < a.waves) {
+      // A block per wavefront and not enough of them to fill the compute units: one after the other round
+      // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
+      // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
+      w = wave * gridDim.x + blockIdx.x;
+      last_wave = w < W ? 0 : -1;
+    }
+    if (w < W) {
+      const ShareMap shares(T, W);
+      pos0 = shares.start(w);
+      nshare = shares.start(w + 1) - pos0;
+    }
+  }
+  // the same for all lanes: the stream's loop and its addresses are scalar (32 requests at D = 64 43.6 -> 43.1 us)
+  pos0 = __builtin_amdgcn_readfirstlane(pos0);
+  nshare = __builtin_amdgcn_readfirstlane(nshare);
+  // An empty request owes zero rows.
+  auto zero_empty_rows = [&]() {
+    for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
+      if (cumB[s + 1] != cumB[s]) continue;
+      uint32_t* dst = (uint32_t*)(layer.out + (int64_t)s * a.Hq * kD);
+      for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
+    }
+  };
+
+  // For the reduce pass.
+  const bool leaves_words = a.leaves == kManySegments || a.leaves == kFewSegments;
+  if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
+  if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
+  }
+  // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
+  // its records do not wait for the launch descriptor to be read again.
+  float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
+  if (last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
+    for (;;) {
+      if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
+      zero_empty_rows();
+      if (!chained || ++of == layer_count(layers)) return;
+      layer = layer_at(a, layers, of);
+    }
+  }
+
+  // Descriptors of stream indices jb .. jb+63 of this share.
+  int search_steps = 0;
+  while ((1 << search_steps) < S) ++search_steps;
+  int refused = 0;   // table entries outside the pool met while describing this share
+  auto place = [&](int pos) -> Place {
+    int lo = 0, hi = S;   // largest s with Hkv * cumB[s] <= pos
+    for (int it = 0; it < search_steps; ++it) {
+      const int mid = (lo + hi) >> 1;
+      if (mid > lo && Hkv * cumB[mid] <= pos) lo = mid; else if (mid > lo) hi = mid;
+    }
+    const int nb = cumB[lo + 1] - cumB[lo];
+    const int o = pos - Hkv * cumB[lo];
+    const int kvh = o / nb;
+    return Place{lo, kvh, o - kvh * nb, nb};
+  };
+  auto describe = [&](int jb) __attribute__((always_inline)) -> Window {
+    const int j = jb + lane;
+    const bool live = j < nshare;
+    const Place at = place(pos0 + max(min(j, nshare - 1), 0));
+    const int s = at.s, kvh = at.kvh, b = at.b, nb = at.nb;
+    int ntok = min(kBlockTokens, lens[s] - kBlockTokens * b);
+    // unit b of the request lies in physical block b / upb, at unit b % upb of the KV head's rows
+    const int tb = b / a.upb;
+    const int id = live ? a.block_tables[(int64_t)s * a.MAXB + tb] : -1;
+    const bool mapped = (unsigned)id < (unsigned)a.NB;   // ids outside the pool are never followed
+    if (!mapped) ntok = 0;
+    refused += __popcll(__ballot(live && !mapped));
+    Window d;
+    d.slab = mapped ? (id * Hkv + kvh) * a.upb + (b - tb * a.upb) : 0;
+    const bool last = (b + 1 == nb) || ((b + 1) % bpp == 0) || (j + 1 == nshare);
+    const bool seg_first = (b == 0) || (j == 0);
+    d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0) |
+             (b + 1 == nb ? kMetaSegEnd : 0) | (b > j ? kMetaOpenLeft : 0);
+    d.seg = s * Hkv + kvh;
+    return d;
+  };
+
+  Window dA = describe(0);
+  Window dB = dA;   // described after the first KV loads are on their way (below)
+  int jbase = 0;
+
+  const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
+  const int tau = 4 * (n & 3) + (n >> 2);
+  // K, in 16-byte pieces of the slab: a wavefront's load is 64 of them in a row, turned in LDS, where piece p of token t
+  // lies in place p ^ t of its row so that neither way has bank conflicts.  Straight in operand order, 4 of each token, where
+  // that is all of a token's (e4m3 at D = 64) and where LDS has no room (stream_lds).
+  constexpr int kPieces = kD * kElemBytes / 16;   // of a token
+  constexpr int kSwizzle = (kPieces < 16 ? kPieces : 16) - 1;
+  const bool turns = kD == 128 ? a.turns : kKLoads > 1;
+  const int koff = turns ? lane : tau * kPieces + c;
+  u32x4* turn = (u32x4*)(wave_lds + kGroupWaves * a.wave_lds_floats) + wave * (kBlockTokens * kPieces);
+  // V, in units of one VReg: token 4*e + c, this lane's dims (of half h when D = 256)
+  const int voff = kD == 256 ? 32 * c + n : lane;
+
+  u32x4 qop[kKSteps];  // q as the B operand: dims 32*jj + 8*c .. +7 of head n; zero rows beyond the group
+  float m = kNegInf;   // running reference maximum of head n (log2 units), same in all four c groups
+  float l = 0.f;       // this lane's share of the softmax denominator
+  f32x4 o[kTiles];     // o[i][r]: head 4*c + r, dim tile_group_dim(i / 4, n) + i % 4
+#pragma unroll
+  for (int i = 0; i < kTiles; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // The loads of stream index j, nontemporal: the stream is read once and must not allocate in the
+  // caches it passes through.  The loads are unconditional so that every wait in the loop knows
+  // exactly how many are outstanding: a block that is unmapped, or an index past
+  // the share's end, reads slab 0 (which always exists) and is masked or skipped.
+  auto slab_at = [&](int j) -> int64_t {   // byte offset of the slab of stream index j
+    const int idx = j - jbase;   // 0 .. 2*kWindow-1
+    const int sa = __builtin_amdgcn_readlane(dA.slab, idx & (kWindow - 1));
+    const int sb = __builtin_amdgcn_readlane(dB.slab, idx & (kWindow - 1));
+    int slab = (idx < kWindow) ? sa : sb;
+    if (j >= nshare) slab = 0;
+    return (int64_t)slab * slab_bytes;
+  };
+  auto issue_k = [&](u32x4 (&k)[kKLoads], int j, int from, int to) {
+    const u32x4* kp = (const u32x4*)((const char*)layer.k_pool + slab_at(j)) + koff;
+    if (turns) {
+#pragma unroll
+      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 64 * jj);
+    } else {
+#pragma unroll
+      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 4 * jj);
+    }
+  };
+  auto issue_v = [&](VReg (&v)[kVLoads], int j) {
+    const VReg* vp = (const VReg*)((const char*)layer.v_pool + slab_at(j)) + voff;
+    if (kD == 256) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[2 * e] = __builtin_nontemporal_load(vp + 128 * e);
+        v[2 * e + 1] = __builtin_nontemporal_load(vp + 128 * e + 16);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_nontemporal_load(vp + 64 * e);
+    }
+  };
+  // K of a block that has arrived, into LDS and back as the A operand: load L of lane (n, c) is piece 4L + c of token tau(n).
+  auto turn_k = [&](u32x4 (&k)[kKLoads]) {
+    if (turns) {
+#pragma unroll
+      for (int jj = 0; jj < kKLoads; ++jj) {
+        const int at = 64 * jj + lane;
+        turn[at ^ ((at / kPieces) & kSwizzle)] = k[jj];
+      }
+#pragma unroll
+      for (int jj = 0; jj < kKLoads; ++jj) k[jj] = turn[tau * kPieces + ((4 * jj + c) ^ (tau & kSwizzle))];
+    }
+  };
+
+  // Finished rows wait in LDS and go out several segments at a time, and the rest when
+  // the share is done.  A store in the middle of the stream is expensive out of
+  // proportion to its size: loads and stores retire through one counter, so the KV loads
+  // issued after it cannot be consumed before it has been acknowledged, and that costs one
+  // stall of several microseconds per burst of stores however few bytes it carries.
+  int nstaged = 0;       // finished segments whose rows are in LDS
+  int staged_segs = 0;   // lane r: staged segment r
+  bool seg_open = false;   // a parked record belongs to the segment being streamed
+  int ends_flags = 0, left = 0, right = 0;   // how the share ends, and the segments in the left and the right record
+  auto store_staged = [&]() __attribute__((always_inline)) {
+    for (int r = 0; r < nstaged; ++r) {
+      const int seg = __builtin_amdgcn_readlane(staged_segs, r);
+      float* dst = (float*)(layer.out + (int64_t)seg * (G * kD));
+      const float* src = (const float*)(staged + r * G * kD);
+      for (int f = 4 * lane; f < G * kD / 2; f += 256) store16(dst + f, *(const u32x4*)(src + f));
+    }
+    nstaged = 0;
+  };
+
+  auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int j) __attribute__((always_inline)) {
+    const int idx = j - jbase;   // always inside window A
+    // The MFMA operands.  bf16 pools: the registers as they are.  e4m3 pools: piece 4L + c of
+    // K's row holds dims 16*(4L + c) .. +15 of token tau(n), which feed steps 2L and 2L + 1 (the
+    // contraction order is free as long as q follows it, see below); a V load holds the same
+    // token and dims as in a bf16 pool, one byte each.
+    u32x4 k[kKSteps];
+    VOp v[kVLoads];
+#pragma unroll
+    for (int jj = 0; jj < kKLoads; ++jj) {
+      const u32x4 x = kraw[jj];
+      if constexpr (kFp8) {
+        const u32x2 y[4] = {widen_e4m3x4(x.x), widen_e4m3x4(x.y), widen_e4m3x4(x.z), widen_e4m3x4(x.w)};
+        k[2 * jj] = u32x4{y[0].x, y[0].y, y[1].x, y[1].y};
+        k[2 * jj + 1] = u32x4{y[2].x, y[2].y, y[3].x, y[3].y};
+      } else {
+        k[jj] = x;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < kVLoads; ++e) {
+      if constexpr (!kFp8) {
+        v[e] = vraw[e];
+      } else if constexpr (kD == 64) {
+        v[e] = widen_e4m3x4(vraw[e]);
+      } else {
+        const u32x2 a2 = widen_e4m3x4(vraw[e].x), b2 = widen_e4m3x4(vraw[e].y);
+        v[e] = VOp{a2.x, a2.y, b2.x, b2.y};
+      }
+    }
+    const int meta = __builtin_amdgcn_readlane(dA.meta, idx);
+    const int ntok = meta & 0xff;
+
+    f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int jj = 0; jj < kKSteps; ++jj)
+      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[jj]),
+                                                   __builtin_bit_cast(bf16x8, qop[jj]), sc, 0, 0, 0);
+    float x[4] = {sc.x * a.scale_log2e, sc.y * a.scale_log2e, sc.z * a.scale_log2e,
+                  sc.w * a.scale_log2e};
+    const bool edge = ntok < kBlockTokens;
+    bool valid[4] = {true, true, true, true};
+    if (edge) {
+      // Last block of a request, or an unmapped one: masked slots may hold anything
+      // (NaN included), so scores, weights and V rows are replaced by select,
+      // never scaled by zero.  Element e of this lane is token 4*e + c.
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        valid[e] = 4 * e + c < ntok;
+        x[e] = valid[e] ? x[e] : kNegInf;
+        if (!valid[e]) {
+          if (kD == 256) { v[2 * e] = VOp{}; v[2 * e + 1] = VOp{}; }
+          else v[e] = VOp{};
+        }
+      }
+    }
+    const float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    if (__any(mx > m + kLazyLog2)) {
+      float mg = fmaxf(mx, __shfl_xor(mx, 16));
+      mg = fmaxf(mg, __shfl_xor(mg, 32));
+      const float mnew = fmaxf(m, mg);   // finite: some lane of the head saw a valid token
+      const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+      l *= alpha;
+      float ar[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ar[r] = __shfl(alpha, 4 * c + r);
+#pragma unroll
+      for (int i = 0; i < kTiles; ++i) {
+        o[i].x *= ar[0]; o[i].y *= ar[1]; o[i].z *= ar[2]; o[i].w *= ar[3];
+      }
+      m = mnew;
+    }
+    float pw[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pw[e] = __builtin_amdgcn_exp2f(x[e] - m);
+    if (edge) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pw[e] = valid[e] ? pw[e] : 0.f;   // m may still be -inf here
+    }
+    l += (pw[0] + pw[1]) + (pw[2] + pw[3]);
+
+    // P = hi + lo in bf16.
+    uint32_t hb[4];
+    float lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) lo[e] = pw[e] - bf16_round(pw[e], hb[e]);
+    const u32x2 phi = {hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16)};
+    const u32x2 plo = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])};
+    const s16x4 pa = __builtin_bit_cast(s16x4, phi);
+    const s16x4 pb = __builtin_bit_cast(s16x4, plo);
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+      // tile i needs, for tokens 4*e + c (e = 0..3), the bf16 of its dim: half (i & 1) of
+      // word ((i % 8) >> 1) of the load that holds token e (and, for D = 256, half i / 8)
+      const int wsel = (i & 7) >> 1, h = kD == 256 ? i >> 3 : 0, st = kD == 256 ? 2 : 1;
+      const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+      const u32x2 vb = {__builtin_amdgcn_perm(v[st + h][wsel], v[h][wsel], sel),
+                        __builtin_amdgcn_perm(v[3 * st + h][wsel], v[2 * st + h][wsel], sel)};
+      const s16x4 vop = __builtin_bit_cast(s16x4, vb);
+      o[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vop, o[i], 0, 0, 0);
+      o[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, vop, o[i], 0, 0, 0);
+    }
+
+    if (meta & kMetaLast) {
+      // The run ends here.  A segment that lies wholly inside the share is finished now:
+      // its rows are normalised, rounded and staged.  Of a segment that other wavefronts
+      // share, or of which more partitions follow, the partial result is parked in a
+      // record in LDS (the left one when the segment begins before the share, else the
+      // right one); a later run of the same segment (the next P-token partition) is folded
+      // into it with the split-K merge formula, so there is one record per (wavefront,
+      // segment) however small P is.
+      const bool open_left = meta & kMetaOpenLeft;
+      const bool done = (meta & kMetaSegEnd) && !open_left;
+      float* rec = open_left ? rec_left : rec_right;
+      float lt = l + __shfl_xor(l, 16);
+      lt += __shfl_xor(lt, 32);
+      if (seg_open) {
+        // parked (m1, l1, rows1) and this run's (m, lt, o): weights 2^(m1-M) and 2^(m-M),
+        // a side whose maximum is -inf (nothing valid seen) gets weight 0 by select
+        const f32x2 ml = *(const f32x2*)(rec + G * kD + 2 * n);
+        const float M = fmaxf(ml.x, m);
+        const float w1 = (ml.x == kNegInf) ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);
+        const float w2 = (m == kNegInf) ? 0.f : __builtin_amdgcn_exp2f(m - M);
+        lt = w1 * ml.y + w2 * lt;
+        m = M;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float keep = __shfl(w1, 4 * c + r), add = __shfl(w2, 4 * c + r);
+          if (4 * c + r < G) {
+#pragma unroll
+            for (int t = 0; t < kTiles / 4; ++t) {
+              const f32x4 p4 = *(const f32x4*)(rec + (4 * c + r) * kD + tile_group_dim<kD>(t, n));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[4 * t + e][r] = keep * p4[e] + add * o[4 * t + e][r];
+            }
+          }
+        }
+      }
+      if (done) {
+        if (nstaged == a.staged_max) store_staged();
+        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
+        staged_segs = (lane == nstaged) ? seg : staged_segs;
+        uint16_t* rows = staged + nstaged * G * kD;
+        const float inv = inverse(lt, a.out_scale);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int h = 4 * c + r;
+          const float f = __shfl(inv, h);
+          if (h < G) {
+#pragma unroll
+            for (int t = 0; t < kTiles / 4; ++t)
+              *(u32x2*)(rows + h * kD + tile_group_dim<kD>(t, n)) =
+                  finish_row4(f32x4{o[4 * t][r], o[4 * t + 1][r], o[4 * t + 2][r], o[4 * t + 3][r]}, f);
+          }
+        }
+        ++nstaged;
+        ends_flags &= ~kEndsRight;
+      } else {
+        if (!open_left) store_staged();   // the staged rows lie where the record goes
+        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
+        ends_flags = !open_left ? ends_flags | kEndsRight
+                     : (meta & kMetaSegEnd) ? kEndsLeft : kEndsLeft | kEndsThrough;
+        left = open_left ? seg : left;
+        right = open_left ? right : seg;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int h = 4 * c + r;
+          if (h < G) {
+#pragma unroll
+            for (int t = 0; t < kTiles / 4; ++t)
+              *(f32x4*)(rec + h * kD + tile_group_dim<kD>(t, n)) =
+                  f32x4{o[4 * t][r], o[4 * t + 1][r], o[4 * t + 2][r], o[4 * t + 3][r]};
+          }
+        }
+        if (c == 0) *(f32x2*)(rec + G * kD + 2 * n) = (n < G) ? f32x2{m, lt} : f32x2{kNegInf, 0.f};
+      }
+      seg_open = true;
+      m = kNegInf;
+      l = 0.f;
+#pragma unroll
+      for (int i = 0; i < kTiles; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+
+  // The query group of a new (request, KV head), one block ahead of use and behind that block's KV
+  // loads, so that nothing has to wait for loads younger than the ones it needs: fetched when its
+  // first block was already to be consumed, it cost the pipeline a drain per segment (512 requests of
+  // 16..512 tokens: 116.5 -> 114.1 us; 8 requests at D = 256: 36.3 -> 35.7).
+  u32x4 qnext[kKSteps];
+  auto load_q = [&](int seg) {
+    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(seg * G + min(n, G - 1)) * kD);
+#pragma unroll
+    for (int jj = 0; jj < kKSteps; ++jj)
+      // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
+      // e4m3 K load, 64*(jj/2) + 16*c + 8*(jj%2) .. +7
+      qnext[jj] = kFp8 ? qrow_p[8 * (jj >> 1) + 2 * c + (jj & 1)] : qrow_p[4 * jj + c];
+  };
+  auto take_q = [&](int j) {   // before the next group is asked for
+    if (!(__builtin_amdgcn_readlane(dA.meta, j - jbase) & kMetaSegFirst)) return;
+    seg_open = false;
+#pragma unroll
+    for (int jj = 0; jj < kKSteps; ++jj) qop[jj] = (n < G) ? qnext[jj] : u32x4{0, 0, 0, 0};
+  };
+  // Waits for loads where it is known how many are younger.
+  auto arrived_k = [](u32x4 (&k)[kKLoads]) {
+#pragma unroll
+    for (int jj = 0; jj < kKLoads; ++jj) asm volatile("" : : "v"(k[jj]));
+  };
+  auto arrived_v = [](VReg (&v)[kVLoads]) {
+#pragma unroll
+    for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
+  };
+  auto ask_q = [&](VReg (&v)[kVLoads], int j) {   // v: of the block before
+    const int idx = j - jbase;
+    const int meta = __builtin_amdgcn_readlane(idx < kWindow ? dA.meta : dB.meta, idx & (kWindow - 1));
+    if (j >= nshare || !(meta & kMetaSegFirst)) return;
+    if (kTwoBlocks) arrived_v(v);
+    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
+  };
+
+  u32x4 kbuf[2][kKLoads];   // two blocks in turn, so that no buffer is ever copied
+  VReg vbuf[2][kVLoads];
+  issue_k(kbuf[0], 0, 0, kKLoads);
+  if (!kLate) issue_v(vbuf[0], 0);
+  load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+  if (nshare > kWindow) dB = describe(kWindow);
+  if (wave == 0 && leaves_words && !by_row) {
+    // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
+    // last block, does it begin here and go on elsewhere?
+    int row = 0, count = 0;
+    if (!whole && first_wave + kGroupWaves < W) {
+      const ShareMap shares(T, W);
+      const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
+      const Place at = place(next - 1);
+      const int seg_pos = next - 1 - at.b;
+      if (seg_pos >= begin && seg_pos + at.nb > next) {
+        row = (at.s * Hkv + at.kvh) * G;
+        count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
+      }
+    }
+    if (lane == 0) word = SharedSegment{row, count};
+  }
+  for (int turned = 0;; turned ^= 1) {   // layers
+  for (int j = 0; j < nshare; j += 2) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      u32x4 (&k)[kKLoads] = kbuf[i], (&knext)[kKLoads] = kbuf[i ^ 1];
+      VReg (&v)[kVLoads] = vbuf[i], (&vnext)[kVLoads] = vbuf[i ^ 1];
+      if (!kTwoBlocks) arrived_k(k);
+      if (!kTwoBlocks && !kLate) arrived_v(v);
+      if (kLate) {
+        issue_v(v, j + i);
+        issue_k(knext, j + i + 1, 0, kAhead);
+      } else {
+        issue_k(knext, j + i + 1, 0, kKLoads);
+        issue_v(vnext, j + i + 1);
+      }
+      if (kTwoBlocks) arrived_k(k);
+      if (j + i < nshare) {
+        take_q(j + i);
+        ask_q(v, j + i + 1);
+        turn_k(k);
+        consume(k, v, j + i);
+      }
+      if (kLate) issue_k(knext, j + i + 1, kAhead, kKLoads);
+    }
+    if (j + 2 == jbase + kWindow) {
+      // The consumer leaves window A: B becomes A, and the window after it is
+      // described now, 64 blocks before its first use.
+      dA = dB;
+      jbase += kWindow;
+      if (jbase + kWindow < nshare) dB = describe(jbase + kWindow);
+    }
+  }
+  store_staged();
+  if (by_row) {
+    // The reduce pass has a workgroup for every row, so each wavefront's records go to memory as they
+    // are, before all else.
+    auto store_record = [&](const float* rec, int seg) {
+      float* dst = row_records + (int64_t)seg * rec_floats;
+      for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
+    };
+    if (ends_flags & kEndsLeft) store_record(rec_left, left);
+    if (ends_flags & kEndsRight) store_record(rec_right, right);
+    // Never: up to here the registers of the query group that was asked for last are its own.  As far as the compiler knows
+    // those loads may still be on their way, and a loop of stores that took the registers over would wait for them in every
+    // turn, and so for the acknowledgement of each hidden store (append and attention of 4 requests of 1360..1840 tokens on
+    // 16/1 heads at D = 64, five stores a record: 15.4 us with such a wait, 14.1 without).
+    int never;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(never));
+    if (never) {
+#pragma unroll
+      for (int jj = 0; jj < kKSteps; ++jj) asm volatile("" : : "v"(qnext[jj]));
+    }
+  }
+  // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
+  if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
+  zero_empty_rows();
+  if (by_row) return;
+  uint16_t* out = layer.out;
+  const bool more = chained && of + 1 < layer_count(layers);
+  const int ends = ends_flags, left_end = left;
+  if (more) {
+    // The next layer: its first loads are on their way while the workgroup meets (six layers of 24 requests, with a
+    // workgroup of its own for each layer's range 760.7 us, this way 755.6).
+    layer = layer_at(a, layers, of + 1);
+    if (jbase) {   // window A is not the first one any more
+      jbase = refused = 0;
+      dA = describe(0);
+    }
+    issue_k(kbuf[0], 0, 0, kKLoads);
+    if (!kLate) issue_v(vbuf[0], 0);
+    load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+    if (nshare > kWindow) dB = describe(kWindow);
+    seg_open = false;
+    ends_flags = left = right = 0;
+  }
+
+  // The workgroup's merge.  Segments that meet inside the workgroup's range are finished from
+  // the records in LDS.  What is left are at most two segments that it shares with other
+  // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
+  // shared segment begins in leaves word of it.
+  const AttnLaunch& b = reread(a);
+  if (lane == 0) {
+    left_seg[wave] = left_end;
+    int chain = 0;
+    if ((ends & kEndsLeft) && (!(ends & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
+    if ((ends & kEndsRight) && wave == last_wave) chain |= 1 << kGroupWaves;
+    if (chain) atomicOr(&chains[turned], chain);
+    if (ends & kEndsThrough) atomicOr(&passes[turned], 1 << wave);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
+    *shared_segment(b, of, blockIdx.x) = word;
+  const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
+  // One chain of LDS records per wavefront v whose left record ends its segment or is the
+  // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
+  // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to
+  // four rounds instead of one took 1 us more (64 requests of 50..100 tokens on 40/8 heads 18.4 -> 16.6).
+  const int ending = chains[turned], through = passes[turned];
+#pragma unroll 1
+  for (int i = threadIdx.x; i < __popc(ending) * q4; i += kThreads) {
+    const int nth = i / q4, item = i - nth * q4;
+    int rest = ending;
+    for (int z = 0; z < nth; ++z) rest &= rest - 1;
+    const int chain = __ffs(rest) - 1;
+    const bool right_only = chain == kGroupWaves;
+    const int v = right_only ? last_wave : chain;
+    int u = v;
+    bool from_right = true;   // the chain begins with wavefront u's right record
+    if (!right_only) {
+      u = 31 - __clz(~through & ((1 << v) - 1));   // the last one before v that the segment does not go through
+      if (u < 0) { u = 0; from_right = false; }
+    }
+    const bool open_right = right_only || ((through >> v) & 1);
+    const int h = item / (kD / 4);
+    Partial p = kNothing;
+#pragma unroll 1
+    for (int k = u; k <= v; k += 2) {
+      const float* rec0 = wave_lds + k * b.wave_lds_floats + (k == u && from_right ? rec_floats : 0);
+      const float* rec1 = wave_lds + min(k + 1, v) * b.wave_lds_floats;
+      f32x2 ml[2] = {*(const f32x2*)(rec0 + G * kD + 2 * h), *(const f32x2*)(rec1 + G * kD + 2 * h)};
+      const f32x4 x[2] = {*(const f32x4*)(rec0 + 4 * item), *(const f32x4*)(rec1 + 4 * item)};
+      if (k == v) ml[1].x = kNegInf;
+      fold(p, ml, x);
+    }
+    if (from_right && !open_right) {
+      *(u32x2*)(out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+    } else {
+      float* rec = group_record(b, kD, of, blockIdx.x, from_right);
+      store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));
+      if (item % (kD / 4) == 0) *(f32x2*)(rec + G * kD + 2 * h) = f32x2{p.m, p.l};
+    }
+  }
+  if (!more) return;
+  ++of;
+  if (threadIdx.x == 0) chains[turned ^ 1] = passes[turned ^ 1] = 0;
+  __syncthreads();   // the records in LDS have been read
+  }
+}
+
+}  // namespace
+}  // namespace pkv

@@ -228,6 +228,22 @@ inline StreamLds stream_lds(int S, int G, int D, bool kv_fp8 = false) {
   return l;
 }
 
+// One workgroup goes from layer to layer; where each segment has a workgroup, each layer has its own.
+inline dim3 stream_grid(const AttnLaunch& a, const AttnLayers* layers) {
+  return dim3(a.waves / group_waves(a.D), layers && a.leaves == kNoRecords ? layers->count : 1);
+}
+// bf16 at D = 256: does V go out when K is there, with a quarter of the next K, and not a block ahead?  Where the bounds allow
+// shares of 24 blocks and more.  A block ahead / late, us for append and attention: 20 requests of 260..350 tokens on 8/8
+// heads (3 blocks a share) 16.6 / 18.4, 20 of 350..470 (4) 22.2 / 22.4, 20 of 700..940 (8) 32.7 / 32.8; 20 of 2600..3500 (30)
+// 86.1 / 85.5, 20 of 6100..8200 (70) 191.7 / 186.8, 125 of 970..1320 on 40/8 heads (70) 196.9 / 192.2.  (With K loaded in operand
+// order and two blocks out the last three took 87.4, 188.9 and 194.)  Both loops in one kernel cost it 75 registers and
+// short shares 5 to 14 %.
+inline bool late_at_256(const AttnLaunch& a) {
+  const int64_t most = (int64_t)a.S * a.Hkv * ((a.max_ctx + kBlockTokens - 1) / kBlockTokens);
+  return a.D == 256 && !a.kv_fp8 && most >= 24 * (int64_t)a.waves;
+}
+void launch_late_256(const AttnLaunch& a, const AttnLayers* layers, size_t lds, hipStream_t stream);
+
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
