@@ -83,6 +83,8 @@
 #include "attn_partial.h"
 #include "pkv_kernels.h"
 
+#include <type_traits>
+
 namespace pkv {
 namespace {
 
@@ -225,9 +227,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   __shared__ int any_long;
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
 
-  // Several layers to a launch: a workgroup streams its range of one after the other, or (cut along the segments) each
-  // layer has workgroups of its own.
-  const bool chained = is_layers(layers) && a.leaves == kManySegments;
+  constexpr bool kChained = std::is_same_v<Layers, ChainedLayers>;   // a workgroup streams its range of one layer after the other
   int of = layer_index(layers);   // layer
   AttnLayer layer = layer_of(a, layers);
   const int wave = threadIdx.x >> 6;
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     for (;;) {
       if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
       zero_empty_rows();
-      if (!chained || ++of == layer_count(layers)) return;
+      if (!kChained || ++of == layer_count(layers)) return;
       layer = layer_at(a, layers, of);
     }
   }
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   zero_empty_rows();
   if (by_row) return;
   uint16_t* out = layer.out;
-  const bool more = chained && of + 1 < layer_count(layers);
+  const bool more = kChained && of + 1 < layer_count(layers);
   const int ends = ends_flags, left_end = left;
   if (more) {
     // The next layer: its first loads are on their way while the workgroup meets (six layers of 24 requests, with a

@@ -159,17 +159,18 @@ struct AttnLaunch {
   int turns;            // there is room in LDS to turn K
   int64_t layer_ws_floats;   // workspace from one layer's records to the next one's
 };
-// The layers of a launch, one after the other in each workgroup (where each segment has a workgroup, blockIdx.y).  A second kernel argument, so that a launch of one
-// layer reads its pointers with the rest (the look-up costs one request of 8191 tokens 0.4 us).
+// The layers of a launch, blockIdx.y being the layer.  A second kernel argument, so that a launch of one layer reads its pointers
+// with the rest (the look-up costs one request of 8191 tokens 0.4 us).
 struct AttnLayers {
   int count;
   AttnLayer layer[kMaxLaunchLayers];
 };
 struct OneLayer {};
+// One after the other in each workgroup.
+struct ChainedLayers : AttnLayers {};
 __device__ __forceinline__ int layer_index(const OneLayer&) { return 0; }
 __device__ __forceinline__ int layer_index(const AttnLayers&) { return blockIdx.y; }
-constexpr bool is_layers(const OneLayer&) { return false; }
-constexpr bool is_layers(const AttnLayers&) { return true; }
+__device__ __forceinline__ int layer_index(const ChainedLayers&) { return 0; }
 __device__ __forceinline__ int layer_count(const OneLayer&) { return 1; }
 __device__ __forceinline__ int layer_count(const AttnLayers& l) { return l.count; }
 __device__ __forceinline__ const AttnLayer& layer_at(const AttnLaunch& a, const OneLayer&, int) { return a.layer; }
@@ -228,10 +229,6 @@ inline StreamLds stream_lds(int S, int G, int D, bool kv_fp8 = false) {
   return l;
 }
 
-// One workgroup goes from layer to layer; where each segment has a workgroup, each layer has its own.
-inline dim3 stream_grid(const AttnLaunch& a, const AttnLayers* layers) {
-  return dim3(a.waves / group_waves(a.D), layers && a.leaves == kNoRecords ? layers->count : 1);
-}
 // bf16 at D = 256: does V go out when K is there, with a quarter of the next K, and not a block ahead?  Where the bounds allow
 // shares of 24 blocks and more.  A block ahead / late, us for append and attention: 20 requests of 260..350 tokens on 8/8
 // heads (3 blocks a share) 16.6 / 18.4, 20 of 350..470 (4) 22.2 / 22.4, 20 of 700..940 (8) 32.7 / 32.8; 20 of 2600..3500 (30)
@@ -242,7 +239,9 @@ inline bool late_at_256(const AttnLaunch& a) {
   const int64_t most = (int64_t)a.S * a.Hkv * ((a.max_ctx + kBlockTokens - 1) / kBlockTokens);
   return a.D == 256 && !a.kv_fp8 && most >= 24 * (int64_t)a.waves;
 }
-void launch_late_256(const AttnLaunch& a, const AttnLayers* layers, size_t lds, hipStream_t stream);
+// The stream pass's kernels for one layer in that way, and for layers one after the other.
+void launch_late_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
+hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.

@@ -30,15 +30,34 @@ def loops_with_hidden_stores(kernel):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """(name, assembly) of every variant"""
-    asm = str(tmp_path_factory.mktemp("asm") / "attn_stream.s")
+def assembly(tmp_path_factory):
+    text = []
     flags = [f for f in pkv_build.FLAGS if f not in ("-fPIC", "-shared")]
-    subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "attn_stream.hip"), "-o", asm],
-                          stderr=subprocess.DEVNULL)
-    found = re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", open(asm).read(), re.S | re.M)
-    assert len(found) == 9
+    for source in ("attn_stream", "attn_stream_large"):
+        asm = str(tmp_path_factory.mktemp("asm") / (source + ".s"))
+        subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, source + ".hip"), "-o", asm],
+                              stderr=subprocess.DEVNULL)
+        text.append(open(asm).read())
+    return text
+
+
+@pytest.fixture(scope="module")
+def kernels(assembly):
+    """(name, assembly) of every variant"""
+    found = [k for text in assembly for k in re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", text, re.S | re.M)]
+    assert len(found) == 14
     return found
+
+
+@pytest.mark.parametrize("dim", [64, 128, 256])
+def test_short_launches_of_layers_carry_nothing_for_the_chain(assembly, dim):
+    """Where each segment has a workgroup the kernel is as for one layer: it saves no scalar registers for layers to come."""
+    spills = {name: int(n) for text in assembly
+              for name, n in re.findall(r"\.name:\s+(\S*attn_stream_kernel\S*).*?\.sgpr_spill_count:\s+(\d+)", text, re.S)}
+    late = "ELb1E" if dim == 128 else "ELb0E"
+    one = [n for name, n in spills.items() if f"ILi{dim}ELb0ENS_8OneLayer{late}" in name]
+    layers = [n for name, n in spills.items() if f"ILi{dim}ELb0ENS_10AttnLayers{late}" in name]
+    assert len(one) == len(layers) == 1 and layers[0] <= one[0] + 8, (one, layers)
 
 
 def test_small_blocks_go_out_before_the_last_has_arrived(kernels):
