@@ -378,12 +378,10 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   int jbase = 0;
 
   const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
-  const int tau = 4 * (n & 3) + (n >> 2);
-  // K, in 16-byte pieces of the slab: a wavefront's load is 64 of them in a row, turned in LDS, where piece p of token t
-  // lies in place p ^ t of its row so that neither way has bank conflicts.  Straight in operand order, 4 of each token, where
-  // that is all of a token's (e4m3 at D = 64) and where LDS has no room (stream_lds).
+  const int tau = turn_token(n);
+  // K, in 16-byte pieces of the slab: a wavefront's load is 64 of them in a row, turned in LDS (turn_place).  Straight in
+  // operand order, 4 of each token, where that is all of a token's (e4m3 at D = 64) and where LDS has no room (stream_lds).
   constexpr int kPieces = kD * kElemBytes / 16;   // of a token
-  constexpr int kSwizzle = (kPieces < 16 ? kPieces : 16) - 1;
   const bool turns = kD == 128 ? a.turns : kKLoads > 1;
   const int koff = turns ? lane : tau * kPieces + c;
   u32x4* turn = (u32x4*)(wave_lds + kGroupWaves * a.wave_lds_floats) + wave * (kBlockTokens * kPieces);
@@ -438,10 +436,10 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
       for (int jj = 0; jj < kKLoads; ++jj) {
         const int at = 64 * jj + lane;
-        turn[at ^ ((at / kPieces) & kSwizzle)] = k[jj];
+        turn[turn_place(kPieces, at / kPieces, at % kPieces)] = k[jj];
       }
 #pragma unroll
-      for (int jj = 0; jj < kKLoads; ++jj) k[jj] = turn[tau * kPieces + ((4 * jj + c) ^ (tau & kSwizzle))];
+      for (int jj = 0; jj < kKLoads; ++jj) k[jj] = turn[turn_place(kPieces, tau, 4 * jj + c)];
     }
   };
 

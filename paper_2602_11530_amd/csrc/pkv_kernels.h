@@ -243,6 +243,17 @@ inline bool late_at_256(const AttnLaunch& a) {
 void launch_late_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
 hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 
+// The turn of a block of K: place, in 16-byte pieces, of piece p of token t (`pieces` of them each: 8, 16 or 32).  A wavefront writes
+// 64 pieces in a row and reads, lane 16*c + n, piece 4*jj + c of token turn_token(n).  The LDS unit takes a read of 16 bytes a
+// lane in four steps of 16 lanes over 64 banks, and a step has lanes of two c (0..3, 12..15 and 20..27; 4..11, 16..19 and 28..31;
+// the same of the upper half); a write in eight steps of 8 lanes in a row over 32 banks.  Here the tokens of a
+// step, all different, differ in the bits of the place that c does not reach: no conflicts either way.  With t itself for a key
+// every read took 8 steps instead of 4 (SQ_LDS_BANK_CONFLICT, profiles/attn_stream_lds.md).
+__host__ __device__ constexpr int turn_token(int n) { return 4 * (n & 3) + (n >> 2); }
+__host__ __device__ constexpr int turn_place(int pieces, int t, int p) {
+  return t * pieces + (p ^ (pieces == 8 ? (t >> 2) | (t & 2) << 1 : (t >> 2) | (t & 3) << 2));
+}
+
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
