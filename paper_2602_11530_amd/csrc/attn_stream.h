@@ -61,7 +61,8 @@
 // Memory traffic.  The KV loads of a block (eight of 16 bytes at D = 128) are
 // nontemporal and unconditional.  A load that takes 64 bytes of each of 16 tokens, as the matrix cores
 // want K, keeps the address unit busy for twice the lines and takes each of them from the caches in two
-// halves; whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
+// halves (e4m3 at D = 256 in large batches and D = 128 without room take it all the same, see large_at_256 and stream_lds);
+// whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
 // latency per block and are faster where that counts (append and attention: 4 requests of 17..300 tokens
 // 11.9 -> 11.1 us, 8 at D = 256 34.5 -> 33.0, 32 at D = 64 45.9 -> 43.3, 64 on 8-bit pools 109.2 -> 105.8)
 // and equal or a little faster where the memory is saturated either way (64 of 1024..8192 190.6 -> 188.9, 128 long ones
@@ -204,14 +205,15 @@ __device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
   return *(const AttnLaunch*)p;
 }
 
-// kLate, bf16: V goes out when K is there, not a block ahead.
-template <int kD, bool kFp8, typename Layers, bool kLate>
+// kLarge: as large batches want it (large_at_256), and at D = 128 all in bf16.
+template <int kD, bool kFp8, typename Layers, bool kLarge>
 __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
   typedef Dim<kD, kFp8> DD;
   typedef typename DD::VReg VReg;                 // one V load as it arrives
   typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
   constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
+  constexpr bool kLate = kLarge && !kFp8;         // V goes out when K is there, not a block ahead
   constexpr bool kTwoBlocks = kD == 64 && kFp8;   // the next block's loads go out before this one's have arrived
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
   extern __shared__ __align__(16) int smem[];
@@ -380,9 +382,10 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
   const int tau = turn_token(n);
   // K, in 16-byte pieces of the slab: a wavefront's load is 64 of them in a row, turned in LDS (turn_place).  Straight in
-  // operand order, 4 of each token, where that is all of a token's (e4m3 at D = 64) and where LDS has no room (stream_lds).
+  // operand order, 4 of each token, where that is all of a token's (e4m3 at D = 64), where LDS has no room (stream_lds), and in
+  // large batches in e4m3 at D = 256.
   constexpr int kPieces = kD * kElemBytes / 16;   // of a token
-  const bool turns = kD == 128 ? a.turns : kKLoads > 1;
+  const bool turns = kD == 128 ? a.turns : !kFp8 || (kD == 256 && !kLarge);
   const int koff = turns ? lane : tau * kPieces + c;
   u32x4* turn = (u32x4*)(wave_lds + kGroupWaves * a.wave_lds_floats) + wave * (kBlockTokens * kPieces);
   // V, in units of one VReg: token 4*e + c, this lane's dims (of half h when D = 256)

@@ -5,11 +5,11 @@ namespace pkv {
 
 template <int kD>
 static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, size_t lds, hipStream_t stream) {
-  constexpr bool kLate = kD == 128;
+  constexpr bool kLarge = kD == 128;
   const dim3 grid(a.waves / group_waves(kD), layers ? layers->count : 1), block(group_waves(kD) * 64);
-  if (layers) hipLaunchKernelGGL((attn_stream_kernel<kD, false, AttnLayers, kLate>), grid, block, lds, stream, a, *layers);
+  if (layers) hipLaunchKernelGGL((attn_stream_kernel<kD, false, AttnLayers, kLarge>), grid, block, lds, stream, a, *layers);
   else if (a.kv_fp8) hipLaunchKernelGGL((attn_stream_kernel<kD, true, OneLayer, false>), grid, block, lds, stream, a, OneLayer{});
-  else hipLaunchKernelGGL((attn_stream_kernel<kD, false, OneLayer, kLate>), grid, block, lds, stream, a, OneLayer{});
+  else hipLaunchKernelGGL((attn_stream_kernel<kD, false, OneLayer, kLarge>), grid, block, lds, stream, a, OneLayer{});
 }
 
 hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, hipStream_t stream) {
@@ -28,7 +28,7 @@ hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, 
   if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
   else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);
   else if (a.D != 256) return hipErrorInvalidValue;
-  else if (late_at_256(a)) launch_late_256(a, lds, stream);
+  else if (large_at_256(a)) launch_large_256(a, lds, stream);
   else launch_dim<256>(a, layers, lds, stream);
   return hipGetLastError();
 }

@@ -210,7 +210,7 @@ struct StreamLds {
   int prefix, wave;   // where the wavefronts' parts begin, and from one to the next
   int staged_max;
   int bytes;
-  int turn_bytes;     // behind them, a block of K per wavefront, to turn it; 0 where K is loaded in operand order
+  int turn_bytes;     // behind them, a block of K per wavefront, to turn it; 0 where there is no room or no need
 };
 inline StreamLds stream_lds(int S, int G, int D, bool kv_fp8 = false) {
   const int group = group_waves(D), rec = record_floats(G, D), rows = G * D / 2;
@@ -229,18 +229,22 @@ inline StreamLds stream_lds(int S, int G, int D, bool kv_fp8 = false) {
   return l;
 }
 
-// bf16 at D = 256: does V go out when K is there, with a quarter of the next K, and not a block ahead?  Where the bounds allow
-// shares of 24 blocks and more.  A block ahead / late, us for append and attention: 20 requests of 260..350 tokens on 8/8
-// heads (3 blocks a share) 16.6 / 18.4, 20 of 350..470 (4) 22.2 / 22.4, 20 of 700..940 (8) 32.7 / 32.8; 20 of 2600..3500 (30)
-// 86.1 / 85.5, 20 of 6100..8200 (70) 191.7 / 186.8, 125 of 970..1320 on 40/8 heads (70) 196.9 / 192.2.  (With K loaded in operand
-// order and two blocks out the last three took 87.4, 188.9 and 194.)  Both loops in one kernel cost it 75 registers and
-// short shares 5 to 14 %.
-inline bool late_at_256(const AttnLaunch& a) {
+// D = 256: does a batch take the kernel for large ones?  Where the bounds allow shares of 24 blocks and more.  Us for append and
+// attention, small / large:
+//   bf16: V goes out a block ahead / when K is there, with a quarter of the next K.  20 requests of 260..350 tokens on 8/8 heads (3
+//       blocks a share) 16.6 / 18.4, 20 of 350..470 (4) 22.2 / 22.4, 20 of 700..940 (8) 32.7 / 32.8; 20 of 2600..3500 (30) 86.1 /
+//       85.5, 20 of 6100..8200 (70) 191.7 / 186.8, 125 of 970..1320 on 40/8 heads (70) 196.9 / 192.2.  (With K loaded in operand
+//       order and two blocks out the last three took 87.4, 188.9 and 194.)  Both loops in one kernel cost it 75 registers and
+//       short shares 5 to 14 %.
+//   e4m3: K turned in LDS / loaded in operand order.  20 of 85..120 on 8/8 heads (1) 11.0 / 11.5; shares of 2 to 16 blocks 0.4 %
+//       either way; 20 of 6100..8200 on 40/8 heads (70) 108.3 / 104.8, 600 of 2800..3750 on 8/1 heads (120) 173.4 / 170.3.  Both
+//       in one kernel cost short shares 1 to 3 %.
+inline bool large_at_256(const AttnLaunch& a) {
   const int64_t most = (int64_t)a.S * a.Hkv * ((a.max_ctx + kBlockTokens - 1) / kBlockTokens);
-  return a.D == 256 && !a.kv_fp8 && most >= 24 * (int64_t)a.waves;
+  return a.D == 256 && most >= 24 * (int64_t)a.waves;
 }
-// The stream pass's kernels for one layer in that way, and for layers one after the other.
-void launch_late_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
+// The stream pass's kernels for one layer of those, and for layers one after the other.
+void launch_large_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
 hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 
 // The turn of a block of K: place, in 16-byte pieces, of piece p of token t (`pieces` of them each: 8, 16 or 32).  A wavefront writes

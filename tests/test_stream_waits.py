@@ -45,7 +45,7 @@ def assembly(tmp_path_factory):
 def kernels(assembly):
     """(name, assembly) of every variant"""
     found = [k for text in assembly for k in re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", text, re.S | re.M)]
-    assert len(found) == 14
+    assert len(found) == 15
     return found
 
 
