@@ -341,8 +341,8 @@ int pkv_set_id_fault_counter(int32_t* device_counter);
 /*
  * Measurement aid (no part of the paper's method): streams total_blocks pairs of
  * 4 KiB slabs -- the K and the V rows of 16 tokens of one KV head at D = 128 in
- * bf16 -- out of two buffers with exactly the launch shape and load instructions
- * of paged_decode_attn's stream pass, at slab numbers drawn by a hash that visits
+ * bf16 -- out of two buffers with exactly the launch shape, load instructions and
+ * order of loads of paged_decode_attn's stream pass, at slab numbers drawn by a hash that visits
  * every slab once before it repeats one (so total_blocks <= num_slabs reads
  * nothing twice and no cache can help), and does nothing with the data.  Timed by the caller (events on `stream`), it gives the
  * rate the machine allows for that access pattern: 8192 * total_blocks bytes per

@@ -91,9 +91,6 @@ namespace {
 
 constexpr int kWindow = 64;       // descriptors per window: one per lane
 
-// kLate: K loads, of four (D = 128) or eight, of the next block that go out with this block's V.
-constexpr int kAhead = 2;
-
 // What depends on the head dimension and the pool format.
 template <int kD, bool kFp8> struct Dim;
 template <> struct Dim<64, false> {

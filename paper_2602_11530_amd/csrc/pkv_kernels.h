@@ -25,6 +25,10 @@ constexpr int kStreamWaves = 8 * kLayerGroups;
 // Wavefronts per workgroup.
 __host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; }
 
+// Stream pass where V goes out when K is there: K loads, of four (D = 128) or eight, of the next block that go out with this
+// block's V.
+constexpr int kAhead = 2;
+
 // How the batch's KV blocks are laid out as one stream and cut into shares.
 //   Segment (s, kvh) holds the nblk_s = ceil(L_s/16) 16-token units ("blocks" below;
 //   a physical block of B tokens is B/16 of them in a row) of request s for KV
@@ -293,7 +297,7 @@ hipError_t launch_kv_append_fp8(const uint16_t* k_new, const uint16_t* v_new, vo
                                 int Hkv, int D, int MAXB, int B, int max_ctx, int NB,
                                 int32_t* id_faults, hipStream_t stream);
 
-// Measurement aid: the stream pass's load pattern with no arithmetic (see stream_probe.hip).
+// Measurement aid: the stream pass's loads at D = 128 in bf16 with no arithmetic (see stream_probe.hip).
 hipError_t launch_stream_read_probe(const void* k_buf, const void* v_buf, uint32_t num_slabs,
                                     int64_t total_blocks, void* sink, hipStream_t stream);
 
