@@ -22,6 +22,13 @@ def layers_call(w, dev, t_d, l_d, shape):
     return outs
 
 
+def chained(w):
+    """Do workgroups go from layer to layer?  Not with few segments, nor where each has a workgroup by the bounds."""
+    segments, waves = w.num_seqs * w.num_kv_heads, 4 if w.head_dim == 256 else 8
+    blocks = w.max_blocks_per_seq * w.block_size // 16
+    return segments > 64 and (segments > 256 or blocks > 6 * waves)
+
+
 def device_layers(w, n, seed):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(seed)
@@ -32,7 +39,8 @@ def device_layers(w, n, seed):
     return [(normal(w.q_shape()), normal(w.pool_shape()), normal(w.pool_shape())) for _ in range(n)]
 
 
-# blocks per share at 2048 wavefronts (1024 at D = 256): under one, 3, 61..64, 65, 130
+# blocks per share at 2048 wavefronts (1024 at D = 256): the first two have a workgroup for each segment, the layers side by
+# side; then 51, 69, 63, 64, 129 and 64
 @pytest.mark.parametrize("dim,lens,hq,hkv", [
     (128, [40, 0, 17] * 24, 2, 2), (128, [300] * 70 + [0] * 5, 4, 2), (64, [5000 + 13 * i for i in range(40)], 8, 8),
     (128, [15700, 15800, 15900] * 6 + [0], 8, 8), (128, [16120] * 16 + [1] * 4, 8, 8), (128, [16384 + 40] * 16, 8, 8),
@@ -41,9 +49,29 @@ def test_equals_single_calls(device, dim, lens, hq, hkv):
     blocks = sum((n + 15) // 16 for n in lens) + 3
     w = wl.custom(lens, hq, hkv, seed=61, num_pool_blocks=blocks, head_dim=dim)
     assert len(lens) * hkv > 64
+    assert chained(w) == (max(lens) > 1000)
     dev = device_layers(w, 5, 7)
     t_d, l_d = to_dev(w.block_tables), to_dev(w.context_lens)
     print(f"D={dim} S={len(lens)} {hq}/{hkv} blocks={blocks}", flush=True)
+    single = [run_attn_dev(w, q, k, v, t_d, l_d) for q, k, v in dev]
+    for got, want in zip(layers_call(w, dev, t_d, l_d, shape_of(w)), single):
+        assert torch.equal(got, want)
+
+
+# Short shares on the chained path, by a table wider than what is in use: less than a block for each wavefront; no segment
+# longer than a workgroup takes (cut along them on the device, some workgroups without any); 3; then exactly 62 to 66, where a
+# window of 64 ends before, with and behind the share
+@pytest.mark.parametrize("dim,lens,hq,hkv,P", [
+    (128, [900] + [40, 0, 17] * 24, 2, 2, 0), (128, [40, 0, 17] * 24, 2, 2, 0), (256, [100, 0, 17] * 24, 8, 2, 0),
+    (128, [180, 0] * 70, 16, 8, 64), (64, [180] * 70, 8, 8, 512)] +
+    [(64, [256 * k] * 16, 8, 8, 64 if k == 64 else 0) for k in range(62, 67)])
+def test_short_shares_equal_single_calls(device, dim, lens, hq, hkv, P):
+    blocks = sum((n + 15) // 16 for n in lens) + 3
+    w = wl.custom(lens, hq, hkv, seed=63, num_pool_blocks=blocks, head_dim=dim, partition_size=P, maxb=max(60, max(lens) // 16 + 1))
+    assert chained(w)
+    dev = device_layers(w, 3, 11)
+    t_d, l_d = to_dev(w.block_tables), to_dev(w.context_lens)
+    print(f"D={dim} S={len(lens)} {hq}/{hkv} blocks={blocks} P={P}", flush=True)
     single = [run_attn_dev(w, q, k, v, t_d, l_d) for q, k, v in dev]
     for got, want in zip(layers_call(w, dev, t_d, l_d, shape_of(w)), single):
         assert torch.equal(got, want)
