@@ -61,20 +61,20 @@
 // Memory traffic.  The KV loads of a block (eight of 16 bytes at D = 128) are
 // nontemporal and unconditional.  A load that takes 64 bytes of each of 16 tokens, as the matrix cores
 // want K, keeps the address unit busy for twice the lines and takes each of them from the caches in two
-// halves (e4m3 at D = 256 in large batches and D = 128 without room take it all the same, see large_at_256 and stream_lds);
-// whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
-// latency per block and are faster where that counts (append and attention: 4 requests of 17..300 tokens
-// 11.9 -> 11.1 us, 8 at D = 256 34.5 -> 33.0, 32 at D = 64 45.9 -> 43.3, 64 on 8-bit pools 109.2 -> 105.8)
-// and equal or a little faster where the memory is saturated either way (64 of 1024..8192 190.6 -> 188.9, 128 long ones
-// 584.7 -> 577.9).  What is in flight per wavefront, 2048 of them (1024 at D = 256):
-//   e4m3 at D = 64 (2 KiB): the next block's loads go out before this one's are waited for (once they are there
+// halves; whole rows and a turn in LDS (no bank conflicts, 32 KiB a workgroup) cost a few hundred cycles of
+// latency per block.  With the order of the loads below, append and attention, us before / after: 4 requests of 17..300
+// tokens 12.2 / 11.5, one of 8191 18.2 / 17.1, 8 at D = 256 35.0 / 33.5, 32 at D = 64 44.1 / 41.8, 64 on 8-bit pools 105.0 /
+// 103.9; where the memory is saturated 64 of 1024..8192 189.1 / 188.8, 128 long ones 592.4 / 588.8.  In operand order all the
+// same: D = 128 without room in LDS (stream_lds), e4m3 at D = 64, and large batches in e4m3 at D = 256 (large_at_256).
+// What is in flight per wavefront, 2048 of them (1024 at D = 256):
+//   e4m3 at D = 64 (blocks of 2 KiB): the next block's loads go out before this one's are waited for (once they are there
 //       instead: 20 requests of 12000..16500 tokens on 40/8 heads 63.8 us, this way 61.3; 20 of 21000..28000 98.6 and 95.3)
-//   blocks of 4 KiB, e4m3 at D = 256 (8 KiB) and small batches in bf16 at D = 256 (16 KiB): the next block's loads go out
-//       once this one's are there
-//   bf16 at D = 128 (8 KiB) and large batches at D = 256 (kLate): V of this block and kAhead loads of the next one's K go out
-//       once K is there, the rest of that K after the block: at D = 128 4 to 6 KiB at any time; with 8 KiB some dies of the chip get more than their
-//       part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584 instead of 578;
-//       with 4 KiB 4-KiB blocks lose a quarter, which is why those have all of theirs ahead)
+//   bf16 at D = 64 and e4m3 at D = 128 (4 KiB), e4m3 at D = 256 (8 KiB), bf16 there in small batches (16 KiB): the next block's
+//       loads go out once this one's are there
+//   bf16 at D = 128 (8 KiB) and in large batches at D = 256 (kLate): V of this block and kAhead loads of the next one's K go
+//       out once K is there, the rest of that K after the block, at D = 128 4 to 6 KiB at any time.  With 8 KiB some dies of the
+//       chip get more than their part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584
+//       instead of 578; with 4 KiB 4-KiB blocks lose a quarter, which is why those have all of theirs ahead)
 // Deeper rings (3 or 7 blocks ahead) only lengthen the queues.
 // Finished rows and records wait in LDS and are written in
 // bursts of full-width write-through stores that the compiler's wait-count
@@ -182,7 +182,7 @@ constexpr int kEndsThrough = 2;   // and goes on after it
 constexpr int kEndsRight = 4;     // the right record is in use: the last segment begins in the share and goes on
 
 // Inclusive prefix sum over the wavefront, in the vector unit.  It stands before the first load of the stream: by six shuffles
-// through LDS, 4 requests of 17..300 tokens took 11.2 us for append and attention, this way 10.9; one of 8191 16.95 and 16.7.
+// through LDS, 4 requests of 17..300 tokens took 11.5 us for append and attention, this way 11.3; one of 8191 17.2 and 16.95.
 __device__ __forceinline__ int wave_prefix(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8 within 16 lanes
   x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
@@ -766,7 +766,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   const int ends = ends_flags, left_end = left;
   if (more) {
     // The next layer: its first loads are on their way while the workgroup meets (six layers of 24 requests, with a
-    // workgroup of its own for each layer's range 760.7 us, this way 755.6).
+    // workgroup of its own for each layer's range 767.9 us, this way 763.5).
     layer = layer_at(a, layers, of + 1);
     if (jbase) {   // window A is not the first one any more
       jbase = refused = 0;

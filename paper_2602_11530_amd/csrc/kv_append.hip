@@ -3,10 +3,11 @@
 // updated with each newly generated token).  A few hundred KiB per call, so latency is all there
 // is: the launch itself (1.65 us for an empty kernel between two others), then length -> table entry ->
 // slot.  A workgroup has one request, K's chunks of 16 bytes and then V's, a lane each: the two look-ups
-// are scalar, nothing is divided, and the new rows are asked for before the length is known (64 requests on
-// 8 KV heads between two long kernels: 2.35 us with a chunk of both pools per lane of a flat grid, 64-bit
-// divisions by the row and rows loaded last; 1.9 this way; appended and attended
-// to, one request of 8191 tokens 17.5 -> 16.7, 64 of 64 tokens on 8-bit pools 12.5 -> 11.75).
+// are scalar, nothing is divided, and the new rows are asked for before the length is known.  Against a chunk of both pools per
+// lane of a flat grid, 64-bit divisions by the row and rows loaded last, us from one launch to the next on tables and slots that
+// are warm: one request on 8 KV heads 2.95 -> 2.81, 64 3.19 -> 3.01, 64 on 8-bit pools 3.64 -> 3.06, 1000 at D = 256 4.88 -> 4.36;
+// with the attention behind it one request of 8191 tokens 18.5 -> 18.2, 64 of 64 on 8-bit pools 13.4 -> 12.9.  Behind a long
+// kernel that has read the pools, 24 requests and more take 4.6 to 5 us either way.
 #include "pkv_kernels.h"
 
 namespace pkv {
