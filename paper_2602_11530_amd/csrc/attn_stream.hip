@@ -28,7 +28,7 @@ hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, 
   if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
   else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);
   else if (a.D != 256) return hipErrorInvalidValue;
-  else if (large_at_256(a)) launch_large_256(a, lds, stream);
+  else if (!layers && large_at_256(a)) launch_large_256(a, lds, stream);   // layers come here with short segments only
   else launch_dim<256>(a, layers, lds, stream);
   return hipGetLastError();
 }
