@@ -161,6 +161,16 @@ __device__ __forceinline__ void store16(void* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
+// A nontemporal load of a buffer, zero out of its bounds.
+constexpr int kRawBuffer = 0x00020000;   // last word of the buffer's descriptor: bytes
+template <typename T>
+__device__ __forceinline__ T load_nt(__amdgpu_buffer_rsrc_t b, int offset) {
+  constexpr int kNt = 2;
+  if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, kNt));
+  else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, offset, 0, kNt));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, offset, 0, kNt));
+}
+
 // One window of block descriptors: lane i describes stream index jbase + i.
 struct Window {
   int slab;   // which slab (16 tokens of one KV head; 4 KiB at D = 128 in bf16), counted from the pool's start; 0 when not read
@@ -369,13 +379,14 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     const bool seg_first = (b == 0) || (j == 0);
     d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0) |
              (b + 1 == nb ? kMetaSegEnd : 0) | (b > j ? kMetaOpenLeft : 0);
+    if (!live) d.meta = 0;
     d.seg = s * Hkv + kvh;
     return d;
   };
 
   Window dA = describe(0);
-  Window dB = dA;   // described after the first KV loads are on their way (below)
-  int jbase = 0;
+  Window dB = {0, 0, 0};   // described after the first KV loads are on their way (below)
+  int jbase = 0;           // stream index of window A's first block
 
   const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
   const int tau = turn_token(n);
@@ -396,39 +407,45 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
   for (int i = 0; i < kTiles; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // The loads of stream index j, nontemporal: the stream is read once and must not allocate in the
-  // caches it passes through.  The loads are unconditional so that every wait in the loop knows
-  // exactly how many are outstanding: a block that is unmapped, or an index past
-  // the share's end, reads slab 0 (which always exists) and is masked or skipped.
-  auto slab_at = [&](int j) -> int64_t {   // byte offset of the slab of stream index j
-    const int idx = j - jbase;   // 0 .. 2*kWindow-1
-    const int sa = __builtin_amdgcn_readlane(dA.slab, idx & (kWindow - 1));
-    const int sb = __builtin_amdgcn_readlane(dB.slab, idx & (kWindow - 1));
-    int slab = (idx < kWindow) ? sa : sb;
-    if (j >= nshare) slab = 0;
-    return (int64_t)slab * slab_bytes;
+  // The streaming loop reads a block's descriptor once, when its first loads go out, and keeps it until the block has been consumed.
+  struct Block {
+    int slab, meta;   // of a Window
   };
-  auto issue_k = [&](u32x4 (&k)[kKLoads], int j, int from, int to) {
-    const u32x4* kp = (const u32x4*)((const char*)layer.k_pool + slab_at(j)) + koff;
+  auto block_at = [&](int j) {
+    return Block{__builtin_amdgcn_readlane(dA.slab, j - jbase), __builtin_amdgcn_readlane(dA.meta, j - jbase)};
+  };
+  // The loads of a block, nontemporal: the stream is read once and must not allocate in the
+  // caches it passes through.  The loads are unconditional so that every wait in the loop knows
+  // exactly how many are outstanding, and their bounds are the block's valid rows: what lies behind a
+  // request's last token, a block that is unmapped and an index past the share's end are not read and arrive as zeros.
+  // Against whole blocks, the first one of the pool past a share's end, and descriptors looked up for each load: 512 requests of
+  // 16..512 tokens 109.5 -> 106.0 us, shares of 1 to 4 blocks at D = 128 0.98 of the time, 72 shapes of 8-bit pools at D = 64 0.983.
+  auto rows_of = [&](const void* pool, Block at) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)pool + at.slab * slab_bytes), 0,
+                                             (at.meta & 0xff) * (kD * kElemBytes), kRawBuffer);
+  };
+  auto issue_k = [&](u32x4 (&k)[kKLoads], Block at, int from, int to) {
+    const __amdgpu_buffer_rsrc_t b = rows_of(layer.k_pool, at);
     if (turns) {
 #pragma unroll
-      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 64 * jj);
+      for (int jj = from; jj < to; ++jj) k[jj] = load_nt<u32x4>(b, 16 * (koff + 64 * jj));
     } else {
 #pragma unroll
-      for (int jj = from; jj < to; ++jj) k[jj] = __builtin_nontemporal_load(kp + 4 * jj);
+      for (int jj = from; jj < to; ++jj) k[jj] = load_nt<u32x4>(b, 16 * (koff + 4 * jj));
     }
   };
-  auto issue_v = [&](VReg (&v)[kVLoads], int j) {
-    const VReg* vp = (const VReg*)((const char*)layer.v_pool + slab_at(j)) + voff;
+  auto issue_v = [&](VReg (&v)[kVLoads], Block at) {
+    const __amdgpu_buffer_rsrc_t b = rows_of(layer.v_pool, at);
+    constexpr int kBytes = sizeof(VReg);
     if (kD == 256) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        v[2 * e] = __builtin_nontemporal_load(vp + 128 * e);
-        v[2 * e + 1] = __builtin_nontemporal_load(vp + 128 * e + 16);
+        v[2 * e] = load_nt<VReg>(b, kBytes * (voff + 128 * e));
+        v[2 * e + 1] = load_nt<VReg>(b, kBytes * (voff + 128 * e + 16));
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = __builtin_nontemporal_load(vp + 64 * e);
+      for (int e = 0; e < 4; ++e) v[e] = load_nt<VReg>(b, kBytes * (voff + 64 * e));
     }
   };
   // K of a block that has arrived, into LDS and back as the A operand: load L of lane (n, c) is piece 4L + c of token tau(n).
@@ -463,8 +480,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     nstaged = 0;
   };
 
-  auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int j) __attribute__((always_inline)) {
-    const int idx = j - jbase;   // always inside window A
+  int seg = 0, seg_next = 0;   // the segment being streamed, and the one of the query group that was asked for last
+  auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int meta) __attribute__((always_inline)) {
     // The MFMA operands.  bf16 pools: the registers as they are.  e4m3 pools: piece 4L + c of
     // K's row holds dims 16*(4L + c) .. +15 of token tau(n), which feed steps 2L and 2L + 1 (the
     // contraction order is free as long as q follows it, see below); a V load holds the same
@@ -493,7 +510,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
         v[e] = VOp{a2.x, a2.y, b2.x, b2.y};
       }
     }
-    const int meta = __builtin_amdgcn_readlane(dA.meta, idx);
     const int ntok = meta & 0xff;
 
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};
@@ -506,17 +522,12 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     const bool edge = ntok < kBlockTokens;
     bool valid[4] = {true, true, true, true};
     if (edge) {
-      // Last block of a request, or an unmapped one: masked slots may hold anything
-      // (NaN included), so scores, weights and V rows are replaced by select,
-      // never scaled by zero.  Element e of this lane is token 4*e + c.
+      // Last block of a request, or an unmapped one: the rows behind it are zeros, and their
+      // scores and weights are replaced by select.  Element e of this lane is token 4*e + c.
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         valid[e] = 4 * e + c < ntok;
         x[e] = valid[e] ? x[e] : kNegInf;
-        if (!valid[e]) {
-          if (kD == 256) { v[2 * e] = VOp{}; v[2 * e + 1] = VOp{}; }
-          else v[e] = VOp{};
-        }
       }
     }
     const float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
@@ -603,7 +614,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       }
       if (done) {
         if (nstaged == a.staged_max) store_staged();
-        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
         staged_segs = (lane == nstaged) ? seg : staged_segs;
         uint16_t* rows = staged + nstaged * G * kD;
         const float inv = inverse(lt, a.out_scale);
@@ -622,7 +632,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
         ends_flags &= ~kEndsRight;
       } else {
         if (!open_left) store_staged();   // the staged rows lie where the record goes
-        const int seg = __builtin_amdgcn_readlane(dA.seg, idx);
         ends_flags = !open_left ? ends_flags | kEndsRight
                      : (meta & kMetaSegEnd) ? kEndsLeft : kEndsLeft | kEndsThrough;
         left = open_left ? seg : left;
@@ -652,17 +661,19 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // first block was already to be consumed, it cost the pipeline a drain per segment (512 requests of
   // 16..512 tokens: 116.5 -> 114.1 us; 8 requests at D = 256: 36.3 -> 35.7).
   u32x4 qnext[kKSteps];
-  auto load_q = [&](int seg) {
-    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(seg * G + min(n, G - 1)) * kD);
+  auto load_q = [&](int j) {   // of the segment that begins at stream index j
+    seg_next = __builtin_amdgcn_readlane(dA.seg, j - jbase);
+    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(seg_next * G + min(n, G - 1)) * kD);
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj)
       // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
       // e4m3 K load, 64*(jj/2) + 16*c + 8*(jj%2) .. +7
       qnext[jj] = kFp8 ? qrow_p[8 * (jj >> 1) + 2 * c + (jj & 1)] : qrow_p[4 * jj + c];
   };
-  auto take_q = [&](int j) {   // before the next group is asked for
-    if (!(__builtin_amdgcn_readlane(dA.meta, j - jbase) & kMetaSegFirst)) return;
+  auto take_q = [&](int meta) {   // before the next group is asked for
+    if (!(meta & kMetaSegFirst)) return;
     seg_open = false;
+    seg = seg_next;
 #pragma unroll
     for (int jj = 0; jj < kKSteps; ++jj) qop[jj] = (n < G) ? qnext[jj] : u32x4{0, 0, 0, 0};
   };
@@ -675,19 +686,18 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 #pragma unroll
     for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
   };
-  auto ask_q = [&](VReg (&v)[kVLoads], int j) {   // v: of the block before
-    const int idx = j - jbase;
-    const int meta = __builtin_amdgcn_readlane(idx < kWindow ? dA.meta : dB.meta, idx & (kWindow - 1));
-    if (j >= nshare || !(meta & kMetaSegFirst)) return;
+  auto ask_q = [&](VReg (&v)[kVLoads], int j, int meta) {   // v: of the block before
+    if (!(meta & kMetaSegFirst)) return;
     if (kTwoBlocks) arrived_v(v);
-    load_q(__builtin_amdgcn_readlane(idx < kWindow ? dA.seg : dB.seg, idx & (kWindow - 1)));
+    load_q(j);
   };
 
   u32x4 kbuf[2][kKLoads];   // two blocks in turn, so that no buffer is ever copied
   VReg vbuf[2][kVLoads];
-  issue_k(kbuf[0], 0, 0, kKLoads);
-  if (!kLate) issue_v(vbuf[0], 0);
-  load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+  Block at = block_at(0);
+  issue_k(kbuf[0], at, 0, kKLoads);
+  if (!kLate) issue_v(vbuf[0], at);
+  load_q(0);
   if (nshare > kWindow) dB = describe(kWindow);
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
@@ -713,28 +723,31 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       VReg (&v)[kVLoads] = vbuf[i], (&vnext)[kVLoads] = vbuf[i ^ 1];
       if (!kTwoBlocks) arrived_k(k);
       if (!kTwoBlocks && !kLate) arrived_v(v);
+      if (i == 1 && j + 2 == jbase + kWindow) {   // the loads leave window A: B becomes A
+        dA = dB;
+        jbase += kWindow;
+      }
+      const Block next = block_at(j + i + 1);
       if (kLate) {
-        issue_v(v, j + i);
-        issue_k(knext, j + i + 1, 0, kAhead);
+        issue_v(v, at);
+        issue_k(knext, next, 0, kAhead);
       } else {
-        issue_k(knext, j + i + 1, 0, kKLoads);
-        issue_v(vnext, j + i + 1);
+        issue_k(knext, next, 0, kKLoads);
+        issue_v(vnext, next);
       }
       if (kTwoBlocks) arrived_k(k);
       if (j + i < nshare) {
-        take_q(j + i);
-        ask_q(v, j + i + 1);
+        take_q(at.meta);
+        ask_q(v, j + i + 1, next.meta);
         turn_k(k);
-        consume(k, v, j + i);
+        consume(k, v, at.meta);
       }
-      if (kLate) issue_k(knext, j + i + 1, kAhead, kKLoads);
+      if (kLate) issue_k(knext, next, kAhead, kKLoads);
+      at = next;
     }
-    if (j + 2 == jbase + kWindow) {
-      // The consumer leaves window A: B becomes A, and the window after it is
-      // described now, 64 blocks before its first use.
-      dA = dB;
-      jbase += kWindow;
+    if (j + 2 == jbase) {   // the window after it is described now, 64 blocks before its first use
       if (jbase + kWindow < nshare) dB = describe(jbase + kWindow);
+      else dB = Window{0, 0, 0};
     }
   }
   store_staged();
@@ -747,15 +760,17 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     };
     if (ends_flags & kEndsLeft) store_record(rec_left, left);
     if (ends_flags & kEndsRight) store_record(rec_right, right);
-    // Never: up to here the registers of the query group that was asked for last are its own.  As far as the compiler knows
-    // those loads may still be on their way, and a loop of stores that took the registers over would wait for them in every
-    // turn, and so for the acknowledgement of each hidden store (append and attention of 4 requests of 1360..1840 tokens on
-    // 16/1 heads at D = 64, five stores a record: 15.4 us with such a wait, 14.1 without).
+    // Never: up to here the registers of the query group that was asked for last, and of the K that goes out behind a block, are
+    // their own.  As far as the compiler knows those loads may still be on their way, and a loop of stores that took the
+    // registers over would wait for them in every turn, and so for the acknowledgement of each hidden store (append and attention
+    // of 4 requests of 1360..1840 tokens on 16/1 heads at D = 64, five stores a record: 15.4 us with such a wait, 14.1 without).
     int never;
     asm volatile("s_mov_b32 %0, 0" : "=s"(never));
     if (never) {
 #pragma unroll
       for (int jj = 0; jj < kKSteps; ++jj) asm volatile("" : : "v"(qnext[jj]));
+#pragma unroll
+      for (int jj = 0; jj < (kD == 128 ? kKLoads : 0); ++jj) asm volatile("" : : "v"(kbuf[0][jj]));
     }
   }
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
@@ -773,9 +788,10 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       jbase = refused = 0;
       dA = describe(0);
     }
-    issue_k(kbuf[0], 0, 0, kKLoads);
-    if (!kLate) issue_v(vbuf[0], 0);
-    load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+    at = block_at(0);
+    issue_k(kbuf[0], at, 0, kKLoads);
+    if (!kLate) issue_v(vbuf[0], at);
+    load_q(0);
     if (nshare > kWindow) dB = describe(kWindow);
     seg_open = false;
     ends_flags = left = right = 0;
