@@ -72,7 +72,7 @@
 //   bf16 at D = 64 and e4m3 at D = 128 (4 KiB), e4m3 at D = 256 (8 KiB), bf16 there in small batches (16 KiB): the next block's
 //       loads go out once this one's are there
 //   bf16 at D = 128 (8 KiB) and in large batches at D = 256 (kLate): V of this block and kAhead loads of the next one's K go
-//       out once K is there, the rest of that K after the block, at D = 128 4 to 6 KiB at any time.  With 8 KiB some dies of the
+//       out once K is there, the rest of that K after the block, at D = 128 4 to 6 KiB at any time, 8 in short shares.  With 8 KiB some dies of the
 //       chip get more than their part and the others end late (64 requests 191.9 us instead of 188.9, 128 long ones 584
 //       instead of 578; with 4 KiB 4-KiB blocks lose a quarter, which is why those have all of theirs ahead)
 // Deeper rings (3 or 7 blocks ahead) only lengthen the queues.
@@ -213,7 +213,7 @@ __device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
   return *(const AttnLaunch*)p;
 }
 
-// kLarge: as large batches want it (large_at_256), and at D = 128 all in bf16.
+// kLarge: as large batches want it (large_at_256; at D = 128 in bf16 all but short ones, short_at_128).
 template <int kD, bool kFp8, typename Layers, bool kLarge>
 __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
   typedef Dim<kD, kFp8> DD;
@@ -221,7 +221,10 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   typedef typename Dim<kD, false>::VReg VOp;      // the same rows as bf16
   constexpr int kKSteps = DD::kKSteps, kKLoads = DD::kKLoads, kVLoads = DD::kVLoads,
                 kTiles = DD::kTiles, kElemBytes = DD::kElemBytes;
-  constexpr bool kLate = kLarge && !kFp8;         // V goes out when K is there, not a block ahead
+  // V goes out when K is there, not a block ahead, and with it some of the next block's K loads: kAhead, or all where shares are
+  // short (short_at_128; AttnLayers have a workgroup for each short segment).
+  constexpr bool kLate = !kFp8 && (kD == 128 || (kD == 256 && kLarge));
+  constexpr int kNextK = kD == 128 && (!kLarge || std::is_same_v<Layers, AttnLayers>) ? kKLoads : kAhead;
   constexpr bool kTwoBlocks = kD == 64 && kFp8;   // the next block's loads go out before this one's have arrived
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
   extern __shared__ __align__(16) int smem[];
@@ -730,7 +733,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       const Block next = block_at(j + i + 1);
       if (kLate) {
         issue_v(v, at);
-        issue_k(knext, next, 0, kAhead);
+        issue_k(knext, next, 0, kNextK);
       } else {
         issue_k(knext, next, 0, kKLoads);
         issue_v(vnext, next);
@@ -742,7 +745,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
         turn_k(k);
         consume(k, v, at.meta);
       }
-      if (kLate) issue_k(knext, next, kAhead, kKLoads);
+      if (kLate) issue_k(knext, next, kNextK, kKLoads);
       at = next;
     }
     if (j + 2 == jbase) {   // the window after it is described now, 64 blocks before its first use

@@ -17,6 +17,7 @@ static void launch_layers(const AttnLaunch& a, const AttnLayers& layers, size_t 
 
 hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream) {
   if (a.D == 64) launch_layers<64, false>(a, layers, lds, stream);
+  else if (short_at_128(a)) launch_chained_short_128(a, layers, lds, stream);
   else if (a.D == 128) launch_layers<128, true>(a, layers, lds, stream);
   else if (a.D != 256) return hipErrorInvalidValue;
   else if (large_at_256(a)) launch_layers<256, true>(a, layers, lds, stream);

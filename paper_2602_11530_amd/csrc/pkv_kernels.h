@@ -26,7 +26,7 @@ constexpr int kStreamWaves = 8 * kLayerGroups;
 __host__ __device__ constexpr int group_waves(int D) { return D == 256 ? 4 : 8; }
 
 // Stream pass where V goes out when K is there: K loads, of four (D = 128) or eight, of the next block that go out with this
-// block's V.
+// block's V.  All four where shares are short (short_at_128).
 constexpr int kAhead = 2;
 
 // How the batch's KV blocks are laid out as one stream and cut into shares.
@@ -247,8 +247,19 @@ inline bool large_at_256(const AttnLaunch& a) {
   const int64_t most = (int64_t)a.S * a.Hkv * ((a.max_ctx + kBlockTokens - 1) / kBlockTokens);
   return a.D == 256 && most >= 24 * (int64_t)a.waves;
 }
+// D = 128 in bf16: does a batch take the kernel for short shares?  There all of the next block's K goes out with this block's V and a
+// wavefront waits for loads once a block; else half of it, see attn_stream.h.  Up to 16 blocks a share by the bounds, which are
+// often twice the mean.  All / half, append and attention, geometric means of 16 shapes each (8 to 600 segments, 1 to 8 heads per
+// KV head): shares of 1 block 0.979, 2 0.966, 3 0.963, 4 0.978, 6 0.985, 8 0.989, 12 0.998, 20 1.002; 70 blocks 1.01.  A choice
+// within one kernel costs what it gains (a second loop: 4 requests of 17..300 tokens 10.9 -> 11.25 us).
+inline bool short_at_128(const AttnLaunch& a) {
+  const int64_t most = (int64_t)a.S * a.Hkv * ((a.max_ctx + kBlockTokens - 1) / kBlockTokens);
+  return a.D == 128 && !a.kv_fp8 && most <= 16 * (int64_t)a.waves;
+}
 // The stream pass's kernels for one layer of those, and for layers one after the other.
 void launch_large_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
+void launch_short_128(const AttnLaunch& a, size_t lds, hipStream_t stream);
+void launch_chained_short_128(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 
 // The turn of a block of K: place, in 16-byte pieces, of piece p of token t (`pieces` of them each: 8, 16 or 32).  A wavefront writes
