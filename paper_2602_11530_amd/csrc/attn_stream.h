@@ -213,6 +213,11 @@ __device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
   return *(const AttnLaunch*)p;
 }
 
+// WholeLayer: the bounds say that each segment has a workgroup.  Where its blocks are then follows from its request's length alone, which
+// is asked for together with the table row and the query group: no prefix sums, no search, no barrier, one round trip to memory
+// before the first K instead of two.  Append and attention against the general kernel, which finds out on the device: 4 requests of
+// 17..300 tokens on 8/2 heads 10.8 -> 9.05 us, geometric means of 100 shapes each (1 to 250 segments of 10 to 300 tokens) D = 64 0.79,
+// e4m3 there 0.79, D = 128 0.80 and 0.81, D = 256 0.85 and 0.85.
 // kLarge: as large batches want it (large_at_256; at D = 128 in bf16 all but short ones, short_at_128).
 template <int kD, bool kFp8, typename Layers, bool kLarge>
 __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
@@ -224,6 +229,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // V goes out when K is there, not a block ahead, and with it some of the next block's K loads: kAhead, or all where shares are
   // short (short_at_128; AttnLayers have a workgroup for each short segment).
   constexpr bool kLate = !kFp8 && (kD == 128 || (kD == 256 && kLarge));
+  constexpr bool kWhole = std::is_same_v<Layers, WholeLayer>;
   constexpr int kNextK = kD == 128 && (!kLarge || std::is_same_v<Layers, AttnLayers>) ? kKLoads : kAhead;
   constexpr bool kTwoBlocks = kD == 64 && kFp8;   // the next block's loads go out before this one's have arrived
   constexpr int kGroupWaves = group_waves(kD), kThreads = kGroupWaves * 64;
@@ -252,71 +258,106 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   float* rec_right = rec_left + rec_floats;
   uint16_t* staged = (uint16_t*)rec_right;
 
-  // Prefix sums over the requests, 64 to a wavefront at a time: first within each 64, then, when
-  // there are more, the sums of the 64s before them (512 requests in turns of one wavefront took 3.6 us
-  // to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
-  int longest = 0;
-  for (int base = 64 * wave; base < S; base += kThreads) {
-    const int i = base + lane;
-    const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
-    const int nb = (L + kBlockTokens - 1) / kBlockTokens;
-    longest = max(longest, nb);
-    const int xb = wave_prefix(nb);
-    if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
-    if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
-  }
-  const bool some_long = __any(longest > a.short_blocks);
-  if (threadIdx.x == 0) { any_long = some_long; chains[0] = passes[0] = 0; }
-  __syncthreads();
-  if (S > 64) {
-    if (some_long && lane == 0) any_long = 1;
-    // lane c: all requests before the c-th 64 (kMaxSeqs = 32 of them)
-    const int mine = lane < (S + 63) >> 6 ? sum64[lane] : 0;
-    int before = wave_prefix(mine);
-    if (threadIdx.x == 63) cumB[S] = before;
-    before -= mine;
-    for (int base = 64 * wave; base < S; base += kThreads) {
-      const int add = __shfl(before, base >> 6);
-      if (base > 0 && base + lane < S) cumB[base + lane] += add;
-    }
-    __syncthreads();
-  }
-
-  // Equal shares: every participating wavefront gets at least one block, so that consecutive
-  // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
-  // short segments is cut along the segments instead, one to a workgroup (see short_segment).
-  const int T = Hkv * cumB[S];
-  const bool whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
-  bool by_row = false;
+  int T = 0, W = 0, first_wave = 0, last_wave = -1, pos0 = 0, nshare = 0;
+  bool whole = kWhole, by_row = false;
   int w = blockIdx.x * kGroupWaves + wave;
-  int W, first_wave, last_wave, pos0 = 0, nshare = 0;
-  if (whole) {
-    const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
-    const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
+  u32x4 qnext[kKSteps];
+  int seg = 0, seg_next = 0;   // the segment being streamed, and the one of the query group that was asked for last
+  auto load_q = [&](int segment) {
+    seg_next = segment;
+    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(segment * G + min(n, G - 1)) * kD);
+#pragma unroll
+    for (int jj = 0; jj < kKSteps; ++jj)
+      // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
+      // e4m3 K load, 64*(jj/2) + 16*c + 8*(jj%2) .. +7
+      qnext[jj] = kFp8 ? qrow_p[8 * (jj >> 1) + 2 * c + (jj & 1)] : qrow_p[4 * jj + c];
+  };
+  if constexpr (!kWhole) {
+    // Prefix sums over the requests, 64 to a wavefront at a time: first within each 64, then, when
+    // there are more, the sums of the 64s before them (512 requests in turns of one wavefront took 3.6 us
+    // to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
+    int longest = 0;
+    for (int base = 64 * wave; base < S; base += kThreads) {
+      const int i = base + lane;
+      const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
+      const int nb = (L + kBlockTokens - 1) / kBlockTokens;
+      longest = max(longest, nb);
+      const int xb = wave_prefix(nb);
+      if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
+      if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
+    }
+    const bool some_long = __any(longest > a.short_blocks);
+    if (threadIdx.x == 0) { any_long = some_long; chains[0] = passes[0] = 0; }
+    __syncthreads();
+    if (S > 64) {
+      if (some_long && lane == 0) any_long = 1;
+      // lane c: all requests before the c-th 64 (kMaxSeqs = 32 of them)
+      const int mine = lane < (S + 63) >> 6 ? sum64[lane] : 0;
+      int before = wave_prefix(mine);
+      if (threadIdx.x == 63) cumB[S] = before;
+      before -= mine;
+      for (int base = 64 * wave; base < S; base += kThreads) {
+        const int add = __shfl(before, base >> 6);
+        if (base > 0 && base + lane < S) cumB[base + lane] += add;
+      }
+      __syncthreads();
+    }
+
+    // Equal shares: every participating wavefront gets at least one block, so that consecutive
+    // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
+    // short segments is cut along the segments instead, one to a workgroup (see short_segment).
+    T = Hkv * cumB[S];
+    whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
+    if (whole) {
+      const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
+      const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
+      W = min(kGroupWaves, nb);
+      first_wave = 0;
+      last_wave = W - 1;
+      if (wave < W) {
+        const ShareMap shares(nb, W);
+        pos0 = Hkv * cumB[s] + kvh * nb + shares.start(wave);
+        nshare = shares.start(wave + 1) - shares.start(wave);
+      }
+    } else {
+      W = share_count(T, a.waves);
+      first_wave = blockIdx.x * kGroupWaves;
+      last_wave = min(kGroupWaves, W - first_wave) - 1;
+      by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
+      if (by_row && T < a.waves) {
+        // A block per wavefront and not enough of them to fill the compute units: one after the other round
+        // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
+        // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
+        w = wave * gridDim.x + blockIdx.x;
+        last_wave = w < W ? 0 : -1;
+      }
+      if (w < W) {
+        const ShareMap shares(T, W);
+        pos0 = shares.start(w);
+        nshare = shares.start(w + 1) - pos0;
+      }
+    }
+  }
+  // What lies where each segment has a workgroup.
+  int whole_len = 0, whole_entry = 0;
+  if constexpr (kWhole) {
+    const int s = blockIdx.z;
+    whole_entry = a.block_tables[(int64_t)s * a.MAXB + min(lane, a.MAXB - 1)];
+    load_q(s * Hkv + blockIdx.x);
+    typedef const int32_t __attribute__((address_space(4))) * ScalarLoad;
+    whole_len = min(max(*(ScalarLoad)(a.context_lens + s), 0), a.max_ctx);
+    const int nb = (whole_len + kBlockTokens - 1) / kBlockTokens;
+    if (nb == 0) {   // an empty request owes zero rows
+      uint32_t* dst = (uint32_t*)(layer.out + (int64_t)seg_next * G * kD);
+      for (int f = threadIdx.x; f < G * kD / 2; f += kThreads) dst[f] = 0;
+      return;
+    }
     W = min(kGroupWaves, nb);
-    first_wave = 0;
     last_wave = W - 1;
     if (wave < W) {
       const ShareMap shares(nb, W);
-      pos0 = Hkv * cumB[s] + kvh * nb + shares.start(wave);
-      nshare = shares.start(wave + 1) - shares.start(wave);
-    }
-  } else {
-    W = share_count(T, a.waves);
-    first_wave = blockIdx.x * kGroupWaves;
-    last_wave = min(kGroupWaves, W - first_wave) - 1;
-    by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
-    if (by_row && T < a.waves) {
-      // A block per wavefront and not enough of them to fill the compute units: one after the other round
-      // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
-      // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
-      w = wave * gridDim.x + blockIdx.x;
-      last_wave = w < W ? 0 : -1;
-    }
-    if (w < W) {
-      const ShareMap shares(T, W);
-      pos0 = shares.start(w);
-      nshare = shares.start(w + 1) - pos0;
+      pos0 = shares.start(wave);
+      nshare = shares.start(wave + 1) - pos0;
     }
   }
   // the same for all lanes: the stream's loop and its addresses are scalar (32 requests at D = 64 43.6 -> 43.1 us)
@@ -332,15 +373,15 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   };
 
   // For the reduce pass.
-  const bool leaves_words = a.leaves == kManySegments || a.leaves == kFewSegments;
+  const bool leaves_words = !kWhole && (a.leaves == kManySegments || a.leaves == kFewSegments);
   if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
-  if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
+  if (!kWhole && (by_row || a.leaves == kRows) && blockIdx.x == 0) {
     for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
   }
   // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
   // its records do not wait for the launch descriptor to be read again.
   float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
-  if (last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
+  if (!kWhole && last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
     for (;;) {
       if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
       zero_empty_rows();
@@ -387,7 +428,26 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     return d;
   };
 
-  Window dA = describe(0);
+  // The blocks of a wavefront that has its part of one segment: all in one window, their table entries in the lanes' hands.
+  auto describe_whole = [&]() -> Window {
+    const bool live = lane < nshare;
+    const int b = pos0 + lane, upb_bits = 31 - __clz(a.upb), tb = b >> upb_bits;
+    const int id = __shfl(whole_entry, tb);   // by all lanes: the entries are in lanes that may have no block
+    const bool mapped = live && (unsigned)id < (unsigned)a.NB;
+    refused += __popcll(__ballot(live && !mapped));
+    Window d;
+    d.slab = mapped ? (((id * Hkv + (int)blockIdx.x) << upb_bits) + (b - (tb << upb_bits))) : 0;
+    const bool ends = 16 * (b + 1) >= whole_len;
+    const bool last = ends || ((b + 1) % bpp == 0) || (lane + 1 == nshare);
+    d.meta = !live ? 0
+                   : (mapped ? min(kBlockTokens, whole_len - kBlockTokens * b) : 0) | (last ? kMetaLast : 0) |
+                         (lane == 0 ? kMetaSegFirst : 0) | (ends ? kMetaSegEnd : 0) | (pos0 > 0 ? kMetaOpenLeft : 0);
+    d.seg = seg_next;
+    return d;
+  };
+  Window dA;
+  if constexpr (kWhole) dA = describe_whole();
+  else dA = describe(0);
   Window dB = {0, 0, 0};   // described after the first KV loads are on their way (below)
   int jbase = 0;           // stream index of window A's first block
 
@@ -483,7 +543,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     nstaged = 0;
   };
 
-  int seg = 0, seg_next = 0;   // the segment being streamed, and the one of the query group that was asked for last
   auto consume = [&](u32x4 (&kraw)[kKLoads], VReg (&vraw)[kVLoads], int meta) __attribute__((always_inline)) {
     // The MFMA operands.  bf16 pools: the registers as they are.  e4m3 pools: piece 4L + c of
     // K's row holds dims 16*(4L + c) .. +15 of token tau(n), which feed steps 2L and 2L + 1 (the
@@ -663,16 +722,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // loads, so that nothing has to wait for loads younger than the ones it needs: fetched when its
   // first block was already to be consumed, it cost the pipeline a drain per segment (512 requests of
   // 16..512 tokens: 116.5 -> 114.1 us; 8 requests at D = 256: 36.3 -> 35.7).
-  u32x4 qnext[kKSteps];
-  auto load_q = [&](int j) {   // of the segment that begins at stream index j
-    seg_next = __builtin_amdgcn_readlane(dA.seg, j - jbase);
-    const u32x4* qrow_p = (const u32x4*)(layer.q + (int64_t)(seg_next * G + min(n, G - 1)) * kD);
-#pragma unroll
-    for (int jj = 0; jj < kKSteps; ++jj)
-      // dims of step jj in this lane: 32*jj + 8*c .. +7, or, following the byte order of an
-      // e4m3 K load, 64*(jj/2) + 16*c + 8*(jj%2) .. +7
-      qnext[jj] = kFp8 ? qrow_p[8 * (jj >> 1) + 2 * c + (jj & 1)] : qrow_p[4 * jj + c];
-  };
   auto take_q = [&](int meta) {   // before the next group is asked for
     if (!(meta & kMetaSegFirst)) return;
     seg_open = false;
@@ -690,9 +739,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(v[e]));
   };
   auto ask_q = [&](VReg (&v)[kVLoads], int j, int meta) {   // v: of the block before
-    if (!(meta & kMetaSegFirst)) return;
+    if (kWhole || !(meta & kMetaSegFirst)) return;
     if (kTwoBlocks) arrived_v(v);
-    load_q(j);
+    load_q(__builtin_amdgcn_readlane(dA.seg, j - jbase));
   };
 
   u32x4 kbuf[2][kKLoads];   // two blocks in turn, so that no buffer is ever copied
@@ -700,8 +749,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   Block at = block_at(0);
   issue_k(kbuf[0], at, 0, kKLoads);
   if (!kLate) issue_v(vbuf[0], at);
-  load_q(0);
-  if (nshare > kWindow) dB = describe(kWindow);
+  if (!kWhole) load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+  if (!kWhole && nshare > kWindow) dB = describe(kWindow);
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it begin here and go on elsewhere?
@@ -726,7 +775,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       VReg (&v)[kVLoads] = vbuf[i], (&vnext)[kVLoads] = vbuf[i ^ 1];
       if (!kTwoBlocks) arrived_k(k);
       if (!kTwoBlocks && !kLate) arrived_v(v);
-      if (i == 1 && j + 2 == jbase + kWindow) {   // the loads leave window A: B becomes A
+      if (!kWhole && i == 1 && j + 2 == jbase + kWindow) {   // the loads leave window A: B becomes A
         dA = dB;
         jbase += kWindow;
       }
@@ -748,7 +797,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       if (kLate) issue_k(knext, next, kNextK, kKLoads);
       at = next;
     }
-    if (j + 2 == jbase) {   // the window after it is described now, 64 blocks before its first use
+    if (!kWhole && j + 2 == jbase) {   // the window after it is described now, 64 blocks before its first use
       if (jbase + kWindow < nshare) dB = describe(jbase + kWindow);
       else dB = Window{0, 0, 0};
     }
@@ -778,7 +827,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   }
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
-  zero_empty_rows();
+  if (!kWhole) zero_empty_rows();
   if (by_row) return;
   uint16_t* out = layer.out;
   const bool more = kChained && of + 1 < layer_count(layers);
@@ -794,7 +843,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     at = block_at(0);
     issue_k(kbuf[0], at, 0, kKLoads);
     if (!kLate) issue_v(vbuf[0], at);
-    load_q(0);
+    load_q(__builtin_amdgcn_readlane(dA.seg, 0));
     if (nshare > kWindow) dB = describe(kWindow);
     seg_open = false;
     ends_flags = left = right = 0;
@@ -805,7 +854,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
   // shared segment begins in leaves word of it.
   const AttnLaunch& b = reread(a);
-  if (lane == 0) {
+  if (!kWhole && lane == 0) {
     left_seg[wave] = left_end;
     int chain = 0;
     if ((ends & kEndsLeft) && (!(ends & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
@@ -814,14 +863,15 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (ends & kEndsThrough) atomicOr(&passes[turned], 1 << wave);
   }
   __syncthreads();
-  if (threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
+  if (!kWhole && threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
     *shared_segment(b, of, blockIdx.x) = word;
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
   // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
   // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to
   // four rounds instead of one took 1 us more (64 requests of 50..100 tokens on 40/8 heads 18.4 -> 16.6).
-  const int ending = chains[turned], through = passes[turned];
+  // Where the workgroup has one segment, there is one chain, through all wavefronts that have blocks of it.
+  const int ending = kWhole ? (W > 1 ? 1 << last_wave : 0) : chains[turned], through = kWhole ? (1 << last_wave) - 2 : passes[turned];
 #pragma unroll 1
   for (int i = threadIdx.x; i < __popc(ending) * q4; i += kThreads) {
     const int nth = i / q4, item = i - nth * q4;
@@ -848,8 +898,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       if (k == v) ml[1].x = kNegInf;
       fold(p, ml, x);
     }
-    if (from_right && !open_right) {
-      *(u32x2*)(out + (int64_t)left_seg[v] * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
+    if (kWhole || (from_right && !open_right)) {
+      *(u32x2*)(out + (int64_t)(kWhole ? seg_next : left_seg[v]) * (G * kD) + 4 * item) = finish_row4(p.x, inverse(p.l, b.out_scale));
     } else {
       float* rec = group_record(b, kD, of, blockIdx.x, from_right);
       store16(rec + 4 * item, __builtin_bit_cast(u32x4, p.x));

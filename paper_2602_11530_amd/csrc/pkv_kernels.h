@@ -170,6 +170,7 @@ struct AttnLayers {
   AttnLayer layer[kMaxLaunchLayers];
 };
 struct OneLayer {};
+struct WholeLayer : OneLayer {};   // a workgroup for each segment (kNoRecords)
 // One after the other in each workgroup.
 struct ChainedLayers : AttnLayers {};
 __device__ __forceinline__ int layer_index(const OneLayer&) { return 0; }
@@ -259,6 +260,7 @@ inline bool short_at_128(const AttnLaunch& a) {
 // The stream pass's kernels for one layer of those, and for layers one after the other.
 void launch_large_256(const AttnLaunch& a, size_t lds, hipStream_t stream);
 void launch_short_128(const AttnLaunch& a, size_t lds, hipStream_t stream);
+void launch_whole(const AttnLaunch& a, size_t lds, hipStream_t stream);
 void launch_chained_short_128(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 hipError_t launch_chained(const AttnLaunch& a, const AttnLayers& layers, size_t lds, hipStream_t stream);
 
