@@ -240,16 +240,16 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // record shares its room with finished rows that wait to be stored
   const int rec_floats = record_floats(a.G, kD);
   float* wave_lds = (float*)(smem + ((2 * (a.S + 1) + 3) & ~3));
-  __shared__ int chains[2], passes[2];    // bit per wavefront, see the workgroup's merge; the next layer uses the other ones
+  __shared__ int share_ends[kGroupWaves];   // how each wavefront's share ends
   __shared__ SharedSegment word;          // the workgroup's, for the reduce pass
   __shared__ int left_seg[kGroupWaves];   // the segment that the share's first block belongs to
-  __shared__ int any_long;
+  __shared__ int any_long;                // with more than 64 requests
   __shared__ int sum64[kMaxSeqs / 64];   // blocks of each 64 requests
 
   constexpr bool kChained = std::is_same_v<Layers, ChainedLayers>;   // a workgroup streams its range of one layer after the other
   int of = layer_index(layers);   // layer
   AttnLayer layer = layer_of(a, layers);
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, c = lane >> 4;
   const int G = a.G, S = a.S, Hkv = a.Hkv;
@@ -273,41 +273,46 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       qnext[jj] = kFp8 ? qrow_p[8 * (jj >> 1) + 2 * c + (jj & 1)] : qrow_p[4 * jj + c];
   };
   if constexpr (!kWhole) {
-    // Prefix sums over the requests, 64 to a wavefront at a time: first within each 64, then, when
-    // there are more, the sums of the 64s before them (512 requests in turns of one wavefront took 3.6 us
-    // to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
-    int longest = 0;
-    for (int base = 64 * wave; base < S; base += kThreads) {
+    // Prefix sums over the requests.  Up to 64: every wavefront for itself, all to the same place and the same values, so that none
+    // waits for another.  More: 64 to a wavefront at a time, first within each 64, then the sums of the 64s before them (512
+    // requests in turns of one wavefront took 3.6 us to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
+    int longest = 0, blocks = 0;
+    for (int base = S > 64 ? 64 * wave : 0; base < S; base += kThreads) {
       const int i = base + lane;
       const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
       const int nb = (L + kBlockTokens - 1) / kBlockTokens;
       longest = max(longest, nb);
       const int xb = wave_prefix(nb);
       if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
-      if (lane == 63) { sum64[base >> 6] = xb; if (S <= 64) cumB[S] = xb; }
+      if (lane == 63) { if (S <= 64) cumB[S] = xb; else sum64[base >> 6] = xb; }
+      blocks = xb;
     }
-    const bool some_long = __any(longest > a.short_blocks);
-    if (threadIdx.x == 0) { any_long = some_long; chains[0] = passes[0] = 0; }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
+    bool some_long = __any(longest > a.short_blocks);
+    blocks = __builtin_amdgcn_readlane(blocks, 63);
     if (S > 64) {
+      if (threadIdx.x == 0) any_long = 0;
+      __syncthreads();
       if (some_long && lane == 0) any_long = 1;
       // lane c: all requests before the c-th 64 (kMaxSeqs = 32 of them)
       const int mine = lane < (S + 63) >> 6 ? sum64[lane] : 0;
       int before = wave_prefix(mine);
       if (threadIdx.x == 63) cumB[S] = before;
+      blocks = __builtin_amdgcn_readlane(before, 63);
       before -= mine;
       for (int base = 64 * wave; base < S; base += kThreads) {
         const int add = __shfl(before, base >> 6);
         if (base > 0 && base + lane < S) cumB[base + lane] += add;
       }
       __syncthreads();
+      some_long = __builtin_amdgcn_readfirstlane(any_long);
     }
 
     // Equal shares: every participating wavefront gets at least one block, so that consecutive
     // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
     // short segments is cut along the segments instead, one to a workgroup (see short_segment).
-    T = Hkv * cumB[S];
-    whole = __builtin_amdgcn_readfirstlane(any_long) == 0 && S * Hkv <= (int)gridDim.x;
+    T = Hkv * blocks;
+    whole = !some_long && S * Hkv <= (int)gridDim.x;
     if (whole) {
       const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
       const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
@@ -390,36 +395,48 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   }
 
-  // Descriptors of stream indices jb .. jb+63 of this share.
-  int search_steps = 0;
-  while ((1 << search_steps) < S) ++search_steps;
   int refused = 0;   // table entries outside the pool met while describing this share
-  auto place = [&](int pos) -> Place {
-    int lo = 0, hi = S;   // largest s with Hkv * cumB[s] <= pos
-    for (int it = 0; it < search_steps; ++it) {
-      const int mid = (lo + hi) >> 1;
-      if (mid > lo && Hkv * cumB[mid] <= pos) lo = mid; else if (mid > lo) hi = mid;
-    }
-    const int nb = cumB[lo + 1] - cumB[lo];
-    const int o = pos - Hkv * cumB[lo];
-    const int kvh = o / nb;
-    return Place{lo, kvh, o - kvh * nb, nb};
+  // The request of a position that is the same for all lanes, the largest s with Hkv * cumB[s] <= pos: all in one look, or two
+  // with more than 64 of them.
+  auto request_of = [&](int pos) -> int {
+    int base = 0;
+    if (S > 64) base = 64 * __popcll(__ballot(64 * lane < S && Hkv * cumB[min(64 * lane, S)] <= pos)) - 64;
+    return base + __popcll(__ballot(base + lane < S && Hkv * cumB[min(base + lane, S)] <= pos)) - 1;
   };
+  auto place = [&](int pos, int s) -> Place {   // of request s
+    const int before = cumB[s], nb = cumB[s + 1] - before, o = pos - Hkv * before;
+    // o / nb, which is less than Hkv (at most kMaxHeads): the estimate is off by less than one
+    int kvh = (int)((float)o * __builtin_amdgcn_rcpf((float)nb)), b = o - kvh * nb;
+    if (b < 0) { --kvh; b += nb; }
+    if (b >= nb) { ++kvh; b -= nb; }
+    return Place{s, kvh, b, nb};
+  };
+  const int upb_bits = 31 - __clz(a.upb);
+  // Descriptors of stream indices jb .. jb+63 of this share.
   auto describe = [&](int jb) __attribute__((always_inline)) -> Window {
     const int j = jb + lane;
     const bool live = j < nshare;
-    const Place at = place(pos0 + max(min(j, nshare - 1), 0));
-    const int s = at.s, kvh = at.kvh, b = at.b, nb = at.nb;
+    const int pos = pos0 + max(min(j, nshare - 1), 0);
+    // the requests that the window reaches over, one as a rule, then each lane's among them
+    int s = request_of(pos0 + jb);
+    const int s_last = request_of(pos0 + max(min(jb + kWindow, nshare) - 1, 0));
+    for (int step = s_last > s ? 1 << (31 - __clz(s_last - s)) : 0; step > 0; step >>= 1) {
+      const int t = s + step;
+      if (t <= s_last && Hkv * cumB[min(t, s_last)] <= pos) s = t;
+    }
+    const Place at = place(pos, s);
+    const int kvh = at.kvh, b = at.b, nb = at.nb;
     int ntok = min(kBlockTokens, lens[s] - kBlockTokens * b);
     // unit b of the request lies in physical block b / upb, at unit b % upb of the KV head's rows
-    const int tb = b / a.upb;
+    const int tb = b >> upb_bits;
     const int id = live ? a.block_tables[(int64_t)s * a.MAXB + tb] : -1;
     const bool mapped = (unsigned)id < (unsigned)a.NB;   // ids outside the pool are never followed
     if (!mapped) ntok = 0;
     refused += __popcll(__ballot(live && !mapped));
     Window d;
-    d.slab = mapped ? (id * Hkv + kvh) * a.upb + (b - tb * a.upb) : 0;
-    const bool last = (b + 1 == nb) || ((b + 1) % bpp == 0) || (j + 1 == nshare);
+    d.slab = mapped ? ((id * Hkv + kvh) << upb_bits) + (b - (tb << upb_bits)) : 0;
+    bool last = (b + 1 == nb) || (j + 1 == nshare);
+    if (__any(nb > bpp)) last |= (unsigned)(b + 1) % (unsigned)bpp == 0;
     const bool seg_first = (b == 0) || (j == 0);
     d.meta = ntok | (last ? kMetaLast : 0) | (seg_first ? kMetaSegFirst : 0) |
              (b + 1 == nb ? kMetaSegEnd : 0) | (b > j ? kMetaOpenLeft : 0);
@@ -431,7 +448,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // The blocks of a wavefront that has its part of one segment: all in one window, their table entries in the lanes' hands.
   auto describe_whole = [&]() -> Window {
     const bool live = lane < nshare;
-    const int b = pos0 + lane, upb_bits = 31 - __clz(a.upb), tb = b >> upb_bits;
+    const int b = pos0 + lane, tb = b >> upb_bits;
     const int id = __shfl(whole_entry, tb);   // by all lanes: the entries are in lanes that may have no block
     const bool mapped = live && (unsigned)id < (unsigned)a.NB;
     refused += __popcll(__ballot(live && !mapped));
@@ -448,7 +465,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   Window dA;
   if constexpr (kWhole) dA = describe_whole();
   else dA = describe(0);
-  Window dB = {0, 0, 0};   // described after the first KV loads are on their way (below)
+  Window dB = {0, 0, 0};   // described when the first blocks have been consumed (below)
   int jbase = 0;           // stream index of window A's first block
 
   const int64_t slab_bytes = (int64_t)kBlockTokens * kD * kElemBytes;  // one (block, KV head) slab
@@ -750,7 +767,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   issue_k(kbuf[0], at, 0, kKLoads);
   if (!kLate) issue_v(vbuf[0], at);
   if (!kWhole) load_q(__builtin_amdgcn_readlane(dA.seg, 0));
-  if (!kWhole && nshare > kWindow) dB = describe(kWindow);
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it begin here and go on elsewhere?
@@ -758,7 +774,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (!whole && first_wave + kGroupWaves < W) {
       const ShareMap shares(T, W);
       const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
-      const Place at = place(next - 1);
+      const Place at = place(next - 1, request_of(next - 1));
       const int seg_pos = next - 1 - at.b;
       if (seg_pos >= begin && seg_pos + at.nb > next) {
         row = (at.s * Hkv + at.kvh) * G;
@@ -767,7 +783,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
     if (lane == 0) word = SharedSegment{row, count};
   }
-  for (int turned = 0;; turned ^= 1) {   // layers
+  for (;;) {   // layers
   for (int j = 0; j < nshare; j += 2) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -797,7 +813,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       if (kLate) issue_k(knext, next, kNextK, kKLoads);
       at = next;
     }
-    if (!kWhole && j + 2 == jbase) {   // the window after it is described now, 64 blocks before its first use
+    if (!kWhole && j == jbase) {   // window A has just been begun: the one after it is described now
       if (jbase + kWindow < nshare) dB = describe(jbase + kWindow);
       else dB = Window{0, 0, 0};
     }
@@ -844,7 +860,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     issue_k(kbuf[0], at, 0, kKLoads);
     if (!kLate) issue_v(vbuf[0], at);
     load_q(__builtin_amdgcn_readlane(dA.seg, 0));
-    if (nshare > kWindow) dB = describe(kWindow);
+    dB = Window{0, 0, 0};
     seg_open = false;
     ends_flags = left = right = 0;
   }
@@ -856,22 +872,27 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   const AttnLaunch& b = reread(a);
   if (!kWhole && lane == 0) {
     left_seg[wave] = left_end;
-    int chain = 0;
-    if ((ends & kEndsLeft) && (!(ends & kEndsThrough) || wave == last_wave)) chain = 1 << wave;
-    if ((ends & kEndsRight) && wave == last_wave) chain |= 1 << kGroupWaves;
-    if (chain) atomicOr(&chains[turned], chain);
-    if (ends & kEndsThrough) atomicOr(&passes[turned], 1 << wave);
+    share_ends[wave] = ends;
   }
   __syncthreads();
   if (!kWhole && threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
     *shared_segment(b, of, blockIdx.x) = word;
   const int q4 = G * kD / 4;   // 16-byte pieces of a record's rows
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
-  // workgroup's last (bit v of `chains`), and one for the last wavefront's right record (bit
+  // workgroup's last (bit v of `ending`), and one for the last wavefront's right record (bit
   // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to
   // four rounds instead of one took 1 us more (64 requests of 50..100 tokens on 40/8 heads 18.4 -> 16.6).
   // Where the workgroup has one segment, there is one chain, through all wavefronts that have blocks of it.
-  const int ending = kWhole ? (W > 1 ? 1 << last_wave : 0) : chains[turned], through = kWhole ? (1 << last_wave) - 2 : passes[turned];
+  int ending, through;
+  if (kWhole) {
+    ending = W > 1 ? 1 << last_wave : 0;
+    through = (1 << last_wave) - 2;
+  } else {
+    const int how = lane < kGroupWaves ? share_ends[lane] : 0;
+    through = (int)__ballot(how & kEndsThrough);
+    ending = (int)__ballot((how & kEndsLeft) && (!(how & kEndsThrough) || lane == last_wave)) |
+             (__ballot((how & kEndsRight) && lane == last_wave) ? 1 << kGroupWaves : 0);
+  }
 #pragma unroll 1
   for (int i = threadIdx.x; i < __popc(ending) * q4; i += kThreads) {
     const int nth = i / q4, item = i - nth * q4;
@@ -908,7 +929,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   }
   if (!more) return;
   ++of;
-  if (threadIdx.x == 0) chains[turned ^ 1] = passes[turned ^ 1] = 0;
   __syncthreads();   // the records in LDS have been read
   }
 }
