@@ -259,7 +259,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   uint16_t* staged = (uint16_t*)rec_right;
 
   int T = 0, W = 0, first_wave = 0, last_wave = -1, pos0 = 0, nshare = 0;
+  int own_len = 0, own_start = 0;   // up to 64 requests: lane s's context length and first position
   bool whole = kWhole, by_row = false;
+  const int groups = a.waves / kGroupWaves;   // of the layer
   int w = blockIdx.x * kGroupWaves + wave;
   u32x4 qnext[kKSteps];
   int seg = 0, seg_next = 0;   // the segment being streamed, and the one of the query group that was asked for last
@@ -277,6 +279,11 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     // waits for another.  More: 64 to a wavefront at a time, first within each 64, then the sums of the 64s before them (512
     // requests in turns of one wavefront took 3.6 us to get here; with the empty window below left out, the call 114.1 -> 111.7 us).
     int longest = 0, blocks = 0;
+    // What else the start needs of the launch descriptor is asked for with the lengths; where it is used it would be waited for,
+    // one word after the other.  With no request's data read back from LDS up to 64 requests: one of 8191 tokens 16.7 -> 16.5 us, 64 of
+    // 64 on 40/8 heads 11.6 -> 11.45, 64 of 1024..8192 on 8-bit pools 101.7 -> 101.0; 696 shapes of up to 4 blocks a share 0.986.
+    asm volatile("" : : "s"(a.waves), "s"(a.leaves), "s"(a.short_blocks), "s"(a.max_ctx), "s"(a.context_lens), "s"(a.block_tables), "s"(a.MAXB),
+                 "s"(a.NB), "s"(a.upb), "s"(a.P), "s"(layer.q), "s"(layer.k_pool), "s"(layer.v_pool), "s"(a.wave_lds_floats));
     for (int base = S > 64 ? 64 * wave : 0; base < S; base += kThreads) {
       const int i = base + lane;
       const int L = (i < S) ? min(max(a.context_lens[i], 0), a.max_ctx) : 0;
@@ -286,6 +293,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       if (i < S) { lens[i] = L; cumB[i] = xb - nb; }
       if (lane == 63) { if (S <= 64) cumB[S] = xb; else sum64[base >> 6] = xb; }
       blocks = xb;
+      own_len = L;
+      own_start = i < S ? Hkv * (xb - nb) : INT32_MAX;
     }
     __builtin_amdgcn_wave_barrier();
     bool some_long = __any(longest > a.short_blocks);
@@ -312,8 +321,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     // runs of a segment always belong to the same or to adjacent wavefronts.  A batch of a few
     // short segments is cut along the segments instead, one to a workgroup (see short_segment).
     T = Hkv * blocks;
-    whole = !some_long && S * Hkv <= (int)gridDim.x;
-    if (whole) {
+    whole = !some_long && S * Hkv <= groups;
+    if (__builtin_expect(whole, 0)) {
       const int s = (int)blockIdx.x / Hkv, kvh = (int)blockIdx.x - s * Hkv;
       const int nb = s < S ? cumB[s + 1] - cumB[s] : 0;
       W = min(kGroupWaves, nb);
@@ -329,11 +338,11 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       first_wave = blockIdx.x * kGroupWaves;
       last_wave = min(kGroupWaves, W - first_wave) - 1;
       by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
-      if (by_row && T < a.waves) {
+      if (__builtin_expect(by_row && T < a.waves, 0)) {
         // A block per wavefront and not enough of them to fill the compute units: one after the other round
         // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
         // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
-        w = wave * gridDim.x + blockIdx.x;
+        w = wave * groups + blockIdx.x;
         last_wave = w < W ? 0 : -1;
       }
       if (w < W) {
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   nshare = __builtin_amdgcn_readfirstlane(nshare);
   // An empty request owes zero rows.
   auto zero_empty_rows = [&]() {
-    for (int s = w; s < S; s += (int)gridDim.x * kGroupWaves) {
+    for (int s = w; s < S; s += groups * kGroupWaves) {
       if (cumB[s + 1] != cumB[s]) continue;
       uint32_t* dst = (uint32_t*)(layer.out + (int64_t)s * a.Hq * kD);
       for (int f = lane; f < a.Hq * kD / 2; f += 64) dst[f] = 0;
@@ -379,14 +388,17 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
   // For the reduce pass.
   const bool leaves_words = !kWhole && (a.leaves == kManySegments || a.leaves == kFewSegments);
-  if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
-  if (!kWhole && (by_row || a.leaves == kRows) && blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
-  }
+  auto tell_of_rows = [&]() {
+    if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
+    if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
+      for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
+    }
+  };
   // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
   // its records do not wait for the launch descriptor to be read again.
   float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
-  if (!kWhole && last_wave < 0) {   // nothing for this workgroup, or for this wavefront of it
+  if (!kWhole && __builtin_expect(last_wave < 0, 0)) {   // nothing for this workgroup, or for this wavefront of it
+    tell_of_rows();
     for (;;) {
       if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
       zero_empty_rows();
@@ -399,17 +411,32 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // The request of a position that is the same for all lanes, the largest s with Hkv * cumB[s] <= pos: all in one look, or two
   // with more than 64 of them.
   auto request_of = [&](int pos) -> int {
-    int base = 0;
-    if (S > 64) base = 64 * __popcll(__ballot(64 * lane < S && Hkv * cumB[min(64 * lane, S)] <= pos)) - 64;
-    return base + __popcll(__ballot(base + lane < S && Hkv * cumB[min(base + lane, S)] <= pos)) - 1;
+    if (S <= 64) return __popcll(__ballot(own_start <= pos)) - 1;
+    const int start64 = Hkv * cumB[min(64 * lane, S)];
+    const int base = 64 * __popcll(__ballot((64 * lane < S) & (start64 <= pos))) - 64;
+    const int start = Hkv * cumB[min(base + lane, S)];
+    return base + __popcll(__ballot((base + lane < S) & (start <= pos))) - 1;
   };
-  auto place = [&](int pos, int s) -> Place {   // of request s
-    const int before = cumB[s], nb = cumB[s + 1] - before, o = pos - Hkv * before;
+  struct Request {
+    int start, nb, len;   // first position, blocks, tokens
+  };
+  auto request = [&](int s) -> Request {   // each lane's
+    return Request{Hkv * cumB[s], cumB[s + 1] - cumB[s], lens[s]};
+  };
+  auto the_request = [&](int s) -> Request {   // the same for all lanes
+    if (S > 64) return request(s);
+    const int len = __builtin_amdgcn_readlane(own_len, s);
+    return Request{__builtin_amdgcn_readlane(own_start, s), (len + kBlockTokens - 1) / kBlockTokens, len};
+  };
+  auto place = [&](int pos, int s, const Request& r) -> Place {
     // o / nb, which is less than Hkv (at most kMaxHeads): the estimate is off by less than one
-    int kvh = (int)((float)o * __builtin_amdgcn_rcpf((float)nb)), b = o - kvh * nb;
-    if (b < 0) { --kvh; b += nb; }
-    if (b >= nb) { ++kvh; b -= nb; }
-    return Place{s, kvh, b, nb};
+    const int o = pos - r.start;
+    int kvh = (int)((float)o * __builtin_amdgcn_rcpf((float)r.nb)), b = o - kvh * r.nb;
+    const bool less = b < 0;
+    kvh -= less;
+    b += less ? r.nb : 0;
+    const bool more = b >= r.nb;
+    return Place{s, kvh + more, more ? b - r.nb : b, r.nb};
   };
   const int upb_bits = 31 - __clz(a.upb);
   // Descriptors of stream indices jb .. jb+63 of this share.
@@ -420,13 +447,19 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     // the requests that the window reaches over, one as a rule, then each lane's among them
     int s = request_of(pos0 + jb);
     const int s_last = request_of(pos0 + max(min(jb + kWindow, nshare) - 1, 0));
-    for (int step = s_last > s ? 1 << (31 - __clz(s_last - s)) : 0; step > 0; step >>= 1) {
-      const int t = s + step;
-      if (t <= s_last && Hkv * cumB[min(t, s_last)] <= pos) s = t;
+    Request r;
+    if (s == s_last) {
+      r = the_request(s);
+    } else {
+      for (int step = 1 << (31 - __clz(s_last - s)); step > 0; step >>= 1) {
+        const int t = min(s + step, s_last);
+        if (Hkv * cumB[t] <= pos) s = t;
+      }
+      r = request(s);
     }
-    const Place at = place(pos, s);
+    const Place at = place(pos, s, r);
     const int kvh = at.kvh, b = at.b, nb = at.nb;
-    int ntok = min(kBlockTokens, lens[s] - kBlockTokens * b);
+    int ntok = min(kBlockTokens, r.len - kBlockTokens * b);
     // unit b of the request lies in physical block b / upb, at unit b % upb of the KV head's rows
     const int tb = b >> upb_bits;
     const int id = live ? a.block_tables[(int64_t)s * a.MAXB + tb] : -1;
@@ -767,6 +800,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   issue_k(kbuf[0], at, 0, kKLoads);
   if (!kLate) issue_v(vbuf[0], at);
   if (!kWhole) load_q(__builtin_amdgcn_readlane(dA.seg, 0));
+  if (!kWhole) tell_of_rows();
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it begin here and go on elsewhere?
@@ -774,7 +808,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     if (!whole && first_wave + kGroupWaves < W) {
       const ShareMap shares(T, W);
       const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
-      const Place at = place(next - 1, request_of(next - 1));
+      const int s = request_of(next - 1);
+      const Place at = place(next - 1, s, the_request(s));
       const int seg_pos = next - 1 - at.b;
       if (seg_pos >= begin && seg_pos + at.nb > next) {
         row = (at.s * Hkv + at.kvh) * G;

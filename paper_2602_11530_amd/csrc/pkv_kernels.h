@@ -55,13 +55,17 @@ constexpr int kAhead = 2;
 //
 // Shares begin at floor(w * T / W), so that the longer ones are spread evenly over the compute
 // units: with the longer ones first, the units that hold them end last (1.5 % on 64 requests of
-// 1024..8192 tokens, whose shares have 70 and 71 blocks).  In 32 bits, and with shifts where W is
-// a power of two, which a full launch's is: both functions sit on short critical chains.
+// 1024..8192 tokens, whose shares have 70 and 71 blocks).  In 32 bits and without divisions, because both functions
+// sit on short critical chains: W is a power of two, as a full launch's and a workgroup's are, or T.
 struct ShareMap {
-  uint32_t T, W, len, more;   // more of the W shares have len + 1 positions
-  __host__ __device__ ShareMap(uint32_t T_, uint32_t W_) : T(T_), W(W_), len(div(T_)), more(T_ - len * W_) {}
-  __host__ __device__ uint32_t div(uint32_t x) const { return (W & (W - 1)) == 0 ? x >> __builtin_ctz(W) : x / W; }
-  __host__ __device__ uint32_t start(uint32_t w) const { return w * len + div(w * more); }   // W <= 2^16
+  uint32_t T, W, shift, len, more;   // more of the W shares have len + 1 positions
+  __host__ __device__ ShareMap(uint32_t T_, uint32_t W_) : T(T_), W(W_) {
+    const bool even = (W & (W - 1)) == 0;
+    shift = even ? __builtin_ctz(W) : 0;
+    len = even ? T >> shift : 1;
+    more = T - len * W;
+  }
+  __host__ __device__ uint32_t start(uint32_t w) const { return w * len + ((w * more) >> shift); }   // W <= 2^16
   // The wavefront whose share holds position pos: an estimate that is off by less than one, put right.
   __host__ __device__ uint32_t owner(uint32_t pos) const {
     uint32_t w = (uint32_t)((float)pos * ((float)W / (float)T));
