@@ -5,26 +5,21 @@
 // records.  Two layouts (pkv_kernels.h):
 //
 // Records of workgroups: at most one shared segment begins in a workgroup of the stream pass, whose
-// wavefronts have met in LDS, so that a segment has a handful of records: one workgroup
-// here for each there (256), which reads one word and is done when nothing begins there.
+// wavefronts have met in LDS: one workgroup here for each there (256), which reads one word and is done when
+// no segment goes on behind that one's range.  A segment of more than a few records has the workgroups of its middle, too.
 //
-// Records of wavefronts (by rows): up to hundreds of a segment, as they come: a workgroup
-// for each row fetches the statistics side by side and then streams the partial rows
-// sixteen at a time.
+// Records of wavefronts (by rows), as they come: a workgroup for each row fetches the statistics side by side and
+// then streams the partial rows sixteen at a time.
 #include "attn_partial.h"
 #include "pkv_kernels.h"
 
 namespace pkv {
 namespace {
 
-constexpr int kBatch = 8;      // records in flight per thread
+constexpr int kBatch = 4;      // records in flight per thread
 constexpr int kRowBatch = 16;  // partial rows in flight per wavefront, by rows
 
-// kPer = D / 64 consecutive floats of a row per lane
-template <int kPer> struct Chunk { typedef float T __attribute__((ext_vector_type(kPer))); };
-template <> struct Chunk<1> { typedef float T; };
-template <int kPer> __device__ __forceinline__ float chunk_get(const typename Chunk<kPer>::T& v, int i) { return v[i]; }
-template <> __device__ __forceinline__ float chunk_get<1>(const float& v, int) { return v; }
+constexpr int kRow = 64;       // floats of a row of a batch that goes by rows (what_is_left): one per lane
 
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
@@ -63,21 +58,17 @@ __device__ __forceinline__ bool locate_records(const AttnLaunch& a, int row, Row
 
 // One wavefront folds `count` records of a row (records begin, begin + stride, ...
 // counted from the row's first): on return M is their largest reference maximum,
-// acc this lane's kPer floats of the sum of their rows weighted by 2^(m - M), and
+// acc this lane's float of the sum of their rows weighted by 2^(m - M), and
 // lsum the wave-wide sum of their partial sums with the same weights.  count = 0
 // leaves (M, lsum, acc) = (-inf, 0, 0).
-template <int kD>
 __device__ __forceinline__ void fold_records(const AttnLaunch& a, const RowRecords& r, int begin,
-                                             int stride, int count, int lane, float& M, float& lsum,
-                                             float (&acc)[kD / 64]) {
-  constexpr int kPer = kD / 64;
-  typedef typename Chunk<kPer>::T Vec;
-  const int rec_floats = record_floats(a.G, kD);
+                                             int stride, int count, int lane, float& M, float& lsum, float& acc) {
+  const int rec_floats = record_floats(a.G, kRow);
   auto record = [&](int i) -> const float* {
     return a.ws_rec + (int64_t)(r.first + begin + i * stride) * rec_floats;
   };
   auto stats = [&](int i) -> float2 {   // (max, sum) of record i for this head
-    return *(const float2*)(record(i) + a.G * kD + 2 * r.g);
+    return *(const float2*)(record(i) + a.G * kRow + 2 * r.g);
   };
   // the statistics of the first 64 records stay in registers for the second pass
   const float2 ml0 = (lane < count) ? stats(lane) : float2{kNegInf, 0.f};
@@ -88,9 +79,7 @@ __device__ __forceinline__ void fold_records(const AttnLaunch& a, const RowRecor
   }
   M = wave_max(M);
 
-  lsum = 0.f;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) acc[i] = 0.f;
+  lsum = acc = 0.f;
   for (int i0 = 0; i0 < count; i0 += 64) {
     const int i = i0 + lane;
     float w = 0.f;
@@ -102,164 +91,193 @@ __device__ __forceinline__ void fold_records(const AttnLaunch& a, const RowRecor
     }
     const int cnt = min(64, count - i0);
     for (int j0 = 0; j0 < cnt; j0 += kRowBatch) {
-      Vec v[kRowBatch];
-      float wj[kRowBatch];
+      float v[kRowBatch], wj[kRowBatch];
 #pragma unroll
       for (int u = 0; u < kRowBatch; ++u) {
         const int j = min(j0 + u, cnt - 1);   // clamped rows get weight 0
         wj[u] = (j0 + u < cnt) ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j)) : 0.f;
-        v[u] = *((const Vec*)(record(i0 + j) + r.g * kD) + lane);
+        v[u] = record(i0 + j)[r.g * kRow + lane];
       }
 #pragma unroll
-      for (int u = 0; u < kRowBatch; ++u) {
-        // a weight of exactly zero must also silence whatever the row holds
-#pragma unroll
-        for (int i = 0; i < kPer; ++i)
-          acc[i] = (wj[u] != 0.f) ? __builtin_fmaf(wj[u], chunk_get<kPer>(v[u], i), acc[i]) : acc[i];
-      }
+      for (int u = 0; u < kRowBatch; ++u)   // a weight of exactly zero must also silence whatever the row holds
+        acc = (wj[u] != 0.f) ? __builtin_fmaf(wj[u], v[u], acc) : acc;
     }
   }
   lsum = wave_sum(lsum);
 }
 
-// Normalise, scale, round once to bf16 and store this lane's kPer elements of the row.
-template <int kPer>
-__device__ __forceinline__ void store_row(uint16_t* dst, const float (&acc)[kPer], float lsum, float out_scale) {
-  const float inv = lsum > 0.f ? out_scale / lsum : 0.f;
-  uint16_t r[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) r[i] = (uint16_t)pack_bf16(acc[i] * inv, 0.f);
-  if (kPer == 1) dst[0] = r[0];
-  else if (kPer == 2) *(uint32_t*)dst = r[0] | ((uint32_t)r[1] << 16);
-  else *(uint2*)dst = make_uint2(r[0] | ((uint32_t)r[1] << 16), r[2] | ((uint32_t)r[3] << 16));
-}
-
+constexpr int kGroupThreads = 512;
 // A row of a batch that goes by rows.  Wavefront i of the workgroup folds records i, i + n, i + 2n, ...
-// (n = wavefronts in the workgroup), the partial results meet in LDS and wavefront 0 folds those.
-template <int kD, int kThreads>
+// (n = wavefronts in the workgroup), the partial results meet in LDS and wavefront 0 folds those, normalises, scales and rounds once
+// to bf16.
 __device__ __forceinline__ void reduce_row(const AttnLaunch& a, int row) {
-  constexpr int kPer = kD / 64, kWidth = kThreads / 64;
+  constexpr int kWidth = kGroupThreads / 64;
   __shared__ float part_stats[kWidth][2];
-  __shared__ float part_acc[kWidth][kD];
+  __shared__ float part_acc[kWidth][kRow];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   RowRecords r;
   if (!locate_records(a, row, r)) return;   // the same for every wavefront of the workgroup
-  float M, lsum, acc[kPer];
+  float M, lsum, acc;
   const int count = r.np > wave ? (r.np - wave + kWidth - 1) / kWidth : 0;
-  fold_records<kD>(a, r, wave, kWidth, count, lane, M, lsum, acc);
+  fold_records(a, r, wave, kWidth, count, lane, M, lsum, acc);
   if (lane == 0) { part_stats[wave][0] = M; part_stats[wave][1] = lsum; }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) part_acc[wave][kPer * lane + i] = acc[i];
+  part_acc[wave][lane] = acc;
   __syncthreads();
   if (wave == 0) {
     float Mall = kNegInf;
     for (int w = 0; w < kWidth; ++w) Mall = fmaxf(Mall, part_stats[w][0]);
-    float lall = 0.f, total[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) total[i] = 0.f;
+    float lall = 0.f, total = 0.f;
     for (int w = 0; w < kWidth; ++w) {
       const float m = part_stats[w][0];
       if (m == kNegInf) continue;   // nothing valid behind this partial result: weight 0
       const float f = __builtin_amdgcn_exp2f(m - Mall);
       lall = __builtin_fmaf(f, part_stats[w][1], lall);
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) total[i] = __builtin_fmaf(f, part_acc[w][kPer * lane + i], total[i]);
+      total = __builtin_fmaf(f, part_acc[w][lane], total);
     }
-    store_row<kPer>(a.layer.out + (int64_t)row * kD + kPer * lane, total, lall, a.out_scale);
+    a.layer.out[(int64_t)row * kRow + lane] = (uint16_t)pack_bf16(total * inverse(lall, a.out_scale), 0.f);
   }
   __syncthreads();   // the next row uses the same LDS
 }
-template <int kD, int kThreads>
 __device__ __forceinline__ void reduce_rows(const AttnLaunch& a) {
-  for (int row = blockIdx.x; row < a.S * a.Hq; row += gridDim.x) reduce_row<kD, kThreads>(a, row);
+  for (int row = blockIdx.x; row < a.S * a.Hq; row += gridDim.x) reduce_row(a, row);
 }
 
-// The segment that begins in a workgroup of the stream pass and goes on in others.  A thread owns 16 bytes
-// of the rows and every sets-th record; the sets meet in LDS.
-constexpr int kGroupThreads = 512;
+// A segment that workgroups of the stream pass share.  16 lanes have a chunk of 64 floats of its rows, so that what a thread does
+// follows from shifts, and offsets are 32-bit.  With 16 bytes to each thread in order, divisions, 64-bit products and eight loads unrolled,
+// 0.85 us passed between the word and the last load going out (time stamps), as long as the loads and the folding take together;
+// 33 records took two turns.  Append and attention, before / this way: one request of 8191 tokens 16.2 / 15.5 us, 8 at D = 256
+// 32.6 / 32.1, 512 of 16..512 106.1 / 104.0, 32 at D = 64 43.2 / 41.9, 64 of 1024..8192 194.3 / 192.7, on 8-bit pools 104.3 / 102.9,
+// six layers of 24 754 / 747.
+//   Up to kBatch records: a thread loads all of them at once and is done.
+//   More: the workgroups in the middle of the segment, in which nothing begins, take some of the chunks each, and in a workgroup
+//   sets of lanes take every sets-th record and meet in LDS, four to one at a time.
+constexpr int kSubs = kGroupThreads / 16;   // G * D / 64 is kSubs at most
+template <int kD>
+struct SegmentRecords {
+  const char* base;    // the segment's first record
+  uint32_t rec_bytes;
+  uint32_t at, stats;  // of this lane's 16 bytes, and of its head's statistics, within a record
+  // records i, i + step, ... of `count`: those past the end are the last one with nothing valid
+  __device__ __forceinline__ void fold_batch(Partial& p, int i, int step, int count) const {
+    f32x4 x[kBatch];
+    f32x2 ml[kBatch];
+#pragma unroll
+    for (int z = 0; z < kBatch; ++z) {
+      const int j = min(i + z * step, count - 1);
+      // the one that begins the segment is its workgroup's second record, the others are first ones
+      const uint32_t off = (uint32_t)(2 * j - (j > 0)) * rec_bytes;
+      x[z] = *(const f32x4*)(base + (off + at));
+      ml[z] = *(const f32x2*)(base + (off + stats));
+    }
+#pragma unroll
+    for (int z = 0; z < kBatch; ++z) {
+      if (i + z * step >= count) ml[z].x = kNegInf;
+    }
+    fold(p, ml, x);
+  }
+};
 template <int kD, typename Layers>
 __device__ __forceinline__ void reduce_segment(const AttnLaunch& a, const Layers& layers, const SharedSegment& seg, int group) {
+  constexpr int kHeadChunks = kD / 64;
+  const int sub = threadIdx.x >> 4, lane16 = threadIdx.x & 15;
+  const int chunks = a.G * kHeadChunks, count = seg.records(), slice = seg.slice();
+  uint16_t* out = layer_of(a, layers).out + (int64_t)seg.row * kD;
+  SegmentRecords<kD> r;
+  r.base = (const char*)group_record(a, kD, layer_index(layers), group - slice, true);
+  r.rec_bytes = record_floats(a.G, kD) * (uint32_t)sizeof(float);
+  auto place = [&](int chunk) {
+    r.at = 256 * chunk + 16 * lane16;
+    r.stats = 4 * a.G * kD + 8 * (chunk / kHeadChunks);
+  };
+  auto finish = [&](const Partial& p, int chunk) {
+    *(u32x2*)(out + 64 * chunk + 4 * lane16) = finish_row4(p.x, inverse(p.l, a.out_scale));
+  };
+  if (count <= kBatch) {
+    if (slice != 0 || sub >= chunks) return;
+    place(sub);
+    Partial p = kNothing;
+    r.fold_batch(p, 0, 1, count);
+    finish(p, sub);
+    return;
+  }
   __shared__ f32x4 rows[kGroupThreads];
   __shared__ f32x2 stats[kGroupThreads];
-  const int items = a.G * (kD / 4);
-  const int sets = min(max(kGroupThreads / items, 1), seg.count);
-  uint16_t* out = layer_of(a, layers).out + (int64_t)seg.row * kD;
-  for (int t = threadIdx.x; t < max(items, kGroupThreads); t += kGroupThreads) {
-    const int set = t / items, item = t - set * items, head = item / (kD / 4);
-    Partial p = kNothing;
-    for (int i0 = set; set < sets && i0 < seg.count; i0 += kBatch * sets) {
-      f32x4 x[kBatch];
-      f32x2 ml[kBatch];
+  // small quotients by way of fp32: (x + 1/2) / n is at least 1 / (2n) away from a whole number
+  auto quotient = [](int x, int n) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)n)); };
+  const int helpers = min(count - 1, chunks);
+  const int mine = quotient(chunks + helpers - 1, helpers);   // chunks of a workgroup
+  if (slice * mine >= chunks) return;
+  int sets = min(quotient(kSubs, mine), count);
+  const int set = quotient(sub, mine), chunk = slice * mine + (sub - set * mine);
+  const bool works = set < sets && chunk < chunks;
+  Partial p = kNothing;
+  if (works) {
+    place(chunk);
+    for (int i = set; i < count; i += kBatch * sets) r.fold_batch(p, i, sets, count);
+  }
+  while (sets > 1) {
+    rows[threadIdx.x] = p.x;
+    stats[threadIdx.x] = f32x2{p.m, p.l};
+    __syncthreads();
+    const int left = (sets + 3) >> 2;
+    if (set < left) {
+      f32x4 x[3];
+      f32x2 ml[3];
 #pragma unroll
-      for (int z = 0; z < kBatch; ++z) {
-        const int i = min(i0 + z * sets, seg.count - 1);
-        const float* rec = group_record(a, kD, layer_index(layers), group + i, i == 0);
-        x[z] = *(const f32x4*)(rec + 4 * item);
-        ml[z] = *(const f32x2*)(rec + a.G * kD + 2 * head);
-        if (i0 + z * sets >= seg.count) ml[z].x = kNegInf;
+      for (int z = 0; z < 3; ++z) {
+        const bool there = set + (z + 1) * left < sets;
+        const int t = threadIdx.x + (there ? (z + 1) * left * mine * 16 : 0);
+        x[z] = rows[t];
+        ml[z] = stats[t];
+        if (!there) ml[z].x = kNegInf;
       }
       fold(p, ml, x);
     }
-    if (sets > 1) {   // then every thread is in its only turn of this loop
-      rows[t] = p.x;
-      stats[t] = f32x2{p.m, p.l};
-      __syncthreads();
-      if (set != 0) return;
-      for (int z = 1; z < sets; ++z) {
-        const f32x2 ml[1] = {stats[t + z * items]};
-        const f32x4 x[1] = {rows[t + z * items]};
-        fold(p, ml, x);
-      }
-    }
-    if (set == 0) *(u32x2*)(out + 4 * item) = finish_row4(p.x, inverse(p.l, a.out_scale));
+    sets = left;
+    __syncthreads();
   }
+  if (works && set == 0) finish(p, chunk);
 }
 
+// The word of this workgroup.  What follows it needs of the launch descriptor is asked for before it: the descriptor is several cache
+// lines, each a round trip of its own.
+template <typename Layers>
+__device__ __forceinline__ SharedSegment read_word(const AttnLaunch& a, const Layers& layers) {
+  asm volatile("" : : "s"(a.ws_words), "s"(a.ws_rec), "s"(a.G), "s"(a.out_scale), "s"(layer_of(a, layers).out));
+  return *shared_segment(a, layer_index(layers), blockIdx.x);
+}
 // Many segments.
 template <int kD, typename Layers>
 __global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
-  const SharedSegment seg = *shared_segment(a, layer_index(layers), blockIdx.x);
-  if (seg.count > 0) reduce_segment<kD>(a, layers, seg, blockIdx.x);
+  const SharedSegment seg = read_word(a, layers);
+  if (seg.told > 0) reduce_segment<kD>(a, layers, seg, blockIdx.x);
 }
-// Few segments: whichever of the two the stream pass has chosen.  Registers as for the two wavefronts per
-// SIMD that there are: left to itself the compiler has fewer loads in flight (8 requests of 6000..12000
-// tokens on 8/1 heads 22.5 -> 21.7 us).
-template <int kD>
-__global__ __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_reduce_few_kernel(AttnLaunch a) {
-  const SharedSegment seg = *shared_segment(a, 0, blockIdx.x);
-  if (seg.count == kByRows) reduce_rows<kD, kGroupThreads>(a);
-  else if (seg.count > 0) reduce_segment<kD>(a, OneLayer{}, seg, blockIdx.x);
+// Few segments: whichever of the two the stream pass has chosen.
+__global__ __launch_bounds__(kGroupThreads) void attn_reduce_few_kernel(AttnLaunch a) {
+  const SharedSegment seg = read_word(a, OneLayer{});
+  if (seg.told == kByRows) reduce_rows(a);
+  else if (seg.told > 0) reduce_segment<kRow>(a, OneLayer{}, seg, blockIdx.x);
 }
-template <int kD, int kThreads>
-__global__ __launch_bounds__(kThreads) void attn_reduce_rows_kernel(AttnLaunch a) {
-  reduce_rows<kD, kThreads>(a);
+__global__ __launch_bounds__(kGroupThreads) void attn_reduce_rows_kernel(AttnLaunch a) {
+  reduce_rows(a);
 }
 
 }  // namespace
 
 template <int kD>
-static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
-  const dim3 groups(a.waves / group_waves(kD), layers ? layers->count : 1), block(kGroupThreads);
-  if (a.leaves == kManySegments) {
-    if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), groups, block, 0, stream, a, *layers);
-    else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), groups, block, 0, stream, a, OneLayer{});
-  } else if (a.leaves == kFewSegments) {
-    hipLaunchKernelGGL(attn_reduce_few_kernel<kD>, groups, block, 0, stream, a);
-  } else if (a.waves / (a.S * a.Hkv) >= 128) {
-    // hundreds of records for a row: 16 wavefronts for it instead of 8 (one request of 6000..12000 tokens on
-    // 8/1 heads 21.0 -> 19.2 us; 16 of 750..1500, 65 records, lose 0.9 by it)
-    hipLaunchKernelGGL((attn_reduce_rows_kernel<kD, 1024>), dim3(a.S * a.Hq), dim3(1024), 0, stream, a);
-  } else {
-    hipLaunchKernelGGL((attn_reduce_rows_kernel<kD, 512>), dim3(a.S * a.Hq), dim3(512), 0, stream, a);
-  }
+static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, dim3 groups, hipStream_t stream) {
+  if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), groups, dim3(kGroupThreads), 0, stream, a, *layers);
+  else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), groups, dim3(kGroupThreads), 0, stream, a, OneLayer{});
 }
 
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
-  if (layers && a.leaves != kManySegments) return hipErrorInvalidValue;   // one layer has the whole workspace
-  if (a.D == 64) launch_dim<64>(a, layers, stream);
-  else if (a.D == 128) launch_dim<128>(a, layers, stream);
-  else if (a.D == 256) launch_dim<256>(a, layers, stream);
+  const dim3 groups(a.waves / group_waves(a.D), layers ? layers->count : 1), block(kGroupThreads);
+  if (a.leaves != kManySegments && (layers || a.D != kRow)) return hipErrorInvalidValue;   // one layer has the whole workspace
+  if (a.leaves == kRows) hipLaunchKernelGGL(attn_reduce_rows_kernel, dim3(a.S * a.Hq), block, 0, stream, a);
+  else if (a.leaves == kFewSegments) hipLaunchKernelGGL(attn_reduce_few_kernel, groups, block, 0, stream, a);
+  else if (a.D == 64) launch_dim<64>(a, layers, groups, stream);
+  else if (a.D == 128) launch_dim<128>(a, layers, groups, stream);
+  else if (a.D == 256) launch_dim<256>(a, layers, groups, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

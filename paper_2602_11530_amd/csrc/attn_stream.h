@@ -20,8 +20,7 @@
 //                    two records per workgroup reach memory (64 requests of 1024..8192 tokens on 40/8 heads:
 //                    194.2 us -> 191.0 with the reduce pass; one of 8191 19.1 -> 17.6)
 //   by rows          the wavefronts' records go to memory as they are and the reduce pass has a workgroup
-//                    per row: few segments where meeting in LDS costs more than it saves (what_is_left,
-//                    row_blocks)
+//                    per row: some dozens of short segments of one small row each (what_is_left)
 //   cut along them   one workgroup per segment, which meets in LDS and finishes it: no records, and no
 //                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
 //                    heads: 14.0 -> 11.3 us and a launch less on the host).  Few and short ones, up to 3
@@ -337,7 +336,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       W = share_count(T, a.waves);
       first_wave = blockIdx.x * kGroupWaves;
       last_wave = min(kGroupWaves, W - first_wave) - 1;
-      by_row = a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves));
+      by_row = a.leaves != kManySegments && (a.leaves == kRows || T <= row_blocks(a.waves));
       if (__builtin_expect(by_row && T < a.waves, 0)) {
         // A block per wavefront and not enough of them to fill the compute units: one after the other round
         // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
@@ -389,7 +388,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // For the reduce pass.
   const bool leaves_words = !kWhole && (a.leaves == kManySegments || a.leaves == kFewSegments);
   auto tell_of_rows = [&]() {
-    if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->count = kByRows;
+    if (__builtin_expect(a.leaves == kManySegments, 1)) return;
+    if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->told = kByRows;
     if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
       for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
     }
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   if (!kWhole && __builtin_expect(last_wave < 0, 0)) {   // nothing for this workgroup, or for this wavefront of it
     tell_of_rows();
     for (;;) {
-      if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->count = 0;
+      if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->told = 0;
       zero_empty_rows();
       if (!kChained || ++of == layer_count(layers)) return;
       layer = layer_at(a, layers, of);
@@ -803,20 +803,21 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   if (!kWhole) tell_of_rows();
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
-    // last block, does it begin here and go on elsewhere?
-    int row = 0, count = 0;
+    // last block, does it go on elsewhere?
+    int row = 0, told = 0;
     if (!whole && first_wave + kGroupWaves < W) {
       const ShareMap shares(T, W);
       const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
       const int s = request_of(next - 1);
       const Place at = place(next - 1, s, the_request(s));
       const int seg_pos = next - 1 - at.b;
-      if (seg_pos >= begin && seg_pos + at.nb > next) {
+      if (seg_pos + at.nb > next) {
+        const int first = seg_pos >= begin ? (int)blockIdx.x : (int)shares.owner(seg_pos) / kGroupWaves;
         row = (at.s * Hkv + at.kvh) * G;
-        count = (int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - (int)blockIdx.x + 1;
+        told = ((int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - first + 1) | ((int)blockIdx.x - first) << 16;
       }
     }
-    if (lane == 0) word = SharedSegment{row, count};
+    if (lane == 0) word = SharedSegment{row, told};
   }
   for (;;) {   // layers
   for (int j = 0; j < nshare; j += 2) {
@@ -854,7 +855,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   }
   store_staged();
-  if (by_row) {
+  if (__builtin_expect(by_row, 0)) {
     // The reduce pass has a workgroup for every row, so each wavefront's records go to memory as they
     // are, before all else.
     auto store_record = [&](const float* rec, int seg) {
@@ -879,7 +880,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
   if (!kWhole) zero_empty_rows();
-  if (by_row) return;
+  if (__builtin_expect(by_row, 0)) return;
   uint16_t* out = layer.out;
   const bool more = kChained && of + 1 < layer_count(layers);
   const int ends = ends_flags, left_end = left;

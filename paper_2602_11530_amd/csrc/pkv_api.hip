@@ -208,7 +208,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
   a->short_blocks = pkv::short_segment(segments, a->D, kv_fp8);
-  a->leaves = pkv::what_is_left(segments, g.G, a->D);
+  a->leaves = pkv::what_is_left(segments, max_blocks, g.G, a->D);
   if (segments <= a->waves / group && max_blocks <= a->short_blocks) {
     // Cut along its segments, a workgroup for each.  Nothing is left in the workspace, and the layers of such
     // a launch may be more than it has room for.
@@ -365,8 +365,8 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
   }
   // Several layers to a launch, as many as the workspace holds records for: a workgroup goes on
   // to the next layer when it is done with its share of one, and the start, the uneven end and the reduce
-  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch of few
-  // segments has the whole workspace for one layer, and one that leaves no records needs none of it.  Layers
+  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch that may go by
+  // rows has the whole workspace for one layer, and one that leaves no records needs none of it.  Layers
   // that depend on each other keep their order.
   Geometry g;
   (void)check_shape(shape, &g);

@@ -51,7 +51,7 @@ constexpr int kAhead = 2;
 //   wavefronts of a workgroup fold their records in LDS, finish the segments that lie
 //   inside the workgroup's range and leave one record for each of the two segments
 //   that may cross its ends (group_record); the workgroup in which a crossing segment
-//   begins leaves word of it (SharedSegment).
+//   begins, and those that lie in the middle of one, leave word of it (SharedSegment).
 //
 // Shares begin at floor(w * T / W), so that the longer ones are spread evenly over the compute
 // units: with the longer ones first, the units that hold them end last (1.5 % on 64 requests of
@@ -91,30 +91,24 @@ __host__ __device__ inline int record_floats(int G, int D) { return G * D + 2 * 
 enum Leaves {
   kManySegments,   // records of workgroups
   kFewSegments,    // records of workgroups, or of wavefronts (by rows) where a batch has few blocks
-  kRows,           // records of wavefronts, however many blocks
+  kRows,           // records of wavefronts: the bounds say that there are few blocks
   kNoRecords       // the bounds alone say that no segment will be shared: no reduce pass
 };
-// Up to kFew segments.  By rows, a workgroup of the reduce pass has one row and its records, and the
-// wavefronts of the stream pass need not meet; otherwise they meet in LDS, and a workgroup of the reduce
-// pass has a whole segment.  Rows / records of workgroups, us for append and attention:
-//   few blocks, so that a wavefront has one at most: one request of 2000..4000 tokens on 8/1 heads (227
-//   blocks) 14.5 / 15.8, 16 of 750..1500 (1047) 16.4 / 16.8; one of 1500..3000 on 32/8 heads at D = 64
-//   (1360) 14.9 / 13.2; 8 of 2000..4000 on 8/1 heads (1472) 18.1 / 16.8, 64 of them (12000) 30.2 / 26.9.
-//   a handful of segments, whose few workgroups of the reduce pass read hundreds of records each: one
-//   of 10000..16000 on 8/1 heads at D = 256 28.7 / 47, one of 16000..32000 on 16/1 heads at D = 128 37 / 47,
-//   5 of 6000..12000 on 8/1 heads at D = 256 24.9 / 27.8, where a workgroup has one thread for each 16 bytes
-//   of the rows; but on 4/1 heads, with two, 23.5 / 22.9, and 6 on 8/1 heads at D = 128 22.4 / 19.7.
-//   small records, which are soon written and read: 8 of 1500..3000 on 32/8 heads at D = 64 (1 KiB) 17.9 /
-//   18.6; 7 on 8/8 heads at D = 64 (256 bytes) 16.4 / 17.5; but 40 on 8/1 heads (2 KiB) 17.0 / 16.3, 4 on
-//   32/8 15.4 / 14.9.
+// By rows, a workgroup of the reduce pass has one row and its records, and the wavefronts of the stream pass need not meet;
+// otherwise they meet in LDS, and the reduce pass has a workgroup for a segment, or several for a long one.  By rows pays
+// for 32 to 64 segments of few blocks with records of one row of 64 floats.  Rows / records of workgroups, us for append and attention:
+//   4 requests of 300..800 tokens on 8/8 heads at D = 64 11.6 / 12.0, 8 of 200..900 12.3 / 12.5
+//   more blocks: 8 of 1500..4000 17.0 / 16.9, 64 of 1000..2000 on one head 14.0 / 13.8
+//   fewer segments: one request of 1000..2000 on 8/8 heads at D = 64 11.9 / 11.5, of 4000..8000 on one head 13.3 / 12.0
+//   more of a row: 64 of 400..900 on 2/1 heads 12.9 / 12.7; 8 of 300..900 on 8/8 heads at D = 128 14.6 / 14.0; one of 2000..4000 on 8/1
+//   heads there 13.3 / 12.6, 16 of 750..1500 15.0 / 13.4, one of 16000..32000 27.8 / 14.3, on 8/1 heads at D = 256 26.0 / 15.7
 constexpr int kFew = 64;
-inline Leaves what_is_left(int64_t segments, int G, int D) {
-  if (segments > kFew) return kManySegments;
-  const int handful = D == 256 && G > 4 ? 8 : 4;
-  return segments <= handful || G * D <= 64 || (segments > kFew / 2 && G * D < 512) ? kRows : kFewSegments;
-}
-// kFewSegments: by rows up to this many blocks.
+// Up to twice the wavefronts where the bounds say so, else, as the words then lie behind the records, by rows up to this many blocks.
 __host__ __device__ constexpr int row_blocks(int waves) { return waves * 5 / 8; }
+inline Leaves what_is_left(int64_t segments, int64_t max_blocks, int G, int D) {
+  if (segments > kFew || segments < kFew / 2 || G * D > 64) return kManySegments;
+  return segments * max_blocks <= 2 * kLayerGroups * group_waves(D) ? kRows : kFewSegments;
+}
 // A batch with no more segments than the launch has workgroups, none longer than this many blocks, is cut
 // along the segments.  Up to 6 blocks per wavefront; with at most kFew of them, which leave most
 // compute units idle, 3 where a block is 8 KiB or more.  Cut along the segments / not, us for append and
@@ -126,10 +120,14 @@ inline int short_segment(int64_t segments, int D, bool kv_fp8) {
   return (segments <= kFew && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
 }
 
-// A segment that several workgroups share, as the workgroup that it begins in leaves it.
+// A segment that several workgroups share, as those of them leave it in which no later one begins: the one that it begins in and
+// those in its middle.
 struct SharedSegment {
-  int row;     // first output row
-  int count;   // workgroups that share it, 0 when there is none, kByRows in a batch that goes by rows
+  int row;    // first output row
+  int told;   // workgroups that share it, and from bit 16 how many of them come before this one; 0 when there is none, kByRows in a
+              // batch that goes by rows
+  __host__ __device__ int records() const { return told & 0xffff; }
+  __host__ __device__ int slice() const { return told >> 16; }
 };
 constexpr int kByRows = -1;
 
