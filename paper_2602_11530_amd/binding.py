@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libpkv.so: argument marshalling only.
+"""Thin binding over libpkv.so: argument marshalling only, in the module _pkv_call for the calls of a serving loop and by
+ctypes for the others and for arguments that module leaves alone.
 
 Function names mirror the C ABI (``include/pkv.h``).  Tensors are torch tensors
 (used purely as device-memory handles); every step of the computation runs in
@@ -13,6 +14,7 @@ from typing import Optional
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libpkv.so")
+CALL_PATH = os.path.join(_PKG, "_pkv_call.so")
 
 PKV_OK = 0
 PKV_ERR_NULL = -1
@@ -53,6 +55,7 @@ class PkvError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
+_call = None         # the module _pkv_call, once the library is loaded
 _raw_stream = None   # () -> handle of the current stream, where this torch has the lookups
 
 
@@ -62,14 +65,29 @@ def _find_raw_stream(torch):
     return (lambda: stream(device())) if device and stream else None
 
 
+def _setup_call(L, torch):
+    """Gives the module _pkv_call the library's addresses and torch's look-ups."""
+    from . import _pkv_call
+    addresses = {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS}
+    device, stream = (getattr(torch._C, x, None) for x in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+    _pkv_call.setup(addresses, AttnShape, torch.cuda.is_initialized, device, stream if device else None)
+    return _pkv_call
+
+
+def _native():
+    lib()
+    return _call
+
+
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises if it is missing."""
-    global _lib, _raw_stream
+    global _lib, _call, _raw_stream
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} is not built; run `python -m paper_2602_11530_amd.build` "
-                "(there is no fallback path)")
+        for path in (LIB_PATH, CALL_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    f"{path} is not built; run `python -m paper_2602_11530_amd.build` "
+                    "(there is no fallback path)")
         # PyTorch owns the device memory and the streams this library is handed,
         # so both must sit on one HIP runtime: load torch (and with it the
         # runtime it ships) before libpkv.so resolves its own dependency.
@@ -115,6 +133,7 @@ def lib() -> ctypes.CDLL:
         L.kv_append.argtypes = [vp, vp, vp, vp, i32p, i32p, shp, vp]
         L.kv_append.restype = ctypes.c_int
         _raw_stream = _find_raw_stream(torch)
+        _call = _setup_call(L, torch)
         _lib = L
     return _lib
 
@@ -185,22 +204,30 @@ def pkv_attn_workspace_bytes(shape: AttnShape) -> int:
 def paged_decode_attn(q, k_pool, v_pool, block_tables, context_lens, scale, out,
                       shape: AttnShape, workspace=None, stream=None) -> None:
     """Enqueue one batched decode-attention call; see ``include/pkv.h``."""
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().paged_decode_attn(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
-                                   _ptr(context_lens), ctypes.c_float(scale), _ptr(out),
-                                   ctypes.byref(shape), _ptr(workspace), ws_bytes,
-                                   _stream(stream)))
+    status = (_call or _native()).paged_decode_attn(q, k_pool, v_pool, block_tables, context_lens, scale, out, shape,
+                                                    workspace, stream)
+    if status is NotImplemented:
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        status = lib().paged_decode_attn(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables), _ptr(context_lens),
+                                         ctypes.c_float(scale), _ptr(out), ctypes.byref(shape), _ptr(workspace),
+                                         ws_bytes, _stream(stream))
+    if status:
+        _check(status)
 
 
 def paged_decode_attn_fp8kv(q, k_pool, v_pool, block_tables, context_lens, scale, k_scale, v_scale,
                             out, shape: AttnShape, workspace=None, stream=None) -> None:
     """Attention over e4m3 KV pools (one byte per element, one fp32 scale per pool)."""
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().paged_decode_attn_fp8kv(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
-                                         _ptr(context_lens), ctypes.c_float(scale),
-                                         ctypes.c_float(k_scale), ctypes.c_float(v_scale), _ptr(out),
-                                         ctypes.byref(shape), _ptr(workspace), ws_bytes,
-                                         _stream(stream)))
+    status = (_call or _native()).paged_decode_attn_fp8kv(q, k_pool, v_pool, block_tables, context_lens, scale,
+                                                          k_scale, v_scale, out, shape, workspace, stream)
+    if status is NotImplemented:
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        status = lib().paged_decode_attn_fp8kv(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
+                                               _ptr(context_lens), ctypes.c_float(scale), ctypes.c_float(k_scale),
+                                               ctypes.c_float(v_scale), _ptr(out), ctypes.byref(shape),
+                                               _ptr(workspace), ws_bytes, _stream(stream))
+    if status:
+        _check(status)
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20
@@ -209,9 +236,14 @@ STATIC_WORKSPACE_BYTES = 32 << 20
 def paged_decode_attn_static(q, k_pool, v_pool, block_tables, context_lens, scale, out,
                              shape: AttnShape, stream=None) -> None:
     """The same call on the library's own fixed workspace: allocates nothing."""
-    _check(lib().paged_decode_attn_static(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
-                                          _ptr(context_lens), ctypes.c_float(scale), _ptr(out),
-                                          ctypes.byref(shape), _stream(stream)))
+    status = (_call or _native()).paged_decode_attn_static(q, k_pool, v_pool, block_tables, context_lens, scale, out,
+                                                           shape, stream)
+    if status is NotImplemented:
+        status = lib().paged_decode_attn_static(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
+                                                _ptr(context_lens), ctypes.c_float(scale), _ptr(out),
+                                                ctypes.byref(shape), _stream(stream))
+    if status:
+        _check(status)
 
 
 def pointer_array(tensors):
@@ -237,49 +269,81 @@ def paged_decode_attn_layers(q, k_pools, v_pools, block_tables, context_lens, sc
 
 def kv_blocks_gather(pool, block_ids, staging, n_blocks: int, block_bytes: int,
                      num_pool_blocks: int, stream=None) -> None:
-    _check(lib().kv_blocks_gather(_ptr(pool), _ptr(block_ids), _ptr(staging), n_blocks,
-                                  block_bytes, num_pool_blocks, _stream(stream)))
+    status = (_call or _native()).kv_blocks_gather(pool, block_ids, staging, n_blocks, block_bytes, num_pool_blocks,
+                                                   stream)
+    if status is NotImplemented:
+        status = lib().kv_blocks_gather(_ptr(pool), _ptr(block_ids), _ptr(staging), n_blocks, block_bytes,
+                                        num_pool_blocks, _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_blocks_scatter(staging, pool, block_ids, n_blocks: int, block_bytes: int,
                       num_pool_blocks: int, stream=None) -> None:
-    _check(lib().kv_blocks_scatter(_ptr(staging), _ptr(pool), _ptr(block_ids), n_blocks,
-                                   block_bytes, num_pool_blocks, _stream(stream)))
+    status = (_call or _native()).kv_blocks_scatter(staging, pool, block_ids, n_blocks, block_bytes, num_pool_blocks,
+                                                    stream)
+    if status is NotImplemented:
+        status = lib().kv_blocks_scatter(_ptr(staging), _ptr(pool), _ptr(block_ids), n_blocks, block_bytes,
+                                         num_pool_blocks, _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_blocks_move(src_pool, src_ids, dst_pool, dst_ids, n_blocks: int, block_bytes: int,
                    src_pool_blocks: int, dst_pool_blocks: int, stream=None) -> None:
     """dst_pool[dst_ids[i]] = src_pool[src_ids[i]] in one pass (pools on the same GPU)."""
-    _check(lib().kv_blocks_move(_ptr(src_pool), _ptr(src_ids), _ptr(dst_pool), _ptr(dst_ids),
-                                n_blocks, block_bytes, src_pool_blocks, dst_pool_blocks,
-                                _stream(stream)))
+    status = (_call or _native()).kv_blocks_move(src_pool, src_ids, dst_pool, dst_ids, n_blocks, block_bytes,
+                                                 src_pool_blocks, dst_pool_blocks, stream)
+    if status is NotImplemented:
+        status = lib().kv_blocks_move(_ptr(src_pool), _ptr(src_ids), _ptr(dst_pool), _ptr(dst_ids), n_blocks,
+                                      block_bytes, src_pool_blocks, dst_pool_blocks, _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_blocks_offload(pool, block_ids, staging, host_dst, n_blocks: int, block_bytes: int,
                       num_pool_blocks: int, stream=None) -> None:
     """Gather the listed blocks and copy the image to the pinned host tensor ``host_dst``."""
-    _check(lib().kv_blocks_offload(_ptr(pool), _ptr(block_ids), _ptr(staging), _ptr(host_dst),
-                                   n_blocks, block_bytes, num_pool_blocks, _stream(stream)))
+    status = (_call or _native()).kv_blocks_offload(pool, block_ids, staging, host_dst, n_blocks, block_bytes,
+                                                    num_pool_blocks, stream)
+    if status is NotImplemented:
+        status = lib().kv_blocks_offload(_ptr(pool), _ptr(block_ids), _ptr(staging), _ptr(host_dst), n_blocks,
+                                         block_bytes, num_pool_blocks, _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_blocks_reload(host_src, staging, pool, block_ids, n_blocks: int, block_bytes: int,
                      num_pool_blocks: int, stream=None) -> None:
     """Copy a saved image from the pinned host tensor and scatter it into the listed blocks."""
-    _check(lib().kv_blocks_reload(_ptr(host_src), _ptr(staging), _ptr(pool), _ptr(block_ids),
-                                  n_blocks, block_bytes, num_pool_blocks, _stream(stream)))
+    status = (_call or _native()).kv_blocks_reload(host_src, staging, pool, block_ids, n_blocks, block_bytes,
+                                                   num_pool_blocks, stream)
+    if status is NotImplemented:
+        status = lib().kv_blocks_reload(_ptr(host_src), _ptr(staging), _ptr(pool), _ptr(block_ids), n_blocks,
+                                        block_bytes, num_pool_blocks, _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_append(k_new, v_new, k_pool, v_pool, block_tables, context_lens, shape: AttnShape,
               stream=None) -> None:
     """Write each request's newest K and V rows into slot context_lens[s] - 1."""
-    _check(lib().kv_append(_ptr(k_new), _ptr(v_new), _ptr(k_pool), _ptr(v_pool),
-                           _ptr(block_tables), _ptr(context_lens), ctypes.byref(shape),
-                           _stream(stream)))
+    status = (_call or _native()).kv_append(k_new, v_new, k_pool, v_pool, block_tables, context_lens, shape, stream)
+    if status is NotImplemented:
+        status = lib().kv_append(_ptr(k_new), _ptr(v_new), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
+                                 _ptr(context_lens), ctypes.byref(shape), _stream(stream))
+    if status:
+        _check(status)
 
 
 def kv_append_fp8(k_new, v_new, k_pool, v_pool, block_tables, context_lens, k_scale, v_scale,
                   shape: AttnShape, stream=None) -> None:
     """Quantise each request's newest K and V rows to E4M3 and write them into slot context_lens[s] - 1."""
-    _check(lib().kv_append_fp8(_ptr(k_new), _ptr(v_new), _ptr(k_pool), _ptr(v_pool),
-                               _ptr(block_tables), _ptr(context_lens), ctypes.c_float(k_scale),
-                               ctypes.c_float(v_scale), ctypes.byref(shape), _stream(stream)))
+    status = (_call or _native()).kv_append_fp8(k_new, v_new, k_pool, v_pool, block_tables, context_lens, k_scale,
+                                                v_scale, shape, stream)
+    if status is NotImplemented:
+        status = lib().kv_append_fp8(_ptr(k_new), _ptr(v_new), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
+                                     _ptr(context_lens), ctypes.c_float(k_scale), ctypes.c_float(v_scale),
+                                     ctypes.byref(shape), _stream(stream))
+    if status:
+        _check(status)

@@ -1,11 +1,12 @@
-"""Builds libpkv.so (gfx950, hipcc), libpascal_sched.so (host only, g++) and the native
-driver program serve_trace in-tree.
+"""Builds libpkv.so (gfx950, hipcc), libpascal_sched.so and the Python module _pkv_call (host only, g++) and the
+native driver program serve_trace in-tree.
 ``python -m paper_2602_11530_amd.build``."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
@@ -49,6 +50,15 @@ def build_sched(verbose: bool = True) -> str:
                     SCHED_LIB, verbose)
 
 
+CALL = os.path.join(PKG, "_pkv_call.so")
+
+
+def build_call(verbose: bool = True) -> str:
+    """The library's calls as a Python module (host code only; it is given the library's addresses, not linked to it)."""
+    return _compile([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-cast-function-type",
+                     "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pkv_call.cpp")], CALL, verbose)
+
+
 DRIVER = os.path.join(PKG, "serve_trace")
 
 
@@ -59,8 +69,9 @@ def build_driver(verbose: bool = True) -> str:
 
 
 def build(verbose: bool = True, extra_flags=()) -> str:
-    """Compile every source of both libraries and the driver; always recompiles (seconds)."""
+    """Compile every source of both libraries, the module and the driver; always recompiles (seconds)."""
     build_sched(verbose)
+    build_call(verbose)
     lib = _compile([HIPCC, *FLAGS, *extra_flags] + [os.path.join(CSRC, s) for s in SOURCES],
                    LIB, verbose)
     build_driver(verbose)

@@ -1,0 +1,91 @@
+"""The module that takes the arguments of the serving loop's calls apart agrees with ctypes: same status for the same arguments, and
+what it leaves alone is converted or refused by ctypes as before (no GPU: calls that end before a launch)."""
+import ctypes
+
+import pytest
+
+from paper_2602_11530_amd import binding as pkv
+
+
+class Buffer:
+    """As much of a tensor as the binding looks at."""
+
+    def __init__(self, address, n=0):
+        self.address, self.n = address, n
+
+    def data_ptr(self):
+        return self.address
+
+    def numel(self):
+        return self.n
+
+    def element_size(self):
+        return 1
+
+
+class Side:
+    cuda_stream = 48
+
+
+T, ODD = Buffer(1 << 20), Buffer((1 << 20) + 2)
+SHAPE, BAD, EMPTY = pkv.make_shape(4, 8, 2, 19, 128), pkv.make_shape(4, 8, 3, 19, 128), pkv.make_shape(0, 8, 2, 19, 128)
+WS = Buffer(1 << 20, 64)
+
+
+def status(fn, *args):
+    try:
+        fn(*args)
+    except pkv.PkvError as e:
+        return e.status
+    return pkv.PKV_OK
+
+
+@pytest.fixture(params=["module", "ctypes"])
+def path(request, monkeypatch):
+    pkv.lib()
+    if request.param == "ctypes":
+        class Nothing:
+            def __getattr__(self, name):
+                return lambda *args: NotImplemented
+        monkeypatch.setattr(pkv, "_call", Nothing())
+
+
+@pytest.mark.parametrize("stream", [0, 16, Side()])
+def test_statuses(path, stream):
+    a, c = (T,) * 5, (T, T, T)
+    assert status(pkv.kv_append, *a, T, EMPTY, stream) == pkv.PKV_OK
+    assert status(pkv.kv_append, *a, T, BAD, stream) == pkv.PKV_ERR_SHAPE
+    assert status(pkv.kv_append, *a, None, SHAPE, stream) == pkv.PKV_ERR_NULL
+    assert status(pkv.kv_append, *a, ODD, SHAPE, stream) == pkv.PKV_ERR_ALIGN
+    assert status(pkv.kv_append_fp8, *a, T, 0.5, -1.0, SHAPE, stream) == pkv.PKV_ERR_SHAPE
+    assert status(pkv.kv_append_fp8, *a, T, 0.5, 1.0, EMPTY, stream) == pkv.PKV_OK
+    assert status(pkv.paged_decode_attn, *a, 0.1, T, SHAPE, WS, stream) == pkv.PKV_ERR_WORKSPACE
+    assert status(pkv.paged_decode_attn, *a, 0.1, T, SHAPE, None, stream) == pkv.PKV_ERR_WORKSPACE
+    assert status(pkv.paged_decode_attn, *a, 0.1, None, EMPTY, None, stream) == pkv.PKV_OK
+    assert status(pkv.paged_decode_attn_fp8kv, *a, 0.1, 0.0, 1.0, T, EMPTY, None, stream) == pkv.PKV_ERR_SHAPE
+    assert status(pkv.paged_decode_attn_fp8kv, *a, 0.1, 1.0, 1.0, T, SHAPE, WS, stream) == pkv.PKV_ERR_WORKSPACE
+    assert status(pkv.paged_decode_attn_static, *a, 0.1, T, BAD, stream) == pkv.PKV_ERR_SHAPE
+    for fn in (pkv.kv_blocks_gather, pkv.kv_blocks_scatter):
+        assert status(fn, *c, 0, 64, 9, stream) == pkv.PKV_OK
+        assert status(fn, *c, 4, 40, 9, stream) == pkv.PKV_ERR_ALIGN
+        assert status(fn, *c, -1, 64, 9, stream) == pkv.PKV_ERR_SHAPE
+    assert status(pkv.kv_blocks_move, *c, T, 4, 64, -1, 9, stream) == pkv.PKV_ERR_SHAPE
+    assert status(pkv.kv_blocks_move, *c, None, 4, 64, 9, 9, stream) == pkv.PKV_ERR_NULL
+    assert status(pkv.kv_blocks_offload, *c, T, 0, 64, 9, stream) == pkv.PKV_OK
+    assert status(pkv.kv_blocks_reload, T, *c, 4, 40, 9, stream) == pkv.PKV_ERR_ALIGN
+
+
+def test_what_the_module_leaves_alone(path):
+    a = (T,) * 5
+    assert status(pkv.paged_decode_attn, *a, 1, T, SHAPE, WS, 0) == pkv.PKV_ERR_WORKSPACE      # a whole number for the scale
+    assert status(pkv.kv_blocks_gather, T, T, T, True, 40, 9, 0) == pkv.PKV_ERR_ALIGN
+    assert status(pkv.kv_blocks_gather, T, T, T, 1 << 64, 40, 9, 0) == pkv.PKV_ERR_ALIGN        # 0 in 64 bits, as ctypes has it
+    with pytest.raises(ctypes.ArgumentError):
+        pkv.kv_blocks_gather(T, T, T, 4.0, 64, 9, 0)
+    with pytest.raises(TypeError):
+        pkv.kv_append(*a, T, None, 0)
+    with pytest.raises(TypeError):
+        pkv.paged_decode_attn(*a, None, T, SHAPE, WS, 0)
+    with pytest.raises(AttributeError):
+        pkv.kv_append(*a, 16, SHAPE, 0)
+    assert pkv.kv_append(*a, context_lens=T, shape=EMPTY, stream=0) is None
