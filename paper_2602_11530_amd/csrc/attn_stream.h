@@ -213,10 +213,11 @@ __device__ __forceinline__ const AttnLaunch& reread(const AttnLaunch&) {
 }
 
 // WholeLayer: the bounds say that each segment has a workgroup.  Where its blocks are then follows from its request's length alone, which
-// is asked for together with the table row and the query group: no prefix sums, no search, no barrier, one round trip to memory
-// before the first K instead of two.  Append and attention against the general kernel, which finds out on the device: 4 requests of
-// 17..300 tokens on 8/2 heads 10.8 -> 9.05 us, geometric means of 100 shapes each (1 to 250 segments of 10 to 300 tokens) D = 64 0.79,
-// e4m3 there 0.79, D = 128 0.80 and 0.81, D = 256 0.85 and 0.85.
+// is asked for together with the query group: no prefix sums, no search, no barrier before the first K.  Append and attention against the
+// general kernel, which finds out on the device: 4 requests of 17..300 tokens on 8/2 heads 10.8 -> 8.75 us, geometric means of 100 shapes
+// each (1 to 250 segments of 10 to 300 tokens) D = 64 0.79, e4m3 there 0.79, D = 128 0.80 and 0.81, D = 256 0.85 and 0.85, measured with the
+// table row asked for together with the length as well.  That took 0.1 to 0.3 us less, but reads entries behind a request's last block,
+// which the caller is promised are not read.
 // kLarge: as large batches want it (large_at_256; at D = 128 in bf16 all but short ones, short_at_128).
 template <int kD, bool kFp8, typename Layers, bool kLarge>
 __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnLaunch a, Layers layers) {
@@ -355,7 +356,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   int whole_len = 0, whole_entry = 0;
   if constexpr (kWhole) {
     const int s = blockIdx.z;
-    whole_entry = a.block_tables[(int64_t)s * a.MAXB + min(lane, a.MAXB - 1)];
     load_q(s * Hkv + blockIdx.x);
     typedef const int32_t __attribute__((address_space(4))) * ScalarLoad;
     whole_len = min(max(*(ScalarLoad)(a.context_lens + s), 0), a.max_ctx);
@@ -365,6 +365,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       for (int f = threadIdx.x; f < G * kD / 2; f += kThreads) dst[f] = 0;
       return;
     }
+    if (lane * a.upb < nb) whole_entry = a.block_tables[(int64_t)s * a.MAXB + lane];   // entries behind the last block are never read
     W = min(kGroupWaves, nb);
     last_wave = W - 1;
     if (wave < W) {
