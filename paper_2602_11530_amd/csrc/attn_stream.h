@@ -904,8 +904,8 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
   // The workgroup's merge.  Segments that meet inside the workgroup's range are finished from
   // the records in LDS.  What is left are at most two segments that it shares with other
-  // workgroups: one record each goes to memory for the reduce pass, and the workgroup that a
-  // shared segment begins in leaves word of it.
+  // workgroups: one record each goes to memory for the reduce pass, and a workgroup whose last
+  // segment goes on behind it leaves word of that.
   const AttnLaunch& b = reread(a);
   const int wave_floats = b.wave_lds_floats;
   const float out_scale = b.out_scale;
