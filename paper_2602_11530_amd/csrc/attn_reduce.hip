@@ -148,7 +148,9 @@ __device__ __forceinline__ void reduce_rows(const AttnLaunch& a) {
 // 33 records took two turns.  Append and attention, before / this way: one request of 8191 tokens 16.2 / 15.5 us, 8 at D = 256
 // 32.6 / 32.1, 512 of 16..512 106.1 / 104.0, 32 at D = 64 43.2 / 41.9, 64 of 1024..8192 194.3 / 192.7, on 8-bit pools 104.3 / 102.9,
 // six layers of 24 754 / 747.
-//   Up to kBatch records: a thread loads all of them at once and is done.
+//   Up to kBatch records, or twice that: a thread loads all of them at once and is done.  From kBatch + 1 to twice as many by several
+//   workgroups and sets of lanes, as below: 8 requests of 1500..3000 tokens on 32/8 heads at D = 64 15.8 us, this way 15.0, 8 at
+//   D = 256 31.5 / 30.8; with four times kBatch at once 0 to 1 % slower than below.
 //   More: the workgroups in the middle of the segment, in which nothing begins, take some of the chunks each, and in a workgroup
 //   sets of lanes take every sets-th record and meet in LDS, four to one at a time.
 constexpr int kSubs = kGroupThreads / 16;   // G * D / 64 is kSubs at most
@@ -157,12 +159,13 @@ struct SegmentRecords {
   const char* base;    // the segment's first record
   uint32_t rec_bytes;
   uint32_t at, stats;  // of this lane's 16 bytes, and of its head's statistics, within a record
-  // records i, i + step, ... of `count`: those past the end are the last one with nothing valid
+  // kN records i, i + step, ... of `count`: those past the end are the last one with nothing valid
+  template <int kN>
   __device__ __forceinline__ void fold_batch(Partial& p, int i, int step, int count) const {
-    f32x4 x[kBatch];
-    f32x2 ml[kBatch];
+    f32x4 x[kN];
+    f32x2 ml[kN];
 #pragma unroll
-    for (int z = 0; z < kBatch; ++z) {
+    for (int z = 0; z < kN; ++z) {
       const int j = min(i + z * step, count - 1);
       // the one that begins the segment is its workgroup's second record, the others are first ones
       const uint32_t off = (uint32_t)(2 * j - (j > 0)) * rec_bytes;
@@ -170,7 +173,7 @@ struct SegmentRecords {
       ml[z] = *(const f32x2*)(base + (off + stats));
     }
 #pragma unroll
-    for (int z = 0; z < kBatch; ++z) {
+    for (int z = 0; z < kN; ++z) {
       if (i + z * step >= count) ml[z].x = kNegInf;
     }
     fold(p, ml, x);
@@ -192,11 +195,12 @@ __device__ __forceinline__ void reduce_segment(const AttnLaunch& a, const Layers
   auto finish = [&](const Partial& p, int chunk) {
     *(u32x2*)(out + 64 * chunk + 4 * lane16) = finish_row4(p.x, inverse(p.l, a.out_scale));
   };
-  if (count <= kBatch) {
+  if (count <= 2 * kBatch) {
     if (slice != 0 || sub >= chunks) return;
     place(sub);
     Partial p = kNothing;
-    r.fold_batch(p, 0, 1, count);
+    if (__builtin_expect(count <= kBatch, 1)) r.template fold_batch<kBatch>(p, 0, 1, count);
+    else r.template fold_batch<2 * kBatch>(p, 0, 1, count);
     finish(p, sub);
     return;
   }
@@ -213,7 +217,7 @@ __device__ __forceinline__ void reduce_segment(const AttnLaunch& a, const Layers
   Partial p = kNothing;
   if (works) {
     place(chunk);
-    for (int i = set; i < count; i += kBatch * sets) r.fold_batch(p, i, sets, count);
+    for (int i = set; i < count; i += kBatch * sets) r.template fold_batch<kBatch>(p, i, sets, count);
   }
   while (sets > 1) {
     rows[threadIdx.x] = p.x;

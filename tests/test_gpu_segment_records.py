@@ -1,4 +1,4 @@
-"""GPU parity of the reduce pass over workgroups' records by how many of them a segment has: up to a turn of loads, one more, enough
+"""GPU parity of the reduce pass over workgroups' records by how many of them a segment has: up to a turn of loads, two turns' worth, one more, enough
 for several workgroups to a segment and for several sets of lanes in each, hundreds; few segments and many; the smallest and the
 largest rows.  Peaked scores, so that the records of a segment have unlike maxima, in one of them by far the largest."""
 import numpy as np
@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("lens", [
     [3000] * 6,                       # tens of records to a segment, few segments
     [900 + 3 * i for i in range(40)],   # half a dozen
+    [1150] * 32,                      # eight and nine
     [12000] + [1] * 70,               # hundreds and none, many segments
     [2600, 40] * 36 + [0, 7],         # two to five
 ])
