@@ -1,10 +1,11 @@
 """Thin binding over libpkv.so: argument marshalling only, in the module _pkv_call for the calls of a serving loop and by
-ctypes for the others and for arguments that module leaves alone.
+ctypes for the others, for arguments that module leaves alone and where it cannot be loaded.
 
 Function names mirror the C ABI (``include/pkv.h``).  Tensors are torch tensors
 (used purely as device-memory handles); every step of the computation runs in
 the library's HIP kernels.  If the library has not been built the first call
-raises — there is no fallback path.
+raises — there is no fallback path.  The module only saves time on the host: without it,
+or with one that is not for this interpreter, every call goes by ctypes.
 """
 from __future__ import annotations
 
@@ -14,7 +15,6 @@ from typing import Optional
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libpkv.so")
-CALL_PATH = os.path.join(_PKG, "_pkv_call.so")
 
 PKV_OK = 0
 PKV_ERR_NULL = -1
@@ -55,7 +55,7 @@ class PkvError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
-_call = None         # the module _pkv_call, once the library is loaded
+_call = None         # the module _pkv_call or _ByCtypes, once the library is loaded
 _raw_stream = None   # () -> handle of the current stream, where this torch has the lookups
 
 
@@ -65,9 +65,19 @@ def _find_raw_stream(torch):
     return (lambda: stream(device())) if device and stream else None
 
 
+class _ByCtypes:
+    """In the module's place where it cannot be loaded: leaves every call to ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
+
+
 def _setup_call(L, torch):
     """Gives the module _pkv_call the library's addresses and torch's look-ups."""
-    from . import _pkv_call
+    try:
+        from . import _pkv_call
+    except ImportError:   # not built, or not for this interpreter
+        return _ByCtypes()
     addresses = {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS}
     device, stream = (getattr(torch._C, x, None) for x in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
     _pkv_call.setup(addresses, AttnShape, torch.cuda.is_initialized, device, stream if device else None)
@@ -83,11 +93,10 @@ def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises if it is missing."""
     global _lib, _call, _raw_stream
     if _lib is None:
-        for path in (LIB_PATH, CALL_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(
-                    f"{path} is not built; run `python -m paper_2602_11530_amd.build` "
-                    "(there is no fallback path)")
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                f"{LIB_PATH} is not built; run `python -m paper_2602_11530_amd.build` "
+                "(there is no fallback path)")
         # PyTorch owns the device memory and the streams this library is handed,
         # so both must sit on one HIP runtime: load torch (and with it the
         # runtime it ships) before libpkv.so resolves its own dependency.

@@ -1,6 +1,10 @@
 """The module that takes the arguments of the serving loop's calls apart agrees with ctypes: same status for the same arguments, and
 what it leaves alone is converted or refused by ctypes as before (no GPU: calls that end before a launch)."""
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
 
 import pytest
 
@@ -44,10 +48,7 @@ def status(fn, *args):
 def path(request, monkeypatch):
     pkv.lib()
     if request.param == "ctypes":
-        class Nothing:
-            def __getattr__(self, name):
-                return lambda *args: NotImplemented
-        monkeypatch.setattr(pkv, "_call", Nothing())
+        monkeypatch.setattr(pkv, "_call", pkv._ByCtypes())
 
 
 @pytest.mark.parametrize("stream", [0, 16, Side()])
@@ -89,3 +90,33 @@ def test_what_the_module_leaves_alone(path):
     with pytest.raises(AttributeError):
         pkv.kv_append(*a, 16, SHAPE, 0)
     assert pkv.kv_append(*a, context_lens=T, shape=EMPTY, stream=0) is None
+
+
+CALLS = """
+import ctypes
+from {package} import binding as pkv
+t = type("Buffer", (), {{"data_ptr": lambda self: 1 << 20}})()
+pkv.kv_blocks_gather(t, t, t, 0, 64, 9, 0)
+try:
+    pkv.kv_blocks_gather(t, t, t, 4, 40, 9, 0)
+except pkv.PkvError as e:
+    assert e.status == pkv.PKV_ERR_ALIGN
+else:
+    assert False
+print("called")
+"""
+
+
+@pytest.mark.parametrize("module", [None, b"not for this interpreter"])
+def test_without_the_module(tmp_path, module):
+    """Every call goes by ctypes where the module was not built, or is no module to this interpreter."""
+    package = os.path.dirname(pkv.__file__)
+    copy = tmp_path / "pkv_copy"
+    copy.mkdir()
+    for name in ("__init__.py", "binding.py", "workloads.py"):
+        shutil.copy(os.path.join(package, name), copy)
+    os.symlink(pkv.LIB_PATH, copy / "libpkv.so")
+    if module:
+        (copy / "_pkv_call.so").write_bytes(module)
+    run = subprocess.run([sys.executable, "-c", CALLS.format(package="pkv_copy")], cwd=tmp_path, capture_output=True, text=True)
+    assert run.returncode == 0 and "called" in run.stdout, run.stderr
