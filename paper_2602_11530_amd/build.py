@@ -7,6 +7,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
@@ -50,13 +51,22 @@ def build_sched(verbose: bool = True) -> str:
                     SCHED_LIB, verbose)
 
 
-CALL = os.path.join(PKG, "_pkv_call.so")
+# for this interpreter alone, as its name says: another one does not load it and goes by ctypes
+CALL = os.path.join(PKG, "_pkv_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
-def build_call(verbose: bool = True) -> str:
-    """The library's calls as a Python module (host code only; it is given the library's addresses, not linked to it)."""
+def build_call(verbose: bool = True) -> Optional[str]:
+    """The library's calls as a Python module (host code only; it is given the library's addresses, not linked to it).  None, and
+    no module, where the interpreter's headers are not installed: the binding then goes by ctypes."""
+    headers = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(headers, "Python.h")):
+        if os.path.exists(CALL):   # of an earlier state of the sources
+            os.remove(CALL)
+        if verbose:
+            print(f"no Python.h in {headers}: _pkv_call is left out", flush=True)
+        return None
     return _compile([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-cast-function-type",
-                     "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pkv_call.cpp")], CALL, verbose)
+                     "-I", headers, os.path.join(CSRC, "pkv_call.cpp")], CALL, verbose)
 
 
 DRIVER = os.path.join(PKG, "serve_trace")
@@ -71,10 +81,10 @@ def build_driver(verbose: bool = True) -> str:
 def build(verbose: bool = True, extra_flags=()) -> str:
     """Compile every source of both libraries, the module and the driver; always recompiles (seconds)."""
     build_sched(verbose)
-    build_call(verbose)
     lib = _compile([HIPCC, *FLAGS, *extra_flags] + [os.path.join(CSRC, s) for s in SOURCES],
                    LIB, verbose)
     build_driver(verbose)
+    build_call(verbose)
     return lib
 
 
