@@ -92,6 +92,23 @@ def test_what_the_module_leaves_alone(path):
     assert pkv.kv_append(*a, context_lens=T, shape=EMPTY, stream=0) is None
 
 
+@pytest.mark.parametrize("error", [KeyboardInterrupt, MemoryError, RuntimeError, ValueError])
+@pytest.mark.parametrize("where", ["data_ptr", "numel", "cuda_stream"])
+def test_other_exceptions_reach_the_caller(path, error, where):
+    """One that is raised while the arguments are taken apart and is not about their kind: once, and not swallowed."""
+    raised = []
+
+    def fail(self):
+        if raised:
+            return 64   # an interrupt comes once
+        raised.append(1)
+        raise error("once")
+    bad = type("Bad", (Buffer,), {where: property(fail) if where == "cuda_stream" else fail})(1 << 20, 64)
+    buffer, stream = (T, bad) if where == "cuda_stream" else (bad, 0)
+    with pytest.raises(error, match="once"):
+        pkv.paged_decode_attn(T, T, T, T, T, 0.1, T, EMPTY, buffer, stream)
+
+
 CALLS = """
 import ctypes
 from {package} import binding as pkv
