@@ -4,6 +4,8 @@ import os
 import re
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_11530_amd", "csrc")
 
@@ -18,12 +20,13 @@ def test_writes_stay_in_the_workspace(tmp_path):
     assert out.returncode == 0 and "failures=0" in out.stdout, out.stdout
 
 
-def test_stream_pass_lds_begins_aligned(tmp_path):
+@pytest.mark.parametrize("source,variants", [("attn_stream", 9), ("attn_stream_large", 6), ("attn_stream_short", 8)])
+def test_stream_pass_lds_begins_aligned(tmp_path, source, variants):
     """The stream pass's dynamic LDS follows its static arrays; records and rows in it are accessed 16 bytes at a time."""
     from paper_2602_11530_amd import build as pkv_build
-    asm = str(tmp_path / "attn_stream.s")
+    asm = str(tmp_path / "out.s")
     flags = [f for f in pkv_build.FLAGS if f not in ("-fPIC", "-shared")]
-    subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "attn_stream.hip"), "-o", asm],
+    subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, source + ".hip"), "-o", asm],
                           stderr=subprocess.DEVNULL)
     sizes = re.findall(r"\.amdhsa_group_segment_fixed_size (\d+)", open(asm).read())
-    assert len(sizes) == 9 and all(int(s) % 16 == 0 for s in sizes), sizes
+    assert len(sizes) == variants and all(int(s) % 16 == 0 for s in sizes), sizes

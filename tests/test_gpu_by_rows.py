@@ -1,0 +1,130 @@
+"""GPU parity of batches that go by rows: 32 to 64 segments (request, KV head) of few blocks, one row of 64 floats each.  The
+wavefronts' records go to memory as they are and the reduce pass has a workgroup for a row; the bounds say so ("rows" on the host), or
+the device finds it ("few").  Fewer blocks than wavefronts, which are then dealt round the workgroups, as many and more; the most that the
+device sends by rows, and one more; batches that turn out to be cut along their segments; replays that go from one to
+the other.  The way of every batch is asserted, so that none of this is left unseen when a rule moves."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import routes
+from gpu_util import REL_L2, abs_error_within_bar, run_attn_dev, shape_of, to_bits, to_dev
+from paper_2602_11530_amd import binding as pkv
+from paper_2602_11530_amd import workloads as wl
+from test_gpu_fp8kv import KS, VS, check as check_fp8, run_fp8
+
+pytestmark = pytest.mark.gpu
+
+
+def spread(total, n, longest, empty=0):
+    """n lengths of `total` blocks together, the first of `longest`, the last `empty` of none, not all of them whole blocks."""
+    rest = n - 1 - empty
+    each = [(total - longest) // rest + (i < (total - longest) % rest) for i in range(rest)]
+    lens = [16 * longest] + [max(16 * b - 5 * i % 16, 1) if b else 0 for i, b in enumerate(each)] + [0] * empty
+    assert len(lens) == n and sum((x + 15) // 16 for x in lens) == total and max(lens) == 16 * longest
+    return lens
+
+
+# lengths, heads, blocks that the table has room for, what becomes of it by host and device
+BATCHES = [
+    (spread(255, 32, 50), 1, 50, "rows", "dealt"),           # a wavefront in all but one of the workgroups
+    (spread(600, 40, 60, 3), 1, 100, "rows", "dealt"),
+    (spread(2047, 32, 70), 1, 128, "rows", "dealt"),         # a block less than wavefronts, as many and one more
+    (spread(2048, 32, 70), 1, 128, "rows", "rows"),
+    (spread(2049, 32, 70), 1, 128, "rows", "rows"),
+    (spread(500, 16, 60, 5), 4, 64, "rows", "dealt"),        # 2000 blocks of 64 segments
+    (spread(510, 9, 60), 7, 65, "rows", "rows"),             # 3570 of 63
+    ([64 * 16] * 8, 8, 64, "rows", "rows"),                  # as many segments, and blocks, as there may be
+    ([128 * 16] * 32, 1, 128, "rows", "rows"),
+    ([48 * 16, 5, 0, 700] * 8, 1, 49, "rows", "whole"),      # by the bounds by rows, but none is long
+    ([0] * 4, 8, 49, "rows", "whole"),                       # nothing at all
+    (spread(1280, 32, 49), 1, 500, "few", "dealt"),          # the most that the device sends by rows, and one more
+    (spread(1281, 32, 49), 1, 500, "few", "records"),
+    (spread(1279, 64, 900), 1, 1000, "few", "dealt"),        # one request has most of the wavefronts
+    (spread(160, 8, 80, 2), 8, 200, "few", "dealt"),         # 1280 blocks again, of eight heads each
+    (spread(161, 8, 80, 2), 8, 200, "few", "records"),
+    (spread(4096, 32, 3000), 1, 3000, "few", "records"),
+    ([48 * 16, 5, 0, 700] * 8, 2, 300, "few", "whole"),
+]
+
+
+def workload(lens, heads, room, **kw):
+    return wl.custom(lens, heads, heads, seed=90 + len(lens), num_pool_blocks=sum((n + 15) // 16 for n in lens) + 1, head_dim=64,
+                     maxb=room, **kw)
+
+
+def peaked(k):
+    """K so that the records of a segment have unlike maxima."""
+    return wl.f32_to_bf16_bits(np.asarray(wl.bf16_bits_to_f64(k), dtype=np.float32) * np.float32(3.0))
+
+
+def check(w, host, got):
+    ref = oracle.paged_decode_attn(*host, w.block_tables, w.context_lens, w.scale)
+    c = oracle.compare(got, ref)
+    assert c["rel_l2"] <= REL_L2 and c["worst_seq_rel_l2"] <= 2 * REL_L2 and abs_error_within_bar(got, ref), c
+    for s in np.flatnonzero(w.context_lens == 0):
+        assert not got.reshape(w.q_shape())[s].any()
+
+
+@pytest.mark.parametrize("i", range(len(BATCHES)))
+@pytest.mark.parametrize("partition", [0, 64])
+def test_batches(device, i, partition):
+    lens, heads, room, host_route, route = BATCHES[i]
+    w = workload(lens, heads, room, partition_size=partition)
+    assert (routes.host_route(w), routes.route(w)) == (host_route, route)
+    q, k, v = wl.make_host_tensors(w, poison_unused=True)
+    k = peaked(k) if i % 2 else k
+    print(f"{i}: {len(lens)} requests, {heads} heads, {route}", flush=True)
+    dev = [to_dev(x) for x in (q, k, v, w.block_tables, w.context_lens)]
+    need, guard = pkv.pkv_attn_workspace_bytes(shape_of(w)), 1 << 20
+    buf = torch.full((2 * guard + need,), 0xA5, dtype=torch.uint8, device=device)
+    first = run_attn_dev(w, *dev, workspace=buf[guard:guard + need])
+    torch.cuda.synchronize()
+    assert bool((buf[:guard] == 0xA5).all()) and bool((buf[guard + need:] == 0xA5).all())
+    check(w, (q, k, v), to_bits(first))
+    buf.random_(0, 256)
+    assert torch.equal(run_attn_dev(w, *dev, workspace=buf[guard:guard + need]), first)   # whoever ends a segment
+
+
+@pytest.mark.parametrize("i", [0, 3, 5, 7, 9, 11, 12, 14])
+def test_8_bit_pools(device, i):
+    lens, heads, room, host_route, route = BATCHES[i]
+    w = workload(lens, heads, room)
+    assert (routes.host_route(w, fp8=True), routes.route(w, fp8=True)) == (host_route, route)
+    q, k8, v8 = wl.make_host_tensors_fp8(w, KS, VS, poison_unused=True)
+    print(f"fp8 {i}: {len(lens)} requests, {heads} heads, {route}", flush=True)
+    check_fp8(w, q, k8, v8, run_fp8(w, q, k8, v8), f"fp8 {route}")
+
+
+@pytest.mark.parametrize("heads,steps,room,host_route,ways", [
+    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [32] * 7 + [51], [49] + [1] * 7], 64, "rows",
+     ["rows", "whole", "dealt", "rows", "dealt"]),
+    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [700, 0, 0, 0, 0, 0, 0, 1], [0] * 7 + [160]], 800, "few",
+     ["records", "whole", "dealt", "records", "dealt"]),
+])
+def test_replays(device, heads, steps, room, host_route, ways):
+    """One launch, replayed with lengths that take it from one way to the next: nothing of an earlier replay may be left over."""
+    most = np.max(steps, axis=0)
+    w = workload([16 * int(b) for b in most], heads, room)
+    q, k, v = wl.make_host_tensors(w)
+    dev = [to_dev(x) for x in (q, k, v, w.block_tables, w.context_lens)]
+    shape, lens = shape_of(w), dev[4]
+    ws = torch.empty(pkv.pkv_attn_workspace_bytes(shape), dtype=torch.uint8, device=device).random_(0, 256)
+    out = torch.empty(w.q_shape(), dtype=torch.int16, device=device)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pkv.paged_decode_attn(*dev, float(w.scale), out, shape, ws, torch.cuda.current_stream())
+    for step, way in zip(steps + steps[1:], ways + ways[1:]):
+        w.context_lens[:] = [max(16 * b - 3 * i, 0) for i, b in enumerate(step)]
+        assert (routes.host_route(w), routes.route(w)) == (host_route, way)
+        lens.copy_(torch.from_numpy(w.context_lens))
+        out.fill_(0x7FC1)
+        graph.replay()
+        torch.cuda.synchronize()
+        print(f"{step}: {way}", flush=True)
+        got = to_bits(out)
+        assert np.array_equal(got, to_bits(run_attn_dev(w, *dev))), step
+        check(w, (q, k, v), got)

@@ -1,6 +1,6 @@
 """D = 256 has two launches, by the bounds (large_at_256), which differ in the order of the loads (bf16) or in the way of K to the
-matrix cores (e4m3) only: they agree bit for bit, and each with the oracle.  Shares of zero, one, two, some and many blocks, by rows,
-by workgroups and in several layers."""
+matrix cores (e4m3) only: they agree bit for bit, and each with the oracle.  Shares of zero, one, two, some and many blocks, one segment and many, and in
+several layers."""
 import copy
 
 import numpy as np
@@ -27,7 +27,7 @@ def is_large(w, max_context_len=0):
 BATCHES = pytest.mark.parametrize("lens,hq,hkv,P", [
     ([400] + [5, 0, 16, 17] * 20, 8, 8, 0),               # most wavefronts have a block, some none
     ([600, 1, 0, 37, 512, 250] * 4, 16, 8, 64),           # shares of 4 and 5, runs of 4
-    ([9000], 8, 1, 0), ([7000, 30], 40, 8, 0),            # by rows; a few segments
+    ([9000], 8, 1, 0), ([7000, 30], 40, 8, 0),            # one segment; a few
     ([2600 + 7 * i for i in range(20)] + [0], 8, 8, 512)])   # 26, large by the tight bound too
 def batch(lens, hq, hkv, P):
     """Its table is wide enough for the bounds of a large batch."""

@@ -8,6 +8,7 @@ import torch
 from paper_2602_11530_amd import binding as pkv
 from paper_2602_11530_amd import workloads as wl
 
+import routes
 from gpu_util import run_attn_dev, shape_of, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -23,10 +24,8 @@ def layers_call(w, dev, t_d, l_d, shape):
 
 
 def chained(w):
-    """Do workgroups go from layer to layer?  Not with few segments, nor where each has a workgroup by the bounds."""
-    segments, waves = w.num_seqs * w.num_kv_heads, 4 if w.head_dim == 256 else 8
-    blocks = w.max_blocks_per_seq * w.block_size // 16
-    return segments > 64 and (segments > 256 or blocks > 6 * waves)
+    """Do workgroups go from layer to layer?  Not in a batch that may go by rows, nor where each segment has one by the bounds."""
+    return routes.host_route(w) == "many"
 
 
 def device_layers(w, n, seed):
@@ -40,15 +39,14 @@ def device_layers(w, n, seed):
 
 
 # blocks per share at 2048 wavefronts (1024 at D = 256): the first two have a workgroup for each segment, the layers side by
-# side; then 51, 69, 63, 64, 129 and 64
+# side; then 51, 69, 63, 64, 129, 64 and, of a few segments, 2 and 66
 @pytest.mark.parametrize("dim,lens,hq,hkv", [
     (128, [40, 0, 17] * 24, 2, 2), (128, [300] * 70 + [0] * 5, 4, 2), (64, [5000 + 13 * i for i in range(40)], 8, 8),
     (128, [15700, 15800, 15900] * 6 + [0], 8, 8), (128, [16120] * 16 + [1] * 4, 8, 8), (128, [16384 + 40] * 16, 8, 8),
-    (128, [33000] * 16, 8, 8), (256, [8200] * 16 + [17] * 3, 8, 8)])
+    (128, [33000] * 16, 8, 8), (256, [8200] * 16 + [17] * 3, 8, 8), (64, [8000, 0, 31], 40, 8), (256, [17000] * 8, 8, 8)])
 def test_equals_single_calls(device, dim, lens, hq, hkv):
     blocks = sum((n + 15) // 16 for n in lens) + 3
     w = wl.custom(lens, hq, hkv, seed=61, num_pool_blocks=blocks, head_dim=dim)
-    assert len(lens) * hkv > 64
     assert chained(w) == (max(lens) > 1000)
     dev = device_layers(w, 5, 7)
     t_d, l_d = to_dev(w.block_tables), to_dev(w.context_lens)

@@ -1,6 +1,6 @@
 """GPU tests of how the partial results of a segment (request, KV head) meet: inside a wavefront's share, in a
-workgroup, over several workgroups (a record for each), by rows (a record for each wavefront), in batches cut
-along their segments; on workspaces whose earlier contents vary, called repeatedly and replayed from a graph."""
+workgroup, over several workgroups (a record for each), in batches cut along their segments; on workspaces whose earlier
+contents vary, called repeatedly and replayed from a graph.  (By rows: test_gpu_by_rows.py, and the cases that say so here.)"""
 import numpy as np
 import pytest
 import torch
@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 # lengths, query heads, KV heads, head dim
 SHAPES = [
-    ([33000], 8, 1, 128),            # a handful of segments, by rows: over all wavefronts
+    ([33000], 8, 1, 128),            # one segment: a record of every workgroup
     ([17000, 16000], 8, 2, 64),      # a boundary inside a workgroup
     ([9000, 1, 20000], 5, 1, 256),   # two long segments and a one-block one between them
-    ([4200] * 8, 16, 1, 128),        # few segments, workgroups' records: 32 each
+    ([4200] * 8, 16, 1, 128),        # 32 records each
     ([4300] * 7 + [2000], 16, 1, 128),
     ([2048] * 64, 8, 4, 128),        # many; shares and segments end together: nothing is shared
     ([1, 16, 17, 0, 33] * 60, 10, 2, 64),    # many segments inside one share
@@ -40,20 +40,20 @@ SHAPES = [
     ([384, 16, 15, 0] * 8, 16, 8, 256),
     ([768, 5, 300, 0] * 8, 32, 8, 64),       # as many segments as workgroups
     ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
-    ([2000, 30] * 4, 8, 8, 64),              # as many as count as few, and fewer, of one head each
+    ([2000, 30] * 4, 8, 8, 64),              # as many as may go by rows, and fewer, of one head each; too many blocks for it
     ([2000, 30] * 4, 7, 7, 64),
-    ([16 * 2047], 8, 1, 64),                 # by rows: a block less than wavefronts, as many and one more
+    ([16 * 2047], 8, 1, 64),                 # a block less than wavefronts, as many and one more
     ([16 * 2048 - 5], 8, 1, 128),
     ([16 * 2049], 8, 1, 128),
     ([16 * 1023, 0], 8, 1, 256),
     ([16 * 1024, 16], 8, 1, 256),
     ([16 * 255, 3, 0, 160], 16, 1, 128),     # fewer wavefronts than twice the workgroups, and an empty request
-    ([16 * 80] * 2, 8, 8, 128),              # 16 segments of 1280 blocks together: by rows, the most that are
-    ([16 * 80, 16 * 81], 8, 8, 128),         # beyond: workgroups' records
-    ([16 * 128, 0, 16 * 32], 16, 4, 256),    # 640 blocks
+    ([16 * 80] * 2, 8, 8, 128),              # 16 segments, ten records each, and eleven of some
+    ([16 * 80, 16 * 81], 8, 8, 128),
+    ([16 * 128, 0, 16 * 32], 16, 4, 256),
     ([16 * 128, 0, 16 * 33], 16, 4, 256),
-    ([16 * 1000, 40] * 4, 64, 4, 128),       # 32 segments: the most that small records leave alone
-    ([16 * 200] * 8 + [9], 14, 7, 64),       # 63 small ones: by rows, however many blocks
+    ([16 * 1000, 40] * 4, 64, 4, 128),       # 32 segments
+    ([16 * 200] * 8 + [9], 14, 7, 64),       # 63
     ([16 * 200] * 8 + [9], 56, 7, 64),
     ([9000, 5, 7000, 400, 1], 5, 1, 64),     # a few long segments, items that do not divide the workgroup
     ([9000, 5, 7000, 400, 1], 4, 1, 256),    # two threads for each 16 bytes, and one
@@ -94,8 +94,8 @@ def test_shared_segments(device, i, partition):
 
 @pytest.mark.parametrize("hq,hkv", [(8, 1), (16, 2), (34, 17)])
 def test_replays_with_growing_lengths(device, hq, hkv):
-    """What becomes of a batch is decided on the device: replays of one launch are cut along the segments, go by rows
-    or leave workgroups' records, and nothing of an earlier one may be left over."""
+    """What becomes of a batch is decided on the device: replays of one launch are cut along the segments or leave
+    workgroups' records, and nothing of an earlier one may be left over."""
     w, (q, k, v, tables, lens) = setup([40, 3000, 9, 12000], hq, hkv, 128, seed=400)
     w.context_lens[:] = [17, 16, 9, 33]
     lens.copy_(torch.from_numpy(w.context_lens))
@@ -124,7 +124,9 @@ def test_replays_with_growing_lengths(device, hq, hkv):
 @pytest.mark.parametrize("lens,hq,hkv,dim", [
     ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # several layers to a launch
     ([3000] * 40, 16, 2, 64),
-    ([700, 5000, 129], 16, 8, 256),                          # by rows: a launch for each
+    ([700, 5000, 129], 16, 8, 256),                          # few segments, likewise
+    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # by rows: a launch for each
+    ([9000, 0, 30, 17] * 8, 1, 1, 64),                       # as the device finds, not by rows: a launch for each
     ([40, 3, 768, 0], 8, 2, 128),                            # cut along the segments
 ])
 @pytest.mark.parametrize("layers", [1, 3, 9])
@@ -152,7 +154,7 @@ def test_layers_in_shared_launches(device, lens, hq, hkv, dim, layers):
 @pytest.mark.parametrize("lens,hq,hkv,dim,bound", [
     ([40, 3, 768, 0] * 4, 40, 8, 128, 768),       # 128 segments, cut along them in one launch: nothing left for a reduce pass
     ([40, 3, 384, 0] * 8, 16, 8, 256, 384),       # as many segments as workgroups
-    ([16] * 13, 10, 5, 64, 16),                   # the fewest that are not by rows
+    ([16] * 13, 10, 5, 64, 16),                   # a block each
     ([40, 3, 769, 0] * 4, 40, 8, 128, 769),       # a token beyond: records, four layers to a launch at most
 ])
 @pytest.mark.parametrize("layers", [5, 8, 9])
@@ -176,7 +178,10 @@ def test_layers_stay_inside_the_workspace(device, lens, hq, hkv, dim, bound, lay
 @pytest.mark.parametrize("lens,hq,hkv,dim", [
     ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # more than 64 segments
     ([3000, 40, 0, 700], 16, 8, 128),                        # few
-    ([1500, 0, 30] * 12, 4, 1, 64),                          # by rows
+    ([1500, 0, 30] * 12, 4, 1, 64),
+    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # by rows, and so with the rows kept in the workspace
+    ([900] * 30 + [0, 5], 1, 1, 64),                         # by rows; with the rows kept there, workgroups' records
+    ([9000, 0, 30, 17] * 8, 1, 1, 64),                       # as the device finds, not by rows
     ([9000, 300], 8, 1, 128),
     ([40, 3, 300, 0], 8, 2, 128),                            # cut along the segments
 ])

@@ -1,5 +1,5 @@
 """D = 128 in bf16 has two launches, by the bounds (short_at_128), which differ in the order of the loads only: they agree bit for bit,
-and each with the oracle.  Shares of zero, one, two, some and many blocks, by rows, by workgroups, one workgroup to a segment and in
+and each with the oracle.  Shares of zero, one, two, some and many blocks, one segment and many, one workgroup to a segment and in
 several layers."""
 import numpy as np
 import pytest
@@ -32,7 +32,7 @@ BATCHES = pytest.mark.parametrize("lens,hq,hkv,P", [
     ([250, 17, 300, 64], 8, 2, 0),                           # a workgroup to a segment
     ([400] + [5, 0, 16, 17] * 20, 8, 8, 0),                  # a block or none
     ([600, 1, 0, 37, 512, 250] * 8, 40, 8, 64),              # two blocks, runs of 4
-    ([8191], 40, 8, 0), ([30000], 8, 1, 0), ([9000, 30], 16, 1, 512),   # a few segments, by rows, no room to turn K
+    ([8191], 40, 8, 0), ([30000], 8, 1, 0), ([9000, 30], 16, 1, 512),   # a few segments; one; no room to turn K
     ([2600 + 7 * i for i in range(18)] + [0], 10, 2, 0)])    # 3
 @BATCHES
 def test_both_launches(device, lens, hq, hkv, P):

@@ -33,7 +33,7 @@ def loops_with_hidden_stores(kernel):
 def assembly(tmp_path_factory):
     text = []
     flags = [f for f in pkv_build.FLAGS if f not in ("-fPIC", "-shared")]
-    for source in ("attn_stream", "attn_stream_large"):
+    for source in ("attn_stream", "attn_stream_large", "attn_stream_short"):
         asm = str(tmp_path_factory.mktemp("asm") / (source + ".s"))
         subprocess.check_call([pkv_build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, source + ".hip"), "-o", asm],
                               stderr=subprocess.DEVNULL)
@@ -45,7 +45,7 @@ def assembly(tmp_path_factory):
 def kernels(assembly):
     """(name, assembly) of every variant"""
     found = [k for text in assembly for k in re.findall(r"^(_ZN\S*attn_stream_kernel\S*):(.*?)^\.Lfunc_end", text, re.S | re.M)]
-    assert len(found) == 15
+    assert len(found) == 23
     return found
 
 
@@ -62,13 +62,14 @@ def test_short_launches_of_layers_carry_nothing_for_the_chain(assembly, dim):
 
 def test_small_blocks_go_out_before_the_last_has_arrived(kernels):
     """e4m3 at D = 64: K of a block is waited for with its four V loads and the five of the next block out."""
-    waits = [max(int(n) for n in re.findall(r"vmcnt\((\d+)\)", body)) for name, body in kernels if "ILi64ELb1E" in name]
-    assert waits == [9]
+    waits = {name: max(int(n) for n in re.findall(r"vmcnt\((\d+)\)", body)) for name, body in kernels if "ILi64ELb1E" in name}
+    assert len(waits) == 2 and set(waits.values()) == {9}, waits
 
 
 def test_store_loops_do_not_wait_for_their_stores(kernels):
     for name, body in kernels:
         found = list(loops_with_hidden_stores(body.split("\n")))
-        assert len(found) >= 7, name   # finished rows in the stream (four copies of it) and behind it, two records
+        # finished rows in the stream (four copies of it) and behind it, and two records, which a workgroup with a segment never leaves
+        assert len(found) >= (5 if "WholeLayer" in name else 7), name
         # three in flight: a record takes up to 9 stores
         assert all(n >= 3 for _, _, waits in found for n in waits), (name, found)
