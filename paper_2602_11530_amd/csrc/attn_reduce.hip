@@ -106,12 +106,11 @@ __device__ __forceinline__ void fold_records(const AttnLaunch& a, const RowRecor
   lsum = wave_sum(lsum);
 }
 
-constexpr int kGroupThreads = 512;
 // A row of a batch that goes by rows.  Wavefront i of the workgroup folds records i, i + n, i + 2n, ...
 // (n = wavefronts in the workgroup), the partial results meet in LDS and wavefront 0 folds those, normalises, scales and rounds once
 // to bf16.
 __device__ __forceinline__ void reduce_row(const AttnLaunch& a, int row) {
-  constexpr int kWidth = kGroupThreads / 64;
+  constexpr int kWidth = kReduceThreads / 64;
   __shared__ float part_stats[kWidth][2];
   __shared__ float part_acc[kWidth][kRow];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -153,7 +152,6 @@ __device__ __forceinline__ void reduce_rows(const AttnLaunch& a) {
 //   D = 256 31.5 / 30.8; with four times kBatch at once 0 to 1 % slower than below.
 //   More: the workgroups in the middle of the segment, in which nothing begins, take some of the chunks each, and in a workgroup
 //   sets of lanes take every sets-th record and meet in LDS, four to one at a time.
-constexpr int kSubs = kGroupThreads / 16;   // G * D / 64 is kSubs at most
 template <int kD>
 struct SegmentRecords {
   const char* base;    // the segment's first record
@@ -204,15 +202,13 @@ __device__ __forceinline__ void reduce_segment(const AttnLaunch& a, const Layers
     finish(p, sub);
     return;
   }
-  __shared__ f32x4 rows[kGroupThreads];
-  __shared__ f32x2 stats[kGroupThreads];
-  // small quotients by way of fp32: (x + 1/2) / n is at least 1 / (2n) away from a whole number
-  auto quotient = [](int x, int n) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)n)); };
-  const int helpers = min(count - 1, chunks);
-  const int mine = quotient(chunks + helpers - 1, helpers);   // chunks of a workgroup
+  __shared__ f32x4 rows[kReduceThreads];
+  __shared__ f32x2 stats[kReduceThreads];
+  const RecordSplit split(count, chunks);
+  const int mine = split.mine;
   if (slice * mine >= chunks) return;
-  int sets = min(quotient(kSubs, mine), count);
-  const int set = quotient(sub, mine), chunk = slice * mine + (sub - set * mine);
+  int sets = split.sets;
+  const int set = split.quotient(sub, mine), chunk = slice * mine + (sub - set * mine);
   const bool works = set < sets && chunk < chunks;
   Partial p = kNothing;
   if (works) {
@@ -252,17 +248,17 @@ __device__ __forceinline__ SharedSegment read_word(const AttnLaunch& a, const La
 }
 // Many segments.
 template <int kD, typename Layers>
-__global__ __launch_bounds__(kGroupThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
+__global__ __launch_bounds__(kReduceThreads) void attn_reduce_group_kernel(AttnLaunch a, Layers layers) {
   const SharedSegment seg = read_word(a, layers);
   if (seg.told > 0) reduce_segment<kD>(a, layers, seg, blockIdx.x);
 }
 // Few segments: whichever of the two the stream pass has chosen.
-__global__ __launch_bounds__(kGroupThreads) void attn_reduce_few_kernel(AttnLaunch a) {
+__global__ __launch_bounds__(kReduceThreads) void attn_reduce_few_kernel(AttnLaunch a) {
   const SharedSegment seg = read_word(a, OneLayer{});
   if (seg.told == kByRows) reduce_rows(a);
   else if (seg.told > 0) reduce_segment<kRow>(a, OneLayer{}, seg, blockIdx.x);
 }
-__global__ __launch_bounds__(kGroupThreads) void attn_reduce_rows_kernel(AttnLaunch a) {
+__global__ __launch_bounds__(kReduceThreads) void attn_reduce_rows_kernel(AttnLaunch a) {
   reduce_rows(a);
 }
 
@@ -270,12 +266,12 @@ __global__ __launch_bounds__(kGroupThreads) void attn_reduce_rows_kernel(AttnLau
 
 template <int kD>
 static void launch_dim(const AttnLaunch& a, const AttnLayers* layers, dim3 groups, hipStream_t stream) {
-  if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), groups, dim3(kGroupThreads), 0, stream, a, *layers);
-  else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), groups, dim3(kGroupThreads), 0, stream, a, OneLayer{});
+  if (layers) hipLaunchKernelGGL((attn_reduce_group_kernel<kD, AttnLayers>), groups, dim3(kReduceThreads), 0, stream, a, *layers);
+  else hipLaunchKernelGGL((attn_reduce_group_kernel<kD, OneLayer>), groups, dim3(kReduceThreads), 0, stream, a, OneLayer{});
 }
 
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream) {
-  const dim3 groups(a.waves / group_waves(a.D), layers ? layers->count : 1), block(kGroupThreads);
+  const dim3 groups(a.waves / group_waves(a.D), layers ? layers->count : 1), block(kReduceThreads);
   if (a.leaves != kManySegments && (layers || a.D != kRow)) return hipErrorInvalidValue;   // one layer has the whole workspace
   if (a.leaves == kRows) hipLaunchKernelGGL(attn_reduce_rows_kernel, dim3(a.S * a.Hq), block, 0, stream, a);
   else if (a.leaves == kFewSegments) hipLaunchKernelGGL(attn_reduce_few_kernel, groups, block, 0, stream, a);

@@ -805,20 +805,15 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   if (wave == 0 && leaves_words && !by_row) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it go on elsewhere?
-    int row = 0, told = 0;
+    SharedSegment of_last = {0, 0};
     if (!whole && first_wave + kGroupWaves < W) {
       const ShareMap shares(T, W);
       const int begin = shares.start(first_wave), next = shares.start(first_wave + kGroupWaves);
       const int s = request_of(next - 1);
       const Place at = place(next - 1, s, the_request(s));
-      const int seg_pos = next - 1 - at.b;
-      if (seg_pos + at.nb > next) {
-        const int first = seg_pos >= begin ? (int)blockIdx.x : (int)shares.owner(seg_pos) / kGroupWaves;
-        row = (at.s * Hkv + at.kvh) * G;
-        told = ((int)shares.owner(seg_pos + at.nb - 1) / kGroupWaves - first + 1) | ((int)blockIdx.x - first) << 16;
-      }
+      of_last = word_of_group<kGroupWaves>(shares, blockIdx.x, begin, next, (at.s * Hkv + at.kvh) * G, next - 1 - at.b, at.nb);
     }
-    if (lane == 0) word = SharedSegment{row, told};
+    if (lane == 0) word = of_last;
   }
   for (;;) {   // layers
   for (int j = 0; j < nshare; j += 2) {

@@ -130,6 +130,42 @@ struct SharedSegment {
   __host__ __device__ int slice() const { return told >> 16; }
 };
 constexpr int kByRows = -1;
+// The word of workgroup `group` of a batch of workgroups' records, which has positions `from` to `next` of the stream: its last block's
+// segment has `blocks` of them from position `begin` on, and `row` is its first output row.
+template <int kGroupWaves>
+__host__ __device__ __forceinline__ SharedSegment word_of_group(const ShareMap& shares, int group, int from, int next, int row, int begin,
+                                                                int blocks) {
+  SharedSegment w = {0, 0};
+  if (begin + blocks > next) {
+    const int first = begin >= from ? group : (int)shares.owner(begin) / kGroupWaves;
+    w.row = row;
+    w.told = ((int)shares.owner(begin + blocks - 1) / kGroupWaves - first + 1) | (group - first) << 16;
+  }
+  return w;
+}
+
+// How the workgroups that leave word of a segment share its records in the reduce pass, where it has more than a thread loads at once: each
+// has `mine` chunks of 64 floats of the rows, 16 lanes to a chunk, and `sets` of lanes a chunk's records in turn.
+constexpr int kReduceThreads = 512;
+constexpr int kReduceSubs = kReduceThreads / 16;   // G * D / 64 is kReduceSubs at most
+struct RecordSplit {
+  int mine, sets;
+  // small quotients by way of fp32: (x + 1/2) / n is at least 1 / (2n) away from a whole number
+  __host__ __device__ static int quotient(int x, int n) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const float per = __builtin_amdgcn_rcpf((float)n);
+#else
+    const float per = 1.f / (float)n;
+#endif
+    return (int)(((float)x + 0.5f) * per);
+  }
+  __host__ __device__ RecordSplit(int count, int chunks) {
+    const int helpers = count - 1 < chunks ? count - 1 : chunks;
+    mine = quotient(chunks + helpers - 1, helpers);
+    sets = quotient(kReduceSubs, mine);
+    sets = sets < count ? sets : count;
+  }
+};
 
 // What differs between the layers of one launch.
 struct AttnLayer {

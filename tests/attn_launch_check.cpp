@@ -4,7 +4,11 @@
 //
 //   - every write lies inside the bytes that the call asked for, in every layer of a launch
 //   - no two writes of one launch overlap
-//   - what the reduce pass reads of a segment are the records that were left of it, all of them
+//   - the reduce pass hears of a segment that workgroups share from each of them but the last, which
+//     say how many they are and the how-manieth they are, and of nothing else
+//   - what it reads of a segment are the records that were left of it, all of them
+//   - the workgroups and the sets of lanes that it has for a segment take every record of every
+//     chunk of its rows once
 //
 // And the stream pass's LDS: every part of it on a 16-byte boundary, large enough for what it holds and,
 // all together, no more than a compute unit has.
@@ -13,6 +17,7 @@
 #include "../include/pkv.h"
 #include "pkv_kernels.h"
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -74,7 +79,7 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
     if (a.leaves == kManySegments || a.leaves == kFewSegments)
       for (int g = 0; g < grid; ++g) writes.add(shared_segment(a, y, g), sizeof(SharedSegment));
     if (whole) continue;
-    std::map<int, int> begins;   // workgroup -> segments that begin in it and go on in another one
+    std::map<int, SharedSegment> heard;   // of a segment that goes on behind the workgroup, as those that read of it need it
     for (int s = 0; s < a.S; ++s)
       for (int kvh = 0; kvh < a.Hkv && nblk[s] > 0; ++kvh) {
         const int first = a.Hkv * cum[s] + kvh * nblk[s], last = first + nblk[s] - 1;
@@ -86,9 +91,30 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
         }
         const int g0 = w0 / group, g1 = w1 / group;
         if (g0 == g1) continue;   // finished in its workgroup
-        if ((a.leaves != kManySegments && a.leaves != kFewSegments) || ++begins[g0] > 1) call.wrong++;   // the reduce pass hears of one per workgroup
-        for (int g = g0; g <= g1; ++g) writes.add(group_record(a, a.D, y, g, g == g0), record_bytes);
+        if (a.leaves != kManySegments && a.leaves != kFewSegments) call.wrong++;   // the reduce pass would not hear of it
+        const float* record = group_record(a, a.D, y, g0, true);
+        for (int g = g0; g <= g1; ++g) {
+          writes.add(group_record(a, a.D, y, g, g == g0), record_bytes);
+          const int j = g - g0;
+          if (group_record(a, a.D, y, g, g == g0) != record + (2 * j - (j > 0)) * record_floats(a.G, a.D)) call.wrong++;
+          if (g < g1 && !heard.insert({g, {(s * a.Hkv + kvh) * a.G, (g1 - g0 + 1) | j << 16}}).second) call.wrong++;   // one per workgroup
+        }
       }
+    if (by_row) continue;
+    const ShareMap shares(T, W);
+    for (int g = 0; g < grid; ++g) {
+      SharedSegment word = {0, 0};
+      if ((g + 1) * group < W) {
+        const int from = shares.start(g * group), next = shares.start((g + 1) * group);
+        const int s = (int)(std::upper_bound(cum.begin(), cum.end(), (next - 1) / a.Hkv) - cum.begin()) - 1;   // not an empty one: the last that begins there
+        const int kvh = (next - 1 - a.Hkv * cum[s]) / nblk[s], begin = a.Hkv * cum[s] + kvh * nblk[s];
+        word = group == 8 ? word_of_group<8>(shares, g, from, next, (s * a.Hkv + kvh) * a.G, begin, nblk[s])
+                          : word_of_group<4>(shares, g, from, next, (s * a.Hkv + kvh) * a.G, begin, nblk[s]);
+      }
+      const auto want = heard.find(g);
+      if (want == heard.end() ? word.told != 0 : word.row != want->second.row || word.told != want->second.told) call.wrong++;
+      if (word.told && word.slice() >= word.records() - 1) call.wrong++;
+    }
   }
   writes.done();
   call.written = writes.spans;
@@ -175,8 +201,35 @@ static void check_lds() {
       }
 }
 
+// What workgroups and sets of lanes take of a segment of `count` records whose rows are `chunks` chunks.
+static void check_split() {
+  using namespace pkv;
+  for (int x = 0; x < 64; ++x)   // with the device's reciprocal, which may be a unit in the last place off
+    for (int n = 1; n <= 64; ++n)
+      for (float per : {std::nextafterf(1.f / n, 0.f), 1.f / n, std::nextafterf(1.f / n, 2.f)})
+        if (((int)(((float)x + 0.5f) * per) != x / n || RecordSplit::quotient(x, n) != x / n) && failures++ < 20) printf("quotient of %d and %d\n", x, n);
+  for (int chunks = 1; chunks <= kReduceSubs; ++chunks)
+    for (int count = 2; count <= kLayerGroups; ++count) {
+      const RecordSplit split(count, chunks);
+      std::vector<int> taken(chunks * count, 0), finished(chunks, 0);
+      for (int slice = 0; slice < count - 1; ++slice) {   // the workgroups that leave word
+        if (slice * split.mine >= chunks) continue;
+        for (int sub = 0; sub < kReduceSubs; ++sub) {
+          const int set = sub / split.mine, chunk = slice * split.mine + sub % split.mine;
+          if (set >= split.sets || chunk >= chunks) continue;
+          for (int i = set; i < count; i += split.sets) taken[chunk * count + i]++;
+          finished[chunk] += set == 0;
+        }
+      }
+      const auto once = [](const std::vector<int>& v) { return std::all_of(v.begin(), v.end(), [](int n) { return n == 1; }); };
+      if ((!once(taken) || !once(finished) || split.mine * split.sets > kReduceSubs) && failures++ < 20)
+        printf("%d records of %d chunks: %d chunks a workgroup, %d sets\n", count, chunks, split.mine, split.sets);
+    }
+}
+
 int main() {
   check_lds();
+  check_split();
   uint64_t x = 41;
   auto rnd = [&](int n) { x = x * 6364136223846793005ULL + 1442695040888963407ULL; return (int)((uint32_t)(x >> 33) % (uint32_t)n); };
   const int heads[][2] = {{40, 8}, {8, 2}, {8, 1}, {16, 8}, {7, 7}, {16, 1}, {10, 5}};

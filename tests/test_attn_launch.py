@@ -1,5 +1,5 @@
 """What the attention calls launch, walked on the host (no GPU): every write to the workspace lies inside
-it, in every layer of a launch, and the reduce pass hears of every segment that several workgroups share."""
+it, in every layer of a launch, and the reduce pass hears of every segment that several workgroups share and reads all of it once."""
 import os
 import re
 import subprocess
