@@ -337,7 +337,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       W = share_count(T, a.waves);
       first_wave = blockIdx.x * kGroupWaves;
       last_wave = min(kGroupWaves, W - first_wave) - 1;
-      by_row = a.leaves != kManySegments && (a.leaves == kRows || T <= row_blocks(a.waves));
+      by_row = a.leaves != kManySegments && T <= row_blocks(a.waves);
       if (__builtin_expect(by_row && T < a.waves, 0)) {
         // A block per wavefront and not enough of them to fill the compute units: one after the other round
         // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
@@ -389,10 +389,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   // For the reduce pass.
   const bool leaves_words = !kWhole && (a.leaves == kManySegments || a.leaves == kFewSegments);
   auto tell_of_rows = [&]() {
-    if (__builtin_expect(a.leaves == kManySegments, 1)) return;
-    if (by_row && leaves_words && threadIdx.x == 0) shared_segment(a, of, blockIdx.x)->told = kByRows;
-    if ((by_row || a.leaves == kRows) && blockIdx.x == 0) {
-      for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = whole && i == 0 ? -1 : cumB[i];
+    if (__builtin_expect(a.leaves != kFewSegments && a.leaves != kRows, 1)) return;
+    if (blockIdx.x == 0) {
+      for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = !by_row && i == 0 ? -1 : cumB[i];
     }
   };
   // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that

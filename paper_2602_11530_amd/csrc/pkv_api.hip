@@ -173,11 +173,6 @@ int pkv_attn_workspace_bytes(const pkv_attn_shape* shape, size_t* out_bytes) {
   return PKV_OK;
 }
 
-static void set_leaves(pkv::AttnLaunch* a, pkv::Leaves leaves) {
-  a->leaves = leaves;
-  a->ws_words = a->ws_rec + (int64_t)pkv::records_before_words(leaves) * pkv::record_floats(a->G, a->D);
-}
-
 // Validation shared by the single-layer and the multi-layer call; fills the
 // launch descriptor except for the per-layer pointers.
 static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens, float scale, bool kv_fp8,
@@ -225,7 +220,7 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->out_scale = 1.f;
   a->kv_fp8 = kv_fp8;
   a->ws_rec = static_cast<float*>(workspace);
-  set_leaves(a, a->leaves);
+  a->ws_words = a->ws_rec + (int64_t)pkv::kRecordsBeforeWords * pkv::record_floats(a->G, a->D);
   a->layer_ws_floats = pkv::layer_ws_floats(g.G, a->D);
   a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
   return PKV_OK;
@@ -276,12 +271,11 @@ static bool writes_own_input(const pkv::AttnLaunch& a, const pkv::AttnLayer& x) 
 }
 
 // One layer.  Where it writes into its own inputs the rows are kept at the end of the workspace's records until all
-// is read: a batch uses no more than kFew + row_blocks of them and a few words' worth, or fewer, except by rows
-// throughout, which is then left out.
+// is read: workgroups' records and words leave three quarters of it, by rows, which may use all, is then left out.
 static int launch_layer(pkv::AttnLaunch a, const pkv::AttnLayer& layer, hipStream_t st) {
   a.layer = layer;
   if (!writes_own_input(a, layer)) return launch_attn(a, nullptr, st);
-  if (a.leaves == pkv::kRows) set_leaves(&a, pkv::kFewSegments);
+  if (a.leaves == pkv::kRows || a.leaves == pkv::kFewSegments) a.leaves = pkv::kManySegments;
   a.layer.out = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.ws_cum) - row_bytes(a));
   const int rc = launch_attn(a, nullptr, st);
   if (rc != PKV_OK) return rc;

@@ -103,11 +103,12 @@ enum Leaves {
 //   more of a row: 64 of 400..900 on 2/1 heads 12.9 / 12.7; 8 of 300..900 on 8/8 heads at D = 128 14.6 / 14.0; one of 2000..4000 on 8/1
 //   heads there 13.3 / 12.6, 16 of 750..1500 15.0 / 13.4, one of 16000..32000 27.8 / 14.3, on 8/1 heads at D = 256 26.0 / 15.7
 constexpr int kFew = 64;
-// Up to twice the wavefronts where the bounds say so, else, as the words then lie behind the records, by rows up to this many blocks.
-__host__ __device__ constexpr int row_blocks(int waves) { return waves * 5 / 8; }
+// Such a batch goes by rows with up to this many blocks, as the bounds or else the device find: where partial sums are split, and so a
+// row's last bit, follows from the lengths and not from the bounds.
+__host__ __device__ constexpr int row_blocks(int waves) { return 2 * waves; }
 inline Leaves what_is_left(int64_t segments, int64_t max_blocks, int G, int D) {
   if (segments > kFew || segments < kFew / 2 || G * D > 64) return kManySegments;
-  return segments * max_blocks <= 2 * kLayerGroups * group_waves(D) ? kRows : kFewSegments;
+  return segments * max_blocks <= row_blocks(kLayerGroups * group_waves(D)) ? kRows : kFewSegments;
 }
 // A batch with no more segments than the launch has workgroups, none longer than this many blocks, is cut
 // along the segments.  Up to 6 blocks per wavefront; with at most kFew of them, which leave most
@@ -124,12 +125,10 @@ inline int short_segment(int64_t segments, int D, bool kv_fp8) {
 // those in its middle.
 struct SharedSegment {
   int row;    // first output row
-  int told;   // workgroups that share it, and from bit 16 how many of them come before this one; 0 when there is none, kByRows in a
-              // batch that goes by rows
+  int told;   // workgroups that share it, and from bit 16 how many of them come before this one; 0 when there is none
   __host__ __device__ int records() const { return told & 0xffff; }
   __host__ __device__ int slice() const { return told >> 16; }
 };
-constexpr int kByRows = -1;
 // The word of workgroup `group` of a batch of workgroups' records, which has positions `from` to `next` of the stream: its last block's
 // segment has `blocks` of them from position `begin` on, and `row` is its first output row.
 template <int kGroupWaves>
@@ -182,7 +181,7 @@ struct AttnLaunch {
   const int32_t* context_lens;
   float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
   float* ws_words; // the first layer's SharedSegments
-  int32_t* ws_cum; // [S + 1] by rows: cumB for the reduce pass (the first one -1 when it has nothing to do)
+  int32_t* ws_cum; // [S + 1] by rows: cumB for the reduce pass (the first one -1 in a batch that may go by rows and does not)
   Leaves leaves;
   int short_blocks;    // see short_segment()
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
@@ -226,21 +225,18 @@ __host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int se
   return a.ws_rec + (int64_t)(segment + wave) * record_floats(a.G, D);
 }
 // Of any other batch: two records per workgroup of the stream pass (of the shared segment that begins in
-// it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.  With few segments
-// the SharedSegments lie behind all records that a batch may leave by rows: they tell the reduce pass which.
+// it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.
 __host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int layer, int group, bool begins_here) {
   return a.ws_rec + layer * a.layer_ws_floats + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
 }
 __host__ __device__ inline SharedSegment* shared_segment(const AttnLaunch& a, int layer, int group) {
   return (SharedSegment*)(a.ws_words + layer * a.layer_ws_floats) + group;
 }
-constexpr int records_before_words(Leaves leaves) {
-  return leaves == kFewSegments ? kFew + row_blocks(kStreamWaves) : 2 * kLayerGroups;
-}
+constexpr int kRecordsBeforeWords = 2 * kLayerGroups;
 // Per layer: a whole number of records, so that every layer's are aligned like the first one's.
 __host__ __device__ inline int64_t layer_ws_floats(int G, int D) {
   const int64_t rec = record_floats(G, D), words = kLayerGroups * (int64_t)sizeof(SharedSegment) / sizeof(float);
-  return 2 * kLayerGroups * rec + (words + rec - 1) / rec * rec;
+  return kRecordsBeforeWords * rec + (words + rec - 1) / rec * rec;
 }
 
 // LDS of a workgroup of the stream pass, in floats: the prefix arrays, then per wavefront a left record

@@ -71,12 +71,13 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
   const int T = a.Hkv * cum[a.S], W = share_count(T, a.waves);
   const bool whole = !any_long && a.S * a.Hkv <= grid;
   if (a.leaves == kNoRecords && !whole) call.wrong++;   // nobody would finish the shared segments
-  const bool by_row = !whole && (a.leaves == kRows || (a.leaves == kFewSegments && T <= row_blocks(a.waves)));
+  const bool by_row = !whole && (a.leaves == kRows || a.leaves == kFewSegments) && T <= row_blocks(a.waves);
+  if (a.leaves == kRows && !whole && !by_row) call.wrong++;   // the reduce pass reads no words then
 
   Writes writes;
-  if (by_row || a.leaves == kRows) writes.add(a.ws_cum, (a.S + 1) * (int64_t)sizeof(int32_t));
+  if (a.leaves == kRows || a.leaves == kFewSegments) writes.add(a.ws_cum, (a.S + 1) * (int64_t)sizeof(int32_t));
   for (int y = 0; y < count; ++y) {
-    if (a.leaves == kManySegments || a.leaves == kFewSegments)
+    if (a.leaves == kManySegments || (a.leaves == kFewSegments && !by_row))
       for (int g = 0; g < grid; ++g) writes.add(shared_segment(a, y, g), sizeof(SharedSegment));
     if (whole) continue;
     std::map<int, SharedSegment> heard;   // of a segment that goes on behind the workgroup, as those that read of it need it
@@ -232,7 +233,7 @@ int main() {
   check_split();
   uint64_t x = 41;
   auto rnd = [&](int n) { x = x * 6364136223846793005ULL + 1442695040888963407ULL; return (int)((uint32_t)(x >> 33) % (uint32_t)n); };
-  const int heads[][2] = {{40, 8}, {8, 2}, {8, 1}, {16, 8}, {7, 7}, {16, 1}, {10, 5}};
+  const int heads[][2] = {{40, 8}, {8, 2}, {8, 1}, {16, 8}, {7, 7}, {16, 1}, {10, 5}, {8, 8}};
   long calls = 0;
   for (int dim : {64, 128, 256})
     for (auto& h : heads)
@@ -256,6 +257,16 @@ int main() {
     attend(std::vector<int>(seqs, 300), 5, 1, 256, 300, 9);
     attend(std::vector<int>(seqs, 1600), 16, 1, 64, 0, 3);
   }
+  // by rows: as many segments and blocks as there may be, and more or fewer of either
+  for (int seqs : {31, 32, 33, 63, 64, 65})
+    for (int blocks : {49, 63, 64, 65, 127, 128, 129, 500})
+      for (int bound : {16 * blocks, 16 * blocks + 1, 20000})
+        for (int into_q : {-1, 0, 128, 256}) {
+          attend(std::vector<int>(seqs, 16 * blocks), 1, 1, 64, bound, 2, into_q);
+          std::vector<int> uneven(seqs, 16);
+          uneven[seqs / 2] = 16 * blocks;
+          attend(uneven, 1, 1, 64, bound, 1, into_q);
+        }
   printf("calls about %ld, failures=%ld\n", calls, failures);
   return failures != 0;
 }

@@ -22,7 +22,8 @@ def short_blocks(segments, dim, fp8=False):
 
 
 def row_blocks(dim):
-    return full_waves(dim) * 5 // 8
+    """The most blocks that go by rows."""
+    return 2 * full_waves(dim)
 
 
 def leaves(segments, max_blocks, G, dim, fp8=False):
@@ -31,7 +32,7 @@ def leaves(segments, max_blocks, G, dim, fp8=False):
         return "none"
     if segments > 64 or segments < 32 or G * dim > 64:
         return "many"
-    return "rows" if segments * max_blocks <= 2 * full_waves(dim) else "few"
+    return "rows" if segments * max_blocks <= row_blocks(dim) else "few"
 
 
 def blocks_of(w):
@@ -50,7 +51,7 @@ def route(w, max_context_len=0, fp8=False):
     if host == "none" or (segments <= GROUPS and nb.max() <= short_blocks(segments, w.head_dim, fp8)):
         return "whole"
     T = int(nb.sum()) * w.num_kv_heads
-    if host == "rows" or (host == "few" and T <= row_blocks(w.head_dim)):
+    if host in ("rows", "few") and T <= row_blocks(w.head_dim):
         return "dealt" if T < full_waves(w.head_dim) else "rows"
     return "records"
 

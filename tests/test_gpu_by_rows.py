@@ -39,12 +39,13 @@ BATCHES = [
     ([128 * 16] * 32, 1, 128, "rows", "rows"),
     ([48 * 16, 5, 0, 700] * 8, 1, 49, "rows", "whole"),      # by the bounds by rows, but none is long
     ([0] * 4, 8, 49, "rows", "whole"),                       # nothing at all
-    (spread(1280, 32, 49), 1, 500, "few", "dealt"),          # the most that the device sends by rows, and one more
-    (spread(1281, 32, 49), 1, 500, "few", "records"),
-    (spread(1279, 64, 900), 1, 1000, "few", "dealt"),        # one request has most of the wavefronts
-    (spread(160, 8, 80, 2), 8, 200, "few", "dealt"),         # 1280 blocks again, of eight heads each
-    (spread(161, 8, 80, 2), 8, 200, "few", "records"),
-    (spread(4096, 32, 3000), 1, 3000, "few", "records"),
+    (spread(300, 32, 49), 1, 500, "few", "dealt"),
+    (spread(2047, 64, 900), 1, 1000, "few", "dealt"),        # one request has much of the wavefronts
+    (spread(2048, 32, 70), 1, 500, "few", "rows"),
+    (spread(4096, 32, 3000), 1, 3000, "few", "rows"),        # the most that the device sends by rows, and one more
+    (spread(4097, 32, 3000), 1, 3000, "few", "records"),
+    (spread(512, 8, 100, 2), 8, 200, "few", "rows"),          # 4096 blocks again, of eight heads each
+    (spread(513, 8, 100, 2), 8, 200, "few", "records"),
     ([48 * 16, 5, 0, 700] * 8, 2, 300, "few", "whole"),
 ]
 
@@ -87,7 +88,7 @@ def test_batches(device, i, partition):
     assert torch.equal(run_attn_dev(w, *dev, workspace=buf[guard:guard + need]), first)   # whoever ends a segment
 
 
-@pytest.mark.parametrize("i", [0, 3, 5, 7, 9, 11, 12, 14])
+@pytest.mark.parametrize("i", [0, 3, 5, 7, 9, 11, 13, 14, 15])
 def test_8_bit_pools(device, i):
     lens, heads, room, host_route, route = BATCHES[i]
     w = workload(lens, heads, room)
@@ -100,8 +101,8 @@ def test_8_bit_pools(device, i):
 @pytest.mark.parametrize("heads,steps,room,host_route,ways", [
     (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [32] * 7 + [51], [49] + [1] * 7], 64, "rows",
      ["rows", "whole", "dealt", "rows", "dealt"]),
-    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [700, 0, 0, 0, 0, 0, 0, 1], [0] * 7 + [160]], 800, "few",
-     ["records", "whole", "dealt", "records", "dealt"]),
+    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [700, 0, 0, 0, 0, 0, 0, 1], [0] * 7 + [160], [90] * 8], 800,
+     "few", ["rows", "whole", "dealt", "records", "dealt", "records"]),
 ])
 def test_replays(device, heads, steps, room, host_route, ways):
     """One launch, replayed with lengths that take it from one way to the next: nothing of an earlier replay may be left over."""
@@ -128,3 +129,18 @@ def test_replays(device, heads, steps, room, host_route, ways):
         got = to_bits(out)
         assert np.array_equal(got, to_bits(run_attn_dev(w, *dev))), step
         check(w, (q, k, v), got)
+
+
+@pytest.mark.parametrize("lens,heads", [
+    (spread(1280, 32, 49), 1), (spread(1281, 32, 49), 1), (spread(2048, 40, 60, 3), 1), (spread(4096, 64, 64), 1), (spread(512, 9, 64), 7),
+    (spread(512, 8, 64), 8), (spread(4097, 64, 66), 1), (spread(3000, 50, 80), 1), ([48 * 16, 5, 0, 700] * 8, 1),
+])
+def test_the_bound_does_not_change_a_bit(device, lens, heads):
+    """Where partial sums are split follows from the lengths alone, whatever the bounds let the host choose."""
+    w = workload(lens, heads, 1200)
+    q, k, v = wl.make_host_tensors(w)
+    dev = [to_dev(x) for x in (peaked(q), k, v, w.block_tables, w.context_lens)]
+    print(f"{len(lens)} requests, {heads} heads", flush=True)
+    wide = run_attn_dev(w, *dev)
+    for bound in (max(lens), max(lens) + 1, 128 * 16, 5000):
+        assert torch.equal(run_attn_dev(w, *dev, max_context_len=bound), wide), (routes.host_route(w), routes.host_route(w, bound))
