@@ -15,12 +15,10 @@
 // 115 us).  Of what it shares with other wavefronts it leaves one record, and the
 // reduce pass (attn_reduce.hip) combines the records of each (request, KV head).
 //
-// Three ways to that end, by what the segments are like:
+// Two ways to that end, by what the segments are like:
 //   workgroups' records   the wavefronts of a workgroup fold what they share in LDS first, so at most
 //                    two records per workgroup reach memory (64 requests of 1024..8192 tokens on 40/8 heads:
 //                    194.2 us -> 191.0 with the reduce pass; one of 8191 19.1 -> 17.6)
-//   by rows          the wavefronts' records go to memory as they are and the reduce pass has a workgroup
-//                    per row: some dozens of short segments of one small row each (what_is_left)
 //   cut along them   one workgroup per segment, which meets in LDS and finishes it: no records, and no
 //                    reduce pass where the bounds say so beforehand (4 requests of 17..300 tokens on 8/2
 //                    heads: 14.0 -> 11.3 us and a launch less on the host).  Few and short ones, up to 3
@@ -260,9 +258,9 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
 
   int T = 0, W = 0, first_wave = 0, last_wave = -1, pos0 = 0, nshare = 0;
   int own_len = 0, own_start = 0;   // up to 64 requests: lane s's context length and first position
-  bool whole = kWhole, by_row = false;
+  bool whole = kWhole;
   const int groups = a.waves / kGroupWaves;   // of the layer
-  int w = blockIdx.x * kGroupWaves + wave;
+  const int w = blockIdx.x * kGroupWaves + wave;
   u32x4 qnext[kKSteps];
   int seg = 0, seg_next = 0;   // the segment being streamed, and the one of the query group that was asked for last
   auto load_q = [&](int segment) {
@@ -282,7 +280,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     // What else the start needs of the launch descriptor is asked for with the lengths; where it is used it would be waited for,
     // one word after the other.  With no request's data read back from LDS up to 64 requests: one of 8191 tokens 16.7 -> 16.5 us, 64 of
     // 64 on 40/8 heads 11.6 -> 11.45, 64 of 1024..8192 on 8-bit pools 101.7 -> 101.0; 696 shapes of up to 4 blocks a share 0.986.
-    asm volatile("" : : "s"(a.waves), "s"(a.leaves), "s"(a.short_blocks), "s"(a.max_ctx), "s"(a.context_lens), "s"(a.block_tables), "s"(a.MAXB),
+    asm volatile("" : : "s"(a.waves), "s"(a.short_blocks), "s"(a.max_ctx), "s"(a.context_lens), "s"(a.block_tables), "s"(a.MAXB),
                  "s"(a.NB), "s"(a.upb), "s"(a.P), "s"(layer.q), "s"(layer.k_pool), "s"(layer.v_pool), "s"(a.wave_lds_floats));
     for (int base = S > 64 ? 64 * wave : 0; base < S; base += kThreads) {
       const int i = base + lane;
@@ -337,14 +335,6 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
       W = share_count(T, a.waves);
       first_wave = blockIdx.x * kGroupWaves;
       last_wave = min(kGroupWaves, W - first_wave) - 1;
-      by_row = a.leaves != kManySegments && T <= row_blocks(a.waves);
-      if (__builtin_expect(by_row && T < a.waves, 0)) {
-        // A block per wavefront and not enough of them to fill the compute units: one after the other round
-        // the workgroups (one request of 11444 tokens on one KV head, 716 blocks: 22.1 us with eight to a
-        // workgroup, 19.4 dealt; with work for all, neighbours in one workgroup are up to 7 % faster).
-        w = wave * groups + blockIdx.x;
-        last_wave = w < W ? 0 : -1;
-      }
       if (w < W) {
         const ShareMap shares(T, W);
         pos0 = shares.start(w);
@@ -386,21 +376,11 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   };
 
-  // For the reduce pass.
-  const bool leaves_words = !kWhole && (a.leaves == kManySegments || a.leaves == kFewSegments);
-  auto tell_of_rows = [&]() {
-    if (__builtin_expect(a.leaves != kFewSegments && a.leaves != kRows, 1)) return;
-    if (blockIdx.x == 0) {
-      for (int i = threadIdx.x; i < S + 1; i += kThreads) a.ws_cum[i] = !by_row && i == 0 ? -1 : cumB[i];
-    }
-  };
-  // By rows: where this wavefront's record of segment 0 would lie, known before the stream ends so that
-  // its records do not wait for the launch descriptor to be read again.
-  float* row_records = by_row ? wave_record(a, kD, 0, w) : nullptr;
-  if (!kWhole && __builtin_expect(last_wave < 0, 0)) {   // nothing for this workgroup, or for this wavefront of it
-    tell_of_rows();
+  // Is there a reduce pass?  AttnLayers have a workgroup for each segment, too.
+  constexpr bool kLeavesWords = !kWhole && !std::is_same_v<Layers, AttnLayers>;
+  if (!kWhole && __builtin_expect(last_wave < 0, 0)) {   // nothing for this workgroup
     for (;;) {
-      if (threadIdx.x == 0 && leaves_words && !by_row) shared_segment(a, of, blockIdx.x)->told = 0;
+      if (threadIdx.x == 0 && kLeavesWords) shared_segment(a, of, blockIdx.x)->told = 0;
       zero_empty_rows();
       if (!kChained || ++of == layer_count(layers)) return;
       layer = layer_at(a, layers, of);
@@ -800,8 +780,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
   issue_k(kbuf[0], at, 0, kKLoads);
   if (!kLate) issue_v(vbuf[0], at);
   if (!kWhole) load_q(__builtin_amdgcn_readlane(dA.seg, 0));
-  if (!kWhole) tell_of_rows();
-  if (wave == 0 && leaves_words && !by_row) {
+  if (wave == 0 && kLeavesWords) {
     // Word for the reduce pass, while the first loads are on their way: the segment of the workgroup's
     // last block, does it go on elsewhere?
     SharedSegment of_last = {0, 0};
@@ -850,32 +829,22 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     }
   }
   store_staged();
-  if (__builtin_expect(by_row, 0)) {
-    // The reduce pass has a workgroup for every row, so each wavefront's records go to memory as they
-    // are, before all else.
-    auto store_record = [&](const float* rec, int seg) {
-      float* dst = row_records + (int64_t)seg * rec_floats;
-      for (int f = 4 * lane; f < rec_floats; f += 256) store16(dst + f, *(const u32x4*)(rec + f));
-    };
-    if (ends_flags & kEndsLeft) store_record(rec_left, left);
-    if (ends_flags & kEndsRight) store_record(rec_right, right);
-    // Never: up to here the registers of the query group that was asked for last, and of the K that goes out behind a block, are
-    // their own.  As far as the compiler knows those loads may still be on their way, and a loop of stores that took the
-    // registers over would wait for them in every turn, and so for the acknowledgement of each hidden store (append and attention
-    // of 4 requests of 1360..1840 tokens on 16/1 heads at D = 64, five stores a record: 15.4 us with such a wait, 14.1 without).
-    int never;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(never));
-    if (never) {
+  // Never: up to here the registers of the loads that went out last, behind the share's end, are their own.  As far as the compiler knows
+  // they may still be on their way, and a loop of stores that took one over would wait for them in every turn, and so for the
+  // acknowledgement of each hidden store.
+  int never = 0;
+  if (!kWhole) asm volatile("s_mov_b32 %0, 0" : "=s"(never));
+  if (never) {
 #pragma unroll
-      for (int jj = 0; jj < kKSteps; ++jj) asm volatile("" : : "v"(qnext[jj]));
+    for (int jj = 0; jj < kKSteps; ++jj) asm volatile("" : : "v"(qnext[jj]));
 #pragma unroll
-      for (int jj = 0; jj < (kD == 128 ? kKLoads : 0); ++jj) asm volatile("" : : "v"(kbuf[0][jj]));
-    }
+    for (int jj = 0; jj < kKLoads; ++jj) asm volatile("" : : "v"(kbuf[0][jj]));
+#pragma unroll
+    for (int e = 0; e < kVLoads; ++e) asm volatile("" : : "v"(vbuf[kLate][e]));
   }
   // Refused ids are reported once per wavefront, after the stream: nothing in the loop waits on it.
   if (a.id_faults && refused && lane == 0) atomicAdd(a.id_faults, refused);
   if (!kWhole) zero_empty_rows();
-  if (__builtin_expect(by_row, 0)) return;
   uint16_t* out = layer.out;
   const bool more = kChained && of + 1 < layer_count(layers);
   const int ends = ends_flags, left_end = left;
@@ -917,8 +886,7 @@ __global__ __launch_bounds__(group_waves(kD) * 64) void attn_stream_kernel(AttnL
     share_ends[wave] = ends;
   }
   __syncthreads();
-  if (!kWhole && threadIdx.x == 0 && (b.leaves == kManySegments || b.leaves == kFewSegments))
-    *shared_segment(b, of, blockIdx.x) = word;
+  if (kLeavesWords && threadIdx.x == 0) *shared_segment(b, of, blockIdx.x) = word;
   // One chain of LDS records per wavefront v whose left record ends its segment or is the
   // workgroup's last (bit v of `ending`), and one for the last wavefront's right record (bit
   // kGroupWaves).  The threads go to the chains that there are: with room for all nine, two to

@@ -24,8 +24,8 @@ hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, 
   // Those are short, and the scalar registers that the chain keeps (76 to 83 spills instead of 4 to 24) cost them 0.8 to 2 us:
   // attention of 4 layers of 4 requests of 51..69 tokens on 8/2 heads at D = 64 8.1 us in the chain's kernel, 7.15 without, 2 layers
   // of 80 of 85..114 15.3 and 13.3.
-  if (layers && a.leaves != kNoRecords) return launch_chained(a, *layers, lds, stream);
-  if (!layers && a.leaves == kNoRecords) launch_whole(a, lds, stream);
+  if (layers && a.leaves_records) return launch_chained(a, *layers, lds, stream);
+  if (!layers && !a.leaves_records) launch_whole(a, lds, stream);
   else if (!layers && short_at_128(a)) launch_short_128(a, lds, stream);
   else if (a.D == 64) launch_dim<64>(a, layers, lds, stream);
   else if (a.D == 128) launch_dim<128>(a, layers, lds, stream);

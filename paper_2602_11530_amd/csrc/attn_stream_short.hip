@@ -1,4 +1,4 @@
-// Launches of the stream pass for short batches: a workgroup for each segment (kNoRecords), and short shares at D = 128 (short_at_128).
+// Launches of the stream pass for short batches: a workgroup for each segment (WholeLayer), and short shares at D = 128 (short_at_128).
 #include "attn_stream.h"
 
 namespace pkv {

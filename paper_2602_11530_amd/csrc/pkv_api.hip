@@ -32,8 +32,12 @@ constexpr int kMaxHeads = 16384;
 
 struct Geometry {
   int G, P, max_ctx;
-  int64_t slots;   // upper bound on partial-record slots
+  int64_t slots;   // records that the workspace has room for
 };
+
+// A record for every (wavefront, request, KV head) that meet, at most, as wavefronts' own records would need.  Workgroups leave far
+// fewer; the rest takes those of further layers of a launch, or rows (launch_layer).
+int64_t record_slots(int S, int Hkv) { return (int64_t)Hkv * S + pkv::kStreamWaves; }
 
 int check_shape(const pkv_attn_shape* sh, Geometry* g) {
   if (!sh) return PKV_ERR_NULL;
@@ -69,26 +73,15 @@ int check_shape(const pkv_attn_shape* sh, Geometry* g) {
   g->G = G;
   g->P = P;
   g->max_ctx = max_ctx;
-  // at most one record per (wavefront, request, KV head) that meet
-  g->slots = (int64_t)sh->num_kv_heads * sh->num_seqs + pkv::kStreamWaves;
+  g->slots = record_slots(sh->num_seqs, sh->num_kv_heads);
   return PKV_OK;
 }
 
-// Workspace: the partial records, then the prefix array.
-struct WorkspaceLayout {
-  size_t rec_bytes, cum_bytes;
-  size_t total() const { return rec_bytes + cum_bytes; }
-};
-
-WorkspaceLayout workspace_layout(const pkv_attn_shape* sh, const Geometry& g) {
-  WorkspaceLayout w;
-  w.rec_bytes = (size_t)g.slots * pkv::record_floats(g.G, sh->head_dim) * sizeof(float);
-  w.cum_bytes = ((size_t)(sh->num_seqs + 1) * sizeof(int32_t) + 15) & ~(size_t)15;
-  return w;
-}
-
+// Workspace: the partial records, then room for a prefix array, which nothing uses but which is part of the size that callers know.
 size_t workspace_bytes(const pkv_attn_shape* sh, const Geometry& g) {
-  return sh->num_seqs == 0 ? 0 : workspace_layout(sh, g).total();
+  if (sh->num_seqs == 0) return 0;
+  const size_t records = (size_t)g.slots * pkv::record_floats(g.G, sh->head_dim) * sizeof(float);
+  return records + (((size_t)(sh->num_seqs + 1) * sizeof(int32_t) + 15) & ~(size_t)15);
 }
 
 int launch_status(hipError_t e) {
@@ -203,11 +196,11 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   const int64_t segments = (int64_t)a->S * a->Hkv;
   const int64_t max_blocks = (g.max_ctx + pkv::kBlockTokens - 1) / pkv::kBlockTokens;
   a->short_blocks = pkv::short_segment(segments, a->D, kv_fp8);
-  a->leaves = pkv::what_is_left(segments, max_blocks, g.G, a->D);
+  a->leaves_records = 1;
   if (segments <= a->waves / group && max_blocks <= a->short_blocks) {
     // Cut along its segments, a workgroup for each.  Nothing is left in the workspace, and the layers of such
     // a launch may be more than it has room for.
-    a->leaves = pkv::kNoRecords;
+    a->leaves_records = 0;
     a->waves = (int)segments * group;
   }
   a->id_faults = g_id_faults;
@@ -222,7 +215,6 @@ static int prepare_attn(const int32_t* block_tables, const int32_t* context_lens
   a->ws_rec = static_cast<float*>(workspace);
   a->ws_words = a->ws_rec + (int64_t)pkv::kRecordsBeforeWords * pkv::record_floats(a->G, a->D);
   a->layer_ws_floats = pkv::layer_ws_floats(g.G, a->D);
-  a->ws_cum = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + workspace_layout(shape, g).rec_bytes);
   return PKV_OK;
 }
 
@@ -240,7 +232,7 @@ static pkv::AttnLayer layer_of(const void* q, const void* k_pool, const void* v_
 // The launches for the layer of `a`, or for `layers`.
 static int launch_attn(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers, hipStream_t st) {
   hipError_t e = pkv::launch_attn_stream(a, layers, st);
-  if (e == hipSuccess && a.leaves != pkv::kNoRecords) e = pkv::launch_attn_reduce(a, layers, st);
+  if (e == hipSuccess && a.leaves_records) e = pkv::launch_attn_reduce(a, layers, st);
   if (e != hipSuccess) return launch_status(e);
   return PKV_OK;
 }
@@ -270,13 +262,12 @@ static bool writes_own_input(const pkv::AttnLaunch& a, const pkv::AttnLayer& x) 
          overlaps(a, x, a.block_tables, (uint64_t)a.S * a.MAXB * 4) || overlaps(a, x, a.context_lens, (uint64_t)a.S * 4);
 }
 
-// One layer.  Where it writes into its own inputs the rows are kept at the end of the workspace's records until all
-// is read: workgroups' records and words leave three quarters of it, by rows, which may use all, is then left out.
+// One layer.  Where it writes into its own inputs the rows are kept at the end of the workspace's room for records until all
+// is read: a layer's records and words leave three quarters of it.
 static int launch_layer(pkv::AttnLaunch a, const pkv::AttnLayer& layer, hipStream_t st) {
   a.layer = layer;
   if (!writes_own_input(a, layer)) return launch_attn(a, nullptr, st);
-  if (a.leaves == pkv::kRows || a.leaves == pkv::kFewSegments) a.leaves = pkv::kManySegments;
-  a.layer.out = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.ws_cum) - row_bytes(a));
+  a.layer.out = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.ws_rec + record_slots(a.S, a.Hkv) * pkv::record_floats(a.G, a.D)) - row_bytes(a));
   const int rc = launch_attn(a, nullptr, st);
   if (rc != PKV_OK) return rc;
   return launch_status(pkv::launch_copy(a.layer.out, layer.out, row_bytes(a), st));
@@ -359,14 +350,11 @@ int paged_decode_attn_layers(const void* const* q, const void* const* k_pools,
   }
   // Several layers to a launch, as many as the workspace holds records for: a workgroup goes on
   // to the next layer when it is done with its share of one, and the start, the uneven end and the reduce
-  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch that may go by
-  // rows has the whole workspace for one layer, and one that leaves no records needs none of it.  Layers
-  // that depend on each other keep their order.
+  // pass of a launch are paid once (6 layers of 24 requests in two launches: 812 -> 789 us).  A batch that
+  // leaves no records needs none of it.  Layers that depend on each other keep their order.
   Geometry g;
   (void)check_shape(shape, &g);
-  const int64_t room = a.leaves == pkv::kNoRecords       ? pkv::kMaxLaunchLayers
-                       : a.leaves != pkv::kManySegments ? 1
-                                                        : g.slots * pkv::record_floats(a.G, a.D) / a.layer_ws_floats;
+  const int64_t room = a.leaves_records ? g.slots * pkv::record_floats(a.G, a.D) / a.layer_ws_floats : pkv::kMaxLaunchLayers;
   const int most = room < pkv::kMaxLaunchLayers ? (int)room : pkv::kMaxLaunchLayers;
   const int launches = (num_layers + most - 1) / most;
   const int even = (num_layers + launches - 1) / launches;

@@ -40,16 +40,9 @@ constexpr int kAhead = 2;
 //   one partition (P tokens of the request); every run yields one partial result
 //   (max, sum, un-normalised row) per query head of the group.  The runs of one
 //   segment inside one share are folded together.  A segment that lies wholly
-//   inside a share is finished there; of any other the wavefront leaves a record.
-//   In a batch that goes by rows it is stored at
-//       slot = s * Hkv + kvh + w,
-//   which is unique and increases along the stream (from one record to the next
-//   the segment, the wavefront or both advance), so the records of a segment are
-//   the consecutive slots from (its index + the owner of its first block) to
-//   (its index + the owner of its last block); slots skipped where a share and a
-//   segment end together belong to nobody and are never read.  Otherwise the
-//   wavefronts of a workgroup fold their records in LDS, finish the segments that lie
-//   inside the workgroup's range and leave one record for each of the two segments
+//   inside a share is finished there; of any other the wavefront leaves a record
+//   in LDS.  The wavefronts of a workgroup fold those, finish the segments that lie
+//   inside the workgroup's range and leave one record in memory for each of the two segments
 //   that may cross its ends (group_record); the workgroup in which a crossing segment
 //   begins, and those that lie in the middle of one, leave word of it (SharedSegment).
 //
@@ -87,38 +80,15 @@ __host__ __device__ inline int share_count(int T, int waves) { return T < waves 
 // log2 units, partial sum) for up to kMaxGroup heads.  Rows are 16-byte multiples.
 __host__ __device__ inline int record_floats(int G, int D) { return G * D + 2 * kMaxGroup; }
 
-// What the stream pass leaves of the shared segments for the reduce pass, as far as the host can tell.
-enum Leaves {
-  kManySegments,   // records of workgroups
-  kFewSegments,    // records of workgroups, or of wavefronts (by rows) where a batch has few blocks
-  kRows,           // records of wavefronts: the bounds say that there are few blocks
-  kNoRecords       // the bounds alone say that no segment will be shared: no reduce pass
-};
-// By rows, a workgroup of the reduce pass has one row and its records, and the wavefronts of the stream pass need not meet;
-// otherwise they meet in LDS, and the reduce pass has a workgroup for a segment, or several for a long one.  By rows pays
-// for 32 to 64 segments of few blocks with records of one row of 64 floats.  Rows / records of workgroups, us for append and attention:
-//   4 requests of 300..800 tokens on 8/8 heads at D = 64 11.6 / 12.0, 8 of 200..900 12.3 / 12.5
-//   more blocks: 8 of 1500..4000 17.0 / 16.9, 64 of 1000..2000 on one head 14.0 / 13.8
-//   fewer segments: one request of 1000..2000 on 8/8 heads at D = 64 11.9 / 11.5, of 4000..8000 on one head 13.3 / 12.0
-//   more of a row: 64 of 400..900 on 2/1 heads 12.9 / 12.7; 8 of 300..900 on 8/8 heads at D = 128 14.6 / 14.0; one of 2000..4000 on 8/1
-//   heads there 13.3 / 12.6, 16 of 750..1500 15.0 / 13.4, one of 16000..32000 27.8 / 14.3, on 8/1 heads at D = 256 26.0 / 15.7
-constexpr int kFew = 64;
-// Such a batch goes by rows with up to this many blocks, as the bounds or else the device find: where partial sums are split, and so a
-// row's last bit, follows from the lengths and not from the bounds.
-__host__ __device__ constexpr int row_blocks(int waves) { return 2 * waves; }
-inline Leaves what_is_left(int64_t segments, int64_t max_blocks, int G, int D) {
-  if (segments > kFew || segments < kFew / 2 || G * D > 64) return kManySegments;
-  return segments * max_blocks <= row_blocks(kLayerGroups * group_waves(D)) ? kRows : kFewSegments;
-}
 // A batch with no more segments than the launch has workgroups, none longer than this many blocks, is cut
-// along the segments.  Up to 6 blocks per wavefront; with at most kFew of them, which leave most
+// along the segments.  Up to 6 blocks per wavefront; with at most 64 of them, which leave most
 // compute units idle, 3 where a block is 8 KiB or more.  Cut along the segments / not, us for append and
 // attention: 8 segments of 40/8 heads at D = 128, 384 tokens (3 blocks) 13.2 / 13.4, 512 13.2 / 12.8, 768
 // 17.3 / 13.7; 16 segments of 8/1 heads, 768 tokens 20.0 / 15.5; 128 of 40/8 heads, 512 17.6 / 18.8, 768
 // 21.4 / 21.7; 240, 768 23.5 / 27.7; blocks of 4 KiB (D = 64), 8 segments of 768 tokens 12.2 / 13.0.
 inline int short_segment(int64_t segments, int D, bool kv_fp8) {
   const int block_bytes = 2 * kBlockTokens * D * (kv_fp8 ? 1 : 2);
-  return (segments <= kFew && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
+  return (segments <= 64 && block_bytes >= 8192 ? 3 : 6) * group_waves(D);
 }
 
 // A segment that several workgroups share, as those of them leave it in which no later one begins: the one that it begins in and
@@ -179,10 +149,9 @@ struct AttnLaunch {
   AttnLayer layer;
   const int32_t* block_tables;
   const int32_t* context_lens;
-  float* ws_rec;   // [slots][record_floats(G)] partial records, see record_floats()
-  float* ws_words; // the first layer's SharedSegments
-  int32_t* ws_cum; // [S + 1] by rows: cumB for the reduce pass (the first one -1 in a batch that may go by rows and does not)
-  Leaves leaves;
+  float* ws_rec;   // the first layer's partial records, see group_record()
+  float* ws_words; // and SharedSegments
+  int leaves_records;  // 0: the bounds alone say that each segment has a workgroup, none is shared, and there is no reduce pass
   int short_blocks;    // see short_segment()
   float scale_log2e;   // softmax scale x log2(e) (x the K pool's scale for an e4m3 pool)
   float out_scale;     // applied to the normalised row: 1, or the V pool's scale
@@ -207,7 +176,7 @@ struct AttnLayers {
   AttnLayer layer[kMaxLaunchLayers];
 };
 struct OneLayer {};
-struct WholeLayer : OneLayer {};   // a workgroup for each segment (kNoRecords)
+struct WholeLayer : OneLayer {};   // a workgroup for each segment
 // One after the other in each workgroup.
 struct ChainedLayers : AttnLayers {};
 __device__ __forceinline__ int layer_index(const OneLayer&) { return 0; }
@@ -220,11 +189,7 @@ __device__ __forceinline__ const AttnLayer& layer_at(const AttnLaunch&, const At
 __device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch& a, const OneLayer&) { return a.layer; }
 __device__ __forceinline__ const AttnLayer& layer_of(const AttnLaunch&, const AttnLayers& l) { return l.layer[layer_index(l)]; }
 
-// The workspace of a batch that goes by rows: a record per (wavefront, shared segment).
-__host__ __device__ inline float* wave_record(const AttnLaunch& a, int D, int segment, int wave) {
-  return a.ws_rec + (int64_t)(segment + wave) * record_floats(a.G, D);
-}
-// Of any other batch: two records per workgroup of the stream pass (of the shared segment that begins in
+// The workspace, per layer: two records per workgroup of the stream pass (of the shared segment that begins in
 // it, and of the one that begins in an earlier one), then each workgroup's SharedSegment.
 __host__ __device__ inline float* group_record(const AttnLaunch& a, int D, int layer, int group, bool begins_here) {
   return a.ws_rec + layer * a.layer_ws_floats + (int64_t)(2 * group + begins_here) * record_floats(a.G, D);
@@ -312,7 +277,7 @@ __host__ __device__ constexpr int turn_place(int pieces, int t, int p) {
 // Stream pass: persistent wavefronts, which finish what they have to themselves and leave records of the rest.
 // `layers`: nullptr for the one layer of `a`.
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
-// Reduce pass: the segments that several workgroups (by rows: wavefronts) share, from their records.
+// Reduce pass: the segments that several workgroups share, from their records.
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers* layers, hipStream_t stream);
 
 // Plain device-to-device copy.

@@ -70,14 +70,11 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
   }
   const int T = a.Hkv * cum[a.S], W = share_count(T, a.waves);
   const bool whole = !any_long && a.S * a.Hkv <= grid;
-  if (a.leaves == kNoRecords && !whole) call.wrong++;   // nobody would finish the shared segments
-  const bool by_row = !whole && (a.leaves == kRows || a.leaves == kFewSegments) && T <= row_blocks(a.waves);
-  if (a.leaves == kRows && !whole && !by_row) call.wrong++;   // the reduce pass reads no words then
+  if (!a.leaves_records && !whole) call.wrong++;   // nobody would finish the shared segments
 
   Writes writes;
-  if (a.leaves == kRows || a.leaves == kFewSegments) writes.add(a.ws_cum, (a.S + 1) * (int64_t)sizeof(int32_t));
   for (int y = 0; y < count; ++y) {
-    if (a.leaves == kManySegments || (a.leaves == kFewSegments && !by_row))
+    if (a.leaves_records)
       for (int g = 0; g < grid; ++g) writes.add(shared_segment(a, y, g), sizeof(SharedSegment));
     if (whole) continue;
     std::map<int, SharedSegment> heard;   // of a segment that goes on behind the workgroup, as those that read of it need it
@@ -86,13 +83,9 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
         const int first = a.Hkv * cum[s] + kvh * nblk[s], last = first + nblk[s] - 1;
         const int w0 = share_owner(first, T, W), w1 = share_owner(last, T, W);
         if (w0 == w1) continue;   // finished by its wavefront
-        if (by_row) {
-          for (int w = w0; w <= w1; ++w) writes.add(wave_record(a, a.D, s * a.Hkv + kvh, w), record_bytes);
-          continue;
-        }
         const int g0 = w0 / group, g1 = w1 / group;
         if (g0 == g1) continue;   // finished in its workgroup
-        if (a.leaves != kManySegments && a.leaves != kFewSegments) call.wrong++;   // the reduce pass would not hear of it
+        if (!a.leaves_records) call.wrong++;   // the reduce pass would not hear of it
         const float* record = group_record(a, a.D, y, g0, true);
         for (int g = g0; g <= g1; ++g) {
           writes.add(group_record(a, a.D, y, g, g == g0), record_bytes);
@@ -101,7 +94,6 @@ void walk(const pkv::AttnLaunch& a, const pkv::AttnLayers* layers) {
           if (g < g1 && !heard.insert({g, {(s * a.Hkv + kvh) * a.G, (g1 - g0 + 1) | j << 16}}).second) call.wrong++;   // one per workgroup
         }
       }
-    if (by_row) continue;
     const ShareMap shares(T, W);
     for (int g = 0; g < grid; ++g) {
       SharedSegment word = {0, 0};
@@ -129,7 +121,7 @@ hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers* layers, hip
   return hipSuccess;
 }
 hipError_t launch_attn_reduce(const AttnLaunch& a, const AttnLayers*, hipStream_t) {
-  if (a.leaves == kNoRecords) call.wrong++;
+  if (!a.leaves_records) call.wrong++;
   return hipSuccess;
 }
 // Rows kept in the workspace until all inputs are read.
@@ -257,7 +249,7 @@ int main() {
     attend(std::vector<int>(seqs, 300), 5, 1, 256, 300, 9);
     attend(std::vector<int>(seqs, 1600), 16, 1, 64, 0, 3);
   }
-  // by rows: as many segments and blocks as there may be, and more or fewer of either
+  // the shortest records
   for (int seqs : {31, 32, 33, 63, 64, 65})
     for (int blocks : {49, 63, 64, 65, 127, 128, 129, 500})
       for (int bound : {16 * blocks, 16 * blocks + 1, 20000})

@@ -1,19 +1,23 @@
 // The host's choice of a way through the attention calls, from the C-ABI layer itself: linked against stand-ins for the launches,
-// it reads "seqs query_heads kv_heads head_dim max_tokens fp8" lines and prints what is left for the reduce pass and how many
+// it reads "seqs query_heads kv_heads head_dim max_tokens fp8" lines and prints whether there is a reduce pass and how many
 // wavefronts are launched.  Run by tests/test_routes.py (host code only, no GPU).
 #include "../include/pkv.h"
 #include "pkv_kernels.h"
 #include <cstdio>
 
-static int leaves, waves;
+static int leaves_records, reduced, waves;
 
 namespace pkv {
 hipError_t launch_attn_stream(const AttnLaunch& a, const AttnLayers*, hipStream_t) {
-  leaves = a.leaves;
+  leaves_records = a.leaves_records;
+  reduced = 0;
   waves = a.waves;
   return hipSuccess;
 }
-hipError_t launch_attn_reduce(const AttnLaunch&, const AttnLayers*, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_reduce(const AttnLaunch&, const AttnLayers*, hipStream_t) {
+  reduced = 1;
+  return hipSuccess;
+}
 hipError_t launch_copy(const void*, void*, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_block_copy(const void*, void*, const int32_t*, int64_t, int64_t, int64_t, bool, int32_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_block_move(const void*, const int32_t*, int64_t, void*, const int32_t*, int64_t, int64_t, int64_t, int32_t*, hipStream_t) { return hipSuccess; }
@@ -23,8 +27,6 @@ hipError_t launch_stream_read_probe(const void*, const void*, uint32_t, int64_t,
 }  // namespace pkv
 
 int main() {
-  const char* const names[] = {"many", "few", "rows", "none"};   // as in pkv::Leaves
-  static_assert(pkv::kManySegments == 0 && pkv::kFewSegments == 1 && pkv::kRows == 2 && pkv::kNoRecords == 3, "");
   char* const base = reinterpret_cast<char*>((uintptr_t)1 << 40);   // addresses only
   const int32_t* ints = reinterpret_cast<const int32_t*>((uintptr_t)1 << 39);
   int seqs, hq, hkv, dim, tokens, fp8;
@@ -38,7 +40,8 @@ int main() {
       rc = fp8 ? paged_decode_attn_fp8kv(p[0], p[1], p[2], ints, ints, 1.f, 1.f, 1.f, p[3], &sh, base, need, nullptr)
                : paged_decode_attn(p[0], p[1], p[2], ints, ints, 1.f, p[3], &sh, base, need, nullptr);
     if (rc != PKV_OK) return printf("status %d\n", rc), 1;
-    printf("%s %d\n", names[leaves], waves);
+    if (reduced != leaves_records) return printf("a reduce pass: %d\n", reduced), 1;
+    printf("%d %d\n", leaves_records, waves);
   }
   return 0;
 }

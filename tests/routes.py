@@ -21,39 +21,22 @@ def short_blocks(segments, dim, fp8=False):
     return (3 if small else 6) * group_waves(dim)
 
 
-def row_blocks(dim):
-    """The most blocks that go by rows."""
-    return 2 * full_waves(dim)
-
-
-def leaves(segments, max_blocks, G, dim, fp8=False):
-    """The host's choice: "none", "rows", "few" or "many"."""
-    if segments <= GROUPS and max_blocks <= short_blocks(segments, dim, fp8):
-        return "none"
-    if segments > 64 or segments < 32 or G * dim > 64:
-        return "many"
-    return "rows" if segments * max_blocks <= row_blocks(dim) else "few"
+def leaves_records(segments, max_blocks, dim, fp8=False):
+    """By the bounds: may workgroups share segments, so that there is a reduce pass?"""
+    return segments > GROUPS or max_blocks > short_blocks(segments, dim, fp8)
 
 
 def blocks_of(w):
     return (np.asarray(w.context_lens, dtype=np.int64) + BLOCK - 1) // BLOCK
 
 
-def host_route(w, max_context_len=0, fp8=False):
-    bound = max_context_len or w.max_blocks_per_seq * w.block_size
-    return leaves(w.num_seqs * w.num_kv_heads, (bound + BLOCK - 1) // BLOCK, w.num_q_heads // w.num_kv_heads, w.head_dim, fp8)
-
-
 def route(w, max_context_len=0, fp8=False):
-    """What becomes of the batch, with the device's part of the choice: "whole" (cut along its segments), "dealt" (by rows,
-    less than a block for each wavefront), "rows" (by rows) or "records" (workgroups' records)."""
-    host, segments, nb = host_route(w, max_context_len, fp8), w.num_seqs * w.num_kv_heads, blocks_of(w)
-    if host == "none" or (segments <= GROUPS and nb.max() <= short_blocks(segments, w.head_dim, fp8)):
+    """What becomes of the batch: "whole" (cut along its segments, as the bounds say), "whole on the device" (as it finds from
+    the lengths) or "records" (workgroups' records)."""
+    bound, segments = max_context_len or w.max_blocks_per_seq * w.block_size, w.num_seqs * w.num_kv_heads
+    if not leaves_records(segments, (bound + BLOCK - 1) // BLOCK, w.head_dim, fp8):
         return "whole"
-    T = int(nb.sum()) * w.num_kv_heads
-    if host in ("rows", "few") and T <= row_blocks(w.head_dim):
-        return "dealt" if T < full_waves(w.head_dim) else "rows"
-    return "records"
+    return "records" if leaves_records(segments, blocks_of(w).max(), w.head_dim, fp8) else "whole on the device"
 
 
 def records(w):

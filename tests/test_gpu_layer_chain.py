@@ -24,8 +24,8 @@ def layers_call(w, dev, t_d, l_d, shape):
 
 
 def chained(w):
-    """Do workgroups go from layer to layer?  Not in a batch that may go by rows, nor where each segment has one by the bounds."""
-    return routes.host_route(w) == "many"
+    """Do workgroups go from layer to layer?  Not where each segment has one by the bounds."""
+    return routes.route(w) != "whole"
 
 
 def device_layers(w, n, seed):

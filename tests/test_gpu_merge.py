@@ -1,6 +1,6 @@
 """GPU tests of how the partial results of a segment (request, KV head) meet: inside a wavefront's share, in a
 workgroup, over several workgroups (a record for each), in batches cut along their segments; on workspaces whose earlier
-contents vary, called repeatedly and replayed from a graph.  (By rows: test_gpu_by_rows.py, and the cases that say so here.)"""
+contents vary, called repeatedly and replayed from a graph."""
 import numpy as np
 import pytest
 import torch
@@ -40,7 +40,7 @@ SHAPES = [
     ([384, 16, 15, 0] * 8, 16, 8, 256),
     ([768, 5, 300, 0] * 8, 32, 8, 64),       # as many segments as workgroups
     ([768, 5, 300, 0] * 8 + [64], 32, 8, 64),
-    ([2000, 30] * 4, 8, 8, 64),              # by rows, as the device finds
+    ([2000, 30] * 4, 8, 8, 64),              # records of one head
     ([2000, 30] * 4, 7, 7, 64),
     ([16 * 2047], 8, 1, 64),                 # a block less than wavefronts, as many and one more
     ([16 * 2048 - 5], 8, 1, 128),
@@ -125,8 +125,7 @@ def test_replays_with_growing_lengths(device, hq, hkv):
     ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # several layers to a launch
     ([3000] * 40, 16, 2, 64),
     ([700, 5000, 129], 16, 8, 256),                          # few segments, likewise
-    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # by rows: a launch for each
-    ([9000, 0, 30, 17] * 8, 1, 1, 64),                       # as the device finds, not by rows: a launch for each
+    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # the shortest records
     ([40, 3, 768, 0], 8, 2, 128),                            # cut along the segments
 ])
 @pytest.mark.parametrize("layers", [1, 3, 9])
@@ -179,9 +178,7 @@ def test_layers_stay_inside_the_workspace(device, lens, hq, hkv, dim, bound, lay
     ([700, 0, 5000, 3, 129, 16, 2000, 31, 1], 40, 8, 128),   # more than 64 segments
     ([3000, 40, 0, 700], 16, 8, 128),                        # few
     ([1500, 0, 30] * 12, 4, 1, 64),
-    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # by rows; with the rows kept in the workspace, workgroups' records
-    ([900] * 31 + [3000], 1, 1, 64),                         # by rows, as the device finds
-    ([9000, 0, 30, 17] * 8, 1, 1, 64),                       # as the device finds, not by rows
+    ([900, 0, 30, 17] * 8, 1, 1, 64),                        # the shortest records
     ([9000, 300], 8, 1, 128),
     ([40, 3, 300, 0], 8, 2, 128),                            # cut along the segments
 ])

@@ -1,8 +1,6 @@
-"""GPU parity of batches that go by rows: 32 to 64 segments (request, KV head) of few blocks, one row of 64 floats each.  The
-wavefronts' records go to memory as they are and the reduce pass has a workgroup for a row; the bounds say so ("rows" on the host), or
-the device finds it ("few").  Fewer blocks than wavefronts, which are then dealt round the workgroups, as many and more; the most that the
-device sends by rows, and one more; batches that turn out to be cut along their segments; replays that go from one to
-the other.  The way of every batch is asserted, so that none of this is left unseen when a rule moves."""
+"""GPU parity of batches of 32 to 64 segments (request, KV head) of one row of 64 floats each: with fewer blocks than wavefronts, as many
+and more, a few blocks each and up to thousands; the bounds tight and wide, which changes no bit; batches that turn out on the device
+to be cut along their segments; replays that go from one to the other."""
 import numpy as np
 import pytest
 import torch
@@ -26,27 +24,24 @@ def spread(total, n, longest, empty=0):
     return lens
 
 
-# lengths, heads, blocks that the table has room for, what becomes of it by host and device
+# lengths, heads, blocks that the table has room for, what becomes of it
 BATCHES = [
-    (spread(255, 32, 50), 1, 50, "rows", "dealt"),           # a wavefront in all but one of the workgroups
-    (spread(600, 40, 60, 3), 1, 100, "rows", "dealt"),
-    (spread(2047, 32, 70), 1, 128, "rows", "dealt"),         # a block less than wavefronts, as many and one more
-    (spread(2048, 32, 70), 1, 128, "rows", "rows"),
-    (spread(2049, 32, 70), 1, 128, "rows", "rows"),
-    (spread(500, 16, 60, 5), 4, 64, "rows", "dealt"),        # 2000 blocks of 64 segments
-    (spread(510, 9, 60), 7, 65, "rows", "rows"),             # 3570 of 63
-    ([64 * 16] * 8, 8, 64, "rows", "rows"),                  # as many segments, and blocks, as there may be
-    ([128 * 16] * 32, 1, 128, "rows", "rows"),
-    ([48 * 16, 5, 0, 700] * 8, 1, 49, "rows", "whole"),      # by the bounds by rows, but none is long
-    ([0] * 4, 8, 49, "rows", "whole"),                       # nothing at all
-    (spread(300, 32, 49), 1, 500, "few", "dealt"),
-    (spread(2047, 64, 900), 1, 1000, "few", "dealt"),        # one request has much of the wavefronts
-    (spread(2048, 32, 70), 1, 500, "few", "rows"),
-    (spread(4096, 32, 3000), 1, 3000, "few", "rows"),        # the most that the device sends by rows, and one more
-    (spread(4097, 32, 3000), 1, 3000, "few", "records"),
-    (spread(512, 8, 100, 2), 8, 200, "few", "rows"),          # 4096 blocks again, of eight heads each
-    (spread(513, 8, 100, 2), 8, 200, "few", "records"),
-    ([48 * 16, 5, 0, 700] * 8, 2, 300, "few", "whole"),
+    (spread(255, 32, 50), 1, 50, "records"),           # a block in all but one of the workgroups
+    (spread(600, 40, 60, 3), 1, 100, "records"),
+    (spread(2047, 32, 70), 1, 128, "records"),         # a block less than wavefronts, as many and one more
+    (spread(2048, 32, 70), 1, 128, "records"),
+    (spread(2049, 32, 70), 1, 128, "records"),
+    (spread(500, 16, 60, 5), 4, 64, "records"),        # 2000 blocks of 64 segments
+    (spread(510, 9, 60), 7, 65, "records"),            # 3570 of 63
+    ([64 * 16] * 8, 8, 64, "records"),
+    ([128 * 16] * 32, 1, 128, "records"),
+    ([48 * 16, 5, 0, 700] * 8, 1, 49, "whole on the device"),      # by the bounds they may be longer, but none is
+    ([0] * 4, 8, 49, "whole on the device"),                       # nothing at all
+    (spread(300, 32, 49), 1, 500, "records"),
+    (spread(2047, 64, 900), 1, 1000, "records"),       # one request has much of the wavefronts
+    (spread(4096, 32, 3000), 1, 3000, "records"),
+    (spread(513, 8, 100, 2), 8, 200, "records"),
+    ([48 * 16, 5, 0, 700] * 8, 2, 300, "whole on the device"),
 ]
 
 
@@ -71,9 +66,9 @@ def check(w, host, got):
 @pytest.mark.parametrize("i", range(len(BATCHES)))
 @pytest.mark.parametrize("partition", [0, 64])
 def test_batches(device, i, partition):
-    lens, heads, room, host_route, route = BATCHES[i]
+    lens, heads, room, route = BATCHES[i]
     w = workload(lens, heads, room, partition_size=partition)
-    assert (routes.host_route(w), routes.route(w)) == (host_route, route)
+    assert routes.route(w) == route
     q, k, v = wl.make_host_tensors(w, poison_unused=True)
     k = peaked(k) if i % 2 else k
     print(f"{i}: {len(lens)} requests, {heads} heads, {route}", flush=True)
@@ -88,26 +83,23 @@ def test_batches(device, i, partition):
     assert torch.equal(run_attn_dev(w, *dev, workspace=buf[guard:guard + need]), first)   # whoever ends a segment
 
 
-@pytest.mark.parametrize("i", [0, 3, 5, 7, 9, 11, 13, 14, 15])
+@pytest.mark.parametrize("i", [0, 3, 5, 7, 9, 12, 14])
 def test_8_bit_pools(device, i):
-    lens, heads, room, host_route, route = BATCHES[i]
+    lens, heads, room, route = BATCHES[i]
     w = workload(lens, heads, room)
-    assert (routes.host_route(w, fp8=True), routes.route(w, fp8=True)) == (host_route, route)
+    assert routes.route(w, fp8=True) == route
     q, k8, v8 = wl.make_host_tensors_fp8(w, KS, VS, poison_unused=True)
     print(f"fp8 {i}: {len(lens)} requests, {heads} heads, {route}", flush=True)
     check_fp8(w, q, k8, v8, run_fp8(w, q, k8, v8), f"fp8 {route}")
 
 
-@pytest.mark.parametrize("heads,steps,room,host_route,ways", [
-    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [32] * 7 + [51], [49] + [1] * 7], 64, "rows",
-     ["rows", "whole", "dealt", "rows", "dealt"]),
-    (8, [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [700, 0, 0, 0, 0, 0, 0, 1], [0] * 7 + [160], [90] * 8], 800,
-     "few", ["rows", "whole", "dealt", "records", "dealt", "records"]),
-])
-def test_replays(device, heads, steps, room, host_route, ways):
+@pytest.mark.parametrize("room", [64, 800])
+def test_replays(device, room):
     """One launch, replayed with lengths that take it from one way to the next: nothing of an earlier replay may be left over."""
-    most = np.max(steps, axis=0)
-    w = workload([16 * int(b) for b in most], heads, room)
+    steps = [[60] * 8, [3, 48, 0, 1, 7, 48, 2, 9], [50, 2, 0, 1, 7, 48, 2, 9], [32] * 7 + [51], [49] + [1] * 7]
+    if room > 64:
+        steps += [[700, 0, 0, 0, 0, 0, 0, 1], [0] * 7 + [160], [90] * 8]
+    w = workload([16 * int(b) for b in np.max(steps, axis=0)], 8, room)
     q, k, v = wl.make_host_tensors(w)
     dev = [to_dev(x) for x in (q, k, v, w.block_tables, w.context_lens)]
     shape, lens = shape_of(w), dev[4]
@@ -118,14 +110,14 @@ def test_replays(device, heads, steps, room, host_route, ways):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=stream):
         pkv.paged_decode_attn(*dev, float(w.scale), out, shape, ws, torch.cuda.current_stream())
-    for step, way in zip(steps + steps[1:], ways + ways[1:]):
+    for step in steps + steps[1:]:
         w.context_lens[:] = [max(16 * b - 3 * i, 0) for i, b in enumerate(step)]
-        assert (routes.host_route(w), routes.route(w)) == (host_route, way)
+        assert routes.route(w) == ("records" if max(step) > 48 else "whole on the device")
         lens.copy_(torch.from_numpy(w.context_lens))
         out.fill_(0x7FC1)
         graph.replay()
         torch.cuda.synchronize()
-        print(f"{step}: {way}", flush=True)
+        print(step, flush=True)
         got = to_bits(out)
         assert np.array_equal(got, to_bits(run_attn_dev(w, *dev))), step
         check(w, (q, k, v), got)
@@ -143,4 +135,4 @@ def test_the_bound_does_not_change_a_bit(device, lens, heads):
     print(f"{len(lens)} requests, {heads} heads", flush=True)
     wide = run_attn_dev(w, *dev)
     for bound in (max(lens), max(lens) + 1, 128 * 16, 5000):
-        assert torch.equal(run_attn_dev(w, *dev, max_context_len=bound), wide), (routes.host_route(w), routes.host_route(w, bound))
+        assert torch.equal(run_attn_dev(w, *dev, max_context_len=bound), wide), bound
