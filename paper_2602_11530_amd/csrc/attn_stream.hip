@@ -21,7 +21,7 @@ hipError_t launch_attn_stream(const AttnLaunch& a_in, const AttnLayers* layers, 
   const size_t lds = l.bytes + l.turn_bytes;
   if (layers && a.kv_fp8) return hipErrorInvalidValue;
   // Layers go one after the other in each workgroup, or, where each segment has a workgroup, each in workgroups of its own.
-  // Those are short, and the scalar registers that the chain keeps (76 to 83 spills instead of 4 to 24) cost them 0.8 to 2 us:
+  // Those are short, and the scalar registers that the chain keeps (then 76 to 83 spills instead of 4 to 24, now 60 to 66 instead of 0 to 10) cost them 0.8 to 2 us:
   // attention of 4 layers of 4 requests of 51..69 tokens on 8/2 heads at D = 64 8.1 us in the chain's kernel, 7.15 without, 2 layers
   // of 80 of 85..114 15.3 and 13.3.
   if (layers && a.leaves_records) return launch_chained(a, *layers, lds, stream);

@@ -26,8 +26,7 @@ inline bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p)
 // is the cheapest.
 constexpr int kDefaultPartition = pkv::kMaxPartition;
 
-// Query heads.  Keeps every size product far inside 64 bits and the merge launch (one
-// wavefront per (request, head)) below 2^32 work-items at the largest batch.
+// Query heads.  Keeps every size product far inside 64 bits.
 constexpr int kMaxHeads = 16384;
 
 struct Geometry {

@@ -1,5 +1,5 @@
 """Host logic of the attention stream decomposition (no GPU): the share map that
-both the stream pass and the reduce pass rely on is checked by brute force."""
+the stream pass relies on is checked by brute force."""
 import os
 import subprocess
 import tempfile
